@@ -1,203 +1,214 @@
 // Forward of one segment: out = softmax(q k^T / sqrt(D), causal with the diagonal shifted by seg_off) v,
 // lse = log-sum-exp of the scaled scores (Section 3.1, Eq. 3, restricted to the segment's rows).
 //
-// One workgroup (NW waves) owns BM = 32*NQ*NW query rows of one head; wave w owns rows 32*NQ*w .. +32*NQ.
-// The transposed products are computed so that a lane always holds ONE query (column ln) and the
+// One workgroup (4 waves) owns 128 query rows of one head; wave w owns rows 32*w .. +32, two column blocks of 16.
+// The transposed products are computed so that a lane always holds TWO queries (column n of either block) and the
 // keys run over registers:
-//     S^T[key][q] = sum_d K[key][d] Q[q][d]        A = K fragment from LDS, B = Q fragment (registers)
+//     S^T[key][q] = sum_d K[key][d] Q[q][d]        A = K from LDS, B = Q (registers)
 //     O^T[d][q]  += sum_key V[key][d] P^T[key][q]  A = V read transposed from LDS, B = P^T slab (registers)
-// Row maximum and sum are then in-lane reductions plus one exchange with the partner lane (lane ^ 32).
+// Row maximum and sum are then in-lane reductions; the four lanes of a query meet at the end only.
 //
-// K/V tiles of BN = 32*KB keys go from HBM straight into a 3-stage ring of swizzled LDS tiles (no register
-// staging); tile j+2 is in flight while tiles j and j+1 are consumed, with one workgroup barrier per tile.
-// The loop advances in steps of one 32-key block and is software-pipelined inside each wave: the score
-// product of block k+1 (matrix pipe) is issued together with the row sums and operand packing of block k's
-// probabilities (vector pipe), then the PV product of block k together with the maximum and the exponentials
-// of block k+1 (see fwd_step).  Key blocks wholly above the shifted diagonal are never visited; blocks wholly
-// below it run a step without any masking code.
+// K/V tiles of 32 keys go from HBM straight into a ring in LDS (TileRing; no register staging), with one workgroup
+// barrier per tile.
+// The loop advances by one tile and is software-pipelined inside each wave: the score product of tile k+1 (matrix
+// pipe) is issued together with the operand packing of tile k's probabilities (vector pipe), then the PV product of
+// tile k together with the exponentials of tile k+1 (see fwd_step).  Tiles wholly above the shifted diagonal are never
+// visited; tiles wholly below it run a step without any masking code.
+//
+// What bounds it: the matrix pipe, at the clock the power limit leaves (head_dim 128: 67 % busy at 1.77 GHz, two waves
+// per SIMD).  Per step and wave it runs 16 * NC matrix instructions of 16 cycles against about 12 * NC vector
+// instructions and 8 * NC exponentials (two issue slots each), so both have to run under each other, and every operand
+// read from LDS should feed as many matrix instructions as registers allow: 48 rows per wave (NC = 3) read a third less
+// LDS per product than 32.  32 heads, 4096 rows behind 28672 keys: head_dim 128 1.86 -> 1.65 ms (1110 -> 1250
+// TFLOP/s), 80 1.51 -> 1.22 ms, 64 1.17 -> 1.00 ms against 32x32x16 instructions on 32 rows per wave, whole swizzled
+// rows in LDS and three waves per SIMD.
 #pragma once
-#include "attn_device.hpp"
+#include <type_traits>
 
+#include "attn_tile.hpp"
 
 namespace s1f {
 
-// Lazy rescaling: the running maximum m of a row is raised only when a new block makes its probabilities
+// Lazy rescaling: the running maximum m of a row is raised only when a new tile makes its probabilities
 // 2^(s*c - m) large, and the steady loop finds that out from their SUM, which it needs anyway, instead of from their
-// maximum: a lane adds up the probabilities of its 16 keys of the block, and if that sum exceeds 2^kRescaleTau in
+// maximum: a lane adds up the probabilities of its 8 keys of the tile, and if that sum exceeds 2^kRescaleTau in
 // any lane of the wave (infinity included: the exponentials are taken before anyone has looked), the loop is left,
-// the block's row maxima are computed, the rows whose maximum exceeds m by more than kRescaleTau - 4 (a sum over 16
-// keys above 2^tau needs one of them above 2^(tau-4)) take it as their new m, O and l are rescaled and the block's
+// the tile's row maxima are computed, the rows whose maximum exceeds m by more than kRescaleTau - 3 (a sum over 8
+// keys above 2^tau needs one of them above 2^(tau-3)) take it as their new m, O and l are rescaled and the tile's
 // probabilities recomputed.  Otherwise every probability is at most 2^kRescaleTau, which fp32 sums and bf16
 // operands hold without loss.  The accumulator rescale (a pass over every O register) and the maximum (a chain of
-// its own through all 16 scores, plus a lane exchange) thereby leave the steady loop.
+// its own through all scores, plus lane exchanges) thereby leave the steady loop.
 constexpr float kRescaleTau = 8.0f;
 constexpr float kRescaleLimit = 256.0f;   // 2^kRescaleTau
 
-template <typename T, int D, int NQ, int KB, int NW> struct FwdCfg {
-  static constexpr int BM = 32 * NQ * NW;
-  static constexpr int BN = 32 * KB;
-  static constexpr int THREADS = 64 * NW;
-  typedef LdsTile<T, BN, D> KT;
-  static constexpr int STAGE_BYTES = 2 * KT::BYTES;      // K tile then V tile
-  static constexpr int LDS_BYTES = 3 * STAGE_BYTES;
+template <typename T, int D, int NC> struct FwdCfg {
+  static constexpr int BM = 64 * NC, BN = 32, THREADS = 256;
+  static constexpr int LDS_BYTES = TileRing<T, D>::LDS_BYTES;
 };
 
-// Number of operand fragments a wave keeps in flight ahead of the matrix instruction that consumes them
-// (LDS latency is three to four 32x32x16 MFMAs).
-constexpr int kPrefetch = 2;
+// Masks the scores of rows 16*rb.. of a tile that crosses the diagonal.
+//   ahead = (absolute row of the wave's first query) - (first key of the tile)
+template <int NC> S1F_DEV void fwd_mask(f32x4 (&s)[2][NC], int rb, int ahead) {
+  const int lane = lane_id(), lim = ahead + (lane & 15) - 4 * (lane >> 4);
+  float hidden = -INFINITY;
+  asm volatile("" : "+v"(hidden));   // made here, not kept in a register across the loop
+#pragma unroll
+  for (int cb = 0; cb < NC; ++cb)
+#pragma unroll
+    for (int v = 0; v < 4; ++v)
+      if (16 * rb + v > lim + 16 * cb) s[rb][cb][v] = hidden;
+}
 
-// S^T blocks of one 32-key block: s[nq] = K[block rows, :] Q^T   (prologue only; the loop uses fwd_step)
-template <typename RD, typename T, int NQ, int NKS>
-S1F_DEV void fwd_scores(f32x16 (&s)[NQ], const typename Elem<T>::Frag (&qf)[NQ][NKS], const RD &rd, lds_addr kblock) {
+// Row maxima of a tile in log2 units (each lane gets the maxima of its two queries' 32 scores).
+template <int NC> S1F_DEV void fwd_row_max(const f32x4 (&s)[2][NC], float (&mx)[NC], float c) {
 #pragma unroll
-  for (int nq = 0; nq < NQ; ++nq)
+  for (int cb = 0; cb < NC; ++cb) {
+    float x = s[0][cb][0];
 #pragma unroll
-    for (int v = 0; v < 16; ++v) s[nq][v] = 0.f;
-#pragma unroll
-  for (int ks = 0; ks < NKS; ++ks) {
-    const typename Elem<T>::Frag kf = rd.nat(kblock, ks);
-#pragma unroll
-    for (int nq = 0; nq < NQ; ++nq) s[nq] = mma(kf, qf[nq][ks], s[nq]);
+    for (int i = 1; i < 8; ++i) x = fmaxf(x, s[i >> 2][cb][i & 3]);
+    mx[cb] = max_over_rows(x) * c;
   }
 }
 
-// Masks the scores of a block that crosses the diagonal.
-//   lim0 = (absolute row of this lane's query in query block 0) - (first key of the block) - 4g
-template <int NQ> S1F_DEV void fwd_mask(f32x16 (&s)[NQ], int lim0) {
+// Probabilities of a tile from its scores, against the running maximum m (log2 units): p = 2^(s*c - m); rs = the
+// sums over this lane's 8 keys.
+template <int NC> S1F_DEV void fwd_probs(f32x4 (&p)[2][NC], const f32x4 (&s)[2][NC], const float (&m)[NC], float c, float (&rs)[NC]) {
 #pragma unroll
-  for (int nq = 0; nq < NQ; ++nq) {
-    const int lim = lim0 + 32 * nq;   // register v is visible iff 8*(v/4) + v%4 <= lim
+  for (int cb = 0; cb < NC; ++cb) {
+    rs[cb] = 0.f;
 #pragma unroll
-    for (int v = 0; v < 16; ++v) s[nq][v] = (8 * (v >> 2) + (v & 3) > lim) ? -INFINITY : s[nq][v];
-  }
-}
-
-// Row maxima of a block in log2 units (each lane gets the maximum of its query's 32 scores).
-template <int NQ> S1F_DEV void fwd_row_max(const f32x16 (&s)[NQ], float (&mx)[NQ], float c) {
-#pragma unroll
-  for (int nq = 0; nq < NQ; ++nq) {
-    float x = -INFINITY;
-#pragma unroll
-    for (int v = 0; v < 16; ++v) x = fmaxf(x, s[nq][v]);
-    mx[nq] = max_xor32(x) * c;
-  }
-}
-
-// Probabilities of a block from its scores, against the running maximum m (log2 units): p = 2^(s*c - m); rs = the
-// sum over this lane's 16 keys.
-template <int NQ>
-S1F_DEV void fwd_probs(f32x16 (&p)[NQ], const f32x16 (&s)[NQ], const float (&m)[NQ], float c, float (&rs)[NQ]) {
-#pragma unroll
-  for (int nq = 0; nq < NQ; ++nq) {
-    rs[nq] = 0.f;
-#pragma unroll
-    for (int v = 0; v < 16; ++v) {
-      p[nq][v] = exp2_fast(fmaf(s[nq][v], c, -m[nq]));
-      rs[nq] += p[nq][v];
+    for (int i = 0; i < 8; ++i) {
+      const float x = exp2_fast(fmaf(s[i >> 2][cb][i & 3], c, -m[cb]));
+      p[i >> 2][cb][i & 3] = x;
+      rs[cb] += x;
     }
   }
 }
 
-// One pipelined step over block k, whose probabilities (against m) are in `p` and already counted in l:
-//   phase 1   sn = scores of block k+1 (matrix pipe)  ||  p packed into operand slabs (vector pipe)
-//   phase 2   O += P V of block k (matrix pipe)        ||  p = 2^(sn*c - m): block k+1's probabilities, and their sums rs
-// The probabilities of block k+1 are computed against the CURRENT m, before anyone knows whether m has to be raised
-// for them: the caller looks at rs afterwards (see kRescaleTau) and, in the rare case that it must raise m, rescales
-// O and l and recomputes p from sn (which this step leaves untouched); otherwise it adds rs to l.  That way the
-// loop carries the probabilities in the registers they were written to; carrying the SCORES of block k+1 over
-// instead (exponentials at the start of the next step) cost a 16-register copy per step and measured 3 % slower.
-// Operand fragments are read from LDS kPrefetch matrix instructions ahead of their use (the V fragments
-// of phase 2 start arriving during the last slots of phase 1).  No scheduling fences: the compiler keeps the
-// reads ahead by itself here, and with fences per slot the kernel measured 0.5-1 % slower.
-//   mask_next: block k+1 crosses the diagonal of the wave's rows
-//   lim0_next = (absolute row of this lane's query in query block 0) - (first key of block k+1) - 4g
-template <typename RD, typename T, bool HAS_NEXT, int NQ, int NKS, int DB>
-S1F_DEV void fwd_step(f32x16 (&p)[NQ], f32x16 (&sn)[NQ], f32x16 (&o)[NQ][DB], const float (&m)[NQ], float (&rs)[NQ],
-                      const typename Elem<T>::Frag (&qf)[NQ][NKS], const RD &rd,
-                      lds_addr kblock_next, lds_addr vblock, float c, bool mask_next, int lim0_next
-                      ) {
-  typedef typename Elem<T>::Frag Frag;
-  constexpr int NSLAB = 16 / Elem<T>::EPL;
-  constexpr int PF = kPrefetch;
-  constexpr int NV = NSLAB * DB;   // V fragments of the block, in the order (slab, d-block)
-  static_assert(NKS >= PF && NV >= PF, "prefetch ring deeper than the products");
+// Scores of a tile: s[rb][cb] = K[rows 16*rb..] Q[cb]^T   (outside the loop, which uses fwd_step)
+template <typename M, int NC>
+S1F_DEV void fwd_scores(f32x4 (&s)[2][NC], const typename M::RowOp (&q)[NC], const M &rd, lds_addr ktile) {
+#pragma unroll
+  for (int rb = 0; rb < 2; ++rb)
+#pragma unroll
+    for (int cb = 0; cb < NC; ++cb) s[rb][cb] = f32x4{0.f, 0.f, 0.f, 0.f};
+  const typename M::Nat ka = rd.nat_at(ktile);
+#pragma unroll
+  for (int i = 0; i < M::NN; ++i) {
+    const typename M::Frag kf = M::nat(ka, i);
+#pragma unroll
+    for (int cb = 0; cb < NC; ++cb) s[i / M::NK][cb] = M::mma_nat(i, kf, q[cb], s[i / M::NK][cb]);
+    __builtin_amdgcn_sched_barrier(0);   // one operand at a time: reading all of them ahead costs the loop registers
+  }
+}
 
-  Frag vf[PF];
-  Frag pf[NQ][NSLAB];
+// K operands read ahead: those of tile k+2 that the next step begins with are read at the end of this one, so that no
+// step starts by waiting for LDS.
+template <typename M> struct KRing {
+  static constexpr int N = M::NN < 4 ? M::NN : 4;
+  typename M::Frag f[N];
+  S1F_DEV void fill(const typename M::Nat &ka) {
+#pragma unroll
+    for (int i = 0; i < N; ++i) f[i] = M::nat(ka, i);
+  }
+};
+
+// One pipelined step over tile k, whose probabilities (against m) are in `p` and already counted in l:
+//   phase 1   sn = scores of tile k+1, first its upper 16 keys, then its lower 16 (matrix pipe)
+//             ||  p packed into operand slabs, then the probabilities of the upper 16 keys (vector pipe)
+//   phase 2   O += P V of tile k (matrix pipe)  ||  the probabilities of the lower 16 keys, and all their sums rs
+// The probabilities of tile k+1, p = 2^(sn*c - m), are computed against the CURRENT m, before anyone knows whether m
+// has to be raised for them: the caller looks at rs afterwards (see kRescaleTau) and, in the rare case that it must
+// raise m, rescales O and l and computes scores and p of tile k+1 again (its keys are still in the ring); otherwise it
+// adds rs to l.  That way p takes the registers of sn, element by element, and the loop carries it there.
+// The order is pinned slot by slot (one operand, its NC matrix instructions, its share of the vector work): two waves
+// share a SIMD, and left alone the compiler puts LDS reads right before their use and the exponentials in heaps.
+//   MASK: tile k+1 may cross the diagonal of the wave's rows; ahead_next: see fwd_mask
+template <typename M, bool HAS_NEXT, bool MASK, int NC>
+S1F_DEV void fwd_step(f32x4 (&p)[2][NC], f32x4 (&o)[NC][M::DB], const float (&m)[NC], float (&rs)[NC],
+                      const typename M::RowOp (&q)[NC], const M &rd, KRing<M> &kr, lds_addr ktile_next, lds_addr ktile_after,
+                      lds_addr vtile, float c, int ahead_next) {
+  typedef typename M::Frag Frag;
+  constexpr int PK = KRing<M>::N, PV = M::NT < 3 ? M::NT : 3, NK = M::NK, NN = M::NN, NT = M::NT;
+  typename M::Slab pf[NC];
+  Frag vf[PV];
+  f32x4 sn[2][NC];
+  const typename M::Tr va = rd.tr_at(vtile);
+#pragma unroll
+  for (int cb = 0; cb < NC; ++cb) rs[cb] = 0.f;
+  auto pack = [&](int cb) {
+    pf[cb] = M::slab(p[0][cb], p[1][cb]);
+    M::settle_slab(pf[cb]);
+  };
+  auto prob = [&](int x) { return p[x / (4 * NC)][(x >> 2) % NC][x & 3]; };
+  auto probs = [&](int x0, int x1) {   // probabilities x0 .. x1-1 of the tile's 8 * NC per lane
+#pragma unroll
+    for (int x = x0; x < x1; ++x) {
+      const int cb = (x >> 2) % NC;
+      const float t = fmaf(sn[x / (4 * NC)][cb][x & 3], c, -m[cb]);
+      if (x > 0) rs[((x - 1) >> 2) % NC] += prob(x - 1);   // one behind: its result is not ready at once
+      float y = exp2_fast(t);
+      settle(y);
+      p[x / (4 * NC)][cb][x & 3] = y;
+    }
+  };
   if (HAS_NEXT) {
+    const typename M::Nat ka = rd.nat_at(ktile_next);
 #pragma unroll
-    for (int nq = 0; nq < NQ; ++nq)
+    for (int rb = 0; rb < 2; ++rb)
 #pragma unroll
-      for (int v = 0; v < 16; ++v) sn[nq][v] = 0.f;
-    Frag kf[PF];
+      for (int cb = 0; cb < NC; ++cb) sn[rb][cb] = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-    for (int i = 0; i < PF; ++i) kf[i] = rd.nat(kblock_next, i);
+    for (int i = 0; i < NN; ++i) {
 #pragma unroll
-    for (int ks = 0; ks < NKS; ++ks) {
-#pragma unroll
-      for (int nq = 0; nq < NQ; ++nq) sn[nq] = mma(kf[ks % PF], qf[nq][ks], sn[nq]);
-      if (ks + PF < NKS) {
-        kf[ks % PF] = rd.nat(kblock_next, ks + PF);
-      } else {   // the K ring drains: its slots go to the first V fragments
-        const int i = ks + PF - NKS;
-        vf[i] = rd.tr(vblock, i / DB, i % DB);
+      for (int cb = 0; cb < NC; ++cb) {
+        sn[i / NK][cb] = M::mma_nat(i, kr.f[i % PK], q[cb], sn[i / NK][cb]);
+        if (cb + 1 == NC) {
+          if (MASK && i + 1 == NK) fwd_mask(sn, 0, ahead_next);
+          if (MASK && i + 1 == NN) fwd_mask(sn, 1, ahead_next);
+          if (i + PK < NN) kr.f[i % PK] = M::nat(ka, i + PK);
+          if (i + PV >= NN) vf[i + PV - NN] = M::tr(va, i + PV - NN);
+        }
+        // vector work under this matrix instruction (of the other row half: this one's results are still in the pipe)
+        const int w = i * NC + cb, W = NK * NC;
+        if (w < NC) pack(w);
+        if (w >= W) probs(4 * NC * (w - W) / W, 4 * NC * (w - W + 1) / W);
+        __builtin_amdgcn_sched_barrier(0);
       }
     }
   } else {
 #pragma unroll
-    for (int i = 0; i < PF; ++i) vf[i] = rd.tr(vblock, i / DB, i % DB);
+    for (int cb = 0; cb < NC; ++cb) pack(cb);
+#pragma unroll
+    for (int i = 0; i < PV; ++i) vf[i] = M::tr(va, i);
   }
+  const typename M::Nat kb = rd.nat_at(ktile_after);
 #pragma unroll
-  for (int nq = 0; nq < NQ; ++nq)
+  for (int i = 0; i < NT; ++i) {
 #pragma unroll
-    for (int t = 0; t < NSLAB; ++t) pf[nq][t] = block_slab<T>(p[nq], t);
-  // Blocks that cross the diagonal of this wave's rows get their mask here, in a branch of its own that holds
-  // no matrix instruction: two instances of the whole step (with and without mask code) in one loop body make
-  // the compiler keep the output accumulators in two places and copy all 64 registers on every step.
-  if (HAS_NEXT && mask_next) {
-    asm volatile("" ::: "memory");   // keeps this a branch: turned into selects it would run on every step
-#pragma unroll
-    for (int nq = 0; nq < NQ; ++nq)
-#pragma unroll
-      for (int v = 0; v < 16; ++v)
-        if (8 * (v >> 2) + (v & 3) > lim0_next + 32 * nq) sn[nq][v] = -INFINITY;
-  }
-
-#pragma unroll
-  for (int nq = 0; nq < NQ; ++nq) rs[nq] = 0.f;
-#pragma unroll
-  for (int t = 0; t < NSLAB; ++t) {
-#pragma unroll
-    for (int db = 0; db < DB; ++db) {
-      const int i = t * DB + db;
-#pragma unroll
-      for (int nq = 0; nq < NQ; ++nq) o[nq][db] = mma(vf[i % PF], pf[nq][t], o[nq][db]);
-      if (i + PF < NV) vf[i % PF] = rd.tr(vblock, (i + PF) / DB, (i + PF) % DB);
-      if (HAS_NEXT) {   // this slot's share of the next block's 16 probabilities per query block
-#pragma unroll
-        for (int v = 16 * i / NV; v < 16 * (i + 1) / NV; ++v)
-#pragma unroll
-          for (int nq = 0; nq < NQ; ++nq) {
-            p[nq][v] = exp2_fast(fmaf(sn[nq][v], c, -m[nq]));
-            rs[nq] += p[nq][v];
-          }
+    for (int cb = 0; cb < NC; ++cb) {
+      M::mma_tr(i, vf[i % PV], pf[cb], o[cb]);
+      if (cb + 1 == NC) {
+        if (i + PV < NT) vf[i % PV] = M::tr(va, i + PV);
+        if (HAS_NEXT && i + PK >= NT) kr.f[i + PK - NT] = M::nat(kb, i + PK - NT);
       }
+      const int w = i * NC + cb, W = NT * NC;
+      if (HAS_NEXT) probs(4 * NC + 4 * NC * w / W, 4 * NC + 4 * NC * (w + 1) / W);
+      __builtin_amdgcn_sched_barrier(0);
     }
   }
+  if (HAS_NEXT) rs[NC - 1] += prob(8 * NC - 1);
 }
 
-template <typename T, int D, int NQ, int KB, int NW, int OCC>
-__global__ void __launch_bounds__(64 * NW, OCC) seg_attn_fwd_kernel(const AttnArgs a) {
-  typedef Elem<T> E;
-  typedef typename E::Frag Frag;
-  typedef FwdCfg<T, D, NQ, KB, NW> Cfg;
-  typedef typename Cfg::KT KT;
-  constexpr int EPL = E::EPL, KSTEP = 2 * EPL, NKS = D / KSTEP;
-  constexpr int DB = KT::DPAD / 32, BM = Cfg::BM, BN = Cfg::BN;
-  static_assert(D % KSTEP == 0, "shape");
+template <typename T, int D, int NC, int OCC>
+__global__ void __launch_bounds__(256, OCC) seg_attn_fwd_kernel(const AttnArgs a) {
+  typedef FwdCfg<T, D, NC> Cfg;
+  typedef Mat<T, D> M;
+  typedef TileRing<T, D> Ring;
+  constexpr int DB = M::DB, BM = Cfg::BM, BN = Cfg::BN;
 
-  extern __shared__ __attribute__((aligned(8192))) char smem[];
-  const int tid = threadIdx.x, lane = tid & 63, g = lane >> 5, ln = lane & 31;
+  extern __shared__ __attribute__((aligned(1024))) char smem[];
+  const int tid = threadIdx.x, lane = tid & 63, j = lane >> 4, n = lane & 15;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const UnitChunk uc = split_unit(blockIdx.x, a.n_whole, a.n_split, a.n_split_units);
   int qt, bh;
@@ -205,177 +216,136 @@ __global__ void __launch_bounds__(64 * NW, OCC) seg_attn_fwd_kernel(const AttnAr
   qt = a.n_tiles - 1 - qt;   // later (heavier) row tiles are scheduled first
   const int h = bh % a.n_q_heads, b = bh / a.n_q_heads, hk = h / a.group;
   const int seg_len = a.seg_len;
-  const int row0 = qt * BM, wrow0 = row0 + wave * 32 * NQ;
+  const int row0 = qt * BM, wrow0 = row0 + wave * 16 * NC;
   const int last_row = (row0 + BM < seg_len ? row0 + BM : seg_len) - 1;
-  // This workgroup's 32-key blocks: all that hold keys 0 .. seg_off+last_row, or one chunk of them.  From here on
+  // This workgroup's 32-key tiles: all that hold keys 0 .. seg_off+last_row, or one chunk of them.  From here on
   // keys are counted from the chunk's first key: seg_off and kv_len are relative to it.
-  int blk0, blk1;
-  chunk_range(uc, (a.seg_off + row0) / 32, (a.seg_off + last_row) / 32 + 1, blk0, blk1);
-  const int seg_off = a.seg_off - 32 * blk0, kv_len = seg_off + seg_len;
-  const int n_blk = blk1 - blk0;
-  const int n_kt = (n_blk + KB - 1) / KB;
+  int kt0, kt1;
+  chunk_range(uc, (a.seg_off + row0) / BN, (a.seg_off + last_row) / BN + 1, kt0, kt1);
+  const int seg_off = a.seg_off - BN * kt0, kv_len = seg_off + seg_len;
+  const int n_kt = kt1 - kt0;
+  if (n_kt <= 0) {   // more chunks than this unit has whole tiles: a result that the merge gives no weight
+    float *po = a.part + (int64_t)uc.slot * (BM * D);
+    float *pml = a.part_ml + (int64_t)uc.slot * (BM * 2);
+    for (int i = tid; i < BM * D; i += 256) po[i] = 0.f;
+    for (int i = tid; i < BM; i += 256) {
+      pml[2 * i] = -INFINITY;
+      pml[2 * i + 1] = 0.f;
+    }
+    return;
+  }
 
   const T *qb = reinterpret_cast<const T *>(a.q) + b * a.q_sb + h * a.q_sh;
-  const int64_t kv_first = b * a.kv_sb + hk * a.kv_sh + (int64_t)(32 * blk0) * a.kv_ss;
+  const int64_t kv_first = b * a.kv_sb + hk * a.kv_sh + (int64_t)(BN * kt0) * a.kv_ss;
   const T *kbase = reinterpret_cast<const T *>(a.k) + kv_first;
   const T *vbase = reinterpret_cast<const T *>(a.v) + kv_first;
 
-  const lds_addr lds0 = to_lds_addr(smem);
-  // The wave's share of a tile's copy is issued in KB parts, one per 32-key step, so that the waves of the
-  // workgroup do not queue behind each other's copies right after the barrier.
-  constexpr int PER_STEP = (2 * BN * KT::RS / (64 * NW)) / KB;   // copy instructions per wave and step
-  typedef AsyncTilePairU<T, BN, D, NW, (PER_STEP < 4 ? PER_STEP : 4)> LD;
-  static_assert(LD::PARTS % KB == 0, "the copy splits evenly over the 32-key steps");
-  LD ld;
-  ld.init(wave, lane, a.kv_ss);
-  auto issue_part = [&](int jt, int step_part) {
-#pragma unroll
-    for (int p = 0; p < LD::PARTS / KB; ++p)
-      ld.issue_part(step_part * (LD::PARTS / KB) + p, kbase, vbase, a.kv_ss, jt * BN, kv_len,
-                    lds0 + (jt % 3) * Cfg::STAGE_BYTES, wave, lane);
-  };
-  // The same for the tile whose first row `krow`/`vrow` point at and whose ring stage is known: the steady loop
-  // keeps these running instead of deriving them from the tile number on every step.
-  auto issue_part_at = [&](const T *krow, const T *vrow, int rows_left, int stage, int step_part) {
-#pragma unroll
-    for (int p = 0; p < LD::PARTS / KB; ++p)
-      ld.issue_part(step_part * (LD::PARTS / KB) + p, krow, vrow, a.kv_ss, 0, rows_left,
-                    lds0 + stage * Cfg::STAGE_BYTES, wave, lane);
-  };
-  auto issue = [&](int jt) {
-#pragma unroll
-    for (int p = 0; p < KB; ++p) issue_part(jt, p);
-  };
-  issue(0);
-  if (n_kt > 1) issue(1);
+  Ring ring;
+  ring.init(kbase, vbase, a.kv_ss, n_kt, kv_len, to_lds_addr(smem), wave, lane);
+  ring.issue(0);
+  ring.issue(1);
 
-  Frag qf[NQ][NKS];
+  typename M::RowOp q[NC];
 #pragma unroll
-  for (int nq = 0; nq < NQ; ++nq) {
-    int r = wrow0 + 32 * nq + ln;
+  for (int cb = 0; cb < NC; ++cb) {
+    int r = wrow0 + 16 * cb + n;
     r = r < seg_len ? r : seg_len - 1;   // rows past the segment are computed on a copy and never stored
-    const T *p = qb + (int64_t)r * a.q_ss + EPL * g;
-#pragma unroll
-    for (int ks = 0; ks < NKS; ++ks) qf[nq][ks] = load_frag_global<T>(p + ks * KSTEP);
+    M::load_row(q[cb], qb + (int64_t)r * a.q_ss, j);
   }
+#pragma unroll
+  for (int cb = 0; cb < NC; ++cb)
+#pragma unroll
+    for (int i = 0; i < M::NK; ++i) settle(q[cb].f[i]);
 
-  f32x16 o[NQ][DB];
-  float m[NQ], l[NQ];
+  f32x4 o[NC][DB];
 #pragma unroll
-  for (int nq = 0; nq < NQ; ++nq) {
-    m[nq] = -INFINITY;
-    l[nq] = 0.f;
+  for (int cb = 0; cb < NC; ++cb)
 #pragma unroll
-    for (int db = 0; db < DB; ++db)
-#pragma unroll
-      for (int v = 0; v < 16; ++v) o[nq][db][v] = 0.f;
-  }
-  const float c = a.scale * kLog2e;
-
-  FragReader<KT, T> rd;
+    for (int db = 0; db < DB; ++db) o[cb][db] = f32x4{0.f, 0.f, 0.f, 0.f};
+  const float c = uniform(a.scale * kLog2e);
+  M rd;
   rd.init(lane);
-  constexpr int BLOCK_BYTES = 32 * KT::RS * 16;
 
   wait_async_tiles();
+  ring.issue(2);
+  ring.issue(3);
   __syncthreads();
-  f32x16 s[NQ], sn[NQ];
-  float mx[NQ];
-  fwd_scores<FragReader<KT, T>, T, NQ, NKS>(s, qf, rd, lds0);
-  if (31 > seg_off + wrow0) fwd_mask(s, seg_off + wrow0 + ln - 4 * g);
-  fwd_row_max(s, mx, c);
-#pragma unroll
-  for (int nq = 0; nq < NQ; ++nq) m[nq] = mx[nq];   // key 0 is visible to every row: finite
-  float rs[NQ];
-  fwd_probs(s, s, m, c, rs);   // from here on `s` holds the probabilities of the current block, l their sums
-#pragma unroll
-  for (int nq = 0; nq < NQ; ++nq) l[nq] = rs[nq];
+  f32x4 s[2][NC];
+  float m[NC], l[NC], mx[NC], rs[NC];
+  fwd_scores<M, NC>(s, q, rd, ring.st[0]);
+  if (BN - 1 > seg_off + wrow0) {
+    fwd_mask(s, 0, seg_off + wrow0);
+    fwd_mask(s, 1, seg_off + wrow0);
+  }
+  fwd_row_max(s, m, c);      // key 0 is visible to every row: finite
+  fwd_probs(s, s, m, c, l);  // from here on `s` holds the probabilities of the current tile, l their sums
 
-  // The steady loop never touches O except through the matrix pipe.  When some row of the wave has to
-  // raise its running maximum the loop is left, O and l are rescaled, and the loop is entered again.
-  typedef FragReader<KT, T> RD;
-  int k = 0;
-  // Ring stages of the tiles holding block k (st_cur) and block k + 1 (st_next), and the tile that the next copy
-  // fills: its first K and V rows, the rows of the prefix from there on, its stage.
-  int st_cur = 0, st_next = KB == 1 ? 1 : 0;
-  int jt_iss = 2, st_iss = 2, rows_iss = kv_len - 2 * BN;
-  const T *k_iss = kbase + (int64_t)(2 * BN) * a.kv_ss, *v_iss = vbase + (int64_t)(2 * BN) * a.kv_ss;
-  while (true) {
-    bool raise_any = false;
-    while (k + 1 < n_blk) {
-      const int kb = k % KB;
-      if (kb == KB - 1) {
-        wait_async_tiles();   // this wave's part of the next tile has landed (it was issued a whole tile ago)
-        __syncthreads();      // ... and everyone's; every wave has also finished reading the previous tile
-      }
-      // the tile two ahead of block k's (for kb = KB-1; the later parts follow in the steps of the next tile) goes
-      // to the stage of the tile before block k's
-      {
-        const int part = (kb + 1) % KB;
-        const bool copying = KB == 1 || k > 0;   // tiles 0 and 1 were copied whole before the loop
-        if (copying && jt_iss < n_kt) issue_part_at(k_iss, v_iss, rows_iss, st_iss, part);
-        if (copying && part == KB - 1) {   // that tile's copy is complete: move on to the following one
-          ++jt_iss;
-          st_iss = st_iss == 2 ? 0 : st_iss + 1;
-          rows_iss -= BN;
-          k_iss += (int64_t)BN * a.kv_ss;
-          v_iss += (int64_t)BN * a.kv_ss;
-        }
-      }
-      const lds_addr vblock = lds0 + st_cur * Cfg::STAGE_BYTES + KT::BYTES + kb * BLOCK_BYTES;
-      const int kn = k + 1;
-      const lds_addr kblock_next = lds0 + st_next * Cfg::STAGE_BYTES + (kn % KB) * BLOCK_BYTES;
-      const int lim0n = seg_off + wrow0 + ln - 32 * kn - 4 * g;
-      // the last block always crosses the diagonal; earlier ones do if their last key is past the wave's first row
-      const bool mask_next = kn + 1 == n_blk || 32 * kn + 31 > seg_off + wrow0;
-      fwd_step<RD, T, true>(s, sn, o, m, rs, qf, rd, kblock_next, vblock, c, mask_next, lim0n);
-      k = kn;
-      st_cur = st_next;
-      if ((k + 1) % KB == 0) st_next = st_next == 2 ? 0 : st_next + 1;
-      bool raise = false;
-#pragma unroll
-      for (int nq = 0; nq < NQ; ++nq) raise = raise || !(rs[nq] <= kRescaleLimit);
-      if (__builtin_amdgcn_ballot_w64(raise) != 0) { raise_any = true; break; }
-#pragma unroll
-      for (int nq = 0; nq < NQ; ++nq) l[nq] += rs[nq];
-    }
-    if (!raise_any) break;
-    fwd_row_max(sn, mx, c);
-#pragma unroll
-    for (int nq = 0; nq < NQ; ++nq) {
-      const float m_up = mx[nq] > m[nq] + (kRescaleTau - 4.f) ? mx[nq] : m[nq];
-      const float alpha = exp2_fast(m[nq] - m_up);   // exactly 1 for rows that keep their maximum
-      m[nq] = m_up;
-      l[nq] *= alpha;
-#pragma unroll
-      for (int db = 0; db < DB; ++db) o[nq][db] = o[nq][db] * alpha;
-    }
-    fwd_probs(s, sn, m, c, rs);   // the current block's probabilities again, against the raised maxima
-#pragma unroll
-    for (int nq = 0; nq < NQ; ++nq) l[nq] += rs[nq];
+  int k = 0;   // current tile
+  if (wrow0 >= seg_len) {   // no rows of its own: the wave only copies its share of the tiles
+    for (; k + 1 < n_kt; ++k, ring.end_step()) ring.template begin_step<false>(n_kt - 1 - k);
+    return;
   }
-  {   // last block: no next scores to compute
-    const lds_addr vblock = lds0 + st_cur * Cfg::STAGE_BYTES + KT::BYTES + (k % KB) * BLOCK_BYTES;
-    fwd_step<RD, T, false>(s, sn, o, m, rs, qf, rd, vblock, vblock, c, false, 0);
-  }
+  KRing<M> kr;
+  kr.fill(rd.nat_at(ring.st[1]));
+  auto steady = [&](auto mask, auto whole) {
+    constexpr bool MASK = decltype(mask)::value, WHOLE = decltype(whole)::value;
+    ring.template begin_step<WHOLE>(n_kt - 1 - k);
+    const int ahead = seg_off + wrow0 - BN * (k + 1);
+    fwd_step<M, true, MASK, NC>(s, o, m, rs, q, rd, kr, ring.st[1], ring.st[2],
+                                ring.st[0] + Tile32<T, D>::BYTES, c, ahead);
+    ++k;
+    ring.end_step();
+    bool raise = false;
+#pragma unroll
+    for (int cb = 0; cb < NC; ++cb) raise = raise || !(rs[cb] <= kRescaleLimit);
+    if (__builtin_expect(__builtin_amdgcn_ballot_w64(raise) != 0, 0)) {
+      asm volatile("" ::: "memory");
+      fwd_scores<M, NC>(s, q, rd, ring.st[0]);
+      if (MASK) {
+        fwd_mask(s, 0, ahead);
+        fwd_mask(s, 1, ahead);
+      }
+      fwd_row_max(s, mx, c);
+#pragma unroll
+      for (int cb = 0; cb < NC; ++cb) {
+        const float m_up = mx[cb] > m[cb] + (kRescaleTau - 3.f) ? mx[cb] : m[cb];
+        const float alpha = exp2_fast(m[cb] - m_up);   // exactly 1 for rows that keep their maximum
+        m[cb] = m_up;
+        l[cb] *= alpha;
+#pragma unroll
+        for (int db = 0; db < DB; ++db) o[cb][db] = o[cb][db] * alpha;
+      }
+      fwd_probs(s, s, m, c, rs);   // the current tile's probabilities again, against the raised maxima
+    }
+#pragma unroll
+    for (int cb = 0; cb < NC; ++cb) l[cb] += rs[cb];
+  };
+  // Tiles that every row of the wave sees in full, first while there is a whole tile to copy (no branches in the step),
+  // then those on the diagonal (the last tile always is; which others are differs between the waves, but every wave
+  // takes one step and one barrier per tile).  A branch around the mask inside one loop would part the step where its
+  // two phases overlap.
+  const std::integral_constant<bool, true> yes;
+  const std::integral_constant<bool, false> no;
+  int n_full = (seg_off + wrow0 + 1) / BN;
+  n_full = n_full < n_kt - 1 ? n_full : n_kt - 1;
+  const int n_fast = n_full < n_kt - 4 ? n_full : n_kt - 4;
+  while (k + 1 < n_fast) steady(no, yes);
+  while (k + 1 < n_full) steady(no, no);
+  while (k + 1 < n_kt) steady(yes, no);
+  // last tile: no next scores to compute
+  fwd_step<M, false, false, NC>(s, o, m, rs, q, rd, kr, ring.st[0], ring.st[0], ring.st[0] + Tile32<T, D>::BYTES, c, 0);
 
   if (uc.slot >= 0) {   // a chunk: unnormalised output rows, running maximum and row sum go to the workspace
     float *po = a.part + (int64_t)uc.slot * (BM * D);
     float *pml = a.part_ml + (int64_t)uc.slot * (BM * 2);
 #pragma unroll
-    for (int nq = 0; nq < NQ; ++nq) {
-      const float lt = sum_xor32(l[nq]);
-      const int rl = wave * 32 * NQ + 32 * nq + ln;   // row within the unit
+    for (int cb = 0; cb < NC; ++cb) {
+      const float lt = sum_over_rows(l[cb]);
+      const int rl = wave * 16 * NC + 16 * cb + n;   // row within the unit
 #pragma unroll
-      for (int db = 0; db < DB; ++db)
-#pragma unroll
-        for (int vq = 0; vq < 4; ++vq) {
-          const int d0 = 32 * db + 8 * vq + 4 * g;
-          if (d0 < D)
-            store4<float>(po + rl * D + d0, o[nq][db][4 * vq], o[nq][db][4 * vq + 1], o[nq][db][4 * vq + 2],
-                          o[nq][db][4 * vq + 3]);
-        }
-      if (g == 0) {
-        pml[2 * rl] = m[nq];
+      for (int x = 0; x < DB; ++x) *reinterpret_cast<f32x4 *>(po + rl * D + M::quad_d0(x, j)) = M::quad(o[cb], x);
+      if (j == 0) {
+        pml[2 * rl] = m[cb];
         pml[2 * rl + 1] = lt;
       }
     }
@@ -384,22 +354,18 @@ __global__ void __launch_bounds__(64 * NW, OCC) seg_attn_fwd_kernel(const AttnAr
   T *ob = reinterpret_cast<T *>(a.out_w) + b * a.q_sb + h * a.q_sh;
   float *lse = a.lse + ((int64_t)b * a.n_q_heads + h) * seg_len;
 #pragma unroll
-  for (int nq = 0; nq < NQ; ++nq) {
-    const float lt = sum_xor32(l[nq]);
+  for (int cb = 0; cb < NC; ++cb) {
+    const float lt = sum_over_rows(l[cb]);
     const float inv = 1.f / lt;
-    const int r = wrow0 + 32 * nq + ln;
+    const int r = wrow0 + 16 * cb + n;
     if (r < seg_len) {
       T *orow = ob + (int64_t)r * a.q_ss;
 #pragma unroll
-      for (int db = 0; db < DB; ++db)
-#pragma unroll
-        for (int vq = 0; vq < 4; ++vq) {
-          const int d0 = 32 * db + 8 * vq + 4 * g;
-          if (d0 < D)
-            store4<T>(orow + d0, o[nq][db][4 * vq] * inv, o[nq][db][4 * vq + 1] * inv, o[nq][db][4 * vq + 2] * inv,
-                      o[nq][db][4 * vq + 3] * inv);
-        }
-      if (g == 0) lse[r] = (m[nq] + __builtin_amdgcn_logf(lt)) * kLn2;
+      for (int x = 0; x < DB; ++x) {
+        const f32x4 y = M::quad(o[cb], x) * inv;
+        store4<T>(orow + M::quad_d0(x, j), y[0], y[1], y[2], y[3]);
+      }
+      if (j == 0) lse[r] = (m[cb] + __builtin_amdgcn_logf(lt)) * kLn2;
     }
   }
 }
@@ -412,12 +378,13 @@ __global__ void __launch_bounds__(64 * NW, OCC) seg_attn_fwd_kernel(const AttnAr
 template <int D> struct MergeRows {
   static constexpr int C4 = D / 4;          // threads per row
   static constexpr int RG = 256 / C4;       // rows per workgroup
-  static constexpr int groups(int bm) { return (bm + RG - 1) / RG; }
+  __host__ __device__ static constexpr int groups(int bm) { return (bm + RG - 1) / RG; }
 };
-template <typename T, int D, int BM>
+template <typename T, int D>
 __global__ void __launch_bounds__(256) seg_attn_fwd_merge_kernel(const AttnArgs a) {
   typedef MergeRows<D> MR;
-  const int unit = (int)blockIdx.x / MR::groups(BM), rg = (int)blockIdx.x % MR::groups(BM);
+  const int BM = a.bm, groups = MR::groups(BM);
+  const int unit = (int)blockIdx.x / groups, rg = (int)blockIdx.x % groups;
   const int rl = rg * MR::RG + (int)threadIdx.x / MR::C4, c4 = (int)threadIdx.x % MR::C4;
   int qt, bh;
   decode_workgroup(a.n_whole + unit, a.n_tiles, a.n_bh, a.tile_major, qt, bh);

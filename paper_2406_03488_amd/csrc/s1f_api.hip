@@ -16,7 +16,7 @@ using namespace s1f;
 // Tile shapes per element type: query blocks per wave (NQ), key blocks per wave (NK), keys per staged
 // K/V tile (BN), rows per staged Q/dO tile (BQ).
 template <typename T> struct Shape;
-//   forward: FNQ query blocks per wave, FKB 32-key blocks per LDS tile, FNW waves, FOCC waves per SIMD
+//   forward: FNC column blocks of 16 rows per wave, FOCC waves per SIMD
 //   dq:      QNQ, QBN keys per LDS tile, QOCC;   dk/dv: KNW waves (32 keys each), copy distance KDIST, phase lag KLAG,
 //            KWGS workgroups per compute unit
 // bf16 dK/dV: two workgroups of 128 keys per compute unit, each with a two-stage tile ring.  Their barriers are
@@ -25,11 +25,11 @@ template <typename T> struct Shape;
 // one workgroup of 256 keys whose upper waves run one phase late (KNW = 8, KDIST = 2, KLAG = 1, KWGS = 1).
 // bf16 dQ: 32-key tiles; 64-key tiles measure the same within noise and hold twice the LDS.
 template <> struct Shape<bf16_t> {
-  static constexpr int FNQ = 1, FKB = 1, FNW = 4, FOCC = 3, QNQ = 1, QBN = 32, QOCC = 2, KNW = 4, KDIST = 1, KLAG = 0,
+  static constexpr int FNC = 3, FOCC = 2, QNQ = 1, QBN = 32, QOCC = 2, KNW = 4, KDIST = 1, KLAG = 0,
                        KWGS = 2;
 };
 template <> struct Shape<float> {
-  static constexpr int FNQ = 1, FKB = 1, FNW = 4, FOCC = 1, QNQ = 1, QBN = 32, QOCC = 1, KNW = 4, KDIST = 1, KLAG = 0,
+  static constexpr int FNC = 2, FOCC = 1, QNQ = 1, QBN = 32, QOCC = 1, KNW = 4, KDIST = 1, KLAG = 0,
                        KWGS = 1;
 };
 
@@ -206,16 +206,16 @@ inline size_t align256(size_t x) { return (x + 255) & ~(size_t)255; }
 // ---- forward ----
 template <typename T, int D> struct FwdLaunch {
   typedef Shape<T> S;
-  typedef FwdCfg<T, D, S::FNQ, S::FKB, S::FNW> Cfg;
+  typedef FwdCfg<T, D, S::FNC> Cfg;
   static constexpr int64_t kPartBytes = (int64_t)Cfg::BM * D * 4, kMlBytes = (int64_t)Cfg::BM * 2 * 4;
-  static auto kernel() { return seg_attn_fwd_kernel<T, D, S::FNQ, S::FKB, S::FNW, S::FOCC>; }
+  static auto kernel() { return seg_attn_fwd_kernel<T, D, S::FNC, S::FOCC>; }
   static int64_t tiles(int64_t seg_len) { return (seg_len + Cfg::BM - 1) / Cfg::BM; }
   // `split`: the caller brought a workspace (only the bf16 kernels split; fp32 is the reference-precision mode)
   static SplitPlan plan(const s1f_desc *d, int64_t seg_off, int64_t seg_len, bool split) {
     const int64_t units = tiles(seg_len) * d->n_q_heads * d->batch;
     if (!split || sizeof(T) != 2) return plan_split(units, 0, 0, 0, 0, 0);
     return plan_split(units, resident_workgroups(kernel(), Cfg::THREADS, Cfg::LDS_BYTES), seg_off,
-                      kFwdSecondsPerKey * (double)(seg_off + seg_len / 2), kPartBytes + kMlBytes, kMaxPartBytes);
+                      kFwdSecondsPerKey * Cfg::BM / 128 * (double)(seg_off + seg_len / 2), kPartBytes + kMlBytes, kMaxPartBytes);
   }
   static size_t workspace_bytes(const SplitPlan &p) {
     const int64_t chunks = p.n_split_units * p.n_split;
@@ -237,7 +237,8 @@ int fwd_impl(const s1f_desc *d, AttnArgs a, hipStream_t st, void *workspace, siz
   if (rc != S1F_OK || chunks == 0) return rc;
   a.n_tiles = (int32_t)L::tiles(a.seg_len); a.n_bh = (int32_t)n_bh; a.tile_major = order;
   a.n_whole = (int32_t)p.n_whole; a.n_split = p.n_split; a.n_split_units = (int32_t)p.n_split_units;
-  return launch_merge(seg_attn_fwd_merge_kernel<T, D, L::Cfg::BM>, a, p, MergeRows<D>::groups(L::Cfg::BM), st);
+  a.bm = L::Cfg::BM;
+  return launch_merge(seg_attn_fwd_merge_kernel<T, D>, a, p, MergeRows<D>::groups(L::Cfg::BM), st);
 }
 template <typename T, int D> size_t fwd_ws_impl(const s1f_desc *d, int64_t seg_off, int64_t seg_len) {
   return FwdLaunch<T, D>::workspace_bytes(FwdLaunch<T, D>::plan(d, seg_off, seg_len, true));
