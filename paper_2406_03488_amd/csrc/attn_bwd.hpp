@@ -11,41 +11,49 @@
 // The probabilities are recomputed in both (7 matrix products in total instead of 5) in exchange for
 // deterministic sums and no dQ workspace.
 #pragma once
-#include "attn_device.hpp"
+#include <type_traits>
+
+#include "attn_tile.hpp"
 
 
 namespace s1f {
 
-template <typename T, int D, int NQ, int BN> struct BwdDqCfg {
-  static constexpr int BM = 128 * NQ;
-  typedef LdsTile<T, BN, D> KT;
-  static constexpr int STAGE_BYTES = 2 * KT::BYTES;    // K tile, V tile right behind it
-  static constexpr int LDS_BYTES = 2 * STAGE_BYTES;    // two stages
-  static_assert(STAGE_BYTES % 8192 == 0, "stages must keep the 8 KiB alignment of the fragment reader");
+template <typename T, int D, int NC> struct BwdDqCfg {
+  static constexpr int BM = 64 * NC, BN = 32, THREADS = 256;
+  static constexpr int LDS_BYTES = TileRing<T, D>::LDS_BYTES;
 };
 
-// Lane = one query (column ln); keys run over registers.
+// One workgroup (4 waves) owns 64*NC query rows of one head, a wave NC column blocks of 16; lane = one query per column
+// block, keys run over registers.
 //   S^T[key][q]  = K Q^T      A = K (LDS),            B = Q (registers)
 //   dP^T[key][q] = V dO^T     A = V (LDS),            B = dO (registers)
 //   dQ^T[d][q]  += K^T dS^T   A = K read transposed,  B = dS^T slab (registers)
-// The accumulators of the first two products start from the row statistics (-lse/scale and -delta, the
-// same in every register of a lane) so that p = exp2(c * s) and dS = p * dp need no further operand.
-// K/V tiles are copied HBM -> LDS asynchronously, one tile ahead of their use.
-template <typename T, int D, int NQ, int BN, int OCC>
-__global__ void __launch_bounds__(256, OCC) seg_attn_bwd_dq_kernel(const AttnArgs a) {
-  typedef Elem<T> E;
-  typedef typename E::Frag Frag;
-  typedef BwdDqCfg<T, D, NQ, BN> Cfg;
-  typedef LdsTile<T, BN, D> KT;
-  typedef FragReader<KT, T> RD;
-  constexpr int EPL = E::EPL, KSTEP = 2 * EPL, NKS = D / KSTEP;
-  constexpr int DB = KT::DPAD / 32, NSLAB = 16 / EPL, KB = BN / 32;
-  constexpr int BM = 128 * NQ;
-  constexpr int BLOCK_BYTES = 32 * KT::RS * 16;
-  constexpr int PF = NKS >= 3 ? 3 : 2;   // operand fragments in flight ahead of their use
+// The accumulators of dP start from -delta (the same in every register of a lane), so that dS = p * dp.
+// K/V tiles of 32 keys travel through a ring as in the forward, with one barrier per tile.  The loop is
+// software-pipelined so that every phase has matrix instructions that do not wait for its vector work:
+//   A  S(k+1)                ||  dS(k) = p(k) * dP(k), packed
+//   B  dQ += K(k)^T dS(k)    ||  p(k+1) = exp2(c * S(k+1) - lse)
+//   C  dP(k+1)
+// The order is pinned matrix instruction by matrix instruction; LDS operands are read kDqRing operands ahead.
+// Bound by the matrix pipe at the clock the power limit leaves (head_dim 128: 60 % busy at 1.85 GHz), with 64 registers
+// of accumulators and 64 of Q and dO per lane at NC = 2.  32 heads, 4096 rows behind 28672 keys: head_dim 128
+// 2.52 -> 2.29 ms (three products executed: 1230 -> 1350 TFLOP/s), 80 1.89 -> 1.57 ms and 64 1.54 -> 1.26 ms (NC = 3).
+// One wave per SIMD with 64 rows (half the LDS reads) ran 15 % slower: half of its registers are accumulator
+// registers, which the vector phases reach by copies only.
+constexpr int kDqRing = 4;
 
-  extern __shared__ __attribute__((aligned(8192))) char smem[];
-  const int tid = threadIdx.x, lane = tid & 63, g = lane >> 5, ln = lane & 31;
+template <typename T, int D, int NC, int OCC>
+__global__ void __launch_bounds__(256, OCC) seg_attn_bwd_dq_kernel(const AttnArgs a) {
+  typedef BwdDqCfg<T, D, NC> Cfg;
+  typedef Mat<T, D> M;
+  typedef typename M::Frag Frag;
+  typedef TileRing<T, D> Ring;
+  constexpr int DB = M::DB, BM = Cfg::BM, BN = Cfg::BN, NN = M::NN, NK = M::NK, NT = M::NT, PR = kDqRing;
+  constexpr int TOTAL = NN + NT + NN;
+  static_assert(NN >= PR && NT >= PR, "operand ring deeper than a product");
+
+  extern __shared__ __attribute__((aligned(1024))) char smem[];
+  const int tid = threadIdx.x, lane = tid & 63, j = lane >> 4, n = lane & 15;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const UnitChunk uc = split_unit(blockIdx.x, a.n_whole, a.n_split, a.n_split_units);
   int qt, bh;
@@ -53,7 +61,7 @@ __global__ void __launch_bounds__(256, OCC) seg_attn_bwd_dq_kernel(const AttnArg
   qt = a.n_tiles - 1 - qt;   // later (heavier) row tiles are scheduled first
   const int h = bh % a.n_q_heads, b = bh / a.n_q_heads, hk = h / a.group;
   const int seg_len = a.seg_len;
-  const int row0 = qt * BM, wrow0 = row0 + wave * 32 * NQ;
+  const int row0 = qt * BM, wrow0 = row0 + wave * 16 * NC;
   const int last_row = (row0 + BM < seg_len ? row0 + BM : seg_len) - 1;
   // This workgroup's key tiles: all that hold keys 0 .. seg_off+last_row, or one chunk of them.  From here on keys
   // are counted from the chunk's first key: seg_off and kv_len are relative to it.
@@ -63,167 +71,215 @@ __global__ void __launch_bounds__(256, OCC) seg_attn_bwd_dq_kernel(const AttnArg
   const int n_kt = kt1 - kt0;
 
   const int64_t qoff = b * a.q_sb + h * a.q_sh;
-  const T *qb = reinterpret_cast<const T *>(a.q) + qoff;
-  const T *dob = reinterpret_cast<const T *>(a.dout) + qoff;
-  const T *ob = reinterpret_cast<const T *>(a.out) + qoff;
   const int64_t kv_first = b * a.kv_sb + hk * a.kv_sh + (int64_t)(BN * kt0) * a.kv_ss;
-  const T *kbase = reinterpret_cast<const T *>(a.k) + kv_first;
-  const T *vbase = reinterpret_cast<const T *>(a.v) + kv_first;
-  const int64_t lse_off = ((int64_t)b * a.n_q_heads + h) * seg_len;
-  const lds_addr lds0 = to_lds_addr(smem);
-  AsyncTilePairU<T, BN, D, 4> ld;
-  ld.init(wave, lane, a.kv_ss);
-  RD rd;
-  rd.init(lane);
-  ld.issue(kbase, vbase, a.kv_ss, 0, kv_len, lds0, wave, lane);
+  Ring ring;
+  ring.init(reinterpret_cast<const T *>(a.k) + kv_first, reinterpret_cast<const T *>(a.v) + kv_first, a.kv_ss, n_kt, kv_len,
+            to_lds_addr(smem), wave, lane);
+  ring.issue(0);
+  ring.issue(1);
 
-  Frag qf[NQ][NKS], dof[NQ][NKS];
-  float nl[NQ], nd[NQ];   // -lse/scale and -delta of the lane's rows
+  typename M::RowOp q[NC], dor[NC];
+  float nl[NC];    // -lse in log2 units
+  f32x4 nd[NC];    // -delta
 #pragma unroll
-  for (int nq = 0; nq < NQ; ++nq) {
-    const int r = wrow0 + 32 * nq + ln;
-    const int rc = r < seg_len ? r : seg_len - 1;
-    const int64_t off = (int64_t)rc * a.q_ss + EPL * g;
-    float part = 0.f;
-#pragma unroll
-    for (int ks = 0; ks < NKS; ++ks) {
-      qf[nq][ks] = load_frag_global<T>(qb + off + ks * KSTEP);
-      dof[nq][ks] = load_frag_global<T>(dob + off + ks * KSTEP);
-      part += frag_dot<T>(dof[nq][ks], load_frag_global<T>(ob + off + ks * KSTEP));
-    }
-    nd[nq] = -sum_xor32(part);
-    nl[nq] = -a.lse[lse_off + rc] / a.scale;
-    if (r < seg_len && g == 0 && uc.chunk == 0) {   // row statistics for the dK/dV kernel
-      a.delta[lse_off + r] = nl[nq];
-      a.delta[a.ws_plane + lse_off + r] = nd[nq];
+  for (int cb = 0; cb < NC; ++cb) {
+    const int r = wrow0 + 16 * cb + n, rc = r < seg_len ? r : seg_len - 1;
+    const int64_t off = qoff + (int64_t)rc * a.q_ss;
+    M::load_row(q[cb], reinterpret_cast<const T *>(a.q) + off, j);
+    M::load_row(dor[cb], reinterpret_cast<const T *>(a.dout) + off, j);
+    typename M::RowOp o;
+    M::load_row(o, reinterpret_cast<const T *>(a.out) + off, j);
+    const float d = -sum_over_rows(M::dot(dor[cb], o));
+    nd[cb] = f32x4{d, d, d, d};
+    const int64_t at = ((int64_t)b * a.n_q_heads + h) * seg_len + rc;
+    const float lse = a.lse[at];
+    nl[cb] = -lse * kLog2e;
+    if (r < seg_len && j == 0 && uc.chunk == 0) {   // row statistics for the dK/dV kernel
+      a.delta[at] = -lse / a.scale;
+      a.delta[a.ws_plane + at] = d;
     }
   }
+  f32x4 dq[NC][DB];
+#pragma unroll
+  for (int cb = 0; cb < NC; ++cb)
+#pragma unroll
+    for (int db = 0; db < DB; ++db) dq[cb][db] = f32x4{0.f, 0.f, 0.f, 0.f};
+  const float c = uniform(a.scale * kLog2e);
+  M rd;
+  rd.init(lane);
+#pragma unroll
+  for (int cb = 0; cb < NC; ++cb)
+#pragma unroll
+    for (int i = 0; i < M::NK; ++i) { settle(q[cb].f[i]); settle(dor[cb].f[i]); }
 
-  f32x16 dq[NQ][DB];
-#pragma unroll
-  for (int nq = 0; nq < NQ; ++nq)
-#pragma unroll
-    for (int db = 0; db < DB; ++db)
-#pragma unroll
-      for (int v = 0; v < 16; ++v) dq[nq][db][v] = 0.f;
-
-  const bool w_active = wrow0 < seg_len;
-  const int w_last = (wrow0 + 32 * NQ < seg_len ? wrow0 + 32 * NQ : seg_len) - 1;
-  const float c = a.scale * kLog2e;
+  if (n_kt <= 0) {   // more chunks than this unit has whole tiles: nothing to add
+    float *pd = a.part + (int64_t)uc.slot * (BM * D);
+    for (int i = tid; i < BM * D; i += 256) pd[i] = 0.f;
+    return;
+  }
   wait_async_tiles();
+  ring.issue(2);
+  ring.issue(3);
   __syncthreads();
+  int k = 0;   // current tile
+  if (wrow0 >= seg_len) {   // no rows of its own: the wave only copies its share of the tiles
+    for (; k + 1 < n_kt; ++k, ring.end_step()) ring.template begin_step<false>(n_kt - 1 - k);
+    return;
+  }
+  const int wfirst = seg_off + wrow0;   // last key that the wave's first row sees
+  // Hidden scores of a tile on the diagonal get probability zero (whatever the exponential made of them).
+  auto hide = [&](f32x4 (&p)[2][NC], int key0) {
+    const int ln = lane_id(), lim = wfirst - key0 + (ln & 15) - 4 * (ln >> 4);
+#pragma unroll
+    for (int rb = 0; rb < 2; ++rb)
+#pragma unroll
+      for (int cb = 0; cb < NC; ++cb)
+#pragma unroll
+        for (int v = 0; v < 4; ++v)
+          if (16 * rb + v > lim + 16 * cb) p[rb][cb][v] = 0.f;
+  };
 
-  for (int jt = 0; jt < n_kt; ++jt) {
-    const lds_addr ktile = lds0 + (jt & 1) * Cfg::STAGE_BYTES;   // the V tile lies KT::BYTES behind it
-    const int key0 = jt * BN;
-    // the other stage was last read before the barrier that ended the previous iteration
-    if (jt + 1 < n_kt) ld.issue(kbase, vbase, a.kv_ss, key0 + BN, kv_len, lds0 + ((jt + 1) & 1) * Cfg::STAGE_BYTES, wave, lane);
-    if (w_active && key0 <= seg_off + w_last) {
+  // Tile 0: S, p and dP by themselves.
+  f32x4 p[2][NC], dp[2][NC];
+  {
+    const typename M::Nat ka = rd.nat_at(ring.st[0]);
 #pragma unroll
-      for (int kb = 0; kb < KB; ++kb) {
-        const int kb0 = key0 + 32 * kb;
-        if (kb0 > seg_off + w_last) continue;
-        const lds_addr kblock = ktile + kb * BLOCK_BYTES;
-        f32x16 s[NQ], dp[NQ];
+    for (int i = 0; i < NN; ++i) {
+      const Frag kf = M::nat(ka, i), vf = M::nat(ka, i, Tile32<T, D>::BYTES);
 #pragma unroll
-        for (int nq = 0; nq < NQ; ++nq)
-#pragma unroll
-          for (int v = 0; v < 16; ++v) { s[nq][v] = nl[nq]; dp[nq][v] = nd[nq]; }
-        // K and V fragments are read from LDS PF steps ahead of the matrix instructions that use them
-        {
-          Frag kf[PF], vf[PF];
-#pragma unroll
-          for (int i = 0; i < PF; ++i) rd.nat2(kblock, KT::BYTES, i, kf[i], vf[i]);
-          __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-          for (int ks = 0; ks < NKS; ++ks) {
-#pragma unroll
-            for (int nq = 0; nq < NQ; ++nq) {
-              s[nq] = mma(kf[ks % PF], qf[nq][ks], s[nq]);
-              dp[nq] = mma(vf[ks % PF], dof[nq][ks], dp[nq]);
-            }
-            if (ks + PF < NKS) rd.nat2(kblock, KT::BYTES, ks + PF, kf[ks % PF], vf[ks % PF]);
-            __builtin_amdgcn_sched_barrier(0);
-          }
-        }
-        // register v holds key kb0 + 8*(v/4) + 4*g + v%4, visible to row r iff key <= seg_off + r; only
-        // the blocks on the diagonal need the test
-        if (kb0 + 31 > seg_off + wrow0) {
-#pragma unroll
-          for (int nq = 0; nq < NQ; ++nq) {
-            const int lim = seg_off + wrow0 + 32 * nq + ln - (kb0 + 4 * g);
-#pragma unroll
-            for (int v = 0; v < 16; ++v) {
-              float p = exp2_fast(s[nq][v] * c);
-              if (8 * (v >> 2) + (v & 3) > lim) p = 0.f;
-              s[nq][v] = p * dp[nq][v];   // dS^T
-            }
-          }
-        } else {
-#pragma unroll
-          for (int nq = 0; nq < NQ; ++nq)
-#pragma unroll
-            for (int v = 0; v < 16; ++v) s[nq][v] = exp2_fast(s[nq][v] * c) * dp[nq][v];
-        }
-#pragma unroll
-        for (int t = 0; t < NSLAB; ++t) {
-          Frag dsf[NQ];
-#pragma unroll
-          for (int nq = 0; nq < NQ; ++nq) dsf[nq] = block_slab<T>(s[nq], t);
-#pragma unroll
-          for (int db = 0; db < DB; ++db) {
-            const Frag ktf = rd.tr(kblock, t, db);
-#pragma unroll
-            for (int nq = 0; nq < NQ; ++nq) dq[nq][db] = mma(ktf, dsf[nq], dq[nq][db]);
-          }
-        }
+      for (int cb = 0; cb < NC; ++cb) {
+        const f32x4 zero = {0.f, 0.f, 0.f, 0.f};
+        p[i / NK][cb] = M::mma_nat(i, kf, q[cb], i % NK ? p[i / NK][cb] : zero);
+        dp[i / NK][cb] = M::mma_nat(i, vf, dor[cb], i % NK ? dp[i / NK][cb] : nd[cb]);
       }
+      __builtin_amdgcn_sched_barrier(0);
     }
-    wait_async_tiles();   // this wave's part of the next tile has landed
-    __syncthreads();
+#pragma unroll
+    for (int rb = 0; rb < 2; ++rb)
+#pragma unroll
+      for (int cb = 0; cb < NC; ++cb)
+#pragma unroll
+        for (int v = 0; v < 4; ++v) p[rb][cb][v] = exp2_fast(fmaf(p[rb][cb][v], c, nl[cb]));
+    if (BN - 1 > wfirst) hide(p, 0);
+  }
+  Frag fr[PR];   // operand ring: operand x of a step sits in fr[x % PR]
+  {
+    const typename M::Nat ka = rd.nat_at(ring.st[1]);
+#pragma unroll
+    for (int i = 0; i < PR; ++i) fr[i] = M::nat(ka, i);
+  }
+  typename M::Slab ds[NC];
+  auto make_ds = [&](int cb) {
+    ds[cb] = M::slab(p[0][cb] * dp[0][cb], p[1][cb] * dp[1][cb]);
+    M::settle_slab(ds[cb]);
+  };
+  auto step = [&](auto mask, auto whole) {
+    constexpr bool MASK = decltype(mask)::value, WHOLE = decltype(whole)::value;
+    ring.template begin_step<WHOLE>(n_kt - 1 - k);
+    const typename M::Nat kn = rd.nat_at(ring.st[1]), ka = rd.nat_at(ring.st[2]);
+    const typename M::Tr kt = rd.tr_at(ring.st[0]);
+    auto next_operand = [&](int x) {   // operand x has been used up: the one that takes its place
+      const int y = x + PR;
+      if (y < NN) fr[x % PR] = M::nat(kn, y);
+      else if (y < NN + NT) fr[x % PR] = M::tr(kt, y - NN);
+      else if (y < TOTAL) fr[x % PR] = M::nat(kn, y - NN - NT, Tile32<T, D>::BYTES);
+      else fr[x % PR] = M::nat(ka, x % PR);   // the next step's first ones
+    };
+    f32x4 sn[2][NC];
+#pragma unroll
+    for (int i = 0; i < NN; ++i)
+#pragma unroll
+      for (int cb = 0; cb < NC; ++cb) {
+        const f32x4 zero = {0.f, 0.f, 0.f, 0.f};
+        sn[i / NK][cb] = M::mma_nat(i, fr[i % PR], q[cb], i % NK ? sn[i / NK][cb] : zero);
+        if (cb + 1 == NC) next_operand(i);
+        if (i == 1) make_ds(cb);
+        __builtin_amdgcn_sched_barrier(0);
+      }
+    // probability x of 8 * NC: column block by column block, so that half of them do not wait for the last scores
+    auto probs = [&](int x0, int x1) {
+#pragma unroll
+      for (int x = x0; x < x1; ++x) {
+        const int rb = x / (4 * NC), cb = (x >> 2) % NC, v = x & 3;
+        float y = exp2_fast(fmaf(sn[rb][cb][v], c, nl[cb]));
+        settle(y);
+        p[rb][cb][v] = y;
+      }
+    };
+#pragma unroll
+    for (int i = 0; i < NT; ++i)
+#pragma unroll
+      for (int cb = 0; cb < NC; ++cb) {
+        M::mma_tr(i, fr[(NN + i) % PR], ds[cb], dq[cb]);
+        if (cb + 1 == NC) next_operand(NN + i);
+        const int w = i * NC + cb, W = NT * NC;
+        probs(8 * NC * w / W, 8 * NC * (w + 1) / W);
+        __builtin_amdgcn_sched_barrier(0);
+      }
+#pragma unroll
+    for (int i = 0; i < NN; ++i)
+#pragma unroll
+      for (int cb = 0; cb < NC; ++cb) {
+        dp[i / NK][cb] = M::mma_nat(i, fr[(NN + NT + i) % PR], dor[cb], i % NK ? dp[i / NK][cb] : nd[cb]);
+        if (cb + 1 == NC) next_operand(NN + NT + i);
+        if (MASK && i == 0 && cb + 1 == NC) hide(p, BN * (k + 1));
+        __builtin_amdgcn_sched_barrier(0);
+      }
+    ++k;
+    ring.end_step();
+  };
+  int n_full = (wfirst + 1) / BN;   // tiles that every row of the wave sees in full
+  n_full = n_full < n_kt - 1 ? n_full : n_kt - 1;
+  const std::integral_constant<bool, true> yes;
+  const std::integral_constant<bool, false> no;
+  const int n_fast = n_full < n_kt - 4 ? n_full : n_kt - 4;   // ... while there is a whole tile to copy
+  while (k + 1 < n_fast) step(no, yes);
+  while (k + 1 < n_full) step(no, no);
+  while (k + 1 < n_kt) step(yes, no);
+  {   // last tile: dS and dQ
+    const typename M::Tr kt = rd.tr_at(ring.st[0]);
+#pragma unroll
+    for (int cb = 0; cb < NC; ++cb) make_ds(cb);
+#pragma unroll
+    for (int i = 0; i < NT; ++i) {
+      const Frag kf = M::tr(kt, i);
+#pragma unroll
+      for (int cb = 0; cb < NC; ++cb) M::mma_tr(i, kf, ds[cb], dq[cb]);
+      __builtin_amdgcn_sched_barrier(0);
+    }
   }
 
   if (uc.slot >= 0) {   // a chunk: its unscaled share of the unit's dQ rows goes to the workspace
     float *pd = a.part + (int64_t)uc.slot * (BM * D);
 #pragma unroll
-    for (int nq = 0; nq < NQ; ++nq) {
-      const int rl = wave * 32 * NQ + 32 * nq + ln;   // row within the unit
+    for (int cb = 0; cb < NC; ++cb) {
+      const int rl = wave * 16 * NC + 16 * cb + n;   // row within the unit
 #pragma unroll
-      for (int db = 0; db < DB; ++db)
-#pragma unroll
-        for (int vq = 0; vq < 4; ++vq) {
-          const int d0 = 32 * db + 8 * vq + 4 * g;
-          if (d0 < D)
-            store4<float>(pd + rl * D + d0, dq[nq][db][4 * vq], dq[nq][db][4 * vq + 1], dq[nq][db][4 * vq + 2],
-                          dq[nq][db][4 * vq + 3]);
-        }
+      for (int x = 0; x < DB; ++x) *reinterpret_cast<f32x4 *>(pd + rl * D + M::quad_d0(x, j)) = M::quad(dq[cb], x);
     }
     return;
   }
   T *dqb = reinterpret_cast<T *>(a.dq) + qoff;
 #pragma unroll
-  for (int nq = 0; nq < NQ; ++nq) {
-    const int r = wrow0 + 32 * nq + ln;
+  for (int cb = 0; cb < NC; ++cb) {
+    const int r = wrow0 + 16 * cb + n;
     if (r < seg_len) {
       T *row = dqb + (int64_t)r * a.q_ss;
 #pragma unroll
-      for (int db = 0; db < DB; ++db)
-#pragma unroll
-        for (int vq = 0; vq < 4; ++vq) {
-          const int d0 = 32 * db + 8 * vq + 4 * g;
-          if (d0 < D)
-            store4<T>(row + d0, dq[nq][db][4 * vq] * a.scale, dq[nq][db][4 * vq + 1] * a.scale,
-                      dq[nq][db][4 * vq + 2] * a.scale, dq[nq][db][4 * vq + 3] * a.scale);
-        }
+      for (int x = 0; x < DB; ++x) {
+        const f32x4 y = M::quad(dq[cb], x) * a.scale;
+        store4<T>(row + M::quad_d0(x, j), y[0], y[1], y[2], y[3]);
+      }
     }
   }
 }
 
 // Sums the chunks of the units that seg_attn_bwd_dq_kernel split along the keys: dq = scale * sum_c part_c.
 // Thread and grid layout as in seg_attn_fwd_merge_kernel.
-template <typename T, int D, int BM>
+template <typename T, int D>
 __global__ void __launch_bounds__(256) seg_attn_bwd_dq_merge_kernel(const AttnArgs a) {
-  constexpr int C4 = D / 4, RG = 256 / C4, GROUPS = (BM + RG - 1) / RG;
+  constexpr int C4 = D / 4, RG = 256 / C4;
+  const int BM = a.bm, GROUPS = (BM + RG - 1) / RG;
   const int unit = (int)blockIdx.x / GROUPS, rg = (int)blockIdx.x % GROUPS;
   const int rl = rg * RG + (int)threadIdx.x / C4, c4 = (int)threadIdx.x % C4;
   int qt, bh;

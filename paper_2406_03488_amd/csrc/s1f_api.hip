@@ -13,23 +13,21 @@
 namespace {
 using namespace s1f;
 
-// Tile shapes per element type: query blocks per wave (NQ), key blocks per wave (NK), keys per staged
-// K/V tile (BN), rows per staged Q/dO tile (BQ).
+// Kernel shapes per element type.
 template <typename T> struct Shape;
 //   forward: FNC column blocks of 16 rows per wave, FOCC waves per SIMD
-//   dq:      QNQ, QBN keys per LDS tile, QOCC;   dk/dv: KNW waves (32 keys each), copy distance KDIST, phase lag KLAG,
+//   dq:      QOCC;   dk/dv: KNW waves (32 keys each), copy distance KDIST, phase lag KLAG,
 //            KWGS workgroups per compute unit
 // bf16 dK/dV: two workgroups of 128 keys per compute unit, each with a two-stage tile ring.  Their barriers are
 // independent, so one's vector phases, prologue and accumulator epilogue overlap the other's matrix phases; in a
 // whole step this kernel measured 4 % (131072 tokens, grouped heads) to 9 % (32768 and 65536 tokens) faster than
 // one workgroup of 256 keys whose upper waves run one phase late (KNW = 8, KDIST = 2, KLAG = 1, KWGS = 1).
-// bf16 dQ: 32-key tiles; 64-key tiles measure the same within noise and hold twice the LDS.
 template <> struct Shape<bf16_t> {
-  static constexpr int FNC = 3, FOCC = 2, QNQ = 1, QBN = 32, QOCC = 2, KNW = 4, KDIST = 1, KLAG = 0,
+  static constexpr int FNC = 3, FOCC = 2, QOCC = 2, KNW = 4, KDIST = 1, KLAG = 0,
                        KWGS = 2;
 };
 template <> struct Shape<float> {
-  static constexpr int FNC = 2, FOCC = 1, QNQ = 1, QBN = 32, QOCC = 1, KNW = 4, KDIST = 1, KLAG = 0,
+  static constexpr int FNC = 2, FOCC = 1, QOCC = 1, KNW = 4, KDIST = 1, KLAG = 0,
                        KWGS = 1;
 };
 
@@ -248,15 +246,16 @@ template <typename T, int D> size_t fwd_ws_impl(const s1f_desc *d, int64_t seg_o
 // Workspace: the two planes of row statistics, then (256-byte aligned) the partial dQ rows of a split dQ launch.
 template <typename T, int D> struct DqLaunch {
   typedef Shape<T> S;
-  typedef BwdDqCfg<T, D, S::QNQ, S::QBN> QC;
+  static constexpr int NC = D == 128 || sizeof(T) == 4 ? 2 : 3;
+  typedef BwdDqCfg<T, D, NC> QC;
   static constexpr int64_t kPartBytes = (int64_t)QC::BM * D * 4;
-  static auto kernel() { return seg_attn_bwd_dq_kernel<T, D, S::QNQ, S::QBN, S::QOCC>; }
+  static auto kernel() { return seg_attn_bwd_dq_kernel<T, D, NC, S::QOCC>; }
   static int64_t tiles(int64_t seg_len) { return (seg_len + QC::BM - 1) / QC::BM; }
   static SplitPlan plan(const s1f_desc *d, int64_t seg_off, int64_t seg_len, int64_t cap) {
     const int64_t units = tiles(seg_len) * d->n_q_heads * d->batch;
     if (sizeof(T) != 2) return plan_split(units, 0, 0, 0, 0, 0);
     return plan_split(units, resident_workgroups(kernel(), 256, QC::LDS_BYTES), seg_off,
-                      kDqSecondsPerKey * (double)(seg_off + seg_len / 2), kPartBytes, cap);
+                      kDqSecondsPerKey * QC::BM / 128 * (double)(seg_off + seg_len / 2), kPartBytes, cap);
   }
 };
 inline size_t stat_bytes(const s1f_desc *d, int64_t seg_len) {
@@ -277,7 +276,8 @@ template <typename T, int D> int bwd_dq_impl(const s1f_desc *d, AttnArgs a, hipS
   if (rc != S1F_OK || !enqueue || p.n_split_units == 0) return rc;
   a.n_tiles = (int32_t)L::tiles(a.seg_len); a.n_bh = (int32_t)n_bh; a.tile_major = order;
   a.n_whole = (int32_t)p.n_whole; a.n_split = p.n_split; a.n_split_units = (int32_t)p.n_split_units;
-  return launch_merge(seg_attn_bwd_dq_merge_kernel<T, D, L::QC::BM>, a, p, MergeRows<D>::groups(L::QC::BM), st);
+  a.bm = L::QC::BM;
+  return launch_merge(seg_attn_bwd_dq_merge_kernel<T, D>, a, p, MergeRows<D>::groups(L::QC::BM), st);
 }
 
 template <typename T, int D> int bwd_dkdv_impl(const s1f_desc *d, const AttnArgs &a, hipStream_t st, bool enqueue) {
