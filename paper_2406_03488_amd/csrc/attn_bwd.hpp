@@ -302,59 +302,54 @@ __global__ void __launch_bounds__(256) seg_attn_bwd_dq_merge_kernel(const AttnAr
   store4<T>(dqb + (int64_t)r * a.q_ss + 4 * c4, acc[0] * a.scale, acc[1] * a.scale, acc[2] * a.scale, acc[3] * a.scale);
 }
 
-// dK/dV kernel.  NW waves of 32 keys each; Q/dO tiles of 32 rows travel through a ring of NST LDS stages.
-// DIST: a tile's copy is issued DIST iterations before the iteration that consumes it.
-// LAG:  with LAG = 1 the upper half of the waves runs one phase behind the lower half (see the kernel), which
-// keeps each tile alive for one more iteration.
-template <typename T, int D, int NW, int DIST, int LAG> struct BwdDkdvCfg {
+template <typename T, int D> struct BwdDkdvCfg {
   static constexpr int BQ = 32;                        // rows per Q/dO tile
-  static constexpr int BNW = 32 * NW;                  // keys per workgroup
-  static constexpr int THREADS = 64 * NW;
-  static constexpr int NST = DIST + LAG + 1;           // ring stages
-  typedef LdsTile<T, BQ, D> QT;
-  static constexpr int STAGE_BYTES = 2 * QT::BYTES;    // Q tile, dO tile right behind it
+  static constexpr int BNW = 128, THREADS = 256;       // keys per workgroup: 4 waves of 32
+  typedef Tile32<T, D> TL;
+  static constexpr int STAGE_BYTES = 2 * TL::BYTES;    // Q tile, dO tile right behind it
   static constexpr int STAT_BYTES = 2 * BQ * 4;        // -lse/scale and -delta of the tile's rows
-  typedef PaddedRows<T, BNW, D> VT;                    // the workgroup's V rows
-  static constexpr int LDS_BYTES = NST * STAGE_BYTES + VT::BYTES + NST * STAT_BYTES;   // stages, V, statistics
-  static_assert(STAGE_BYTES % 8192 == 0, "stages must keep the 8 KiB alignment of the fragment reader");
-  static_assert(DIST >= 1 && LAG >= 0 && LAG <= 1 && NW % 4 == 0, "schedule");
+  static constexpr int V_BYTES = 4 * TL::BYTES;        // the workgroup's V rows
+  static constexpr int LOOP_BYTES = 2 * STAGE_BYTES + V_BYTES + 2 * STAT_BYTES;   // two stages, V, statistics
+  static constexpr int EPI_ROW = pow2_at_least(D * 4); // bytes per row of the epilogue's staging regions
+  static constexpr int EPI_BYTES = 4 * 32 * EPI_ROW;
+  static constexpr int LDS_BYTES = LOOP_BYTES > EPI_BYTES ? LOOP_BYTES : EPI_BYTES;
 };
 
-// Lane = one key (column ln); queries run over registers.
+// dK/dV kernel.  A workgroup owns 128 keys of one K/V head, a wave 32 of them in two column blocks of 16; lane = one key
+// per column block; queries run over registers.  Q/dO tiles of 32 rows and their row statistics travel through a
+// two-stage LDS ring, copied HBM -> LDS asynchronously.
 //   S[q][key]  = Q K^T         A = Q (LDS),              B = K (registers)
 //   dP[q][key] = dO V^T        A = dO (LDS),             B = V (LDS)
 //   dV^T[d][key] += dO^T P     A = dO read transposed,   B = P slab (registers)
 //   dK^T[d][key] += Q^T dS     A = Q read transposed,    B = dS slab (registers)
-// The wave's K fragments, its dK and dV accumulators and the block's S and dP fill the register budget of
-// two waves per SIMD; its V rows are therefore read from LDS (copied there once, in padded rows).
-// Q/dO tiles and their row statistics are copied HBM -> LDS asynchronously (no staging registers).
-//
-// A wave's work on one tile has three phases: B (S and dP on the matrix pipe), C (exp and dS on the vector
-// pipe), D (dV and dK on the matrix pipe).  Two waves share a SIMD, and one's vector phase should meet the other's
-// matrix phases instead of both queueing for the same pipe.  Either the two belong to different workgroups (NW = 4,
-// WGS = 2: two workgroups per compute unit with barriers of their own, which also overlaps one's prologue and
-// epilogue with the other's loop; the shape the library launches for bf16), or to the two halves of one workgroup
-// (NW = 8) whose upper half, with LAG = 1, runs the sequence one phase late (C and D of the previous tile, then B of
-// the current one).
-template <typename T, int D, int NW, int DIST, int LAG, int WGS = 1>   // WGS: workgroups meant to share a compute unit
-__global__ void __launch_bounds__(64 * NW, WGS * NW / 4) seg_attn_bwd_dkdv_kernel(const AttnArgs a) {
-  typedef Elem<T> E;
-  typedef typename E::Frag Frag;
-  typedef BwdDkdvCfg<T, D, NW, DIST, LAG> Cfg;
-  typedef typename Cfg::QT QT;
-  typedef FragReader<QT, T> RD;
-  constexpr int EPL = E::EPL, KSTEP = 2 * EPL, NKS = D / KSTEP;
-  constexpr int DB = QT::DPAD / 32, NSLAB = 16 / EPL, BQ = Cfg::BQ, NST = Cfg::NST;
-  constexpr int PF = 2;              // steps by which operand fragments are read ahead in phase B ...
-  constexpr int PFD = 2;             // ... and in phase D (deeper rings spill at two waves per SIMD and run slower)
-  constexpr int NV = NSLAB * DB;     // (slab, d-block) steps of the second pair of products
-  static_assert(NKS >= PF && NV >= PFD && PFD >= PF, "prefetch ring deeper than the products");
+// The wave's K rows, its dK and dV accumulators and the tile's S and dP fill the register budget of two waves per SIMD;
+// its V rows are therefore read from LDS (copied there once).
+// The accumulators of S and dP start from the row statistics instead of zero, so that s = q.k - lse/scale and
+// dp = dO.v - delta come out of the matrix pipe ready for p = exp2(c*s) and dS = p*dp.
+// Vector work runs under the matrix instructions of the next product: the exponentials under dP, dS under dV; the order
+// is pinned matrix instruction by matrix instruction, LDS operands are read kDkdvRing operands ahead.  Two workgroups
+// share a compute unit, with barriers of their own: one's prologue, epilogue and waits overlap the other's products.
+// Bound by the matrix pipe at the clock the power limit leaves (head_dim 128: 69 % busy at 1.78 GHz).  32 heads, 4096
+// rows behind 28672 keys: head_dim 128 3.70 -> 3.41 ms (1114 -> 1210 TFLOP/s), 80 2.80 -> 2.54 ms; head_dim 64 with
+// three workgroups per compute unit 1.94 -> 1.74 ms (two: 1.89).  A ring of 6 operands measures the same, one of 8
+// 12 % slower.
+constexpr int kDkdvRing = 4;
 
-  extern __shared__ __attribute__((aligned(8192))) char smem[];
-  const int tid = threadIdx.x, lane = tid & 63, g = lane >> 5, ln = lane & 31;
+template <typename T, int D, int WGS>   // WGS: workgroups meant to share a compute unit
+__global__ void __launch_bounds__(256, WGS) seg_attn_bwd_dkdv_kernel(const AttnArgs a) {
+  typedef BwdDkdvCfg<T, D> Cfg;
+  typedef Mat<T, D> M;
+  typedef typename M::Frag Frag;
+  typedef TilePairCopy<T, D> Copy;
+  constexpr int DB = M::DB, BQ = Cfg::BQ, NN = M::NN, NK = M::NK, NT = M::NT, PR = kDkdvRing;
+  constexpr int TB = Tile32<T, D>::BYTES, X1 = NN, X2 = X1 + 4 * NK, X3 = X2 + NT, TOTAL = X3 + NT;
+
+  extern __shared__ __attribute__((aligned(1024))) char smem[];
+  const int tid = threadIdx.x, lane = tid & 63, j = lane >> 4, n = lane & 15;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const UnitChunk uc = split_unit(blockIdx.x, a.n_whole, a.n_split, a.n_split_units);
   int kt, bh;
-  decode_workgroup(blockIdx.x, a.n_tiles, a.n_bh, a.tile_major, kt, bh);   // early key tiles see every query row: heaviest first
+  decode_workgroup(uc.unit, a.n_tiles, a.n_bh, a.tile_major, kt, bh);   // early key tiles see every query row: heaviest first
   const int n_kv_heads = a.n_q_heads / a.group;
   const int hk = bh % n_kv_heads, b = bh / n_kv_heads;
   const int seg_off = a.seg_off, seg_len = a.seg_len, kv_len = seg_off + seg_len;
@@ -371,18 +366,27 @@ __global__ void __launch_bounds__(64 * NW, WGS * NW / 4) seg_attn_bwd_dkdv_kerne
   const int qt_first = r_first / BQ;
   const int n_qt = (seg_len + BQ - 1) / BQ;
   const int per_head = n_qt - qt_first;            // >= 1 because j0 < kv_len
-  const int n_it = per_head * a.group;
-  const float c = a.scale * kLog2e;
+  // All iterations, or one chunk of them.
+  const int it_begin = (int)((int64_t)uc.chunk * per_head * a.group / uc.n_chunks);
+  const int it_end = (int)((int64_t)(uc.chunk + 1) * per_head * a.group / uc.n_chunks);
+  const float c = uniform(a.scale * kLog2e);
   const bool w_active = wkey0 < kv_len;
 
   const lds_addr lds0 = to_lds_addr(smem);
-  const lds_addr vtile = lds0 + NST * Cfg::STAGE_BYTES;
-  const lds_addr stats0 = vtile + Cfg::VT::BYTES;
-  AsyncTilePairU<T, BQ, D, NW> ld;
-  ld.init(wave, lane, a.q_ss);
-  RD rd;
+  const lds_addr vtile = lds0 + 2 * Cfg::STAGE_BYTES;
+  const lds_addr stats0 = vtile + Cfg::V_BYTES;
+  M rd;
   rd.init(lane);
-
+  {   // V rows of the workgroup's keys -> LDS (keys past the prefix: copies of its last row, products never stored)
+    Copy lv;
+    lv.init(wave, lane, a.kv_ss);
+#pragma unroll
+    for (int i = 0; i < 4; i += 2) {
+      const int key0 = j0 + 32 * (i + (wave >> 1)), at = key0 < kv_len ? key0 : kv_len - 1;
+      const T *row = vbase + (int64_t)at * a.kv_ss;
+      lv.issue(row, row, a.kv_ss, kv_len - at, kv_len - at, vtile + i * TB, wave);
+    }
+  }
   // Tile cursors (row offset of the tile, its query head, its ring stage), advanced once per iteration.
   struct Cursor {
     int r0, hq, stage;
@@ -390,241 +394,232 @@ __global__ void __launch_bounds__(64 * NW, WGS * NW / 4) seg_attn_bwd_dkdv_kerne
   auto advance = [&](Cursor &t) {
     t.r0 += BQ;
     if (t.r0 >= n_qt * BQ) { t.r0 = qt_first * BQ; ++t.hq; }
-    t.stage = t.stage + 1 == NST ? 0 : t.stage + 1;
+    t.stage ^= 1;
   };
+  Copy ld;
+  ld.init(wave, lane, a.q_ss);
   auto issue = [&](const Cursor &t) {   // rows past the segment re-read its last row
-    const int64_t qoff = b * a.q_sb + t.hq * a.q_sh;
-    ld.issue(reinterpret_cast<const T *>(a.q) + qoff, reinterpret_cast<const T *>(a.dout) + qoff, a.q_ss, t.r0, seg_len,
-             lds0 + t.stage * Cfg::STAGE_BYTES, wave, lane);
-    if (wave < 2 * BQ / 64) {   // lane `lane` copies entry 64*wave + lane of {-lse/scale [BQ], -delta [BQ]}
-      const int st_idx = wave * 64 + fresh(lane), rr = t.r0 + st_idx % BQ;
-      const unsigned st_plane = (unsigned)((st_idx / BQ) * a.ws_plane);
+    const int64_t qoff = b * a.q_sb + t.hq * a.q_sh + (int64_t)t.r0 * a.q_ss;
+    ld.issue(reinterpret_cast<const T *>(a.q) + qoff, reinterpret_cast<const T *>(a.dout) + qoff, a.q_ss, seg_len - t.r0,
+             seg_len - t.r0, lds0 + t.stage * Cfg::STAGE_BYTES, wave);
+    if (wave == 0) {   // lane l copies entry l of {-lse/scale [32], -delta [32]}
+      const int l = lane_id(), rr = t.r0 + l % BQ;
+      const unsigned plane = (unsigned)((l / BQ) * a.ws_plane);
       const float *sb = a.delta + ((int64_t)b * a.n_q_heads + t.hq) * seg_len;     // wave-uniform
-      const unsigned so = (st_plane + (unsigned)(rr < seg_len ? rr : seg_len - 1)) * 4u;
-      const unsigned dst = stats0 + (unsigned)(t.stage * Cfg::STAT_BYTES + wave * 256);
+      const unsigned so = (plane + (unsigned)(rr < seg_len ? rr : seg_len - 1)) * 4u;
+      const unsigned dst = stats0 + (unsigned)(t.stage * Cfg::STAT_BYTES);
       asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dword %1, %2" : : "s"(dst), "v"(so), "s"(sb) : "m0");
     }
   };
-
-  // V rows of the workgroup's keys -> LDS (rows past the prefix are zero: their products are never stored)
-  Cfg::VT::template copy<Cfg::THREADS>(smem + NST * Cfg::STAGE_BYTES, vbase + (int64_t)j0 * a.kv_ss, a.kv_ss, kv_len - j0, tid);
-  // K fragments of the wave's keys stay in registers for the whole kernel.
-  Frag kf[NKS];
-  {
-    int key = wkey0 + ln;
+  Cursor t_iss = {(qt_first + it_begin % per_head) * BQ, hk * a.group + it_begin / per_head, 0};   // next tile to copy
+  Cursor cur = t_iss;                                                                              // tile of the current iteration
+  if (it_begin < it_end) issue(t_iss);
+  advance(t_iss);
+  // K rows of the wave's keys stay in registers for the whole kernel.
+  typename M::RowOp kr[2];
+#pragma unroll
+  for (int cb = 0; cb < 2; ++cb) {
+    int key = wkey0 + 16 * cb + n;
     key = key < kv_len ? key : kv_len - 1;     // keys past the prefix are computed on a copy and never stored
-    const int64_t off = (int64_t)key * a.kv_ss + EPL * g;
+    M::load_row(kr[cb], kbase + (int64_t)key * a.kv_ss, j);
 #pragma unroll
-    for (int ks = 0; ks < NKS; ++ks) kf[ks] = load_frag_global<T>(kbase + off + ks * KSTEP);
+    for (int i = 0; i < M::NK; ++i) settle(kr[cb].f[i]);
   }
-  Cursor t_iss = {qt_first * BQ, hk * a.group, 0};   // next tile to copy
-  for (int i = 0; i < DIST; ++i) {
-    if (i < n_it) issue(t_iss);
-    advance(t_iss);
-  }
-  f32x16 dk[DB], dv[DB];
+  f32x4 dk[2][DB], dv[2][DB];
 #pragma unroll
-  for (int db = 0; db < DB; ++db)
+  for (int cb = 0; cb < 2; ++cb)
 #pragma unroll
-    for (int v = 0; v < 16; ++v) { dk[db][v] = 0.f; dv[db][v] = 0.f; }
-#pragma unroll
-  for (int ks = 0; ks < NKS; ++ks) settle(kf[ks]);
-  const lds_addr vrow = Cfg::VT::lane_base(vtile, wave * 32 + ln, g);   // the lane's row of V
+    for (int db = 0; db < DB; ++db) dk[cb][db] = dv[cb][db] = f32x4{0.f, 0.f, 0.f, 0.f};
   wait_async_tiles();
   __syncthreads();
 
-  // State of the tile in flight.  Operand fragments are read from LDS PF steps ahead of the matrix
-  // instruction that consumes them (the compiler, left alone, reads each one right before its use and
-  // exposes the LDS latency on every step); the scheduling fences keep that order.
-  struct State {
-    f32x16 s, dp;
-    Frag qa[PF], da[PF], va[PF], tq[PFD], tdo[PFD];
-  };
-  auto active = [&](const Cursor &t) { return w_active && wkey0 <= seg_off + t.r0 + 31; };
-
-  // Phase B: the accumulators start from the row statistics instead of zero (register v holds row
-  // r0 + 8*(v/4) + 4*g + v%4), so that s = q.k - lse/scale and dp = dO.v - delta come out of the matrix
-  // pipe ready for p = exp2(c*s) and dS = p*dp.
-  // The matrix phases run at a raised wave priority, the vector phase at the default one: when the two waves of a
-  // SIMD both have instructions ready, the one feeding the matrix pipe goes first (1.3 % of the kernel, measured).
-  auto phase_b = [&](State &z, const Cursor &t) {
-    __builtin_amdgcn_s_setprio(2);
-    const lds_addr qblock = lds0 + t.stage * Cfg::STAGE_BYTES;   // the dO block lies QT::BYTES behind it
-    const lds_addr st = stats0 + (unsigned)(t.stage * Cfg::STAT_BYTES + 16 * g);
-#pragma unroll
-    for (int vq = 0; vq < 4; ++vq) {
-      const f32x4 nl = lds_load<f32x4>(st + 32 * vq);
-      const f32x4 nd = lds_load<f32x4>(st + 4 * BQ + 32 * vq);
-#pragma unroll
-      for (int e = 0; e < 4; ++e) { z.s[4 * vq + e] = nl[e]; z.dp[4 * vq + e] = nd[e]; }
-    }
-#pragma unroll
-    for (int i = 0; i < PF; ++i) {
-      rd.nat2(qblock, QT::BYTES, i, z.qa[i], z.da[i]);
-      z.va[i] = Cfg::VT::frag(vrow, i);
-    }
-    __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-    for (int ks = 0; ks < NKS; ++ks) {
-      z.s = mma(z.qa[ks % PF], kf[ks], z.s);
-      z.dp = mma(z.da[ks % PF], z.va[ks % PF], z.dp);
-      if (ks + PF < NKS) {
-        rd.nat2(qblock, QT::BYTES, ks + PF, z.qa[ks % PF], z.da[ks % PF]);
-        z.va[ks % PF] = Cfg::VT::frag(vrow, ks + PF);
-      } else {   // the rings drain: start on the operands of phase D
-        const int i = ks + PF - NKS;
-        rd.tr2(qblock, QT::BYTES, i / DB, i % DB, z.tq[i], z.tdo[i]);
-      }
-      __builtin_amdgcn_sched_barrier(0);
-    }
-  };
-  // Phase C.  Visible iff key <= seg_off + row and row < seg_len, row = r0 + 4g + 8*(v/4) + v%4; blocks that
-  // lie wholly below the diagonal and inside the segment (nearly all of them) skip the test.
-  auto phase_c = [&](State &z, const Cursor &t) {
-    __builtin_amdgcn_s_setprio(0);
-    const lds_addr qblock = lds0 + t.stage * Cfg::STAGE_BYTES;
-#pragma unroll
-    for (int i = PF; i < PFD; ++i) rd.tr2(qblock, QT::BYTES, i / DB, i % DB, z.tq[i], z.tdo[i]);   // rest of phase D's ring
-    __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-    for (int v = 0; v < 16; ++v) {
-      const float p = exp2_fast(z.s[v] * c);
-      z.s[v] = p;
-      z.dp[v] = p * z.dp[v];
-    }
-    // Tiles on the diagonal or at the end of the segment: entries above the diagonal and rows past the segment are
-    // set to zero afterwards, in a branch that holds nothing else (whatever the exponential made of them, infinity
-    // included, is overwritten).  One instance of the arithmetic above keeps p and dS in place: with a masked and an
-    // unmasked copy of it the compiler moved all 16 dS registers on every step.
-    const bool edge = (wkey0 + 31 > seg_off + t.r0) || (t.r0 + 32 > seg_len);
-    if (edge) {
-      asm volatile("" ::: "memory");   // keeps this a branch
-      const int fl = fresh(lane), fg = fl >> 5;
-      const int lo = wkey0 + (fl & 31) - seg_off - t.r0 - 4 * fg;   // need 8*(v/4)+v%4 >= lo
-      const int hi = seg_len - t.r0 - 4 * fg;                       // and  8*(v/4)+v%4 <  hi
-#pragma unroll
-      for (int v = 0; v < 16; ++v) {
-        const int rr = 8 * (v >> 2) + (v & 3);
-        if (rr < lo || rr >= hi) {
-          z.s[v] = 0.f;
-          z.dp[v] = 0.f;
+  for (int it = it_begin; it < it_end; ++it) {
+    // the stage this copy overwrites was last read before the barrier that ended the previous iteration
+    if (it + 1 < it_end) issue(t_iss);
+    advance(t_iss);
+    if (w_active && wkey0 <= seg_off + cur.r0 + 31) {
+      const lds_addr qt = lds0 + cur.stage * Cfg::STAGE_BYTES;   // the dO tile lies TB behind it
+      const lds_addr st = opaque(stats0 + (unsigned)(cur.stage * Cfg::STAT_BYTES + 16 * j));
+      const typename M::Nat qn = rd.nat_at(qt), vn = rd.nat_at(vtile + wave * TB);
+      const typename M::Tr qx = rd.tr_at(qt);
+      // Operand x of the iteration: Q [NN], then per step along D dO, V, V, dO, then dO and Q transposed [NT each].
+      auto operand = [&](int x) {
+        if (x < X1) return M::nat(qn, x);
+        if (x < X2) {
+          const int ks = (x - X1) / 4, w = (x - X1) % 4;
+          return w == 0 ? M::nat(qn, ks, TB) : w == 3 ? M::nat(qn, NK + ks, TB) : M::nat(vn, (w - 1) * NK + ks);
         }
-      }
-    }
-    __builtin_amdgcn_sched_barrier(0);
-  };
-  auto phase_d = [&](State &z, const Cursor &t) {
-    __builtin_amdgcn_s_setprio(2);
-    const lds_addr qblock = lds0 + t.stage * Cfg::STAGE_BYTES;
-    Frag pf, dsf;
+        return x < X3 ? M::tr(qx, x - X2, TB) : M::tr(qx, x - X3);
+      };
+      Frag fr[PR];
+      auto used = [&](int x) {   // operand x has been used up: read the one that takes its place
+        if (x + PR < TOTAL) fr[x % PR] = operand(x + PR);
+      };
+      f32x4 s[2][2], dp[2][2];
+      f32x4 nl[2], nd[2];
 #pragma unroll
-    for (int i = 0; i < NV; ++i) {
-      const int sl = i / DB, db = i % DB;
-      if (db == 0) {
-        pf = block_slab<T>(z.s, sl);
-        dsf = block_slab<T>(z.dp, sl);
-      }
-      dv[db] = mma(z.tdo[i % PFD], pf, dv[db]);
-      dk[db] = mma(z.tq[i % PFD], dsf, dk[db]);
-      if (i + PFD < NV) rd.tr2(qblock, QT::BYTES, (i + PFD) / DB, (i + PFD) % DB, z.tq[i % PFD], z.tdo[i % PFD]);
+      for (int x = 0; x < 2; ++x) fr[x] = operand(x);
+#pragma unroll
+      for (int rb = 0; rb < 2; ++rb) nl[rb] = lds_load<f32x4>(st + 64 * rb);
+#pragma unroll
+      for (int x = 2; x < PR; ++x) fr[x] = operand(x);
       __builtin_amdgcn_sched_barrier(0);
-    }
-  };
-
-  // End of an iteration: the wave's share of the NEXT tile must have landed.  With DIST = 2 the copy issued at the top
-  // of this iteration (PER instructions, one more for the statistics on wave 0) belongs to the tile after it and
-  // stays in flight across the barrier.
-  constexpr int kCopyInsts = AsyncTilePairU<T, BQ, D, NW>::PER;
-  auto wait_next_tile = [&](bool issued_this_iteration) {
-    if (DIST >= 2 && issued_this_iteration) {
-      if (wave < 2 * BQ / 64) wait_async_tiles_but_last<kCopyInsts + 1>();
-      else wait_async_tiles_but_last<kCopyInsts>();
-    } else {
-      wait_async_tiles();
-    }
-  };
-  Cursor cur = {qt_first * BQ, hk * a.group, 0};   // tile of the current iteration
-  const bool late = LAG > 0 && wave >= NW / 2;
-  if (!late) {
-    for (int it = 0; it < n_it; ++it) {
-      // the stage this copy overwrites was last read before the barrier that ended the previous iteration
-      if (it + DIST < n_it) issue(t_iss);
-      advance(t_iss);
-      if (active(cur)) {
-        State z;
-        phase_b(z, cur);
-        phase_c(z, cur);
-        phase_d(z, cur);
+#pragma unroll
+      for (int i = 0; i < NN; ++i)
+#pragma unroll
+        for (int cb = 0; cb < 2; ++cb) {
+          s[i / NK][cb] = M::mma_nat(i, fr[i % PR], kr[cb], i % NK ? s[i / NK][cb] : nl[i / NK]);
+          if (cb == 1) used(i);
+          if (cb == 1 && i + 2 >= NN) nd[i + 2 - NN] = lds_load<f32x4>(st + 4 * BQ + 64 * (i + 2 - NN));
+          __builtin_amdgcn_sched_barrier(0);
+        }
+      auto probs = [&](int x0, int x1) {   // probabilities x0 .. x1-1 of the lane's 16
+#pragma unroll
+        for (int x = x0; x < x1; ++x) {
+          float y = exp2_fast(s[x >> 3][(x >> 2) & 1][x & 3] * c);
+          settle(y);
+          s[x >> 3][(x >> 2) & 1][x & 3] = y;
+        }
+      };
+#pragma unroll
+      for (int ks = 0; ks < NK; ++ks)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          const int rb = i >> 1, cb = i & 1, x = X1 + 4 * ks;
+          dp[rb][cb] = M::mma_op(ks, fr[(x + (rb ? 3 : 0)) % PR], fr[(x + 1 + cb) % PR], ks ? dp[rb][cb] : nd[rb]);
+          if (i > 0) used(x + i - 1);
+          if (i == 3) used(x + 3);
+          const int w = 4 * ks + i, W = 4 * NK;
+          probs(16 * w / W, 16 * (w + 1) / W);
+          __builtin_amdgcn_sched_barrier(0);
+        }
+      // Visible iff key <= seg_off + row and row < seg_len.  Tiles on the diagonal or at the end of the segment: entries
+      // above the diagonal and rows past the segment are set to zero here, in a branch that holds nothing else (whatever
+      // the exponential made of them, infinity included, is overwritten).
+      if ((wkey0 + 31 > seg_off + cur.r0) || (cur.r0 + 32 > seg_len)) {
+        asm volatile("" ::: "memory");   // keeps this a branch
+        const int fl = lane_id(), fj = fl >> 4;
+        const int lo = wkey0 + (fl & 15) - seg_off - cur.r0 - 4 * fj;   // need 16*rb + v >= lo + 16*cb
+        const int hi = seg_len - cur.r0 - 4 * fj;                       // and  16*rb + v <  hi
+#pragma unroll
+        for (int rb = 0; rb < 2; ++rb)
+#pragma unroll
+          for (int cb = 0; cb < 2; ++cb)
+#pragma unroll
+            for (int v = 0; v < 4; ++v)
+              if (16 * rb + v < lo + 16 * cb || 16 * rb + v >= hi) {
+                s[rb][cb][v] = 0.f;
+                dp[rb][cb][v] = 0.f;
+              }
       }
-      advance(cur);
-      wait_next_tile(it + DIST < n_it);   // this wave's part of tile it+1 has landed
-      __syncthreads();
-    }
-  } else {
-    State z;
-    Cursor prev = cur;
-    for (int it = 0; it < n_it; ++it) {
-      if (it + DIST < n_it) issue(t_iss);
-      advance(t_iss);
-      if (it > 0 && active(prev)) {
-        phase_c(z, prev);
-        phase_d(z, prev);
+      typename M::Slab pf[2], ds[2];
+#pragma unroll
+      for (int cb = 0; cb < 2; ++cb) {
+        pf[cb] = M::slab(s[0][cb], s[1][cb]);
+        M::settle_slab(pf[cb]);
       }
-      if (active(cur)) phase_b(z, cur);
-      prev = cur;
-      advance(cur);
-      wait_next_tile(it + DIST < n_it);
-      __syncthreads();
+#pragma unroll
+      for (int i = 0; i < NT; ++i)
+#pragma unroll
+        for (int cb = 0; cb < 2; ++cb) {
+          M::mma_tr(i, fr[(X2 + i) % PR], pf[cb], dv[cb]);
+          if (cb == 1) used(X2 + i);
+          if (i == 1) {
+            ds[cb] = M::slab(s[0][cb] * dp[0][cb], s[1][cb] * dp[1][cb]);
+            M::settle_slab(ds[cb]);
+          }
+          __builtin_amdgcn_sched_barrier(0);
+        }
+#pragma unroll
+      for (int i = 0; i < NT; ++i)
+#pragma unroll
+        for (int cb = 0; cb < 2; ++cb) {
+          M::mma_tr(i, fr[(X3 + i) % PR], ds[cb], dk[cb]);
+          if (cb == 1) used(X3 + i);
+          __builtin_amdgcn_sched_barrier(0);
+        }
     }
-    if (active(prev)) {
-      phase_c(z, prev);
-      phase_d(z, prev);
-    }
+    advance(cur);
+    wait_async_tiles();   // this wave's part of tile it+1 has landed
+    __syncthreads();
   }
 
   // Epilogue: acc[key][d] += result, each element touched by exactly one lane of the grid.  In the accumulators a
-  // lane holds ONE key and 4-element pieces of its row 32 bytes apart: read-modify-write straight from there would
-  // touch 64 different cache lines per instruction.  Each wave therefore passes its 32 x D block through LDS (its
-  // own region; rows padded by 16 bytes so that the row-per-lane writes spread over all banks) and updates the
+  // lane holds ONE key per column block and 4-element pieces of its row: read-modify-write straight from there would
+  // touch 16 cache lines per 64 lanes.  Each wave therefore passes its 32 x D block through LDS (its own region; 16-byte
+  // chunk c of row r at position c ^ (r & 15), so that the row-per-lane writes spread over all banks) and updates the
   // accumulators row by row, LPR lanes side by side on one row.
-  __syncthreads();   // the late half's last phases still read the tile ring that the regions below overlay
   float *dkb = a.dk_acc + kvoff, *dvb = a.dv_acc + kvoff;
-  constexpr int ROWB = QT::DPAD * 4 + 16;           // bytes per staged row
   constexpr int LPR = D / 4;                        // lanes per row (16 bytes each)
   constexpr int RPI = 64 / LPR;                     // rows per instruction
   constexpr int NI = (32 + RPI - 1) / RPI;          // instructions per block
-  static_assert(NW * 32 * ROWB <= Cfg::LDS_BYTES, "the epilogue's staging regions must fit the kernel's LDS");
-  char *region = smem + wave * (32 * ROWB);
+  char *region = smem + wave * (32 * Cfg::EPI_ROW);
   const int row_in = lane / LPR, col = lane % LPR;
 #pragma unroll
   for (int which = 0; which < 2; ++which) {
-    const f32x16(&acc)[DB] = which == 0 ? dk : dv;
     const float mul = which == 0 ? a.scale : 1.f;
     float *base = which == 0 ? dkb : dvb;
 #pragma unroll
-    for (int db = 0; db < DB; ++db)
+    for (int cb = 0; cb < 2; ++cb)
 #pragma unroll
-      for (int vq = 0; vq < 4; ++vq) {
-        const int d0 = 32 * db + 8 * vq + 4 * g;
-        *reinterpret_cast<f32x4 *>(region + ln * ROWB + d0 * 4) =
-            f32x4{acc[db][4 * vq] * mul, acc[db][4 * vq + 1] * mul, acc[db][4 * vq + 2] * mul, acc[db][4 * vq + 3] * mul};
+      for (int x = 0; x < DB; ++x) {
+        const int r = 16 * cb + n, ch = M::quad_d0(x, j) >> 2;
+        *reinterpret_cast<f32x4 *>(region + r * Cfg::EPI_ROW + 16 * (ch ^ n)) = M::quad(which == 0 ? dk[cb] : dv[cb], x) * mul;
       }
-    f32x4 cur[NI];
+    if (uc.slot >= 0) {   // a chunk: its share goes to the workspace, [chunk][dK, dV][key][head_dim]
+      float *part = a.part + ((int64_t)uc.slot * 2 + which) * (Cfg::BNW * D) + (int64_t)(wave * 32) * D;
+#pragma unroll
+      for (int i = 0; i < NI; ++i) {
+        const int r = i * RPI + row_in, rc = r < 32 ? r : 31;
+        const f32x4 x = *reinterpret_cast<const f32x4 *>(region + rc * Cfg::EPI_ROW + 16 * (col ^ (rc & 15)));
+        if (row_in < RPI && r < 32) *reinterpret_cast<f32x4 *>(part + (int64_t)r * D + 4 * col) = x;
+      }
+      continue;
+    }
+    f32x4 old[NI];   // rows that are not this lane's to update are read all the same, from a valid place
 #pragma unroll
     for (int i = 0; i < NI; ++i) {
-      const int r = i * RPI + row_in, key = wkey0 + r;
-      if (row_in < RPI && r < 32 && key < kv_len)
-        cur[i] = *reinterpret_cast<const f32x4 *>(base + (int64_t)key * a.kv_ss + 4 * col);
+      const int key = wkey0 + i * RPI + row_in;
+      old[i] = *reinterpret_cast<const f32x4 *>(base + (int64_t)(key < kv_len ? key : kv_len - 1) * a.kv_ss + 4 * col);
     }
 #pragma unroll
     for (int i = 0; i < NI; ++i) {
-      const int r = i * RPI + row_in, key = wkey0 + r;
-      if (row_in < RPI && r < 32 && key < kv_len) {
-        const f32x4 add = *reinterpret_cast<const f32x4 *>(region + r * ROWB + 16 * col);
-        *reinterpret_cast<f32x4 *>(base + (int64_t)key * a.kv_ss + 4 * col) = cur[i] + add;
-      }
+      const int r = i * RPI + row_in, key = wkey0 + r, rc = r < 32 ? r : 31;
+      const f32x4 sum = old[i] + *reinterpret_cast<const f32x4 *>(region + rc * Cfg::EPI_ROW + 16 * (col ^ (rc & 15)));
+      if (row_in < RPI && r < 32 && key < kv_len) *reinterpret_cast<f32x4 *>(base + (int64_t)key * a.kv_ss + 4 * col) = sum;
     }
   }
+}
+
+// Adds the chunks of the units that seg_attn_bwd_dkdv_kernel split along the queries into the accumulators:
+// acc += sum_c part_c, in the order of the chunks.  A thread handles 4 consecutive head_dim elements of one key of one
+// of the two accumulators (grid: split units x DkdvMerge<D>::GROUPS).
+template <int D> struct DkdvMerge {
+  static constexpr int PER = 128 * D / 4;                  // threads per unit and accumulator
+  static constexpr int GROUPS = 2 * PER / 256;
+  static_assert(PER % 256 == 0, "whole workgroups per accumulator");
+};
+template <typename T, int D> __global__ void __launch_bounds__(256) seg_attn_bwd_dkdv_merge_kernel(const AttnArgs a) {
+  typedef DkdvMerge<D> DM;
+  const int unit = (int)blockIdx.x / DM::GROUPS, g = (int)blockIdx.x % DM::GROUPS;
+  const int which = g / (DM::GROUPS / 2), t = (g % (DM::GROUPS / 2)) * 256 + (int)threadIdx.x;
+  int kt, bh;
+  decode_workgroup(a.n_whole + unit, a.n_tiles, a.n_bh, a.tile_major, kt, bh);
+  const int n_kv_heads = a.n_q_heads / a.group, hk = bh % n_kv_heads, b = bh / n_kv_heads;
+  const int key = kt * 128 + t / (D / 4), S = a.n_split;
+  if (key >= a.seg_off + a.seg_len) return;
+  int slot0, slot_step;
+  chunk_slots(unit, a.n_split_units, slot0, slot_step);
+  const float *part = a.part + ((int64_t)slot0 * 2 + which) * (128 * D) + 4 * t;
+  f32x4 pc[kMaxChunks];
+#pragma unroll
+  for (int c = 0; c < kMaxChunks; ++c)
+    pc[c] = c < S ? *reinterpret_cast<const f32x4 *>(part + (int64_t)c * slot_step * (2 * 128 * D)) : f32x4{0.f, 0.f, 0.f, 0.f};
+  float *acc = (which ? a.dv_acc : a.dk_acc) + b * a.kv_sb + hk * a.kv_sh + (int64_t)key * a.kv_ss + 4 * (t % (D / 4));
+  f32x4 sum = pc[0];
+#pragma unroll
+  for (int c = 1; c < kMaxChunks; ++c) sum += pc[c];
+  *reinterpret_cast<f32x4 *>(acc) = *reinterpret_cast<const f32x4 *>(acc) + sum;
 }
 
 }  // namespace s1f

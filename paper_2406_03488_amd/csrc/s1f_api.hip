@@ -16,19 +16,12 @@ using namespace s1f;
 // Kernel shapes per element type.
 template <typename T> struct Shape;
 //   forward: FNC column blocks of 16 rows per wave, FOCC waves per SIMD
-//   dq:      QOCC;   dk/dv: KNW waves (32 keys each), copy distance KDIST, phase lag KLAG,
-//            KWGS workgroups per compute unit
-// bf16 dK/dV: two workgroups of 128 keys per compute unit, each with a two-stage tile ring.  Their barriers are
-// independent, so one's vector phases, prologue and accumulator epilogue overlap the other's matrix phases; in a
-// whole step this kernel measured 4 % (131072 tokens, grouped heads) to 9 % (32768 and 65536 tokens) faster than
-// one workgroup of 256 keys whose upper waves run one phase late (KNW = 8, KDIST = 2, KLAG = 1, KWGS = 1).
+//   dq:      QOCC
 template <> struct Shape<bf16_t> {
-  static constexpr int FNC = 3, FOCC = 2, QOCC = 2, KNW = 4, KDIST = 1, KLAG = 0,
-                       KWGS = 2;
+  static constexpr int FNC = 3, FOCC = 2, QOCC = 2;
 };
 template <> struct Shape<float> {
-  static constexpr int FNC = 2, FOCC = 1, QOCC = 1, KNW = 4, KDIST = 1, KLAG = 0,
-                       KWGS = 1;
+  static constexpr int FNC = 2, FOCC = 1, QOCC = 1;
 };
 
 bool aligned16(const void *p) { return (reinterpret_cast<uintptr_t>(p) & 15u) == 0; }
@@ -281,10 +274,10 @@ template <typename T, int D> int bwd_dq_impl(const s1f_desc *d, AttnArgs a, hipS
 }
 
 template <typename T, int D> int bwd_dkdv_impl(const s1f_desc *d, const AttnArgs &a, hipStream_t st, bool enqueue) {
-  typedef Shape<T> S;
-  typedef BwdDkdvCfg<T, D, S::KNW, S::KDIST, S::KLAG> KC;
+  typedef BwdDkdvCfg<T, D> KC;
+  constexpr int WGS = sizeof(T) == 4 ? (D == 64 ? 2 : 1) : D == 64 ? 3 : 2;
   const int64_t kv_len = (int64_t)a.seg_off + a.seg_len;
-  return launch(seg_attn_bwd_dkdv_kernel<T, D, S::KNW, S::KDIST, S::KLAG, S::KWGS>, (kv_len + KC::BNW - 1) / KC::BNW,
+  return launch(seg_attn_bwd_dkdv_kernel<T, D, WGS>, (kv_len + KC::BNW - 1) / KC::BNW,
                 (int64_t)d->n_kv_heads * d->batch, 2 * (int64_t)a.seg_off < (int64_t)a.seg_len, KC::THREADS, KC::LDS_BYTES,
                 a, st, enqueue);
 }
