@@ -130,11 +130,11 @@ int s1f_seg_attn_fwd(const s1f_desc *desc, const void *q_seg, const void *k_pref
  * method turns one long launch into n_seg short ones (Sections 3.1-3.2), and a short launch ends with most of the
  * chip idle while its last few row tiles walk their whole prefix.  With a workspace the last row tiles are cut into
  * chunks along the keys that run side by side; each chunk leaves an unnormalised partial result there and a small
- * second kernel merges them by their log-sum-exp.  Same results up to fp32 rounding of that merge; bf16 only (fp32
- * descriptors run unsplit).
+ * second kernel merges them by their log-sum-exp.  Same results up to fp32 rounding of that merge.
  *   workspace        device memory, 16-byte aligned, at least s1f_fwd_workspace_bytes(desc, seg_off, seg_len) bytes
  *                    (0 when this launch is not split: workspace may then be NULL); contents undefined afterwards
- * Errors as s1f_seg_attn_fwd, plus S1F_EINVAL if the workspace is too small, NULL or misaligned. */
+ * Errors as s1f_seg_attn_fwd, plus S1F_EINVAL if the workspace is too small, NULL or misaligned (an fp32 call whose
+ * workspace is too small or NULL runs unsplit). */
 int s1f_seg_attn_fwd_ws(const s1f_desc *desc, const void *q_seg, const void *k_prefix, const void *v_prefix,
                         int64_t seg_off, int64_t seg_len, void *out, float *lse, void *workspace,
                         size_t workspace_bytes, void *hip_stream);
@@ -156,7 +156,9 @@ size_t s1f_fwd_workspace_bytes(const s1f_desc *desc, int64_t seg_off, int64_t se
  *             (two fp32 values per query row and head: -lse/scale and -rowsum(dout * out), the row
  *             statistics the dK/dV kernel starts its products from; behind them up to 512 MiB of partial dQ
  *             rows when the dQ kernel cuts its last row tiles into chunks along the keys, as
- *             s1f_seg_attn_fwd_ws does); contents are undefined afterwards.
+ *             s1f_seg_attn_fwd_ws does, and, once those have been merged, up to 32 MiB of partial dK/dV when that
+ *             launch is too small to fill the chip and is cut along the queries); contents are undefined afterwards.
+ *             An fp32 call accepts any workspace that holds the statistics and then runs uncut.
  * Errors as above, plus S1F_EINVAL if workspace is NULL or workspace_bytes is too small, and
  * S1F_EUNSUPPORTED if batch * n_q_heads * seg_len > 2^28 (the kernels' asynchronous copies use 32-bit byte
  * offsets inside the workspace). */
@@ -166,7 +168,8 @@ int s1f_seg_attn_bwd(const s1f_desc *desc, const void *dout, const void *q_seg, 
                      void *workspace, size_t workspace_bytes, void *hip_stream);
 
 /* The two halves of s1f_seg_attn_bwd as separate calls (same arguments, same validation), for callers
- * that schedule or time them separately; s1f_seg_attn_bwd is exactly _dq followed by _dkdv on one stream.
+ * that schedule or time them separately; s1f_seg_attn_bwd is _dq followed by _dkdv on one stream, except that _dkdv,
+ * which only reads the workspace, never cuts its launch along the queries (same sums in another order).
  *   s1f_seg_attn_bwd_dq    overwrites dq and writes the row statistics (-lse/scale, -rowsum(dout * out))
  *                          into workspace
  *   s1f_seg_attn_bwd_dkdv  reads the statistics left in workspace by _dq for the same segment (lse is

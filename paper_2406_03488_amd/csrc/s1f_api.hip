@@ -13,15 +13,16 @@
 namespace {
 using namespace s1f;
 
-// Kernel shapes per element type.
-template <typename T> struct Shape;
-//   forward: FNC column blocks of 16 rows per wave, FOCC waves per SIMD
-//   dq:      QOCC
-template <> struct Shape<bf16_t> {
-  static constexpr int FNC = 3, FOCC = 2, QOCC = 2;
+// Column blocks of 16 rows per wave (NC) that the forward and dQ kernels are built for: row tiles of 64 * NC rows.  Wide
+// tiles use every K/V operand read from LDS for more matrix instructions, narrow ones leave a small launch more
+// workgroups; plan_rows chooses per launch.  The widest ones are what two waves per SIMD have registers for.
+// Waves per SIMD of the dK/dV kernel: what its accumulators leave room for.
+template <typename T, int D> struct Shape;
+template <int D> struct Shape<bf16_t, D> {
+  static constexpr int FWD_MAX = 3, DQ_MAX = D == 128 ? 2 : 3, OCC = 2, KWGS = D == 64 ? 3 : 2;
 };
-template <> struct Shape<float> {
-  static constexpr int FNC = 2, FOCC = 1, QOCC = 1;
+template <int D> struct Shape<float, D> {
+  static constexpr int FWD_MAX = 2, DQ_MAX = 2, OCC = 1, KWGS = D == 64 ? 2 : 1;
 };
 
 bool aligned16(const void *p) { return (reinterpret_cast<uintptr_t>(p) & 15u) == 0; }
@@ -92,94 +93,145 @@ int row_tile_order(const s1f_desc *d, const AttnArgs &a) {
   return 2 * (int64_t)a.seg_off < (int64_t)a.seg_len && units <= kTileMajorMaxUnits;
 }
 
-// Key-split of the last units of a launch (see split_unit in attn_device.hpp).  A launch of `units` equal-sized
-// units runs in rounds of `slots` (the workgroups the chip holds at once); its last round holds only r = units mod
-// slots of them and still lasts as long as a full one.  Cutting each of those r units into n chunks turns that round
-// into ceil(r n / slots) rounds of 1/n the length; n (at most kMaxSplit, chunks at least kMinChunkKeys keys long,
-// partial results within `cap` bytes) is chosen to minimise that plus what the chunks cost: their own start-up and
-// the merge kernel, which reads every partial result once, both measured against the time a whole unit takes
-// (its keys times the kernel's time per key).  Deterministic in (shape, device, cap): the workspace-size queries
-// and the launches derive the same plan.
-constexpr int kMaxSplit = kMaxChunks;
-constexpr int64_t kMinChunkKeys = 256;
+// ---- how a launch is cut ----------------------------------------------------------------------------------------
+// A launch of units of equal length runs in rounds of as many workgroups as the chip holds at once; its last round may
+// leave most of the chip idle and still lasts as long as a unit.  Two things can be chosen per launch: the width of the
+// row tiles (forward and dQ), and into how many chunks the units of the last round are cut (along the keys in the
+// forward and dQ kernels, see split_unit; along the queries in the dK/dV kernel), to run side by side and be merged by a
+// second kernel.  The plan with the shortest predicted time is taken.  It is a function of shape, device and workspace
+// limit only, so that the workspace-size queries and the launches derive the same one.
 constexpr int64_t kMaxPartBytes = int64_t(512) << 20;      // partial results of one launch with a caller's workspace
 constexpr int64_t kStaticPartBytes = int64_t(32) << 20;    // ... with the library's built-in scratch
-constexpr double kChunkStartup = 0.004;                    // a chunk's prologue and epilogue, in whole-unit times
-constexpr double kMergeSeconds = 12e-6, kMergeBytesPerSecond = 2.5e12;   // the merge kernel: fixed part, read rate
-constexpr double kFwdSecondsPerKey = 0.035e-6, kDqSecondsPerKey = 0.05e-6;   // a 128-row tile against one key
+constexpr double kStartUs = 4.0, kRoundUs = 1.0;           // prologue and epilogue of the first workgroups, of a further round
+constexpr double kMergeUs = 4.5, kMergeBytesPerUs = 2.5e6; // the merge kernel: fixed part, rate of its reads
+
+// Time of one loop step of a workgroup, in microseconds, measured on launches of one workgroup per compute unit (alone),
+// of two (shared) and of all it holds where that is more (crowd: per workgroup), 64 heads behind 4096 and 16384 keys;
+// linear in the tile width.
+struct StepUs {
+  double alone0, alone_nc, shared0, shared_nc, crowd0, crowd_nc;
+  double at(int nc, int64_t per_cu) const {
+    if (per_cu <= 1) return alone0 + alone_nc * nc;
+    const double two = shared0 + shared_nc * nc, all = (crowd0 + crowd_nc * nc) * (double)per_cu;
+    return two > all ? two : all;
+  }
+};
+template <typename T, int D> struct Cost;   // forward, dQ (steps of 32 keys), dK/dV (steps of 32 rows, nc = 0)
+template <> struct Cost<bf16_t, 64> {
+  static constexpr StepUs fwd = {0.225, 0.11, 0.175, 0.23, 0.15, 0.065}, dq = {0.075, 0.16, 0.12, 0.31, 0.07, 0.12},
+                          dkdv = {0.75, 0, 0.9, 0, 0.42, 0};
+};
+template <> struct Cost<bf16_t, 80> {
+  static constexpr StepUs fwd = {0.28, 0.12, 0.25, 0.26, 0, 0}, dq = {0.165, 0.175, 0.285, 0.335, 0, 0}, dkdv = {0.85, 0, 1.2, 0, 0, 0};
+};
+template <> struct Cost<bf16_t, 128> {
+  static constexpr StepUs fwd = {0.29, 0.17, 0.36, 0.32, 0, 0}, dq = {0.2, 0.26, 0.32, 0.52, 0, 0}, dkdv = {1.05, 0, 1.65, 0, 0, 0};
+};
+template <int D> struct Cost<float, D> {   // bound by the matrix instructions: two workgroups take twice as long as one
+  static constexpr double k = D / 64.0;
+  static constexpr StepUs fwd = {0.07 * k, 1.1 * k, 0.14 * k, 2.2 * k, 0.07 * k, 1.1 * k}, dq = {0, 1.6 * k, 0, 3.2 * k, 0, 1.6 * k},
+                          dkdv = {5.4 * k, 0, 9.5 * k, 0, 4.75 * k, 0};
+};
+
+// Workgroups of a kernel that the current device holds at once, and its compute units (0 if that cannot be found out,
+// e.g. without a device: launches are then never cut).
+struct Slots {
+  int total = 0, cus = 0;
+};
+
+// Time of `units` workgroups of `steps` loop steps each.  `longest`: steps of the longest of them.
+double rounds_us(int64_t units, double steps, double longest, const StepUs &us, int nc, const Slots &s) {
+  const int64_t full = units / s.total, rest = units % s.total;
+  double t = kStartUs + full * (steps * us.at(nc, (s.total + s.cus - 1) / s.cus) + kRoundUs);
+  if (rest > 0) {
+    const double last = steps * us.at(nc, (rest + s.cus - 1) / s.cus), one = longest * us.at(nc, 1);
+    t += (last > one ? last : one) + kRoundUs;
+  }
+  return t;
+}
+
 struct SplitPlan {
+  int nc = 1;                 // tile width (forward and dQ)
+  int64_t n_tiles = 0;        // row tiles per (batch, head)
   int64_t n_whole = 0;        // leading workgroup ids that are whole units
   int64_t n_split_units = 0;  // units cut into chunks
   int n_split = 1;            // chunks per split unit
   int64_t grid() const { return n_whole + n_split_units * n_split; }
+  int64_t chunks() const { return n_split_units * n_split; }
 };
 
-SplitPlan plan_split(int64_t units, int slots, int64_t seg_off, double unit_seconds, int64_t part_bytes_per_chunk,
-                     int64_t cap) {
-  SplitPlan p;
-  p.n_whole = units;
-  if (slots <= 0 || units <= 0 || unit_seconds <= 0) return p;
-  const int64_t r = units % slots;
-  if (r == 0) return p;
-  int best = 1;
-  double best_t = 1.0;   // length of the last round in units of a whole unit's time
-  for (int n = 2; n <= kMaxSplit; ++n) {
-    if (n > seg_off / kMinChunkKeys || r * n * part_bytes_per_chunk > cap) break;
-    const double merge = (kMergeSeconds + (double)(r * n * part_bytes_per_chunk) / kMergeBytesPerSecond) / unit_seconds;
-    const double t = (double)((r * n + slots - 1) / slots) / n + kChunkStartup * n + merge;
-    if (t < best_t - 1e-9) { best = n; best_t = t; }
+// Chooses between whole units and, with cap > 0, each number of chunks for those of the last round; `*t` is the time of
+// the best plan known so far.
+void plan_units(SplitPlan *best, double *t, int nc, int64_t n_tiles, int64_t units, double steps, double longest,
+                const StepUs &us, const Slots &s, int64_t part_bytes, int64_t cap) {
+  const int64_t r = units % s.total, whole = units - r;
+  for (int n = 1; n <= kMaxChunks; ++n) {
+    double now;
+    if (n == 1) {
+      now = rounds_us(units, steps, longest, us, nc, s);
+    } else {
+      if (r == 0 || steps < (double)n || r * n * part_bytes > cap) break;
+      now = rounds_us(r * n, steps / n, longest / n, us, nc, s) + kMergeUs + (double)(r * n * part_bytes) / kMergeBytesPerUs;
+      if (whole > 0) now += rounds_us(whole, steps, steps, us, nc, s) - kStartUs;
+      now *= 1.02;   // not for nothing
+    }
+    if (now < *t) {
+      *t = now;
+      best->nc = nc;
+      best->n_tiles = n_tiles;
+      best->n_whole = n == 1 ? units : whole;
+      best->n_split_units = n == 1 ? 0 : r;
+      best->n_split = n;
+    }
   }
-  if (best_t > 0.95) return p;   // not worth a second kernel
-  p.n_whole = units - r;
-  p.n_split_units = r;
-  p.n_split = best;
-  return p;
 }
 
-// Workgroups of `kernel` that the current device holds at once (0 if that cannot be found out, e.g. without a
-// device: launches are then never split).  Looked up once per kernel instantiation and device.
-template <typename K> int resident_workgroups(K kernel, int threads, int lds_bytes) {
-  static std::atomic<int> cached[kMaxDevices];
+// Looked up once per kernel and device.
+template <typename K> Slots resident_slots(K kernel, int lds_bytes, std::atomic<int64_t> *cache) {
+  Slots s;
   int dev = 0;
   if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= kMaxDevices) {
     (void)hipGetLastError();
-    return 0;
+    return s;
   }
-  int n = cached[dev].load(std::memory_order_acquire);
-  if (n > 0) return n;
+  const int64_t known = cache[dev].load(std::memory_order_acquire);
+  if (known > 0) {
+    s.total = (int)(known >> 32);
+    s.cus = (int)(known & 0xffffffff);
+    return s;
+  }
   int per_cu = 0, cus = 0;
   if (prepare(kernel, lds_bytes) != S1F_OK ||
-      hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, reinterpret_cast<const void *>(kernel), threads,
+      hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, reinterpret_cast<const void *>(kernel), 256,
                                                    (size_t)lds_bytes) != hipSuccess ||
-      hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess) {
+      hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || per_cu <= 0 || cus <= 0) {
     (void)hipGetLastError();
-    return 0;
+    return s;
   }
-  n = per_cu * cus;
-  if (n > 0) cached[dev].store(n, std::memory_order_release);
-  return n;
+  s.total = per_cu * cus;
+  s.cus = cus;
+  cache[dev].store(((int64_t)s.total << 32) | cus, std::memory_order_release);
+  return s;
 }
 
 // One-dimensional grid; the kernels decode (unit -> tile, batch*head; chunk) themselves.
 // `tile_major`: order of the workgroups within an XCD; chosen per kernel from the shape of the segment.
-// With `enqueue` false only the one-time preparation runs, so that a caller of several kernels can finish
-// everything that may fail before the first of them is enqueued.  The status reflects this launch only (the
-// return code of the launch call, not the runtime's sticky last error).
-template <typename K>
-int launch(K kernel, int64_t n_tiles, int64_t n_bh, int tile_major, int threads, int lds_bytes, AttnArgs a, hipStream_t st,
-           bool enqueue, const SplitPlan *plan = nullptr) {
-  if (n_tiles * n_bh > 0x7fffffff) return S1F_EUNSUPPORTED;
+// The status reflects this launch only (the return code of the launch call, not the runtime's sticky last error).
+void fill_launch(AttnArgs *a, int64_t n_bh, int tile_major, const SplitPlan &p) {
+  a->n_tiles = (int32_t)p.n_tiles;
+  a->n_bh = (int32_t)n_bh;
+  a->tile_major = tile_major;
+  a->n_whole = (int32_t)p.n_whole;
+  a->n_split = p.n_split;
+  a->n_split_units = (int32_t)p.n_split_units;
+  a->bm = 64 * p.nc;
+}
+template <typename K> int launch(K kernel, int lds_bytes, const SplitPlan &p, int64_t n_bh, AttnArgs a, hipStream_t st) {
+  if (p.n_tiles * n_bh > 0x7fffffff || p.grid() > 0x7fffffff) return S1F_EUNSUPPORTED;
   const int rc = prepare(kernel, lds_bytes);
-  if (rc != S1F_OK || !enqueue) return rc;
-  a.n_tiles = (int32_t)n_tiles;
-  a.n_bh = (int32_t)n_bh;
-  a.tile_major = tile_major;
-  a.n_whole = (int32_t)(plan ? plan->n_whole : n_tiles * n_bh);
-  a.n_split = plan ? plan->n_split : 1;
-  a.n_split_units = (int32_t)(plan ? plan->n_split_units : 0);
-  const int64_t grid = plan ? plan->grid() : n_tiles * n_bh;
+  if (rc != S1F_OK) return rc;
   void *params[] = {&a};
-  const hipError_t e = hipLaunchKernel(reinterpret_cast<const void *>(kernel), dim3((unsigned)grid), dim3(threads), params,
+  const hipError_t e = hipLaunchKernel(reinterpret_cast<const void *>(kernel), dim3((unsigned)p.grid()), dim3(256), params,
                                        (size_t)lds_bytes, st);
   return e == hipSuccess ? S1F_OK : S1F_EDEVICE;
 }
@@ -194,94 +246,147 @@ template <typename K> int launch_merge(K kernel, AttnArgs a, const SplitPlan &pl
 
 inline size_t align256(size_t x) { return (x + 255) & ~(size_t)255; }
 
-// ---- forward ----
-template <typename T, int D> struct FwdLaunch {
-  typedef Shape<T> S;
-  typedef FwdCfg<T, D, S::FNC> Cfg;
-  static constexpr int64_t kPartBytes = (int64_t)Cfg::BM * D * 4, kMlBytes = (int64_t)Cfg::BM * 2 * 4;
-  static auto kernel() { return seg_attn_fwd_kernel<T, D, S::FNC, S::FOCC>; }
-  static int64_t tiles(int64_t seg_len) { return (seg_len + Cfg::BM - 1) / Cfg::BM; }
-  // `split`: the caller brought a workspace (only the bf16 kernels split; fp32 is the reference-precision mode)
-  static SplitPlan plan(const s1f_desc *d, int64_t seg_off, int64_t seg_len, bool split) {
-    const int64_t units = tiles(seg_len) * d->n_q_heads * d->batch;
-    if (!split || sizeof(T) != 2) return plan_split(units, 0, 0, 0, 0, 0);
-    return plan_split(units, resident_workgroups(kernel(), Cfg::THREADS, Cfg::LDS_BYTES), seg_off,
-                      kFwdSecondsPerKey * Cfg::BM / 128 * (double)(seg_off + seg_len / 2), kPartBytes + kMlBytes, kMaxPartBytes);
-  }
-  static size_t workspace_bytes(const SplitPlan &p) {
-    const int64_t chunks = p.n_split_units * p.n_split;
-    return chunks == 0 ? 0 : align256((size_t)(chunks * kPartBytes)) + (size_t)(chunks * kMlBytes);
-  }
+// ---- forward and dQ: row tiles of one kernel family ----
+// KERNEL<NC> of a family F: F::kernel<NC>(), F::LDS, F::MAX (widest NC), F::cost
+template <typename T, int D> struct FwdFamily {
+  static constexpr int MAX = Shape<T, D>::FWD_MAX, LDS = TileRing<T, D>::LDS_BYTES;
+  static constexpr StepUs cost = Cost<T, D>::fwd;
+  static constexpr int64_t row_bytes = D * 4 + 8;   // of a partial result: output, running maximum, row sum
+  template <int NC> static auto kernel() { return seg_attn_fwd_kernel<T, D, NC, Shape<T, D>::OCC>; }
 };
+template <typename T, int D> struct DqFamily {
+  static constexpr int MAX = Shape<T, D>::DQ_MAX, LDS = TileRing<T, D>::LDS_BYTES;
+  static constexpr StepUs cost = Cost<T, D>::dq;
+  static constexpr int64_t row_bytes = D * 4;
+  template <int NC> static auto kernel() { return seg_attn_bwd_dq_kernel<T, D, NC, Shape<T, D>::OCC>; }
+};
+template <typename F, int NC> Slots family_slots() {
+  static std::atomic<int64_t> cache[kMaxDevices];
+  return resident_slots(F::template kernel<NC>(), F::LDS, cache);
+}
+template <typename F, int NC> void plan_rows_nc(const s1f_desc *d, int64_t seg_off, int64_t seg_len, int64_t cap, SplitPlan *best, double *t) {
+  const Slots s = family_slots<F, NC>();
+  const int64_t tiles = (seg_len + 64 * NC - 1) / (64 * NC), units = tiles * d->n_q_heads * d->batch;
+  if (s.total <= 0) {   // nothing known about the device: the widest tiles, uncut
+    if (best->n_tiles == 0) { best->nc = NC; best->n_tiles = tiles; best->n_whole = units; }
+    return;
+  }
+  plan_units(best, t, NC, tiles, units, (double)(seg_off + (seg_len + 1) / 2) / 32 + 1, (double)(seg_off + seg_len) / 32 + 1, F::cost,
+             s, F::row_bytes * 64 * NC, cap);
+}
+// Wide tiles first: a narrower one has to be faster.
+template <typename F> SplitPlan plan_rows(const s1f_desc *d, int64_t seg_off, int64_t seg_len, int64_t cap) {
+  SplitPlan p;
+  double t = 1e300;
+  if constexpr (F::MAX >= 3) plan_rows_nc<F, 3>(d, seg_off, seg_len, cap, &p, &t);
+  plan_rows_nc<F, 2>(d, seg_off, seg_len, cap, &p, &t);
+  plan_rows_nc<F, 1>(d, seg_off, seg_len, cap, &p, &t);
+  return p;
+}
+template <typename F> int launch_rows(const SplitPlan &p, int64_t n_bh, const AttnArgs &a, hipStream_t st) {
+  if constexpr (F::MAX >= 3)
+    if (p.nc == 3) return launch(F::template kernel<3>(), F::LDS, p, n_bh, a, st);
+  if (p.nc == 2) return launch(F::template kernel<2>(), F::LDS, p, n_bh, a, st);
+  return launch(F::template kernel<1>(), F::LDS, p, n_bh, a, st);
+}
 
+template <typename T, int D> size_t fwd_workspace(const SplitPlan &p) {
+  const int64_t rows = p.chunks() * 64 * p.nc;
+  return rows == 0 ? 0 : align256((size_t)(rows * D * 4)) + (size_t)(rows * 8);
+}
 template <typename T, int D>
 int fwd_impl(const s1f_desc *d, AttnArgs a, hipStream_t st, void *workspace, size_t workspace_bytes, bool split) {
-  typedef FwdLaunch<T, D> L;
-  const SplitPlan p = L::plan(d, a.seg_off, a.seg_len, split);
-  if (L::workspace_bytes(p) > workspace_bytes) return S1F_EINVAL;
-  const int64_t chunks = p.n_split_units * p.n_split;
+  typedef FwdFamily<T, D> F;
+  SplitPlan p = plan_rows<F>(d, a.seg_off, a.seg_len, split ? kMaxPartBytes : 0);
+  if (fwd_workspace<T, D>(p) > workspace_bytes) {
+    if (sizeof(T) == 2) return S1F_EINVAL;
+    p = plan_rows<F>(d, a.seg_off, a.seg_len, 0);   // fp32 runs with any workspace
+  }
   a.part = reinterpret_cast<float *>(workspace);
-  a.part_ml = reinterpret_cast<float *>(reinterpret_cast<char *>(workspace) + align256((size_t)(chunks * L::kPartBytes)));
+  a.part_ml = reinterpret_cast<float *>(reinterpret_cast<char *>(workspace) + align256((size_t)(p.chunks() * 64 * p.nc * D * 4)));
   const int64_t n_bh = (int64_t)d->n_q_heads * d->batch;
-  const int order = row_tile_order(d, a);
-  int rc = launch(L::kernel(), L::tiles(a.seg_len), n_bh, order, L::Cfg::THREADS, L::Cfg::LDS_BYTES, a, st, true, &p);
-  if (rc != S1F_OK || chunks == 0) return rc;
-  a.n_tiles = (int32_t)L::tiles(a.seg_len); a.n_bh = (int32_t)n_bh; a.tile_major = order;
-  a.n_whole = (int32_t)p.n_whole; a.n_split = p.n_split; a.n_split_units = (int32_t)p.n_split_units;
-  a.bm = L::Cfg::BM;
-  return launch_merge(seg_attn_fwd_merge_kernel<T, D>, a, p, MergeRows<D>::groups(L::Cfg::BM), st);
+  fill_launch(&a, n_bh, row_tile_order(d, a), p);
+  const int rc = launch_rows<F>(p, n_bh, a, st);
+  if (rc != S1F_OK || p.n_split_units == 0) return rc;
+  return launch_merge(seg_attn_fwd_merge_kernel<T, D>, a, p, MergeRows<D>::groups(a.bm), st);
 }
 template <typename T, int D> size_t fwd_ws_impl(const s1f_desc *d, int64_t seg_off, int64_t seg_len) {
-  return FwdLaunch<T, D>::workspace_bytes(FwdLaunch<T, D>::plan(d, seg_off, seg_len, true));
+  return fwd_workspace<T, D>(plan_rows<FwdFamily<T, D>>(d, seg_off, seg_len, kMaxPartBytes));
 }
 
 // ---- backward ----
-// Workspace: the two planes of row statistics, then (256-byte aligned) the partial dQ rows of a split dQ launch.
-template <typename T, int D> struct DqLaunch {
-  typedef Shape<T> S;
-  static constexpr int NC = D == 128 || sizeof(T) == 4 ? 2 : 3;
-  typedef BwdDqCfg<T, D, NC> QC;
-  static constexpr int64_t kPartBytes = (int64_t)QC::BM * D * 4;
-  static auto kernel() { return seg_attn_bwd_dq_kernel<T, D, NC, S::QOCC>; }
-  static int64_t tiles(int64_t seg_len) { return (seg_len + QC::BM - 1) / QC::BM; }
-  static SplitPlan plan(const s1f_desc *d, int64_t seg_off, int64_t seg_len, int64_t cap) {
-    const int64_t units = tiles(seg_len) * d->n_q_heads * d->batch;
-    if (sizeof(T) != 2) return plan_split(units, 0, 0, 0, 0, 0);
-    return plan_split(units, resident_workgroups(kernel(), 256, QC::LDS_BYTES), seg_off,
-                      kDqSecondsPerKey * QC::BM / 128 * (double)(seg_off + seg_len / 2), kPartBytes, cap);
-  }
-};
+// Workspace: the two planes of row statistics, then (256-byte aligned) the partial results of a cut launch, first those
+// of the dQ kernel, then (its merge kernel has read them) those of the dK/dV kernel.
 inline size_t stat_bytes(const s1f_desc *d, int64_t seg_len) {
   return align256(2 * (size_t)d->batch * (size_t)d->n_q_heads * (size_t)seg_len * sizeof(float));
 }
+template <typename T, int D> struct DkdvFamily {
+  typedef BwdDkdvCfg<T, D> Cfg;
+  static constexpr int LDS = Cfg::LDS_BYTES;
+  static constexpr int64_t part_bytes = 2 * (int64_t)Cfg::BNW * D * 4;
+  static auto kernel() { return seg_attn_bwd_dkdv_kernel<T, D, Shape<T, D>::KWGS>; }
+  static SplitPlan plan(const s1f_desc *d, int64_t seg_off, int64_t seg_len, int64_t cap) {
+    static std::atomic<int64_t> cache[kMaxDevices];
+    const int64_t kv_len = seg_off + seg_len, units = (kv_len + Cfg::BNW - 1) / Cfg::BNW * d->n_kv_heads * d->batch;
+    SplitPlan p;
+    p.n_tiles = (kv_len + Cfg::BNW - 1) / Cfg::BNW;
+    p.n_whole = units;
+    if (cap <= 0) return p;
+    const Slots s = resident_slots(kernel(), LDS, cache);
+    // cut only where the units fill less than one round: with more of them, light and heavy ones even out by themselves
+    if (s.total <= 0 || units >= s.total) return p;
+    const double most = (double)(d->n_q_heads / d->n_kv_heads) * (double)((seg_len + 31) / 32);
+    const double mean = most * ((double)seg_off + 0.5 * (double)seg_len) / (double)kv_len;
+    double t = 1e300;
+    // never more partial results than the built-in scratch holds: s1f_seg_attn_bwd and its _noalloc form then cut alike
+    // and add in the same order
+    plan_units(&p, &t, 0, p.n_tiles, units, mean, most, Cost<T, D>::dkdv, s, part_bytes, cap < kStaticPartBytes ? cap : kStaticPartBytes);
+    return p;
+  }
+};
 template <typename T, int D> size_t bwd_ws_impl(const s1f_desc *d, int64_t seg_off, int64_t seg_len, int64_t cap) {
-  const SplitPlan p = DqLaunch<T, D>::plan(d, seg_off, seg_len, cap);
-  return stat_bytes(d, seg_len) + (size_t)(p.n_split_units * p.n_split * DqLaunch<T, D>::kPartBytes);
+  const SplitPlan q = plan_rows<DqFamily<T, D>>(d, seg_off, seg_len, cap), k = DkdvFamily<T, D>::plan(d, seg_off, seg_len, cap);
+  const int64_t qb = q.chunks() * 64 * q.nc * D * 4, kb = k.chunks() * DkdvFamily<T, D>::part_bytes;
+  return stat_bytes(d, seg_len) + (size_t)(qb > kb ? qb : kb);
 }
 
-template <typename T, int D> int bwd_dq_impl(const s1f_desc *d, AttnArgs a, hipStream_t st, bool enqueue) {
-  typedef DqLaunch<T, D> L;
-  const SplitPlan p = L::plan(d, a.seg_off, a.seg_len, a.part_cap);
+template <typename T, int D> int bwd_dq_impl(const s1f_desc *d, AttnArgs a, hipStream_t st) {
+  typedef DqFamily<T, D> F;
+  const SplitPlan p = plan_rows<F>(d, a.seg_off, a.seg_len, a.part_cap);
   a.part = reinterpret_cast<float *>(reinterpret_cast<char *>(a.delta) + stat_bytes(d, a.seg_len));
   const int64_t n_bh = (int64_t)d->n_q_heads * d->batch;
-  const int order = row_tile_order(d, a);
-  int rc = launch(L::kernel(), L::tiles(a.seg_len), n_bh, order, 256, L::QC::LDS_BYTES, a, st, enqueue, &p);
-  if (rc != S1F_OK || !enqueue || p.n_split_units == 0) return rc;
-  a.n_tiles = (int32_t)L::tiles(a.seg_len); a.n_bh = (int32_t)n_bh; a.tile_major = order;
-  a.n_whole = (int32_t)p.n_whole; a.n_split = p.n_split; a.n_split_units = (int32_t)p.n_split_units;
-  a.bm = L::QC::BM;
-  return launch_merge(seg_attn_bwd_dq_merge_kernel<T, D>, a, p, MergeRows<D>::groups(L::QC::BM), st);
+  fill_launch(&a, n_bh, row_tile_order(d, a), p);
+  const int rc = launch_rows<F>(p, n_bh, a, st);
+  if (rc != S1F_OK || p.n_split_units == 0) return rc;
+  return launch_merge(seg_attn_bwd_dq_merge_kernel<T, D>, a, p, MergeRows<D>::groups(a.bm), st);
 }
 
-template <typename T, int D> int bwd_dkdv_impl(const s1f_desc *d, const AttnArgs &a, hipStream_t st, bool enqueue) {
-  typedef BwdDkdvCfg<T, D> KC;
-  constexpr int WGS = sizeof(T) == 4 ? (D == 64 ? 2 : 1) : D == 64 ? 3 : 2;
-  const int64_t kv_len = (int64_t)a.seg_off + a.seg_len;
-  return launch(seg_attn_bwd_dkdv_kernel<T, D, WGS>, (kv_len + KC::BNW - 1) / KC::BNW,
-                (int64_t)d->n_kv_heads * d->batch, 2 * (int64_t)a.seg_off < (int64_t)a.seg_len, KC::THREADS, KC::LDS_BYTES,
-                a, st, enqueue);
+// `may_split`: the call owns the workspace (s1f_seg_attn_bwd_dkdv only reads it)
+template <typename T, int D> int bwd_dkdv_impl(const s1f_desc *d, AttnArgs a, hipStream_t st, bool may_split) {
+  typedef DkdvFamily<T, D> F;
+  const SplitPlan p = F::plan(d, a.seg_off, a.seg_len, may_split ? a.part_cap : 0);
+  a.part = reinterpret_cast<float *>(reinterpret_cast<char *>(a.delta) + stat_bytes(d, a.seg_len));
+  const int64_t n_bh = (int64_t)d->n_kv_heads * d->batch;
+  fill_launch(&a, n_bh, 2 * (int64_t)a.seg_off < (int64_t)a.seg_len, p);
+  const int rc = launch(F::kernel(), F::LDS, p, n_bh, a, st);
+  if (rc != S1F_OK || p.n_split_units == 0) return rc;
+  return launch_merge(seg_attn_bwd_dkdv_merge_kernel<T, D>, a, p, DkdvMerge<D>::GROUPS, st);
 }
 
+
+// What a launch of either backward kernel could be refused for before it reaches the runtime.
+template <typename F, int NC> int prepare_rows() {
+  const int rc = prepare(F::template kernel<NC>(), F::LDS);
+  if constexpr (NC > 1) return rc != S1F_OK ? rc : prepare_rows<F, NC - 1>();
+  return rc;
+}
+template <typename T, int D> int bwd_ready_impl(const s1f_desc *d, const AttnArgs &a) {
+  const int64_t kv_tiles = ((int64_t)a.seg_off + a.seg_len + DkdvFamily<T, D>::Cfg::BNW - 1) / DkdvFamily<T, D>::Cfg::BNW;
+  const int64_t row_tiles = ((int64_t)a.seg_len + 63) / 64;
+  if (kv_tiles * d->n_kv_heads * d->batch > 0x7fffffff || row_tiles * d->n_q_heads * d->batch > 0x7fffffff) return S1F_EUNSUPPORTED;
+  const int rc = prepare_rows<DqFamily<T, D>, DqFamily<T, D>::MAX>();
+  return rc != S1F_OK ? rc : prepare(DkdvFamily<T, D>::kernel(), DkdvFamily<T, D>::LDS);
+}
 
 #define S1F_DISPATCH(fn, d, ...)                                                        \
   do {                                                                                  \
@@ -321,22 +426,10 @@ int fwd_entry(const s1f_desc *desc, const void *q_seg, const void *k_prefix, con
 }
 // (callers have validated the descriptor: the dispatch below always finds its kernel)
 size_t fwd_ws_dispatch(const s1f_desc *d, int64_t seg_off, int64_t seg_len) {
-  if (d->dtype != S1F_BF16) return 0;   // fp32 launches are never split
-  switch (d->head_dim) {
-    case 64: return fwd_ws_impl<bf16_t, 64>(d, seg_off, seg_len);
-    case 80: return fwd_ws_impl<bf16_t, 80>(d, seg_off, seg_len);
-    case 128: return fwd_ws_impl<bf16_t, 128>(d, seg_off, seg_len);
-  }
-  return 0;
+  S1F_DISPATCH(fwd_ws_impl, d, d, seg_off, seg_len);
 }
 size_t bwd_ws_dispatch(const s1f_desc *d, int64_t seg_off, int64_t seg_len, int64_t cap) {
-  if (d->dtype != S1F_BF16) return stat_bytes(d, seg_len);
-  switch (d->head_dim) {
-    case 64: return bwd_ws_impl<bf16_t, 64>(d, seg_off, seg_len, cap);
-    case 80: return bwd_ws_impl<bf16_t, 80>(d, seg_off, seg_len, cap);
-    case 128: return bwd_ws_impl<bf16_t, 128>(d, seg_off, seg_len, cap);
-  }
-  return stat_bytes(d, seg_len);
+  S1F_DISPATCH(bwd_ws_impl, d, d, seg_off, seg_len, cap);
 }
 }  // namespace
 
@@ -362,12 +455,14 @@ extern "C" size_t s1f_bwd_workspace_bytes(const s1f_desc *desc, int64_t seg_off,
 }
 
 namespace {
-int bwd_dq_dispatch(const s1f_desc *d, const AttnArgs &a, hipStream_t st, bool enqueue) {
-  S1F_DISPATCH(bwd_dq_impl, d, d, a, st, enqueue);
+int bwd_dq_dispatch(const s1f_desc *d, const AttnArgs &a, hipStream_t st) {
+  S1F_DISPATCH(bwd_dq_impl, d, d, a, st);
 }
-int bwd_dkdv_dispatch(const s1f_desc *d, const AttnArgs &a, hipStream_t st, bool enqueue) {
-  S1F_DISPATCH(bwd_dkdv_impl, d, d, a, st, enqueue);
+int bwd_dkdv_dispatch(const s1f_desc *d, const AttnArgs &a, hipStream_t st, bool may_split) {
+  S1F_DISPATCH(bwd_dkdv_impl, d, d, a, st, may_split);
 }
+
+int bwd_ready_dispatch(const s1f_desc *d, const AttnArgs &a) { S1F_DISPATCH(bwd_ready_impl, d, d, a); }
 
 // Validation shared by the backward entry points; fills `a` on success.
 int bwd_prepare(const s1f_desc *desc, const void *dout, const void *q_seg, const void *k_prefix, const void *v_prefix,
@@ -380,7 +475,11 @@ int bwd_prepare(const s1f_desc *desc, const void *dout, const void *q_seg, const
     return S1F_EINVAL;
   rc = check_seg(desc, seg_off, seg_len);
   if (rc != S1F_OK) return rc;
-  if (workspace_bytes < bwd_ws_dispatch(desc, seg_off, seg_len, part_cap)) return S1F_EINVAL;
+  if (workspace_bytes < bwd_ws_dispatch(desc, seg_off, seg_len, part_cap)) {
+    // fp32 runs with any workspace that holds the row statistics; its launches are then left whole
+    if (desc->dtype == S1F_BF16 || workspace_bytes < stat_bytes(desc, seg_len)) return S1F_EINVAL;
+    part_cap = 0;
+  }
   // the asynchronous copies address the workspace with 32-bit byte offsets
   const int64_t stat_rows = (int64_t)desc->batch * desc->n_q_heads * seg_len;
   if (stat_rows > (int64_t(1) << 28)) return S1F_EUNSUPPORTED;
@@ -406,12 +505,9 @@ int bwd_entry(const s1f_desc *desc, const void *dout, const void *q_seg, const v
   a.out = out; a.dq = dq; a.dk_acc = dk_prefix_acc; a.dv_acc = dv_prefix_acc;
   hipStream_t st = reinterpret_cast<hipStream_t>(hip_stream);
   // everything that can fail short of the launches themselves happens before the first kernel is enqueued
-  int rc2 = bwd_dq_dispatch(desc, a, st, false);
-  if (rc2 == S1F_OK) rc2 = bwd_dkdv_dispatch(desc, a, st, false);
-  if (rc2 != S1F_OK) return rc2;
-  rc2 = bwd_dq_dispatch(desc, a, st, true);
-  if (rc2 != S1F_OK) return rc2;
-  return bwd_dkdv_dispatch(desc, a, st, true);
+  int rc2 = bwd_ready_dispatch(desc, a);
+  if (rc2 == S1F_OK) rc2 = bwd_dq_dispatch(desc, a, st);
+  return rc2 == S1F_OK ? bwd_dkdv_dispatch(desc, a, st, true) : rc2;
 }
 }  // namespace
 
@@ -424,7 +520,7 @@ extern "C" int s1f_seg_attn_bwd_dq(const s1f_desc *desc, const void *dout, const
   if (rc != S1F_OK) return rc;
   if (!out || !dq || !aligned16(out) || !aligned16(dq)) return S1F_EINVAL;
   a.out = out; a.dq = dq;
-  return bwd_dq_dispatch(desc, a, reinterpret_cast<hipStream_t>(hip_stream), true);
+  return bwd_dq_dispatch(desc, a, reinterpret_cast<hipStream_t>(hip_stream));
 }
 
 extern "C" int s1f_seg_attn_bwd_dkdv(const s1f_desc *desc, const void *dout, const void *q_seg, const void *k_prefix,
@@ -436,7 +532,7 @@ extern "C" int s1f_seg_attn_bwd_dkdv(const s1f_desc *desc, const void *dout, con
   if (rc != S1F_OK) return rc;
   if (!dk_prefix_acc || !dv_prefix_acc || !aligned16(dk_prefix_acc) || !aligned16(dv_prefix_acc)) return S1F_EINVAL;
   a.dk_acc = dk_prefix_acc; a.dv_acc = dv_prefix_acc;
-  return bwd_dkdv_dispatch(desc, a, reinterpret_cast<hipStream_t>(hip_stream), true);
+  return bwd_dkdv_dispatch(desc, a, reinterpret_cast<hipStream_t>(hip_stream), false);
 }
 
 extern "C" int s1f_seg_attn_bwd(const s1f_desc *desc, const void *dout, const void *q_seg, const void *k_prefix,

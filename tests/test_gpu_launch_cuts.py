@@ -1,0 +1,70 @@
+"""Launches at the edges of what the planner chooses between: row tiles of 64, 128 and 192 rows, last tiles that are
+nearly empty or nearly full, launches cut along the keys (forward, dQ) and along the queries (dK/dV) with more chunks
+than some of their units have tiles, in both element types.  Compared with the oracle within the contract's tolerances;
+the two halves of the backward as separate calls (whose dK/dV launch is never cut) within the rounding of fp32 sums."""
+import numpy as np
+import pytest
+import torch
+
+import paper_2406_03488_amd as s1f
+import s1f_synth as S
+from oracle import attention as A
+from test_gpu_batch_sweep import _check, _sequence
+
+pytestmark = pytest.mark.gpu
+
+# (query heads, K/V heads, offset, rows): one row; one row more and less than a tile of each width; a first segment (its
+# early units have fewer key tiles than chunks); enough heads to fill the chip with wide tiles and ragged last ones
+SHAPES = [(2, 1, 700, 1), (4, 2, 0, 63), (4, 2, 33, 65), (8, 2, 400, 127), (3, 1, 1000, 129), (2, 2, 5, 191),
+          (8, 8, 95, 193), (4, 4, 0, 640), (64, 8, 300, 200)]
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+@pytest.mark.parametrize("d", [64, 80, 128])
+@pytest.mark.parametrize("hq,hkv,off,m", SHAPES)
+def test_edges_of_the_launch_plan(dtype, d, hq, hkv, off, m):
+    from gpu_harness import run_segment, to_device
+    n = off + m
+    q, k, v, do = _sequence(8000 + d + off + m, hq, hkv, n, d, dtype)
+    out, lse = A.segment_forward(q[:, off:], k, v, off)
+    dq, dk, dv = A.segment_backward(do[:, off:], q[:, off:], k, v, off)
+    want = {"out": out, "lse": lse, "dq": dq, "dk": dk, "dv": dv}
+    got = run_segment(q[:, off:], k, v, do[:, off:], off, dtype)
+    _check(got, want, dtype)
+    plain = run_segment(q[:, off:], k, v, do[:, off:], off, dtype, layout="bshd", fwd_workspace=False)
+    _check(plain, want, dtype, where="without a forward workspace: ")
+
+    dev = lambda x: to_device(x, dtype)[None].contiguous()
+    qd, kd, vd, dod = dev(q[:, off:]), dev(k), dev(v), dev(do[:, off:])
+    o, dqd = torch.empty_like(qd), torch.empty_like(qd)
+    l = torch.empty((1, hq, m), dtype=torch.float32, device="cuda")
+    s1f.seg_attn_fwd(qd, kd, vd, off, o, l)
+    ws = torch.empty(s1f.bwd_workspace_bytes(qd, kd, off), dtype=torch.uint8, device="cuda")
+    acc = {}
+    for how in ("one call", "two calls"):
+        a, b = (torch.zeros((1, hkv, n, d), dtype=torch.float32, device="cuda") for _ in range(2))
+        if how == "one call":
+            s1f.seg_attn_bwd(dod, qd, kd, vd, o, l, off, dqd, a, b, ws)
+        else:
+            s1f.seg_attn_bwd_dq(dod, qd, kd, vd, o, l, off, dqd, ws)
+            s1f.seg_attn_bwd_dkdv(dod, qd, kd, vd, l, off, a, b, ws)
+        acc[how] = (a.cpu().numpy(), b.cpu().numpy())
+    # the same products in another order of summation: every partial sum carries at most 2^-24 of the largest one
+    bound = 2.0 ** -20 * max(1.0, float(np.abs(dk).max()), float(np.abs(dv).max())) * np.sqrt(hq * m)
+    for x, y in zip(acc["one call"], acc["two calls"]):
+        assert np.abs(x - y).max() <= bound
+
+
+def test_fp32_forward_takes_any_workspace():
+    """fp32 calls were never cut before they could be: a caller that brings no workspace, or a small one, is served."""
+    q, k, v, _ = (torch.from_numpy(x)[None].cuda() for x in _sequence(77, 4, 2, 900, 64, "f32"))
+    qs = q[:, :, 700:].contiguous()
+    assert s1f.fwd_workspace_bytes(qs, k, 700) > 16
+    outs = []
+    for ws in (None, torch.empty(16, dtype=torch.uint8, device="cuda"),
+               torch.empty(s1f.fwd_workspace_bytes(qs, k, 700), dtype=torch.uint8, device="cuda")):
+        out, lse = torch.empty_like(qs), torch.empty(qs.shape[:3], device="cuda")
+        s1f.seg_attn_fwd_ws(qs, k, v, 700, out, lse, ws)
+        outs.append(out)
+    assert torch.equal(outs[0], outs[1])
+    assert (outs[0] - outs[2]).abs().max().item() <= 1e-5
