@@ -185,6 +185,7 @@ __global__ void __launch_bounds__(256, OCC) seg_attn_bwd_dq_kernel(const AttnArg
       else if (y < TOTAL) fr[x % PR] = M::nat(kn, y - NN - NT, Tile32<T, D>::BYTES);
       else fr[x % PR] = M::nat(ka, x % PR);   // the next step's first ones
     };
+    if (D != 80) __builtin_amdgcn_s_setprio(1);   // phase A first: of two ready waves the one with little else to issue
     f32x4 sn[2][NC];
 #pragma unroll
     for (int i = 0; i < NN; ++i)
@@ -196,6 +197,7 @@ __global__ void __launch_bounds__(256, OCC) seg_attn_bwd_dq_kernel(const AttnArg
         if (i == 1) make_ds(cb);
         __builtin_amdgcn_sched_barrier(0);
       }
+    if (D != 80) __builtin_amdgcn_s_setprio(0);
     // probability x of 8 * NC: column block by column block, so that half of them do not wait for the last scores
     auto probs = [&](int x0, int x1) {
 #pragma unroll
@@ -549,12 +551,13 @@ __global__ void __launch_bounds__(256, WGS) seg_attn_bwd_dkdv_kernel(const AttnA
   // touch 16 cache lines per 64 lanes.  Each wave therefore passes its 32 x D block through LDS (its own region; 16-byte
   // chunk c of row r at position c ^ (r & 15), so that the row-per-lane writes spread over all banks) and updates the
   // accumulators row by row, LPR lanes side by side on one row.
+  const int el = lane_id(), en = el & 15, ej = el >> 4;   // (anew: not kept in registers across the loop)
   float *dkb = a.dk_acc + kvoff, *dvb = a.dv_acc + kvoff;
   constexpr int LPR = D / 4;                        // lanes per row (16 bytes each)
   constexpr int RPI = 64 / LPR;                     // rows per instruction
   constexpr int NI = (32 + RPI - 1) / RPI;          // instructions per block
   char *region = smem + wave * (32 * Cfg::EPI_ROW);
-  const int row_in = lane / LPR, col = lane % LPR;
+  const int row_in = el / LPR, col = el % LPR;
 #pragma unroll
   for (int which = 0; which < 2; ++which) {
     const float mul = which == 0 ? a.scale : 1.f;
@@ -563,8 +566,8 @@ __global__ void __launch_bounds__(256, WGS) seg_attn_bwd_dkdv_kernel(const AttnA
     for (int cb = 0; cb < 2; ++cb)
 #pragma unroll
       for (int x = 0; x < DB; ++x) {
-        const int r = 16 * cb + n, ch = M::quad_d0(x, j) >> 2;
-        *reinterpret_cast<f32x4 *>(region + r * Cfg::EPI_ROW + 16 * (ch ^ n)) = M::quad(which == 0 ? dk[cb] : dv[cb], x) * mul;
+        const int r = 16 * cb + en, ch = M::quad_d0(x, ej) >> 2;
+        *reinterpret_cast<f32x4 *>(region + r * Cfg::EPI_ROW + 16 * (ch ^ en)) = M::quad(which == 0 ? dk[cb] : dv[cb], x) * mul;
       }
     if (uc.slot >= 0) {   // a chunk: its share goes to the workspace, [chunk][dK, dV][key][head_dim]
       float *part = a.part + ((int64_t)uc.slot * 2 + which) * (Cfg::BNW * D) + (int64_t)(wave * 32) * D;

@@ -130,6 +130,7 @@ S1F_DEV void fwd_step(f32x4 (&p)[2][NC], f32x4 (&o)[NC][M::DB], const float (&m)
                       lds_addr vtile, float c, int ahead_next) {
   typedef typename M::Frag Frag;
   constexpr int PK = KRing<M>::N, PV = M::NT < 3 ? M::NT : 3, NK = M::NK, NN = M::NN, NT = M::NT;
+  __builtin_amdgcn_s_setprio(1);   // of two ready waves the one in phase 1, which has little else to issue, feeds the matrix pipe
   typename M::Slab pf[NC];
   Frag vf[PV];
   f32x4 sn[2][NC];
@@ -182,6 +183,7 @@ S1F_DEV void fwd_step(f32x4 (&p)[2][NC], f32x4 (&o)[NC][M::DB], const float (&m)
 #pragma unroll
     for (int i = 0; i < PV; ++i) vf[i] = M::tr(va, i);
   }
+  __builtin_amdgcn_s_setprio(0);
   const typename M::Nat kb = rd.nat_at(ktile_after);
 #pragma unroll
   for (int i = 0; i < NT; ++i) {
