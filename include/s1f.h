@@ -156,8 +156,8 @@ size_t s1f_fwd_workspace_bytes(const s1f_desc *desc, int64_t seg_off, int64_t se
  *             (two fp32 values per query row and head: -lse/scale and -rowsum(dout * out), the row
  *             statistics the dK/dV kernel starts its products from; behind them up to 512 MiB of partial dQ
  *             rows when the dQ kernel cuts its last row tiles into chunks along the keys, as
- *             s1f_seg_attn_fwd_ws does, and, once those have been merged, up to 32 MiB of partial dK/dV when that
- *             launch is too small to fill the chip and is cut along the queries); contents are undefined afterwards.
+ *             s1f_seg_attn_fwd_ws does, and, once those have been merged, up to 32 MiB of partial dK/dV when the
+ *             last key tiles of that launch are cut along the queries); contents are undefined afterwards.
  *             An fp32 call accepts any workspace that holds the statistics and then runs uncut.
  * Errors as above, plus S1F_EINVAL if workspace is NULL or workspace_bytes is too small, and
  * S1F_EUNSUPPORTED if batch * n_q_heads * seg_len > 2^28 (the kernels' asynchronous copies use 32-bit byte

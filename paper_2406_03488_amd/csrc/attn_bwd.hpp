@@ -278,7 +278,7 @@ __global__ void __launch_bounds__(256, OCC) seg_attn_bwd_dq_kernel(const AttnArg
 
 // Sums the chunks of the units that seg_attn_bwd_dq_kernel split along the keys: dq = scale * sum_c part_c.
 // Thread and grid layout as in seg_attn_fwd_merge_kernel.
-template <typename T, int D>
+template <typename T, int D, int MC>
 __global__ void __launch_bounds__(256) seg_attn_bwd_dq_merge_kernel(const AttnArgs a) {
   constexpr int C4 = D / 4, RG = 256 / C4;
   const int BM = a.bm, GROUPS = (BM + RG - 1) / RG;
@@ -293,13 +293,14 @@ __global__ void __launch_bounds__(256) seg_attn_bwd_dq_merge_kernel(const AttnAr
   int slot0, slot_step;
   chunk_slots(unit, a.n_split_units, slot0, slot_step);
   const float *pd = a.part + (int64_t)slot0 * (BM * D) + rl * D + 4 * c4;
-  f32x4 pc[kMaxChunks];
+  f32x4 pc[MC];
 #pragma unroll
-  for (int c = 0; c < kMaxChunks; ++c)
-    pc[c] = c < S ? *reinterpret_cast<const f32x4 *>(pd + (int64_t)c * slot_step * (BM * D)) : f32x4{0.f, 0.f, 0.f, 0.f};
+  for (int c = 0; c < MC; ++c)   // past the last chunk: that one again, not added
+    pc[c] = *reinterpret_cast<const f32x4 *>(pd + (int64_t)(c < S ? c : S - 1) * slot_step * (BM * D));
   f32x4 acc = pc[0];
 #pragma unroll
-  for (int c = 1; c < kMaxChunks; ++c) acc += pc[c];
+  for (int c = 1; c < MC; ++c)
+    if (c < S) acc += pc[c];
   T *dqb = reinterpret_cast<T *>(a.dq) + b * a.q_sb + h * a.q_sh;
   store4<T>(dqb + (int64_t)r * a.q_ss + 4 * c4, acc[0] * a.scale, acc[1] * a.scale, acc[2] * a.scale, acc[3] * a.scale);
 }
@@ -569,8 +570,8 @@ __global__ void __launch_bounds__(256, WGS) seg_attn_bwd_dkdv_kernel(const AttnA
         const int r = 16 * cb + en, ch = M::quad_d0(x, ej) >> 2;
         *reinterpret_cast<f32x4 *>(region + r * Cfg::EPI_ROW + 16 * (ch ^ en)) = M::quad(which == 0 ? dk[cb] : dv[cb], x) * mul;
       }
-    if (uc.slot >= 0) {   // a chunk: its share goes to the workspace, [chunk][dK, dV][key][head_dim]
-      float *part = a.part + ((int64_t)uc.slot * 2 + which) * (Cfg::BNW * D) + (int64_t)(wave * 32) * D;
+    if (uc.chunk > 0) {   // a chunk other than the first: its share goes to the workspace, [chunk - 1][dK, dV][key][head_dim]
+      float *part = a.part + ((int64_t)(uc.slot - a.n_split_units) * 2 + which) * (Cfg::BNW * D) + (int64_t)(wave * 32) * D;
 #pragma unroll
       for (int i = 0; i < NI; ++i) {
         const int r = i * RPI + row_in, rc = r < 32 ? r : 31;
@@ -594,34 +595,35 @@ __global__ void __launch_bounds__(256, WGS) seg_attn_bwd_dkdv_kernel(const AttnA
   }
 }
 
-// Adds the chunks of the units that seg_attn_bwd_dkdv_kernel split along the queries into the accumulators:
-// acc += sum_c part_c, in the order of the chunks.  A thread handles 4 consecutive head_dim elements of one key of one
+// Adds the chunks of the units that seg_attn_bwd_dkdv_kernel split along the queries into the accumulators, which chunk
+// 0 has updated itself: acc += sum_c part_c, c = 1 .. n_split - 1, in the order of the chunks.  A thread handles 4 consecutive head_dim elements of one key of one
 // of the two accumulators (grid: split units x DkdvMerge<D>::GROUPS).
 template <int D> struct DkdvMerge {
   static constexpr int PER = 128 * D / 4;                  // threads per unit and accumulator
   static constexpr int GROUPS = 2 * PER / 256;
   static_assert(PER % 256 == 0, "whole workgroups per accumulator");
 };
-template <typename T, int D> __global__ void __launch_bounds__(256) seg_attn_bwd_dkdv_merge_kernel(const AttnArgs a) {
+template <typename T, int D, int MC> __global__ void __launch_bounds__(256) seg_attn_bwd_dkdv_merge_kernel(const AttnArgs a) {
   typedef DkdvMerge<D> DM;
   const int unit = (int)blockIdx.x / DM::GROUPS, g = (int)blockIdx.x % DM::GROUPS;
   const int which = g / (DM::GROUPS / 2), t = (g % (DM::GROUPS / 2)) * 256 + (int)threadIdx.x;
   int kt, bh;
   decode_workgroup(a.n_whole + unit, a.n_tiles, a.n_bh, a.tile_major, kt, bh);
   const int n_kv_heads = a.n_q_heads / a.group, hk = bh % n_kv_heads, b = bh / n_kv_heads;
-  const int key = kt * 128 + t / (D / 4), S = a.n_split;
+  const int key = kt * 128 + t / (D / 4), S = a.n_split - 1;   // partial results
   if (key >= a.seg_off + a.seg_len) return;
   int slot0, slot_step;
   chunk_slots(unit, a.n_split_units, slot0, slot_step);
   const float *part = a.part + ((int64_t)slot0 * 2 + which) * (128 * D) + 4 * t;
-  f32x4 pc[kMaxChunks];
+  f32x4 pc[MC];
 #pragma unroll
-  for (int c = 0; c < kMaxChunks; ++c)
-    pc[c] = c < S ? *reinterpret_cast<const f32x4 *>(part + (int64_t)c * slot_step * (2 * 128 * D)) : f32x4{0.f, 0.f, 0.f, 0.f};
+  for (int c = 0; c < MC; ++c)   // past the last chunk: that one again, not added
+    pc[c] = *reinterpret_cast<const f32x4 *>(part + (int64_t)(c < S ? c : S - 1) * slot_step * (2 * 128 * D));
   float *acc = (which ? a.dv_acc : a.dk_acc) + b * a.kv_sb + hk * a.kv_sh + (int64_t)key * a.kv_ss + 4 * (t % (D / 4));
   f32x4 sum = pc[0];
 #pragma unroll
-  for (int c = 1; c < kMaxChunks; ++c) sum += pc[c];
+  for (int c = 1; c < MC; ++c)
+    if (c < S) sum += pc[c];
   *reinterpret_cast<f32x4 *>(acc) = *reinterpret_cast<const f32x4 *>(acc) + sum;
 }
 

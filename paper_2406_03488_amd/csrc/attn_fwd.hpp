@@ -382,7 +382,9 @@ template <int D> struct MergeRows {
   static constexpr int RG = 256 / C4;       // rows per workgroup
   __host__ __device__ static constexpr int groups(int bm) { return (bm + RG - 1) / RG; }
 };
-template <typename T, int D>
+// MC: most chunks this instance merges (loads of all of them are in flight together; more of them than there are cost
+// registers and with them waves: at 16 for a cut into 2, 256 units of 128 rows and head_dim 128 took 14 us instead of 8).
+template <typename T, int D, int MC>
 __global__ void __launch_bounds__(256) seg_attn_fwd_merge_kernel(const AttnArgs a) {
   typedef MergeRows<D> MR;
   const int BM = a.bm, groups = MR::groups(BM);
@@ -398,25 +400,26 @@ __global__ void __launch_bounds__(256) seg_attn_fwd_merge_kernel(const AttnArgs 
   chunk_slots(unit, a.n_split_units, slot0, slot_step);
   const float *po = a.part + (int64_t)slot0 * (BM * D) + rl * D + 4 * c4;
   const float *pml = a.part_ml + (int64_t)slot0 * (BM * 2) + 2 * rl;
-  float mc[kMaxChunks], lc[kMaxChunks];
-  f32x4 oc[kMaxChunks];
+  f32x2 ml[MC];
+  f32x4 oc[MC];
 #pragma unroll
-  for (int c = 0; c < kMaxChunks; ++c) {
-    const bool on = c < S;
-    mc[c] = on ? pml[(int64_t)c * slot_step * (BM * 2)] : -INFINITY;
-    lc[c] = on ? pml[(int64_t)c * slot_step * (BM * 2) + 1] : 0.f;
-    oc[c] = on ? *reinterpret_cast<const f32x4 *>(po + (int64_t)c * slot_step * (BM * D)) : f32x4{0.f, 0.f, 0.f, 0.f};
+  for (int c = 0; c < MC; ++c) {   // past the last chunk: that one again, without weight
+    const int64_t at = (int64_t)(c < S ? c : S - 1) * slot_step;
+    ml[c] = *reinterpret_cast<const f32x2 *>(pml + at * (BM * 2));
+    oc[c] = *reinterpret_cast<const f32x4 *>(po + at * (BM * D));
   }
-  float m = mc[0];
+  float m = ml[0][0];
 #pragma unroll
-  for (int c = 1; c < kMaxChunks; ++c) m = fmaxf(m, mc[c]);
+  for (int c = 1; c < MC; ++c) m = fmaxf(m, ml[c][0]);
   float l = 0.f;
   f32x4 acc = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-  for (int c = 0; c < kMaxChunks; ++c) {
-    const float w = exp2_fast(mc[c] - m);   // 0 for the chunks past S
-    l += w * lc[c];
-    acc += w * oc[c];
+  for (int c = 0; c < MC; ++c) {
+    const float w = exp2_fast(ml[c][0] - m);
+    if (c < S) {
+      l += w * ml[c][1];
+      acc += w * oc[c];
+    }
   }
   const float inv = 1.f / l;
   T *ob = reinterpret_cast<T *>(a.out_w) + b * a.q_sb + h * a.q_sh;

@@ -160,18 +160,19 @@ struct SplitPlan {
   int64_t chunks() const { return n_split_units * n_split; }
 };
 
-// Chooses between whole units and, with cap > 0, each number of chunks for those of the last round; `*t` is the time of
-// the best plan known so far.
+// Chooses between whole units and, with cap > 0, each number of chunks for those of the last round, of which `direct` per
+// unit need no partial result; `*t` is the time of the best plan known so far.
 void plan_units(SplitPlan *best, double *t, int nc, int64_t n_tiles, int64_t units, double steps, double longest,
-                const StepUs &us, const Slots &s, int64_t part_bytes, int64_t cap) {
+                const StepUs &us, const Slots &s, int64_t part_bytes, int direct, int64_t cap) {
   const int64_t r = units % s.total, whole = units - r;
   for (int n = 1; n <= kMaxChunks; ++n) {
     double now;
     if (n == 1) {
       now = rounds_us(units, steps, longest, us, nc, s);
     } else {
-      if (r == 0 || steps < (double)n || r * n * part_bytes > cap) break;
-      now = rounds_us(r * n, steps / n, longest / n, us, nc, s) + kMergeUs + (double)(r * n * part_bytes) / kMergeBytesPerUs;
+      const int64_t bytes = r * (n - direct) * part_bytes;
+      if (r == 0 || steps < (double)n || bytes > cap) break;
+      now = rounds_us(r * n, steps / n, longest / n, us, nc, s) + kMergeUs + (double)bytes / kMergeBytesPerUs;
       if (whole > 0) now += rounds_us(whole, steps, steps, us, nc, s) - kStartUs;
       now *= 1.02;   // not for nothing
     }
@@ -244,6 +245,13 @@ template <typename K> int launch_merge(K kernel, AttnArgs a, const SplitPlan &pl
   return e == hipSuccess ? S1F_OK : S1F_EDEVICE;
 }
 
+// The instance of a merge kernel for a number of partial results per unit.
+#define S1F_MERGE(KERNEL, T, D, parts, ...)                                                                       \
+  ((parts) <= 2   ? launch_merge(KERNEL<T, D, 2>, __VA_ARGS__)                                                    \
+   : (parts) <= 4 ? launch_merge(KERNEL<T, D, 4>, __VA_ARGS__)                                                    \
+   : (parts) <= 8 ? launch_merge(KERNEL<T, D, 8>, __VA_ARGS__)                                                    \
+                  : launch_merge(KERNEL<T, D, kMaxChunks>, __VA_ARGS__))
+
 inline size_t align256(size_t x) { return (x + 255) & ~(size_t)255; }
 
 // ---- forward and dQ: row tiles of one kernel family ----
@@ -272,7 +280,7 @@ template <typename F, int NC> void plan_rows_nc(const s1f_desc *d, int64_t seg_o
     return;
   }
   plan_units(best, t, NC, tiles, units, (double)(seg_off + (seg_len + 1) / 2) / 32 + 1, (double)(seg_off + seg_len) / 32 + 1, F::cost,
-             s, F::row_bytes * 64 * NC, cap);
+             s, F::row_bytes * 64 * NC, 0, cap);
 }
 // Wide tiles first: a narrower one has to be faster.
 template <typename F> SplitPlan plan_rows(const s1f_desc *d, int64_t seg_off, int64_t seg_len, int64_t cap) {
@@ -308,7 +316,7 @@ int fwd_impl(const s1f_desc *d, AttnArgs a, hipStream_t st, void *workspace, siz
   fill_launch(&a, n_bh, row_tile_order(d, a), p);
   const int rc = launch_rows<F>(p, n_bh, a, st);
   if (rc != S1F_OK || p.n_split_units == 0) return rc;
-  return launch_merge(seg_attn_fwd_merge_kernel<T, D>, a, p, MergeRows<D>::groups(a.bm), st);
+  return S1F_MERGE(seg_attn_fwd_merge_kernel, T, D, p.n_split, a, p, MergeRows<D>::groups(a.bm), st);
 }
 template <typename T, int D> size_t fwd_ws_impl(const s1f_desc *d, int64_t seg_off, int64_t seg_len) {
   return fwd_workspace<T, D>(plan_rows<FwdFamily<T, D>>(d, seg_off, seg_len, kMaxPartBytes));
@@ -333,20 +341,19 @@ template <typename T, int D> struct DkdvFamily {
     p.n_whole = units;
     if (cap <= 0) return p;
     const Slots s = resident_slots(kernel(), LDS, cache);
-    // cut only where the units fill less than one round: with more of them, light and heavy ones even out by themselves
-    if (s.total <= 0 || units >= s.total) return p;
+    if (s.total <= 0) return p;
     const double most = (double)(d->n_q_heads / d->n_kv_heads) * (double)((seg_len + 31) / 32);
     const double mean = most * ((double)seg_off + 0.5 * (double)seg_len) / (double)kv_len;
     double t = 1e300;
     // never more partial results than the built-in scratch holds: s1f_seg_attn_bwd and its _noalloc form then cut alike
     // and add in the same order
-    plan_units(&p, &t, 0, p.n_tiles, units, mean, most, Cost<T, D>::dkdv, s, part_bytes, cap < kStaticPartBytes ? cap : kStaticPartBytes);
+    plan_units(&p, &t, 0, p.n_tiles, units, mean, most, Cost<T, D>::dkdv, s, part_bytes, 1, cap < kStaticPartBytes ? cap : kStaticPartBytes);
     return p;
   }
 };
 template <typename T, int D> size_t bwd_ws_impl(const s1f_desc *d, int64_t seg_off, int64_t seg_len, int64_t cap) {
   const SplitPlan q = plan_rows<DqFamily<T, D>>(d, seg_off, seg_len, cap), k = DkdvFamily<T, D>::plan(d, seg_off, seg_len, cap);
-  const int64_t qb = q.chunks() * 64 * q.nc * D * 4, kb = k.chunks() * DkdvFamily<T, D>::part_bytes;
+  const int64_t qb = q.chunks() * 64 * q.nc * D * 4, kb = (k.chunks() - k.n_split_units) * DkdvFamily<T, D>::part_bytes;
   return stat_bytes(d, seg_len) + (size_t)(qb > kb ? qb : kb);
 }
 
@@ -358,7 +365,7 @@ template <typename T, int D> int bwd_dq_impl(const s1f_desc *d, AttnArgs a, hipS
   fill_launch(&a, n_bh, row_tile_order(d, a), p);
   const int rc = launch_rows<F>(p, n_bh, a, st);
   if (rc != S1F_OK || p.n_split_units == 0) return rc;
-  return launch_merge(seg_attn_bwd_dq_merge_kernel<T, D>, a, p, MergeRows<D>::groups(a.bm), st);
+  return S1F_MERGE(seg_attn_bwd_dq_merge_kernel, T, D, p.n_split, a, p, MergeRows<D>::groups(a.bm), st);
 }
 
 // `may_split`: the call owns the workspace (s1f_seg_attn_bwd_dkdv only reads it)
@@ -370,7 +377,7 @@ template <typename T, int D> int bwd_dkdv_impl(const s1f_desc *d, AttnArgs a, hi
   fill_launch(&a, n_bh, 2 * (int64_t)a.seg_off < (int64_t)a.seg_len, p);
   const int rc = launch(F::kernel(), F::LDS, p, n_bh, a, st);
   if (rc != S1F_OK || p.n_split_units == 0) return rc;
-  return launch_merge(seg_attn_bwd_dkdv_merge_kernel<T, D>, a, p, DkdvMerge<D>::GROUPS, st);
+  return S1F_MERGE(seg_attn_bwd_dkdv_merge_kernel, T, D, p.n_split - 1, a, p, DkdvMerge<D>::GROUPS, st);
 }
 
 
