@@ -234,32 +234,41 @@ def pipeline_simulate(pp_size: int, n_micro: int, n_seg: int, n_chunks: int, t_f
 
 def _dtype_code(t):
     import torch
-    if t.dtype == torch.float32:
-        return S1F_F32
     if t.dtype == torch.bfloat16:
         return S1F_BF16
+    if t.dtype == torch.float32:
+        return S1F_F32
     raise TypeError(f"unsupported dtype {t.dtype}")
 
 
 def make_desc(q_like, kv_like) -> Desc:
     """Descriptor from a [B, Hq, S, D] query-shaped tensor and a [B, Hkv, C, D] prefix-shaped tensor."""
-    if q_like.dim() != 4 or kv_like.dim() != 4 or q_like.stride(3) != 1 or kv_like.stride(3) != 1:
+    qs, ks = q_like.stride(), kv_like.stride()
+    if len(qs) != 4 or len(ks) != 4 or qs[3] != 1 or ks[3] != 1:
         raise ValueError("expected [batch, heads, seq, head_dim] tensors with contiguous head_dim")
     b, hq, _, d = q_like.shape
-    return Desc(batch=b, n_q_heads=hq, n_kv_heads=kv_like.shape[1], head_dim=d, dtype=_dtype_code(q_like), reserved=0,
-                q_stride_b=q_like.stride(0), q_stride_h=q_like.stride(1), q_stride_s=q_like.stride(2),
-                kv_stride_b=kv_like.stride(0), kv_stride_h=kv_like.stride(1), kv_stride_s=kv_like.stride(2),
-                kv_capacity=kv_like.shape[2])
+    _, hk, cap, _ = kv_like.shape
+    return Desc(b, hq, hk, d, _dtype_code(q_like), 0, qs[0], qs[1], qs[2], ks[0], ks[1], ks[2], cap)
+
+
+_raw_stream = None
 
 
 def _stream_ptr():
+    """torch's current stream on the current device, without building the Stream object around it (3 us of a call that
+    launches one kernel takes 8)."""
+    global _raw_stream
     import torch
-    return ctypes.c_void_p(torch.cuda.current_stream().cuda_stream)
+    if _raw_stream is None:
+        _raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None) or (
+            lambda device: torch.cuda.current_stream(device).cuda_stream)
+    return _raw_stream(torch.cuda.current_device())
 
 
 def _same_layout(ref, *others):
+    shape, stride, dtype = ref.shape, ref.stride(), ref.dtype
     for t in others:
-        if t.shape != ref.shape or t.stride() != ref.stride() or t.dtype != ref.dtype:
+        if t.shape != shape or t.stride() != stride or t.dtype != dtype:
             raise ValueError("tensors sharing a stride set must have identical shape, strides and dtype")
 
 
@@ -398,12 +407,11 @@ def seg_attn_bwd_dkdv(dout, q_seg, k_prefix, v_prefix, lse, seg_off: int, dk_pre
 
 def _kv_desc(cache) -> Desc:
     """Descriptor for the cache-side calls: only the kv_* fields, dtype, batch and head_dim are read."""
-    if cache.dim() != 4 or cache.stride(3) != 1:
+    s = cache.stride()
+    if len(s) != 4 or s[3] != 1:
         raise ValueError("expected a [batch, kv_heads, capacity, head_dim] tensor with contiguous head_dim")
     b, h, cap, d = cache.shape
-    return Desc(batch=b, n_q_heads=h, n_kv_heads=h, head_dim=d, dtype=0, reserved=0, q_stride_b=0, q_stride_h=0,
-                q_stride_s=d, kv_stride_b=cache.stride(0), kv_stride_h=cache.stride(1), kv_stride_s=cache.stride(2),
-                kv_capacity=cap)
+    return Desc(b, h, h, d, 0, 0, 0, 0, d, s[0], s[1], s[2], cap)
 
 
 def kv_append(k_seg, v_seg, seg_off: int, k_cache, v_cache):
@@ -413,11 +421,11 @@ def kv_append(k_seg, v_seg, seg_off: int, k_cache, v_cache):
     _same_layout(k_cache, v_cache)
     desc = _kv_desc(k_cache)
     desc.dtype = _dtype_code(k_cache)
-    if k_seg.dtype != k_cache.dtype or k_seg.stride(3) != 1:
+    s = k_seg.stride()
+    if k_seg.dtype != k_cache.dtype or s[3] != 1:
         raise ValueError("segment and cache must share the element type; head_dim must be contiguous")
-    rc = lib.s1f_kv_append(ctypes.byref(desc), k_seg.data_ptr(), v_seg.data_ptr(), k_seg.stride(0), k_seg.stride(1),
-                           k_seg.stride(2), int(seg_off), k_seg.shape[2], k_cache.data_ptr(), v_cache.data_ptr(),
-                           _stream_ptr())
+    rc = lib.s1f_kv_append(ctypes.byref(desc), k_seg.data_ptr(), v_seg.data_ptr(), s[0], s[1], s[2], int(seg_off),
+                           k_seg.shape[2], k_cache.data_ptr(), v_cache.data_ptr(), _stream_ptr())
     if rc != 0:
         raise S1FError(rc, "s1f_kv_append")
 
@@ -428,12 +436,12 @@ def kv_grad_emit(dk_prefix_acc, dv_prefix_acc, seg_off: int, dk_seg, dv_seg):
     lib = load_library()
     _same_layout(dk_prefix_acc, dv_prefix_acc)
     _same_layout(dk_seg, dv_seg)
-    if dk_prefix_acc.dtype != torch.float32 or dk_seg.stride(3) != 1:
+    s = dk_seg.stride()
+    if dk_prefix_acc.dtype != torch.float32 or s[3] != 1:
         raise ValueError("accumulators must be fp32; head_dim must be contiguous")
     desc = _kv_desc(dk_prefix_acc)
     desc.dtype = _dtype_code(dk_seg)
     rc = lib.s1f_kv_grad_emit(ctypes.byref(desc), dk_prefix_acc.data_ptr(), dv_prefix_acc.data_ptr(), int(seg_off),
-                              dk_seg.shape[2], dk_seg.data_ptr(), dv_seg.data_ptr(), dk_seg.stride(0), dk_seg.stride(1),
-                              dk_seg.stride(2), _stream_ptr())
+                              dk_seg.shape[2], dk_seg.data_ptr(), dv_seg.data_ptr(), s[0], s[1], s[2], _stream_ptr())
     if rc != 0:
         raise S1FError(rc, "s1f_kv_grad_emit")
