@@ -35,7 +35,7 @@ template <typename T, int D, int NC> struct BwdDqCfg {
 //   B  dQ += K(k)^T dS(k)    ||  p(k+1) = exp2(c * S(k+1) - lse)
 //   C  dP(k+1)
 // The order is pinned matrix instruction by matrix instruction; LDS operands are read kDqRing operands ahead.
-// Bound by the matrix pipe at the clock the power limit leaves (head_dim 128: 60 % busy at 1.85 GHz), with 64 registers
+// Bound by the matrix pipe at the clock the power limit leaves (head_dim 128, 56 heads: 77 % busy at 1.63 GHz), with 64 registers
 // of accumulators and 64 of Q and dO per lane at NC = 2.  32 heads, 4096 rows behind 28672 keys: head_dim 128
 // 2.52 -> 2.29 ms (three products executed: 1230 -> 1350 TFLOP/s), 80 1.89 -> 1.57 ms and 64 1.54 -> 1.26 ms (NC = 3).
 // One wave per SIMD with 64 rows (half the LDS reads) ran 15 % slower: half of its registers are accumulator
@@ -596,8 +596,8 @@ __global__ void __launch_bounds__(256, WGS) seg_attn_bwd_dkdv_kernel(const AttnA
 }
 
 // Adds the chunks of the units that seg_attn_bwd_dkdv_kernel split along the queries into the accumulators, which chunk
-// 0 has updated itself: acc += sum_c part_c, c = 1 .. n_split - 1, in the order of the chunks.  A thread handles 4 consecutive head_dim elements of one key of one
-// of the two accumulators (grid: split units x DkdvMerge<D>::GROUPS).
+// 0 has updated itself: acc += sum_c part_c, c = 1 .. n_split - 1, in the order of the chunks.  A thread handles 4
+// consecutive head_dim elements of one key of one of the two accumulators (grid: split units x DkdvMerge<D>::GROUPS).
 template <int D> struct DkdvMerge {
   static constexpr int PER = 128 * D / 4;                  // threads per unit and accumulator
   static constexpr int GROUPS = 2 * PER / 256;
