@@ -157,6 +157,7 @@ struct AttnArgs {
   // are whole units; the n_split_units units after them are cut into n_split chunks each.
   int32_t n_whole, n_split, n_split_units;
   int32_t bm;                            // forward and dQ: rows per unit
+  int32_t first_id;                      // forward: > 0 in a second launch, over the rows of the units from n_whole = first_id on
   float *part;                           // partial results of the chunks: [chunk][split unit][rows per unit][head_dim]
   float *part_ml;                        // forward only: running maximum (log2 units) and row sum, [..][rows per unit][2]
   int64_t part_cap;                      // host side only: most bytes of partial results a launch may plan for

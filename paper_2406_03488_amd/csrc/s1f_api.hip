@@ -307,6 +307,25 @@ template <typename T, int D> size_t fwd_workspace(const SplitPlan &p) {
   const int64_t rows = p.chunks() * 64 * p.nc;
   return rows == 0 ? 0 : align256((size_t)(rows * D * 4)) + (size_t)(rows * 8);
 }
+// An uncut launch whose last round fills only part of the chip: is it faster to leave the units of that round to a second
+// launch, in tiles of 64 rows (more of them side by side, each a shorter walk per key)?  Sets `whole` to the units that
+// stay.  kDrainUs: the first launch has to end, its workgroups at slightly different times, before the second begins
+// (launches of 200 to 300 us lost 1 % where 2 % were predicted).
+// head_dim 128, no workspace: 56 heads, 3678 rows behind 39549 keys (96 units of 192 rows left over) 4221 -> 3951 us, 4600
+// rows behind 20000 keys 2530 -> 2424; 64/8 heads, 4100 rows behind 60000 keys 6933 -> 6808.
+constexpr double kDrainUs = 10.0;
+template <typename F, int NC> bool row_tail(const AttnArgs &a, const SplitPlan &p, int64_t *whole) {
+  const Slots s = family_slots<F, NC>(), s1 = family_slots<F, 1>();
+  if (s.total <= 0 || s1.total <= 0) return false;
+  const int64_t units = p.n_whole, r = units % s.total;
+  const double mean = (double)(a.seg_off + (a.seg_len + 1) / 2) / 32 + 1, most = (double)(a.seg_off + a.seg_len) / 32 + 1;
+  *whole = units - r;
+  if (r == 0 || *whole == 0 || most > 1.3 * mean) return false;
+  const double now = rounds_us(units, mean, most, F::cost, NC, s);
+  const double two = rounds_us(*whole, mean, mean, F::cost, NC, s) + rounds_us(r * NC, mean, mean, F::cost, 1, s1);
+  return two + kDrainUs < 0.98 * now;
+}
+
 template <typename T, int D>
 int fwd_impl(const s1f_desc *d, AttnArgs a, hipStream_t st, void *workspace, size_t workspace_bytes, bool split) {
   typedef FwdFamily<T, D> F;
@@ -319,6 +338,27 @@ int fwd_impl(const s1f_desc *d, AttnArgs a, hipStream_t st, void *workspace, siz
   a.part_ml = reinterpret_cast<float *>(reinterpret_cast<char *>(workspace) + align256((size_t)(p.chunks() * 64 * p.nc * D * 4)));
   const int64_t n_bh = (int64_t)d->n_q_heads * d->batch;
   fill_launch(&a, n_bh, row_tile_order(d, a), p);
+  a.first_id = 0;
+  int64_t whole = 0;
+  bool tail = false;
+  if (p.n_split_units == 0 && p.nc == 2) tail = row_tail<F, 2>(a, p, &whole);
+  if constexpr (F::MAX >= 3)
+    if (p.n_split_units == 0 && p.nc == 3) tail = row_tail<F, 3>(a, p, &whole);
+  if (tail) {
+    SplitPlan head = p, rest = p;
+    head.n_whole = whole;
+    rest.nc = 1;
+    rest.n_whole = 0;
+    rest.n_split_units = p.n_whole - whole;
+    rest.n_split = p.nc;
+    fill_launch(&a, n_bh, row_tile_order(d, a), head);
+    const int rc = launch_rows<F>(head, n_bh, a, st);
+    if (rc != S1F_OK) return rc;
+    a.first_id = (int32_t)whole;
+    a.n_split = p.nc;
+    a.n_split_units = (int32_t)rest.n_split_units;
+    return launch_rows<F>(rest, n_bh, a, st);
+  }
   const int rc = launch_rows<F>(p, n_bh, a, st);
   if (rc != S1F_OK || p.n_split_units == 0) return rc;
   return S1F_MERGE(seg_attn_fwd_merge_kernel, T, D, p.n_split, a, p, MergeRows<D>::groups(a.bm), st);

@@ -68,3 +68,22 @@ def test_fp32_forward_takes_any_workspace():
         outs.append(out)
     assert torch.equal(outs[0], outs[1])
     assert (outs[0] - outs[2]).abs().max().item() <= 1e-5
+
+
+# More row tiles than the chip holds at once and a small rest, no workspace: in the first shape the rest (the first rows
+# of every head) runs in a second launch of narrower tiles, the second stays in one launch.
+@pytest.mark.parametrize("hq,hkv,off,m,heads", [(64, 8, 5000, 3214, [0, 31, 63]), (112, 112, 9000, 1770, [12, 13, 111])])
+def test_rows_of_a_partial_last_round(hq, hkv, off, m, heads):
+    g = torch.Generator(device="cuda")
+    g.manual_seed(off + m)
+    rnd = lambda h, n: torch.empty((1, h, n, 128), device="cuda", dtype=torch.bfloat16).normal_(generator=g)
+    q, k, v = rnd(hq, m), rnd(hkv, off + m), rnd(hkv, off + m)
+    out, lse = torch.full_like(q, 9.0), torch.full((1, hq, m), 9.0, device="cuda")
+    s1f.seg_attn_fwd(q, k, v, off, out, lse)
+    host = lambda x: x[0].double().cpu().numpy()
+    for h in heads:
+        g0 = h // (hq // hkv)
+        want, want_lse = A.segment_forward(host(q[:, h:h + 1]), host(k[:, g0:g0 + 1]), host(v[:, g0:g0 + 1]), off)
+        none = dict.fromkeys(("dq", "dk", "dv"), np.ones(1))
+        _check({"out": host(out[:, h:h + 1]), "lse": host(lse[:, h:h + 1]), **none},
+               {"out": want, "lse": want_lse, **none}, "bf16", where="head %d: " % h)
