@@ -230,6 +230,7 @@ __global__ void __launch_bounds__(256, OCC) seg_attn_bwd_dq_kernel(const AttnArg
     ++k;
     ring.end_step();
   };
+  const int n_own = own_tiles<BN>(seg_off, wrow0, wrow0 + 16 * NC < seg_len ? wrow0 + 16 * NC : seg_len, n_kt);
   int n_full = (wfirst + 1) / BN;   // tiles that every row of the wave sees in full
   n_full = n_full < n_kt - 1 ? n_full : n_kt - 1;
   const std::integral_constant<bool, true> yes;
@@ -237,8 +238,11 @@ __global__ void __launch_bounds__(256, OCC) seg_attn_bwd_dq_kernel(const AttnArg
   const int n_fast = n_full < n_kt - 4 ? n_full : n_kt - 4;   // ... while there is a whole tile to copy
   while (k + 1 < n_fast) step(no, yes);
   while (k + 1 < n_full) step(no, no);
-  while (k + 1 < n_kt) step(yes, no);
-  {   // last tile: dS and dQ
+  while (k + 1 < n_own) step(yes, no);
+  // The wave's last tile: dS and dQ.  Waves that have more tiles to walk are let into their next step first.
+  if (k + 1 < n_kt) ring.template begin_step<false>(n_kt - 1 - k);
+  {
+    const int hidden = hidden_blocks<BN>(wfirst, n_own);
     const typename M::Tr kt = rd.tr_at(ring.st[0]);
 #pragma unroll
     for (int cb = 0; cb < NC; ++cb) make_ds(cb);
@@ -246,9 +250,14 @@ __global__ void __launch_bounds__(256, OCC) seg_attn_bwd_dq_kernel(const AttnArg
     for (int i = 0; i < NT; ++i) {
       const Frag kf = M::tr(kt, i);
 #pragma unroll
-      for (int cb = 0; cb < NC; ++cb) M::mma_tr(i, kf, ds[cb], dq[cb]);
+      for (int cb = 0; cb < NC; ++cb)
+        if (cb + 1 == NC || cb >= hidden) M::mma_tr(i, kf, ds[cb], dq[cb]);   // (the last block is never hidden)
       __builtin_amdgcn_sched_barrier(0);
     }
+  }
+  if (k + 1 < n_kt) {   // its share of the others' tiles
+    ring.end_step();
+    for (++k; k + 1 < n_kt; ++k, ring.end_step()) ring.template begin_step<false>(n_kt - 1 - k);
   }
 
   if (uc.slot >= 0) {   // a chunk: its unscaled share of the unit's dQ rows goes to the workspace

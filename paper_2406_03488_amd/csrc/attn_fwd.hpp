@@ -124,10 +124,11 @@ template <typename M> struct KRing {
 // The order is pinned slot by slot (one operand, its NC matrix instructions, its share of the vector work): two waves
 // share a SIMD, and left alone the compiler puts LDS reads right before their use and the exponentials in heaps.
 //   MASK: tile k+1 may cross the diagonal of the wave's rows; ahead_next: see fwd_mask
+//   hidden (without a next tile): column blocks, from the first on, that tile k is wholly hidden from (never the last)
 template <typename M, bool HAS_NEXT, bool MASK, int NC>
 S1F_DEV void fwd_step(f32x4 (&p)[2][NC], f32x4 (&o)[NC][M::DB], const float (&m)[NC], float (&rs)[NC],
                       const typename M::RowOp (&q)[NC], const M &rd, KRing<M> &kr, lds_addr ktile_next, lds_addr ktile_after,
-                      lds_addr vtile, float c, int ahead_next) {
+                      lds_addr vtile, float c, int ahead_next, int hidden) {
   typedef typename M::Frag Frag;
   constexpr int PK = KRing<M>::N, PV = M::NT < 3 ? M::NT : 3, NK = M::NK, NN = M::NN, NT = M::NT;
   __builtin_amdgcn_s_setprio(1);   // of two ready waves the one in phase 1, which has little else to issue, feeds the matrix pipe
@@ -189,7 +190,7 @@ S1F_DEV void fwd_step(f32x4 (&p)[2][NC], f32x4 (&o)[NC][M::DB], const float (&m)
   for (int i = 0; i < NT; ++i) {
 #pragma unroll
     for (int cb = 0; cb < NC; ++cb) {
-      M::mma_tr(i, vf[i % PV], pf[cb], o[cb]);
+      if (HAS_NEXT || cb + 1 == NC || cb >= hidden) M::mma_tr(i, vf[i % PV], pf[cb], o[cb]);
       if (cb + 1 == NC) {
         if (i + PV < NT) vf[i % PV] = M::tr(va, i + PV);
         if (HAS_NEXT && i + PK >= NT) kr.f[i + PK - NT] = M::nat(kb, i + PK - NT);
@@ -300,7 +301,7 @@ __global__ void __launch_bounds__(256, OCC) seg_attn_fwd_kernel(const AttnArgs a
     ring.template begin_step<WHOLE>(n_kt - 1 - k);
     const int ahead = seg_off + wrow0 - BN * (k + 1);
     fwd_step<M, true, MASK, NC>(s, o, m, rs, q, rd, kr, ring.st[1], ring.st[2],
-                                ring.st[0] + Tile32<T, D>::BYTES, c, ahead);
+                                ring.st[0] + Tile32<T, D>::BYTES, c, ahead, 0);
     ++k;
     ring.end_step();
     bool raise = false;
@@ -329,19 +330,24 @@ __global__ void __launch_bounds__(256, OCC) seg_attn_fwd_kernel(const AttnArgs a
     for (int cb = 0; cb < NC; ++cb) l[cb] += rs[cb];
   };
   // Tiles that every row of the wave sees in full, first while there is a whole tile to copy (no branches in the step),
-  // then those on the diagonal (the last tile always is; which others are differs between the waves, but every wave
-  // takes one step and one barrier per tile).  A branch around the mask inside one loop would part the step where its
-  // two phases overlap.
+  // then those on its diagonal.  A branch around the mask inside one loop would part the step where its two phases overlap.
   const std::integral_constant<bool, true> yes;
   const std::integral_constant<bool, false> no;
+  const int n_own = own_tiles<BN>(seg_off, wrow0, wrow0 + 16 * NC < seg_len ? wrow0 + 16 * NC : seg_len, n_kt);
   int n_full = (seg_off + wrow0 + 1) / BN;
   n_full = n_full < n_kt - 1 ? n_full : n_kt - 1;
   const int n_fast = n_full < n_kt - 4 ? n_full : n_kt - 4;
   while (k + 1 < n_fast) steady(no, yes);
   while (k + 1 < n_full) steady(no, no);
-  while (k + 1 < n_kt) steady(yes, no);
-  // last tile: no next scores to compute
-  fwd_step<M, false, false, NC>(s, o, m, rs, q, rd, kr, ring.st[0], ring.st[0], ring.st[0] + Tile32<T, D>::BYTES, c, 0);
+  while (k + 1 < n_own) steady(yes, no);
+  // the wave's last tile: no next scores to compute.  Waves that have more tiles to walk are let into their next step first.
+  if (k + 1 < n_kt) ring.template begin_step<false>(n_kt - 1 - k);
+  fwd_step<M, false, false, NC>(s, o, m, rs, q, rd, kr, ring.st[0], ring.st[0], ring.st[0] + Tile32<T, D>::BYTES, c, 0,
+                                hidden_blocks<BN>(seg_off + wrow0, n_own));
+  if (k + 1 < n_kt) {   // its share of the others' tiles
+    ring.end_step();
+    for (++k; k + 1 < n_kt; ++k, ring.end_step()) ring.template begin_step<false>(n_kt - 1 - k);
+  }
 
   if (uc.slot >= 0) {   // a chunk: unnormalised output rows, running maximum and row sum go to the workspace
     float *po = a.part + (int64_t)uc.slot * (BM * D);

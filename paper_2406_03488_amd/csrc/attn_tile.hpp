@@ -385,4 +385,20 @@ template <typename T, int D> struct TileRing {
   }
 };
 
+// How far a wave of the forward and dQ kernels walks: to the last tile that one of its rows sees, and in that tile only
+// the column blocks (16 rows) that see it take part in the second product.  The tiles of a workgroup reach further for its
+// other waves; walked all the same, with probabilities of zero, they would cost products, and an infinity or NaN in a key
+// that the rows do not see would reach them as 0 * inf.  So a row is touched by the keys of the tile in which its block
+// ends and by none behind it.
+// rows [row0, row_end) of the segment, row r seeing the keys up to seg_off + r, counted like the n_kt tiles at hand
+template <int BN> S1F_DEV int own_tiles(int seg_off, int row0, int row_end, int n_kt) {
+  const int n = row_end > row0 ? (seg_off + row_end - 1) / BN + 1 : n_kt;
+  return n < n_kt ? n : n_kt;
+}
+// column blocks, from the first on, that tile n_own - 1 is wholly hidden from; first: last key that the wave's first row sees
+template <int BN> S1F_DEV int hidden_blocks(int first, int n_own) {
+  const int past = BN * (n_own - 1) - first;
+  return past > 0 ? past / 16 : 0;
+}
+
 }  // namespace s1f

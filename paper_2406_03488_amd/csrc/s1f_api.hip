@@ -20,9 +20,12 @@ using namespace s1f;
 template <typename T, int D> struct Shape;
 template <int D> struct Shape<bf16_t, D> {
   static constexpr int FWD_MAX = 3, DQ_MAX = D == 128 ? 2 : 3, OCC = 2, KWGS = D == 64 ? 3 : 2;
+  // the 128-row forward at head_dim 64 takes 130 registers if left alone; LDS has room for the four workgroups that 128 allow
+  static constexpr int fwd_occ(int nc) { return D == 64 && nc == 2 ? 4 : OCC; }
 };
 template <int D> struct Shape<float, D> {
   static constexpr int FWD_MAX = 2, DQ_MAX = 2, OCC = 1, KWGS = D == 64 ? 2 : 1;
+  static constexpr int fwd_occ(int) { return OCC; }
 };
 
 bool aligned16(const void *p) { return (reinterpret_cast<uintptr_t>(p) & 15u) == 0; }
@@ -265,7 +268,7 @@ template <typename T, int D> struct FwdFamily {
   static constexpr int MAX = Shape<T, D>::FWD_MAX, LDS = TileRing<T, D>::LDS_BYTES;
   static constexpr StepUs cost = Cost<T, D>::fwd;
   static constexpr int64_t row_bytes = D * 4 + 8;   // of a partial result: output, running maximum, row sum
-  template <int NC> static auto kernel() { return seg_attn_fwd_kernel<T, D, NC, Shape<T, D>::OCC>; }
+  template <int NC> static auto kernel() { return seg_attn_fwd_kernel<T, D, NC, Shape<T, D>::fwd_occ(NC)>; }
 };
 template <typename T, int D> struct DqFamily {
   static constexpr int MAX = Shape<T, D>::DQ_MAX, LDS = TileRing<T, D>::LDS_BYTES;
