@@ -168,12 +168,14 @@ int s1f_seg_attn_bwd(const s1f_desc *desc, const void *dout, const void *q_seg, 
                      void *workspace, size_t workspace_bytes, void *hip_stream);
 
 /* The two halves of s1f_seg_attn_bwd as separate calls (same arguments, same validation), for callers
- * that schedule or time them separately; s1f_seg_attn_bwd is _dq followed by _dkdv on one stream, except that _dkdv,
- * which only reads the workspace, never cuts its launch along the queries (same sums in another order).
+ * that schedule or time them separately; s1f_seg_attn_bwd is exactly _dq followed by _dkdv on one stream (given the
+ * same workspace_bytes).
  *   s1f_seg_attn_bwd_dq    overwrites dq and writes the row statistics (-lse/scale, -rowsum(dout * out))
  *                          into workspace
  *   s1f_seg_attn_bwd_dkdv  reads the statistics left in workspace by _dq for the same segment (lse is
- *                          validated but not read) and updates dk_prefix_acc / dv_prefix_acc */
+ *                          validated but not read) and updates dk_prefix_acc / dv_prefix_acc.  It leaves the
+ *                          statistics as they are, but uses the bytes behind them as _bwd does: calls that overlap in
+ *                          time need workspaces of their own */
 int s1f_seg_attn_bwd_dq(const s1f_desc *desc, const void *dout, const void *q_seg, const void *k_prefix,
                         const void *v_prefix, const void *out, const float *lse, int64_t seg_off,
                         int64_t seg_len, void *dq, void *workspace, size_t workspace_bytes, void *hip_stream);

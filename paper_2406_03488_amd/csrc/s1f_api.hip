@@ -416,10 +416,9 @@ template <typename T, int D> int bwd_dq_impl(const s1f_desc *d, AttnArgs a, hipS
   return S1F_MERGE(seg_attn_bwd_dq_merge_kernel, T, D, p.n_split, a, p, MergeRows<D>::groups(a.bm), st);
 }
 
-// `may_split`: the call owns the workspace (s1f_seg_attn_bwd_dkdv only reads it)
-template <typename T, int D> int bwd_dkdv_impl(const s1f_desc *d, AttnArgs a, hipStream_t st, bool may_split) {
+template <typename T, int D> int bwd_dkdv_impl(const s1f_desc *d, AttnArgs a, hipStream_t st) {
   typedef DkdvFamily<T, D> F;
-  const SplitPlan p = F::plan(d, a.seg_off, a.seg_len, may_split ? a.part_cap : 0);
+  const SplitPlan p = F::plan(d, a.seg_off, a.seg_len, a.part_cap);
   a.part = reinterpret_cast<float *>(reinterpret_cast<char *>(a.delta) + stat_bytes(d, a.seg_len));
   const int64_t n_bh = (int64_t)d->n_kv_heads * d->batch;
   fill_launch(&a, n_bh, 2 * (int64_t)a.seg_off < (int64_t)a.seg_len, p);
@@ -513,8 +512,8 @@ namespace {
 int bwd_dq_dispatch(const s1f_desc *d, const AttnArgs &a, hipStream_t st) {
   S1F_DISPATCH(bwd_dq_impl, d, d, a, st);
 }
-int bwd_dkdv_dispatch(const s1f_desc *d, const AttnArgs &a, hipStream_t st, bool may_split) {
-  S1F_DISPATCH(bwd_dkdv_impl, d, d, a, st, may_split);
+int bwd_dkdv_dispatch(const s1f_desc *d, const AttnArgs &a, hipStream_t st) {
+  S1F_DISPATCH(bwd_dkdv_impl, d, d, a, st);
 }
 
 int bwd_ready_dispatch(const s1f_desc *d, const AttnArgs &a) { S1F_DISPATCH(bwd_ready_impl, d, d, a); }
@@ -562,7 +561,7 @@ int bwd_entry(const s1f_desc *desc, const void *dout, const void *q_seg, const v
   // everything that can fail short of the launches themselves happens before the first kernel is enqueued
   int rc2 = bwd_ready_dispatch(desc, a);
   if (rc2 == S1F_OK) rc2 = bwd_dq_dispatch(desc, a, st);
-  return rc2 == S1F_OK ? bwd_dkdv_dispatch(desc, a, st, true) : rc2;
+  return rc2 == S1F_OK ? bwd_dkdv_dispatch(desc, a, st) : rc2;
 }
 }  // namespace
 
@@ -587,7 +586,7 @@ extern "C" int s1f_seg_attn_bwd_dkdv(const s1f_desc *desc, const void *dout, con
   if (rc != S1F_OK) return rc;
   if (!dk_prefix_acc || !dv_prefix_acc || !aligned16(dk_prefix_acc) || !aligned16(dv_prefix_acc)) return S1F_EINVAL;
   a.dk_acc = dk_prefix_acc; a.dv_acc = dv_prefix_acc;
-  return bwd_dkdv_dispatch(desc, a, reinterpret_cast<hipStream_t>(hip_stream), false);
+  return bwd_dkdv_dispatch(desc, a, reinterpret_cast<hipStream_t>(hip_stream));
 }
 
 extern "C" int s1f_seg_attn_bwd(const s1f_desc *desc, const void *dout, const void *q_seg, const void *k_prefix,

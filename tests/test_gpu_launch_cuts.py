@@ -1,7 +1,7 @@
 """Launches at the edges of what the planner chooses between: row tiles of 64, 128 and 192 rows, last tiles that are
 nearly empty or nearly full, launches cut along the keys (forward, dQ) and along the queries (dK/dV) with more chunks
 than some of their units have tiles, in both element types.  Compared with the oracle within the contract's tolerances;
-the two halves of the backward as separate calls (whose dK/dV launch is never cut) within the rounding of fp32 sums."""
+the two halves of the backward as separate calls bit for bit with the one call."""
 import numpy as np
 import pytest
 import torch
@@ -40,19 +40,20 @@ def test_edges_of_the_launch_plan(dtype, d, hq, hkv, off, m):
     l = torch.empty((1, hq, m), dtype=torch.float32, device="cuda")
     s1f.seg_attn_fwd(qd, kd, vd, off, o, l)
     ws = torch.empty(s1f.bwd_workspace_bytes(qd, kd, off), dtype=torch.uint8, device="cuda")
-    acc = {}
-    for how in ("one call", "two calls"):
+    acc, dqs = {}, {}
+    for how in ("one call", "two calls", "second half again"):   # (it leaves the statistics in place)
         a, b = (torch.zeros((1, hkv, n, d), dtype=torch.float32, device="cuda") for _ in range(2))
         if how == "one call":
             s1f.seg_attn_bwd(dod, qd, kd, vd, o, l, off, dqd, a, b, ws)
-        else:
+        elif how == "two calls":
             s1f.seg_attn_bwd_dq(dod, qd, kd, vd, o, l, off, dqd, ws)
             s1f.seg_attn_bwd_dkdv(dod, qd, kd, vd, l, off, a, b, ws)
-        acc[how] = (a.cpu().numpy(), b.cpu().numpy())
-    # the same products in another order of summation: every partial sum carries at most 2^-24 of the largest one
-    bound = 2.0 ** -20 * max(1.0, float(np.abs(dk).max()), float(np.abs(dv).max())) * np.sqrt(hq * m)
-    for x, y in zip(acc["one call"], acc["two calls"]):
-        assert np.abs(x - y).max() <= bound
+        else:
+            s1f.seg_attn_bwd_dkdv(dod, qd, kd, vd, l, off, a, b, ws)
+        acc[how], dqs[how] = (a, b), dqd.clone()
+    assert torch.equal(dqs["one call"], dqs["two calls"])
+    for how in ("two calls", "second half again"):
+        assert all(torch.equal(x, y) for x, y in zip(acc["one call"], acc[how])), how
 
 
 def test_fp32_forward_takes_any_workspace():
