@@ -19,8 +19,7 @@
 namespace s1f {
 
 template <typename T, int D, int NC> struct BwdDqCfg {
-  static constexpr int BM = 64 * NC, BN = 32, THREADS = 256;
-  static constexpr int LDS_BYTES = TileRing<T, D>::LDS_BYTES;
+  static constexpr int BM = 64 * NC, BN = 32;
 };
 
 // One workgroup (4 waves) owns 64*NC query rows of one head, a wave NC column blocks of 16; lane = one query per column
@@ -316,7 +315,7 @@ __global__ void __launch_bounds__(256) seg_attn_bwd_dq_merge_kernel(const AttnAr
 
 template <typename T, int D> struct BwdDkdvCfg {
   static constexpr int BQ = 32;                        // rows per Q/dO tile
-  static constexpr int BNW = 128, THREADS = 256;       // keys per workgroup: 4 waves of 32
+  static constexpr int BNW = 128;                      // keys per workgroup: 4 waves of 32
   typedef Tile32<T, D> TL;
   static constexpr int STAGE_BYTES = 2 * TL::BYTES;    // Q tile, dO tile right behind it
   static constexpr int STAT_BYTES = 2 * BQ * 4;        // -lse/scale and -delta of the tile's rows

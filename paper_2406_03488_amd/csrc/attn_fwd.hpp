@@ -42,8 +42,7 @@ constexpr float kRescaleTau = 8.0f;
 constexpr float kRescaleLimit = 256.0f;   // 2^kRescaleTau
 
 template <typename T, int D, int NC> struct FwdCfg {
-  static constexpr int BM = 64 * NC, BN = 32, THREADS = 256;
-  static constexpr int LDS_BYTES = TileRing<T, D>::LDS_BYTES;
+  static constexpr int BM = 64 * NC, BN = 32;
 };
 
 // Masks the scores of rows 16*rb.. of a tile that crosses the diagonal.

@@ -242,14 +242,15 @@ template <int D> struct Mat<float, D> {
       const int rv = t / NG, g = t % NG;
 #pragma unroll
       for (int e = 0; e < 4; ++e) acc[4 * g + e] = mma16(a[e], s.r[rv >> 2][rv & 3], acc[4 * g + e]);
-    } else {
+    } else if constexpr (TAIL) {
       const int rv = t - 8 * NG;
       acc[4 * NG] = mma16(a[0], s.r[rv >> 2][rv & 3], acc[4 * NG]);
     }
   }
   S1F_DEV static int quad_d0(int q, int j) { return q < 4 * NG ? 64 * (q >> 2) + 16 * j + 4 * (q & 3) : 64 * NG + 4 * j; }
   S1F_DEV static f32x4 quad(const f32x4 (&acc)[DB], int q) {
-    if (q >= 4 * NG) return acc[4 * NG];
+    if constexpr (TAIL)
+      if (q >= 4 * NG) return acc[4 * NG];
     const int g = 4 * (q >> 2), v = q & 3;
     return f32x4{acc[g][v], acc[g + 1][v], acc[g + 2][v], acc[g + 3][v]};
   }
