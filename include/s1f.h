@@ -208,6 +208,17 @@ int s1f_seg_attn_bwd_noalloc(const s1f_desc *desc, const void *dout, const void 
                              void *hip_stream);
 size_t s1f_static_scratch_rows(void);
 
+/* How a call of this shape is launched on the current device: a question about speed only, for tests and measurements.
+ * HOST function; nothing is enqueued.  `launch` names the call: the forward without and with a workspace, and the two
+ * kernels of the backward (s1f_seg_attn_bwd and its halves).  Writes
+ *   plan[0]  rows (dK/dV: keys) per unit, the work of one workgroup
+ *   plan[1]  units that are left whole
+ *   plan[2]  units cut along the keys (dK/dV: along the queries), plan[3] the chunks per cut unit
+ *   plan[4]  forward: units whose rows run in a second launch of 64-row tiles
+ * Errors: S1F_EINVAL, S1F_EUNSUPPORTED, S1F_ERANGE as for the calls themselves. */
+typedef enum { S1F_PLAN_FWD = 0, S1F_PLAN_FWD_WS = 1, S1F_PLAN_DQ = 2, S1F_PLAN_DKDV = 3 } s1f_launch;
+int s1f_launch_plan(const s1f_desc *desc, int32_t launch, int64_t seg_off, int64_t seg_len, int64_t *plan);
+
 /* The two data movements on either side of a segment's attention calls (Section 3.2: the keys and values of
  * all preceding tokens are retained; gradients of earlier tokens are accumulated until the backward passes
  * of all later segments have run).

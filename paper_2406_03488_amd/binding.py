@@ -83,6 +83,8 @@ def load_library():
     lib.s1f_static_scratch_rows.restype = sz
     lib.s1f_bwd_workspace_bytes.argtypes = [dp, i64, i64]
     lib.s1f_bwd_workspace_bytes.restype = sz
+    lib.s1f_launch_plan.argtypes = [dp, i32, i64, i64, ctypes.POINTER(i64)]
+    lib.s1f_launch_plan.restype = ctypes.c_int
     lib.s1f_kv_append.argtypes = [dp, vp, vp, i64, i64, i64, i64, i64, vp, vp, vp]
     lib.s1f_kv_append.restype = ctypes.c_int
     lib.s1f_kv_grad_emit.argtypes = [dp, vp, vp, i64, i64, vp, vp, i64, i64, i64, vp]
@@ -293,6 +295,18 @@ def seg_attn_fwd(q_seg, k_prefix, v_prefix, seg_off: int, out, lse):
 def fwd_workspace_bytes(q_seg, k_prefix, seg_off: int) -> int:
     desc = make_desc(q_seg, k_prefix)
     return int(load_library().s1f_fwd_workspace_bytes(ctypes.byref(desc), int(seg_off), int(q_seg.shape[2])))
+
+
+PLAN_FWD, PLAN_FWD_WS, PLAN_DQ, PLAN_DKDV = range(4)
+
+
+def launch_plan(q_seg, k_prefix, seg_off: int, launch: int):
+    """s1f_launch_plan: (rows per unit, whole units, cut units, chunks per cut unit, units of a second launch)."""
+    desc, plan = make_desc(q_seg, k_prefix), (ctypes.c_int64 * 5)()
+    rc = load_library().s1f_launch_plan(ctypes.byref(desc), int(launch), int(seg_off), int(q_seg.shape[2]), plan)
+    if rc != 0:
+        raise S1FError(rc, "s1f_launch_plan")
+    return tuple(plan)
 
 
 def seg_attn_fwd_ws(q_seg, k_prefix, v_prefix, seg_off: int, out, lse, workspace):

@@ -329,6 +329,15 @@ template <typename F, int NC> bool row_tail(const AttnArgs &a, const SplitPlan &
   return two + kDrainUs < 0.98 * now;
 }
 
+// ... for a plan of either width; 64-row tiles have no narrower ones to go to.
+template <typename F> bool row_tail_of(const AttnArgs &a, const SplitPlan &p, int64_t *whole) {
+  if (p.n_split_units != 0) return false;
+  if (p.nc == 2) return row_tail<F, 2>(a, p, whole);
+  if constexpr (F::MAX >= 3)
+    if (p.nc == 3) return row_tail<F, 3>(a, p, whole);
+  return false;
+}
+
 template <typename T, int D>
 int fwd_impl(const s1f_desc *d, AttnArgs a, hipStream_t st, void *workspace, size_t workspace_bytes, bool split) {
   typedef FwdFamily<T, D> F;
@@ -343,11 +352,7 @@ int fwd_impl(const s1f_desc *d, AttnArgs a, hipStream_t st, void *workspace, siz
   fill_launch(&a, n_bh, row_tile_order(d, a), p);
   a.first_id = 0;
   int64_t whole = 0;
-  bool tail = false;
-  if (p.n_split_units == 0 && p.nc == 2) tail = row_tail<F, 2>(a, p, &whole);
-  if constexpr (F::MAX >= 3)
-    if (p.n_split_units == 0 && p.nc == 3) tail = row_tail<F, 3>(a, p, &whole);
-  if (tail) {
+  if (row_tail_of<F>(a, p, &whole)) {
     SplitPlan head = p, rest = p;
     head.n_whole = whole;
     rest.nc = 1;
@@ -440,6 +445,22 @@ template <typename T, int D> int bwd_ready_impl(const s1f_desc *d, const AttnArg
   if (kv_tiles * d->n_kv_heads * d->batch > 0x7fffffff || row_tiles * d->n_q_heads * d->batch > 0x7fffffff) return S1F_EUNSUPPORTED;
   const int rc = prepare_rows<DqFamily<T, D>, DqFamily<T, D>::MAX>();
   return rc != S1F_OK ? rc : prepare(DkdvFamily<T, D>::kernel(), DkdvFamily<T, D>::LDS);
+}
+
+// What s1f_launch_plan reports.
+template <typename T, int D> int plan_impl(const s1f_desc *d, const AttnArgs &a, int launch, int64_t *out) {
+  SplitPlan p;
+  int64_t whole = 0;
+  if (launch == S1F_PLAN_FWD || launch == S1F_PLAN_FWD_WS) p = plan_rows<FwdFamily<T, D>>(d, a.seg_off, a.seg_len, a.part_cap);
+  else if (launch == S1F_PLAN_DQ) p = plan_rows<DqFamily<T, D>>(d, a.seg_off, a.seg_len, a.part_cap);
+  else p = DkdvFamily<T, D>::plan(d, a.seg_off, a.seg_len, a.part_cap);
+  const bool fwd = launch == S1F_PLAN_FWD || launch == S1F_PLAN_FWD_WS, tail = fwd && row_tail_of<FwdFamily<T, D>>(a, p, &whole);
+  out[0] = launch == S1F_PLAN_DKDV ? DkdvFamily<T, D>::Cfg::BNW : 64 * p.nc;
+  out[1] = tail ? whole : p.n_whole;
+  out[2] = p.n_split_units;
+  out[3] = p.n_split;
+  out[4] = tail ? p.n_whole - whole : 0;
+  return S1F_OK;
 }
 
 #define S1F_DISPATCH(fn, d, ...)                                                        \
@@ -641,6 +662,17 @@ extern "C" int s1f_seg_attn_bwd_noalloc(const s1f_desc *desc, const void *dout, 
   // every plane entry the dK/dV kernel reads is written by the dQ kernel of the same call: nothing to clear
   return bwd_entry(desc, dout, q_seg, k_prefix, v_prefix, out, lse, seg_off, seg_len, dq, dk_prefix_acc, dv_prefix_acc, ws,
                    kStaticScratchBytes, kStaticPartBytes, hip_stream);
+}
+
+extern "C" int s1f_launch_plan(const s1f_desc *desc, int32_t launch, int64_t seg_off, int64_t seg_len, int64_t *plan) {
+  int rc = check_desc(desc);
+  if (rc != S1F_OK) return rc;
+  if (plan == nullptr || launch < S1F_PLAN_FWD || launch > S1F_PLAN_DKDV) return S1F_EINVAL;
+  rc = check_seg(desc, seg_off, seg_len);
+  if (rc != S1F_OK) return rc;
+  AttnArgs a = make_args(desc, seg_off, seg_len);
+  a.part_cap = launch == S1F_PLAN_FWD ? 0 : kMaxPartBytes;
+  S1F_DISPATCH(plan_impl, desc, desc, a, launch, plan);
 }
 
 extern "C" const char *s1f_strerror(int status) {

@@ -1,7 +1,10 @@
-"""Launches at the edges of what the planner chooses between: row tiles of 64, 128 and 192 rows, last tiles that are
-nearly empty or nearly full, launches cut along the keys (forward, dQ) and along the queries (dK/dV) with more chunks
-than some of their units have tiles, in both element types.  Compared with the oracle within the contract's tolerances;
-the two halves of the backward as separate calls bit for bit with the one call."""
+"""Launches at the edges of what the planner chooses between, in both element types, compared with the oracle: few row
+tiles (of 64 rows: the narrowest) that are nearly empty or nearly full, whole and cut along the keys (forward, dQ) or along
+the queries (dK/dV) with more chunks than some of their units have tiles; every wider tile of the forward and the dQ
+kernel, whole and cut, with waves that are partly or wholly empty, on data that raises the running maximum as well as on
+data that does not; rows of a partial last round in a second launch.  Which plan a shape gets is asked of the library, so
+that a test whose shape no longer takes the path it is about fails.  The two halves of the backward as separate calls
+equal the one call bit for bit."""
 import numpy as np
 import pytest
 import torch
@@ -13,8 +16,8 @@ from test_gpu_batch_sweep import _check, _sequence
 
 pytestmark = pytest.mark.gpu
 
-# (query heads, K/V heads, offset, rows): one row; one row more and less than a tile of each width; a first segment (its
-# early units have fewer key tiles than chunks); enough heads to fill the chip with wide tiles and ragged last ones
+# (query heads, K/V heads, offset, rows): one row; one row more and less than 64, 128 and 192; a first segment (its early
+# units have fewer key tiles than chunks); 64 heads.  All of them run in tiles of 64 rows.
 SHAPES = [(2, 1, 700, 1), (4, 2, 0, 63), (4, 2, 33, 65), (8, 2, 400, 127), (3, 1, 1000, 129), (2, 2, 5, 191),
           (8, 8, 95, 193), (4, 4, 0, 640), (64, 8, 300, 200)]
 
@@ -88,3 +91,108 @@ def test_rows_of_a_partial_last_round(hq, hkv, off, m, heads):
         none = dict.fromkeys(("dq", "dk", "dv"), np.ones(1))
         _check({"out": host(out[:, h:h + 1]), "lse": host(lse[:, h:h + 1]), **none},
                {"out": want, "lse": want_lse, **none}, "bf16", where="head %d: " % h)
+
+
+# (dtype, head_dim, (batch, query heads, K/V heads, offset, rows), rows per unit and whether units are cut: forward without
+# and with a workspace, dQ).  Between them every width that the kernels are built for, whole and cut, last tiles of 1 to
+# 65 rows (tiles of 64, 128, 192 rows: waves of 16, 32, 48) and of one row less than a whole one.
+WIDTHS = [
+    ("bf16", 64, (3, 112, 112, 40, 129), ("128", "128", "64")),
+    ("bf16", 64, (3, 112, 112, 0, 193), ("128", "128", "128")),
+    ("bf16", 64, (1, 112, 112, 1500, 769), ("192", "192", "128 cut")),
+    ("bf16", 64, (3, 56, 56, 1500, 769), ("192", "192 cut", "128")),
+    ("bf16", 64, (1, 32, 32, 1500, 577), ("64", "128 cut", "64")),
+    ("bf16", 64, (3, 56, 56, 196, 554), ("128", "128", "192")),
+    ("bf16", 64, (1, 32, 32, 4165, 151), ("64", "192 cut", "192 cut")),
+    ("bf16", 80, (3, 112, 112, 0, 65), ("128", "128", "128")),
+    ("bf16", 80, (3, 64, 8, 0, 129), ("192", "192", "192")),
+    ("bf16", 80, (1, 112, 112, 1500, 769), ("128", "192 cut", "192 cut")),
+    ("bf16", 80, (1, 32, 32, 1500, 577), ("64", "128 cut", "128 cut")),
+    ("bf16", 128, (3, 112, 112, 0, 65), ("128", "128", "128")),
+    ("bf16", 128, (3, 64, 8, 0, 129), ("192", "192", "64")),
+    ("bf16", 128, (1, 112, 112, 1500, 769), ("128", "192 cut", "64")),
+    ("bf16", 128, (1, 32, 32, 1500, 577), ("64", "128 cut", "128 cut")),
+    ("f32", 64, (3, 112, 112, 0, 193), ("128", "128", "128")),
+    ("f32", 64, (1, 32, 32, 700, 321), ("64", "128 cut", "64 cut")),
+    ("f32", 64, (3, 56, 56, 333, 65), ("64", "64", "128 cut")),
+    ("f32", 80, (3, 112, 112, 0, 193), ("128", "128", "128")),
+    ("f32", 80, (1, 32, 32, 700, 321), ("64", "128 cut", "128 cut")),
+    ("f32", 128, (3, 112, 112, 0, 193), ("128", "128", "128")),
+    ("f32", 128, (1, 32, 32, 700, 321), ("64", "128 cut", "64 cut")),
+    ("f32", 128, (1, 32, 32, 0, 450), ("64", "64", "128 cut")),
+]
+
+
+def _device_data(seed, dtype, d, nb, hq, hkv, off, m, rising):
+    """q, dout [nb, hq, m, d] and k, v [nb, hkv, off + m, d] of N(0, 1) numbers.  `rising`: scores that climb along the keys
+    by tens of nats for some rows and fall for others (key j carries a_j * u, a_j from 0 to 2 in four steps, u of +-1, and
+    row r carries c_r * u, c_r in [-2, 2], on top of 0.6 * N(0, 1)), so that the forward raises its running maximum."""
+    g = torch.Generator(device="cuda")
+    g.manual_seed(seed)
+    rnd = lambda *shape: torch.empty(shape, device="cuda").normal_(generator=g)
+    n = off + m
+    q, do, k, v = rnd(nb, hq, m, d), rnd(nb, hq, m, d), rnd(nb, hkv, n, d), rnd(nb, hkv, n, d)
+    if rising:
+        u = rnd(d).sign()
+        k = 0.6 * k + (torch.arange(n, device="cuda") * 4 // n * (2.0 / 3.0))[:, None] * u
+        q = 0.6 * q + (1.5 * rnd(nb, hq, m, 1)).clamp(-2.0, 2.0) * u
+    t = torch.bfloat16 if dtype == "bf16" else torch.float32
+    return [x.to(t) for x in (q, do, k, v)]
+
+
+def _close(got, want, dtype, where):
+    """The contract's bounds; where results exceed order one, the absolute ones grow by a rounding of the largest value
+    (bf16: 2^-9 of it, and as much again for the probabilities; fp32: the rounding of its sums)."""
+    from gpu_harness import errors
+    for name in want:
+        mx, fro = errors(got[name], want[name])
+        top = float(np.abs(want[name]).max())
+        assert np.isfinite(got[name]).all(), where + name
+        if dtype == "f32":
+            assert mx <= 1e-4 + 2.0 ** -18 * top, f"{where}{name}: max abs {mx}"
+        elif name == "lse":
+            assert mx <= 1e-3, f"{where}lse: max abs {mx}"
+        else:
+            assert mx <= 2e-2 + 2.0 ** -8 * top and fro <= 1e-2, f"{where}{name}: max abs {mx} (of {top}) rel fro {fro}"
+
+
+@pytest.mark.parametrize("rising", [False, True])
+@pytest.mark.parametrize("dtype,d,shape,plans", WIDTHS)
+def test_every_tile_width_whole_and_cut(dtype, d, shape, plans, rising):
+    nb, hq, hkv, off, m = shape
+    q, do, k, v = _device_data(9000 + off + m + d, dtype, d, *shape, rising)
+    for launch, want in zip((s1f.PLAN_FWD, s1f.PLAN_FWD_WS, s1f.PLAN_DQ), plans):
+        rows, whole, cut, chunks, second = s1f.launch_plan(q, k, off, launch)
+        assert f"{rows}{' cut' if cut else ''}" == want and second == 0, "the shape no longer takes the path it is here for"
+    outs = {}
+    for how in ("plain", "workspace"):
+        out, lse = torch.full_like(q, float("nan")), torch.full(q.shape[:3], float("nan"), device="cuda")
+        if how == "plain":
+            s1f.seg_attn_fwd(q, k, v, off, out, lse)
+        else:
+            nbytes = s1f.fwd_workspace_bytes(q, k, off)
+            s1f.seg_attn_fwd_ws(q, k, v, off, out, lse, torch.empty(nbytes, dtype=torch.uint8, device="cuda") if nbytes else None)
+        outs[how] = (out, lse)
+    dq = torch.full_like(q, float("nan"))
+    dk, dv = (torch.zeros(k.shape, device="cuda") for _ in range(2))
+    ws = torch.empty(s1f.bwd_workspace_bytes(q, k, off), dtype=torch.uint8, device="cuda")
+    s1f.seg_attn_bwd(do, q, k, v, *outs["workspace"], off, dq, dk, dv, ws)
+    host = lambda x: x.double().cpu().numpy()
+    grp = hq // hkv
+    for b, g in sorted({(0, 0), (nb - 1, hkv - 1), (nb // 2, hkv // 2)}):
+        hs = slice(g * grp, (g + 1) * grp)
+        qh, doh, kh, vh = host(q[b, hs]), host(do[b, hs]), host(k[b, g:g + 1]), host(v[b, g:g + 1])
+        out, lse = A.segment_forward(qh, kh, vh, off)
+        wdq, wdk, wdv = A.segment_backward(doh, qh, kh, vh, off)
+        # The backward reads delta = rowsum(dout * out) from the `out` that the forward saved.  What that row-wise difference
+        # makes of dQ and dK is linear in it (dQ: times -scale * P K, dK: -scale * P^T (. * Q)) and part of what is expected:
+        # keys with a common direction make P K large, and the rounding of a bf16 `out` alone then is 1e-2 of dQ.
+        ddelta = (doh * (host(outs["workspace"][0][b, hs]) - out)).sum(-1, keepdims=True) / np.sqrt(d)
+        wdq = wdq - ddelta * A.segment_forward(qh, kh, kh, off)[0]
+        wdk = wdk - A.segment_backward(ddelta * qh, qh, kh, vh, off)[2]
+        where = f"entry {b} K/V head {g}: "
+        for how in outs:
+            _close({"out": host(outs[how][0][b, hs]), "lse": host(outs[how][1][b, hs])}, {"out": out, "lse": lse}, dtype,
+                   where + how + " ")
+        _close({"dq": host(dq[b, hs]), "dk": host(dk[b, g:g + 1]), "dv": host(dv[b, g:g + 1])},
+               {"dq": wdq, "dk": wdk, "dv": wdv}, dtype, where)

@@ -211,6 +211,20 @@ def test_attention_entry_points_validate_before_any_launch():
         assert isinstance(s1f.strerror(code), str) and s1f.strerror(code)
 
 
+def test_launch_plan_validates_and_is_whole_without_a_device():
+    lib = s1f.load_library()
+    plan = (ctypes.c_int64 * 5)()
+    ask = lambda desc, launch, off, m, out=plan: lib.s1f_launch_plan(ctypes.byref(desc), launch, off, m, out)
+    for launch in (s1f.PLAN_FWD, s1f.PLAN_FWD_WS, s1f.PLAN_DQ, s1f.PLAN_DKDV):
+        assert ask(_desc(), launch, 100, 200) == 0
+        assert plan[0] in (64, 128, 192) and plan[2] == 0 and plan[3] == 1 and plan[4] == 0
+        units = 2 * -(-300 // 128) if launch == s1f.PLAN_DKDV else 4 * -(-200 // plan[0])
+        assert plan[1] == units
+    assert ask(_desc(), -1, 0, 64) == 1 and ask(_desc(), 4, 0, 64) == 1 and ask(_desc(), 0, 0, 64, None) == 1
+    assert ask(_desc(head_dim=96), 0, 0, 64) == 2 and ask(_desc(), 0, 500, 64) == 3
+    assert lib.s1f_launch_plan(None, 0, 0, 64, plan) == 1
+
+
 def test_noalloc_backward_rejects_more_rows_than_the_array_holds():
     lib = s1f.load_library()
     rows = s1f.static_scratch_rows()
