@@ -314,16 +314,25 @@ template <typename T, int D> size_t fwd_workspace(const SplitPlan &p) {
 // launch, in tiles of 64 rows (more of them side by side, each a shorter walk per key)?  Sets `whole` to the units that
 // stay.  kDrainUs: the first launch has to end, its workgroups at slightly different times, before the second begins
 // (launches of 200 to 300 us lost 1 % where 2 % were predicted).
-// head_dim 128, no workspace: 56 heads, 3678 rows behind 39549 keys (96 units of 192 rows left over) 4221 -> 3951 us, 4600
-// rows behind 20000 keys 2530 -> 2424; 64/8 heads, 4100 rows behind 60000 keys 6933 -> 6808.
-constexpr double kDrainUs = 10.0;
+// Each of 110 shapes for which the prediction says yes, timed both ways (second launch / one launch):
+//   bf16, grouped heads (units run tile by tile, those left over are the shortest)   0.85 .. 0.94 of 29, mean 0.91
+//   bf16, ungrouped (head by head), longest unit <= 1.12 of the mean                 0.87 .. 1.01 of 27, mean 0.95
+//   bf16, ungrouped, longest unit > 1.15 of the mean: long and short ones already fill each other's gaps
+//                                                                                    1.02 .. 1.10 of 10, mean 1.06
+//   bf16 at head_dim 64, three or four workgroups per compute unit: no round ends at once
+//                                                                                    0.95 .. 1.06 of 36, mean 1.03
+//   fp32, grouped 0.98 of 3; ungrouped, uneven 1.02 .. 1.05 of 5
+// hence the two further conditions.  56 heads, 3678 rows behind 39549 keys (96 units of 192 rows left over) 4286 -> 3974
+// us; 64/8 heads, 3214 rows behind 5000 keys 645 -> 592.
+constexpr double kDrainUs = 10.0, kTailUneven = 1.12, kTailUnevenGrouped = 1.3;
 template <typename F, int NC> bool row_tail(const AttnArgs &a, const SplitPlan &p, int64_t *whole) {
   const Slots s = family_slots<F, NC>(), s1 = family_slots<F, 1>();
   if (s.total <= 0 || s1.total <= 0) return false;
   const int64_t units = p.n_whole, r = units % s.total;
   const double mean = (double)(a.seg_off + (a.seg_len + 1) / 2) / 32 + 1, most = (double)(a.seg_off + a.seg_len) / 32 + 1;
   *whole = units - r;
-  if (r == 0 || *whole == 0 || most > 1.3 * mean) return false;
+  if (r == 0 || *whole == 0 || s.total > 2 * s.cus) return false;
+  if (most > (a.group > 1 ? kTailUnevenGrouped : kTailUneven) * mean) return false;
   const double now = rounds_us(units, mean, most, F::cost, NC, s);
   const double two = rounds_us(*whole, mean, mean, F::cost, NC, s) + rounds_us(r * NC, mean, mean, F::cost, 1, s1);
   return two + kDrainUs < 0.98 * now;

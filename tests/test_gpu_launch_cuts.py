@@ -74,6 +74,73 @@ def test_fp32_forward_takes_any_workspace():
     assert (outs[0] - outs[2]).abs().max().item() <= 1e-5
 
 
+# No workspace and a last round that fills a part of the chip, in which the rest runs in a second launch of 64-row tiles:
+# both wide tiles, grouped heads (the rest are the first rows of every head) and ungrouped ones (the last heads, whose last
+# tile has rows for one or two of its 64-row tiles only), every head_dim that has the path, both element types and layouts.
+SECOND_LAUNCH = [
+    ("bf16", 128, 192, (3, 40, 8, 2887, 1597), "bhsd"), ("bf16", 128, 192, (2, 112, 112, 12736, 775), "bshd"),
+    ("bf16", 128, 128, (3, 96, 96, 6899, 390), "bhsd"), ("bf16", 128, 128, (2, 40, 8, 20462, 1787), "bshd"),
+    ("bf16", 80, 192, (3, 96, 96, 8535, 659), "bshd"), ("bf16", 80, 192, (3, 40, 8, 4914, 1575), "bhsd"),
+    ("bf16", 80, 128, (3, 96, 96, 5253, 194), "bhsd"), ("f32", 64, 128, (2, 64, 8, 7244, 3873), "bshd"),
+    ("f32", 80, 128, (2, 64, 8, 4146, 3339), "bhsd"), ("f32", 128, 128, (2, 64, 8, 5390, 3597), "bhsd"),
+]
+# ... and in which it stays in the one launch although that is predicted to be slower: it is not, where the units differ in
+# length and run head by head, and at head_dim 64 in bf16.
+ONE_LAUNCH = [
+    ("bf16", 64, (2, 40, 8, 4760, 1734)), ("bf16", 64, (1, 112, 112, 3563, 1191)), ("bf16", 64, (3, 96, 96, 6985, 388)),
+    ("bf16", 80, (1, 56, 56, 5982, 3539)), ("bf16", 128, (1, 56, 56, 9203, 5220)), ("bf16", 128, (2, 32, 32, 4048, 3145)),
+    ("f32", 128, (3, 112, 112, 1357, 969)),
+]
+
+
+def _empty(layout, nb, h, n, d, dtype):
+    if layout == "bshd":
+        return torch.empty((nb, n, h, d), device="cuda", dtype=dtype).permute(0, 2, 1, 3)
+    return torch.empty((nb, h, n, d), device="cuda", dtype=dtype)
+
+
+@pytest.mark.parametrize("dtype,d,rows,shape,layout", SECOND_LAUNCH)
+def test_second_launch_of_a_partial_last_round(dtype, d, rows, shape, layout):
+    nb, hq, hkv, off, m = shape
+    t = torch.bfloat16 if dtype == "bf16" else torch.float32
+    g = torch.Generator(device="cuda")
+    g.manual_seed(off + m)
+    q, k, v = (_empty(layout, nb, h, n, d, t).normal_(generator=g) for h, n in ((hq, m), (hkv, off + m), (hkv, off + m)))
+    plan = s1f.launch_plan(q, k, off, s1f.PLAN_FWD)
+    assert plan[0] == rows and plan[1] > 0 and plan[2] == 0 and plan[4] > 0, plan
+    assert plan[1] + plan[4] == nb * hq * -(-m // rows)
+    res = []
+    for workspace in (False, True):
+        out, lse = torch.full_like(q, float("nan")), torch.full((nb, hq, m), float("nan"), device="cuda")
+        if workspace:
+            nbytes = s1f.fwd_workspace_bytes(q, k, off)
+            s1f.seg_attn_fwd_ws(q, k, v, off, out, lse, torch.empty(nbytes, dtype=torch.uint8, device="cuda") if nbytes else None)
+        else:
+            s1f.seg_attn_fwd(q, k, v, off, out, lse)
+        res.append((out, lse))
+    # every row of every head against the call that cuts along the keys instead: one bf16 rounding apart; fp32: sums of up
+    # to 2e4 terms in another order
+    top = res[1][0].float().abs().max().item()
+    assert (res[0][0].float() - res[1][0].float()).abs().max().item() <= (2.0 ** -7 if dtype == "bf16" else 2.0 ** -17) * top
+    assert (res[0][1] - res[1][1]).abs().max().item() <= 1e-5
+    host = lambda x: x.double().cpu().numpy()
+    for b, h in ((0, 0), (nb - 1, hq // 2), (nb - 1, hq - 1)):
+        g0 = h // (hq // hkv)
+        for r0, r1 in ((0, 8), (m // 2, m // 2 + 8), (m - 8, m)):
+            want, want_lse = A.segment_forward(host(q[b, h:h + 1, r0:r1]), host(k[b, g0:g0 + 1]), host(v[b, g0:g0 + 1]), off + r0)
+            _close({"out": host(res[0][0][b, h:h + 1, r0:r1]), "lse": host(res[0][1][b, h:h + 1, r0:r1])},
+                   {"out": want, "lse": want_lse}, dtype, f"entry {b} head {h} rows {r0}: ")
+
+
+@pytest.mark.parametrize("dtype,d,shape", ONE_LAUNCH)
+def test_one_launch_where_a_second_does_not_pay(dtype, d, shape):
+    nb, hq, hkv, off, m = shape
+    q, k = (torch.empty((nb, h, n, d), device="cuda", dtype=torch.bfloat16 if dtype == "bf16" else torch.float32)
+            for h, n in ((hq, m), (hkv, off + m)))
+    plan = s1f.launch_plan(q, k, off, s1f.PLAN_FWD)
+    assert plan[0] > 64 and plan[2] == 0 and plan[4] == 0, plan
+
+
 # More row tiles than the chip holds at once and a small rest, no workspace: in the first shape the rest (the first rows
 # of every head) runs in a second launch of narrower tiles, the second stays in one launch.
 @pytest.mark.parametrize("hq,hkv,off,m,heads", [(64, 8, 5000, 3214, [0, 31, 63]), (112, 112, 9000, 1770, [12, 13, 111])])
