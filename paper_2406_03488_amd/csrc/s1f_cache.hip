@@ -21,9 +21,11 @@ struct CopyArgs {
 
 // One thread moves 8 consecutive head_dim elements of one row of both tensors of one (batch entry, head); the grid's y and
 // z run over heads and batch entries (in strides, should there be more than a grid holds): one launch per call, where
-// one per batch entry took 3 us each for two sequences of 340 rows.  Bound by memory.  The rows read are not read again
-// by this path (new K/V rows, gradients that have become final) and are loaded past the caches: append and emit of 32
-// heads x 3652 rows (300 MB) 59.9 -> 56.6 us, 5.0 -> 5.3 TB/s (a plain device copy reaches 4.8 TB/s).
+// one per batch entry took 3 us each for two sequences of 340 rows.  Bound by memory: append and emit of 32 heads x 3652
+// rows (300 MB) take 60 us, 5.0 TB/s (a plain device copy reaches 4.8 TB/s).  Loading the rows past the caches took 57 us
+// there, but rows that are still in a cache, as they are when something has just produced them, are then fetched again
+// (append of the same rows 18.1 -> 21.8 us, emit 26.5 -> 31.6), and fp32 lost at every size (append of 32 heads x 30000 rows,
+// head_dim 64: 235 -> 285 us).
 // SRC/DST: element types (float or bf16_t); float -> bf16 rounds to nearest even.
 template <typename SRC, typename DST> __global__ void __launch_bounds__(256) rows_kernel(const CopyArgs a) {
   const int64_t id = (int64_t)blockIdx.x * 256 + threadIdx.x;
@@ -47,14 +49,13 @@ template <typename SRC, typename DST> __global__ void __launch_bounds__(256) row
         DST *d = reinterpret_cast<DST *>(t ? a.dst1 : a.dst0) + dof;
         if (sizeof(SRC) == sizeof(DST)) {
           if (sizeof(SRC) == 2) {
-            *reinterpret_cast<u32x4 *>(d) = __builtin_nontemporal_load(reinterpret_cast<const u32x4 *>(s));
+            *reinterpret_cast<u32x4 *>(d) = *reinterpret_cast<const u32x4 *>(s);
           } else {
-            reinterpret_cast<u32x4 *>(d)[0] = __builtin_nontemporal_load(reinterpret_cast<const u32x4 *>(s));
-            reinterpret_cast<u32x4 *>(d)[1] = __builtin_nontemporal_load(reinterpret_cast<const u32x4 *>(s) + 1);
+            reinterpret_cast<u32x4 *>(d)[0] = reinterpret_cast<const u32x4 *>(s)[0];
+            reinterpret_cast<u32x4 *>(d)[1] = reinterpret_cast<const u32x4 *>(s)[1];
           }
         } else {   // fp32 -> bf16
-          const f32x4 x = __builtin_nontemporal_load(reinterpret_cast<const f32x4 *>(s));
-          const f32x4 y = __builtin_nontemporal_load(reinterpret_cast<const f32x4 *>(s) + 1);
+          const f32x4 x = reinterpret_cast<const f32x4 *>(s)[0], y = reinterpret_cast<const f32x4 *>(s)[1];
           bf16x8 o;
 #pragma unroll
           for (int e = 0; e < 4; ++e) { o[e] = (bf16_t)x[e]; o[4 + e] = (bf16_t)y[e]; }
