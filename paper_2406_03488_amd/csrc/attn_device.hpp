@@ -160,7 +160,6 @@ struct AttnArgs {
   int32_t first_id;                      // forward: > 0 in a second launch, over the rows of the units from n_whole = first_id on
   float *part;                           // partial results of the chunks: [chunk][split unit][rows per unit][head_dim]
   float *part_ml;                        // forward only: running maximum (log2 units) and row sum, [..][rows per unit][2]
-  int64_t part_cap;                      // host side only: most bytes of partial results a launch may plan for
 };
 
 }  // namespace s1f

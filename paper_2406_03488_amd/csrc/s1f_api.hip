@@ -180,9 +180,10 @@ void plan_units(SplitPlan *best, double *t, int nc, int64_t n_tiles, int64_t uni
     } else {
       const int64_t bytes = r * (n - direct) * part_bytes;
       if (r == 0 || steps < (double)n || bytes > cap) break;
-      now = rounds_us(r * n, steps / n, longest / n, us, nc, s) + kMergeUs + (double)bytes / kMergeBytesPerUs;
+      const double extra = kMergeUs + (double)bytes / kMergeBytesPerUs + 1.0;   // (1.0: not for nothing)
+      if (kStartUs + extra >= *t) break;   // nor can more chunks win (the smallest launches end here, after one prediction)
+      now = rounds_us(r * n, steps / n, longest / n, us, nc, s) + extra;
       if (whole > 0) now += rounds_us(whole, steps, steps, us, nc, s) - kStartUs;
-      now += 1.0;   // not for nothing
     }
     if (now < *t) {
       *t = now;
@@ -413,15 +414,21 @@ template <typename T, int D> struct DkdvFamily {
     return p;
   }
 };
-template <typename T, int D> size_t bwd_ws_impl(const s1f_desc *d, int64_t seg_off, int64_t seg_len, int64_t cap) {
-  const SplitPlan q = plan_rows<DqFamily<T, D>>(d, seg_off, seg_len, cap), k = DkdvFamily<T, D>::plan(d, seg_off, seg_len, cap);
-  const int64_t qb = q.chunks() * 64 * q.nc * D * 4, kb = (k.chunks() - k.n_split_units) * DkdvFamily<T, D>::part_bytes;
-  return stat_bytes(d, seg_len) + (size_t)(qb > kb ? qb : kb);
+// The plans of both launches of a backward, made once per call: the size check and the launches use the same ones.
+struct BwdPlans {
+  SplitPlan q, k;
+  size_t bytes = 0;   // of the workspace they need
+};
+template <typename T, int D> int bwd_plans_impl(const s1f_desc *d, int64_t seg_off, int64_t seg_len, int64_t cap, BwdPlans *p) {
+  p->q = plan_rows<DqFamily<T, D>>(d, seg_off, seg_len, cap);
+  p->k = DkdvFamily<T, D>::plan(d, seg_off, seg_len, cap);
+  const int64_t qb = p->q.chunks() * 64 * p->q.nc * D * 4, kb = (p->k.chunks() - p->k.n_split_units) * DkdvFamily<T, D>::part_bytes;
+  p->bytes = stat_bytes(d, seg_len) + (size_t)(qb > kb ? qb : kb);
+  return S1F_OK;
 }
 
-template <typename T, int D> int bwd_dq_impl(const s1f_desc *d, AttnArgs a, hipStream_t st) {
+template <typename T, int D> int bwd_dq_impl(const s1f_desc *d, AttnArgs a, const SplitPlan &p, hipStream_t st) {
   typedef DqFamily<T, D> F;
-  const SplitPlan p = plan_rows<F>(d, a.seg_off, a.seg_len, a.part_cap);
   a.part = reinterpret_cast<float *>(reinterpret_cast<char *>(a.delta) + stat_bytes(d, a.seg_len));
   const int64_t n_bh = (int64_t)d->n_q_heads * d->batch;
   fill_launch(&a, n_bh, row_tile_order(d, a), p);
@@ -430,9 +437,8 @@ template <typename T, int D> int bwd_dq_impl(const s1f_desc *d, AttnArgs a, hipS
   return S1F_MERGE(seg_attn_bwd_dq_merge_kernel, T, D, p.n_split, a, p, MergeRows<D>::groups(a.bm), st);
 }
 
-template <typename T, int D> int bwd_dkdv_impl(const s1f_desc *d, AttnArgs a, hipStream_t st) {
+template <typename T, int D> int bwd_dkdv_impl(const s1f_desc *d, AttnArgs a, const SplitPlan &p, hipStream_t st) {
   typedef DkdvFamily<T, D> F;
-  const SplitPlan p = F::plan(d, a.seg_off, a.seg_len, a.part_cap);
   a.part = reinterpret_cast<float *>(reinterpret_cast<char *>(a.delta) + stat_bytes(d, a.seg_len));
   const int64_t n_bh = (int64_t)d->n_kv_heads * d->batch;
   fill_launch(&a, n_bh, 2 * (int64_t)a.seg_off < (int64_t)a.seg_len, p);
@@ -457,12 +463,12 @@ template <typename T, int D> int bwd_ready_impl(const s1f_desc *d, const AttnArg
 }
 
 // What s1f_launch_plan reports.
-template <typename T, int D> int plan_impl(const s1f_desc *d, const AttnArgs &a, int launch, int64_t *out) {
+template <typename T, int D> int plan_impl(const s1f_desc *d, const AttnArgs &a, int launch, int64_t cap, int64_t *out) {
   SplitPlan p;
   int64_t whole = 0;
-  if (launch == S1F_PLAN_FWD || launch == S1F_PLAN_FWD_WS) p = plan_rows<FwdFamily<T, D>>(d, a.seg_off, a.seg_len, a.part_cap);
-  else if (launch == S1F_PLAN_DQ) p = plan_rows<DqFamily<T, D>>(d, a.seg_off, a.seg_len, a.part_cap);
-  else p = DkdvFamily<T, D>::plan(d, a.seg_off, a.seg_len, a.part_cap);
+  if (launch == S1F_PLAN_FWD || launch == S1F_PLAN_FWD_WS) p = plan_rows<FwdFamily<T, D>>(d, a.seg_off, a.seg_len, cap);
+  else if (launch == S1F_PLAN_DQ) p = plan_rows<DqFamily<T, D>>(d, a.seg_off, a.seg_len, cap);
+  else p = DkdvFamily<T, D>::plan(d, a.seg_off, a.seg_len, cap);
   const bool fwd = launch == S1F_PLAN_FWD || launch == S1F_PLAN_FWD_WS, tail = fwd && row_tail_of<FwdFamily<T, D>>(a, p, &whole);
   out[0] = launch == S1F_PLAN_DKDV ? DkdvFamily<T, D>::Cfg::BNW : 64 * p.nc;
   out[1] = tail ? whole : p.n_whole;
@@ -508,12 +514,12 @@ int fwd_entry(const s1f_desc *desc, const void *q_seg, const void *k_prefix, con
   hipStream_t st = reinterpret_cast<hipStream_t>(hip_stream);
   S1F_DISPATCH(fwd_impl, desc, desc, a, st, workspace, workspace_bytes, split);
 }
-// (callers have validated the descriptor: the dispatch below always finds its kernel)
+// (callers have validated the descriptor: the dispatches below always find their kernel)
 size_t fwd_ws_dispatch(const s1f_desc *d, int64_t seg_off, int64_t seg_len) {
   S1F_DISPATCH(fwd_ws_impl, d, d, seg_off, seg_len);
 }
-size_t bwd_ws_dispatch(const s1f_desc *d, int64_t seg_off, int64_t seg_len, int64_t cap) {
-  S1F_DISPATCH(bwd_ws_impl, d, d, seg_off, seg_len, cap);
+int bwd_plans_dispatch(const s1f_desc *d, int64_t seg_off, int64_t seg_len, int64_t cap, BwdPlans *p) {
+  S1F_DISPATCH(bwd_plans_impl, d, d, seg_off, seg_len, cap, p);
 }
 }  // namespace
 
@@ -535,23 +541,25 @@ extern "C" int s1f_seg_attn_fwd_ws(const s1f_desc *desc, const void *q_seg, cons
 
 extern "C" size_t s1f_bwd_workspace_bytes(const s1f_desc *desc, int64_t seg_off, int64_t seg_len) {
   if (check_desc(desc) != S1F_OK || check_seg(desc, seg_off, seg_len) != S1F_OK) return 0;
-  return bwd_ws_dispatch(desc, seg_off, seg_len, kMaxPartBytes);
+  BwdPlans p;
+  bwd_plans_dispatch(desc, seg_off, seg_len, kMaxPartBytes, &p);
+  return p.bytes;
 }
 
 namespace {
-int bwd_dq_dispatch(const s1f_desc *d, const AttnArgs &a, hipStream_t st) {
-  S1F_DISPATCH(bwd_dq_impl, d, d, a, st);
+int bwd_dq_dispatch(const s1f_desc *d, const AttnArgs &a, const BwdPlans &p, hipStream_t st) {
+  S1F_DISPATCH(bwd_dq_impl, d, d, a, p.q, st);
 }
-int bwd_dkdv_dispatch(const s1f_desc *d, const AttnArgs &a, hipStream_t st) {
-  S1F_DISPATCH(bwd_dkdv_impl, d, d, a, st);
+int bwd_dkdv_dispatch(const s1f_desc *d, const AttnArgs &a, const BwdPlans &p, hipStream_t st) {
+  S1F_DISPATCH(bwd_dkdv_impl, d, d, a, p.k, st);
 }
 
 int bwd_ready_dispatch(const s1f_desc *d, const AttnArgs &a) { S1F_DISPATCH(bwd_ready_impl, d, d, a); }
 
-// Validation shared by the backward entry points; fills `a` on success.
+// Validation shared by the backward entry points; fills `a` and `plans` on success.
 int bwd_prepare(const s1f_desc *desc, const void *dout, const void *q_seg, const void *k_prefix, const void *v_prefix,
                 const float *lse, int64_t seg_off, int64_t seg_len, const void *workspace, size_t workspace_bytes,
-                AttnArgs *a, int64_t part_cap = kMaxPartBytes) {
+                AttnArgs *a, BwdPlans *plans, int64_t part_cap = kMaxPartBytes) {
   int rc = check_desc(desc);
   if (rc != S1F_OK) return rc;
   if (!dout || !q_seg || !k_prefix || !v_prefix || !lse || !workspace) return S1F_EINVAL;
@@ -559,10 +567,11 @@ int bwd_prepare(const s1f_desc *desc, const void *dout, const void *q_seg, const
     return S1F_EINVAL;
   rc = check_seg(desc, seg_off, seg_len);
   if (rc != S1F_OK) return rc;
-  if (workspace_bytes < bwd_ws_dispatch(desc, seg_off, seg_len, part_cap)) {
+  bwd_plans_dispatch(desc, seg_off, seg_len, part_cap, plans);
+  if (workspace_bytes < plans->bytes) {
     // fp32 runs with any workspace that holds the row statistics; its launches are then left whole
     if (desc->dtype == S1F_BF16 || workspace_bytes < stat_bytes(desc, seg_len)) return S1F_EINVAL;
-    part_cap = 0;
+    bwd_plans_dispatch(desc, seg_off, seg_len, 0, plans);
   }
   // the asynchronous copies address the workspace with 32-bit byte offsets
   const int64_t stat_rows = (int64_t)desc->batch * desc->n_q_heads * seg_len;
@@ -572,7 +581,6 @@ int bwd_prepare(const s1f_desc *desc, const void *dout, const void *q_seg, const
   a->lse = const_cast<float *>(lse);
   a->delta = reinterpret_cast<float *>(const_cast<void *>(workspace));
   a->ws_plane = stat_rows;
-  a->part_cap = part_cap;
   return S1F_OK;
 }
 
@@ -581,7 +589,8 @@ int bwd_entry(const s1f_desc *desc, const void *dout, const void *q_seg, const v
               const void *out, const float *lse, int64_t seg_off, int64_t seg_len, void *dq, float *dk_prefix_acc,
               float *dv_prefix_acc, void *workspace, size_t workspace_bytes, int64_t part_cap, void *hip_stream) {
   AttnArgs a;
-  const int rc = bwd_prepare(desc, dout, q_seg, k_prefix, v_prefix, lse, seg_off, seg_len, workspace, workspace_bytes, &a,
+  BwdPlans p;
+  const int rc = bwd_prepare(desc, dout, q_seg, k_prefix, v_prefix, lse, seg_off, seg_len, workspace, workspace_bytes, &a, &p,
                              part_cap);
   if (rc != S1F_OK) return rc;
   if (!out || !dq || !dk_prefix_acc || !dv_prefix_acc) return S1F_EINVAL;
@@ -590,8 +599,8 @@ int bwd_entry(const s1f_desc *desc, const void *dout, const void *q_seg, const v
   hipStream_t st = reinterpret_cast<hipStream_t>(hip_stream);
   // everything that can fail short of the launches themselves happens before the first kernel is enqueued
   int rc2 = bwd_ready_dispatch(desc, a);
-  if (rc2 == S1F_OK) rc2 = bwd_dq_dispatch(desc, a, st);
-  return rc2 == S1F_OK ? bwd_dkdv_dispatch(desc, a, st) : rc2;
+  if (rc2 == S1F_OK) rc2 = bwd_dq_dispatch(desc, a, p, st);
+  return rc2 == S1F_OK ? bwd_dkdv_dispatch(desc, a, p, st) : rc2;
 }
 }  // namespace
 
@@ -600,11 +609,12 @@ extern "C" int s1f_seg_attn_bwd_dq(const s1f_desc *desc, const void *dout, const
                                    int64_t seg_len, void *dq, void *workspace, size_t workspace_bytes,
                                    void *hip_stream) {
   AttnArgs a;
-  const int rc = bwd_prepare(desc, dout, q_seg, k_prefix, v_prefix, lse, seg_off, seg_len, workspace, workspace_bytes, &a);
+  BwdPlans p;
+  const int rc = bwd_prepare(desc, dout, q_seg, k_prefix, v_prefix, lse, seg_off, seg_len, workspace, workspace_bytes, &a, &p);
   if (rc != S1F_OK) return rc;
   if (!out || !dq || !aligned16(out) || !aligned16(dq)) return S1F_EINVAL;
   a.out = out; a.dq = dq;
-  return bwd_dq_dispatch(desc, a, reinterpret_cast<hipStream_t>(hip_stream));
+  return bwd_dq_dispatch(desc, a, p, reinterpret_cast<hipStream_t>(hip_stream));
 }
 
 extern "C" int s1f_seg_attn_bwd_dkdv(const s1f_desc *desc, const void *dout, const void *q_seg, const void *k_prefix,
@@ -612,11 +622,12 @@ extern "C" int s1f_seg_attn_bwd_dkdv(const s1f_desc *desc, const void *dout, con
                                      float *dk_prefix_acc, float *dv_prefix_acc, const void *workspace,
                                      size_t workspace_bytes, void *hip_stream) {
   AttnArgs a;
-  const int rc = bwd_prepare(desc, dout, q_seg, k_prefix, v_prefix, lse, seg_off, seg_len, workspace, workspace_bytes, &a);
+  BwdPlans p;
+  const int rc = bwd_prepare(desc, dout, q_seg, k_prefix, v_prefix, lse, seg_off, seg_len, workspace, workspace_bytes, &a, &p);
   if (rc != S1F_OK) return rc;
   if (!dk_prefix_acc || !dv_prefix_acc || !aligned16(dk_prefix_acc) || !aligned16(dv_prefix_acc)) return S1F_EINVAL;
   a.dk_acc = dk_prefix_acc; a.dv_acc = dv_prefix_acc;
-  return bwd_dkdv_dispatch(desc, a, reinterpret_cast<hipStream_t>(hip_stream));
+  return bwd_dkdv_dispatch(desc, a, p, reinterpret_cast<hipStream_t>(hip_stream));
 }
 
 extern "C" int s1f_seg_attn_bwd(const s1f_desc *desc, const void *dout, const void *q_seg, const void *k_prefix,
@@ -679,9 +690,8 @@ extern "C" int s1f_launch_plan(const s1f_desc *desc, int32_t launch, int64_t seg
   if (plan == nullptr || launch < S1F_PLAN_FWD || launch > S1F_PLAN_DKDV) return S1F_EINVAL;
   rc = check_seg(desc, seg_off, seg_len);
   if (rc != S1F_OK) return rc;
-  AttnArgs a = make_args(desc, seg_off, seg_len);
-  a.part_cap = launch == S1F_PLAN_FWD ? 0 : kMaxPartBytes;
-  S1F_DISPATCH(plan_impl, desc, desc, a, launch, plan);
+  const AttnArgs a = make_args(desc, seg_off, seg_len);
+  S1F_DISPATCH(plan_impl, desc, desc, a, launch, launch == S1F_PLAN_FWD ? 0 : kMaxPartBytes, plan);
 }
 
 extern "C" const char *s1f_strerror(int status) {
