@@ -110,7 +110,10 @@ constexpr double kMergeUs = 4.5, kMergeBytesPerUs = 2.5e6; // the merge kernel: 
 
 // Time of one loop step of a workgroup, in microseconds, measured on launches of one workgroup per compute unit (alone),
 // of two (shared) and of all it holds where that is more (crowd: per workgroup), 64 heads behind 4096 and 16384 keys;
-// linear in the tile width.
+// linear in the tile width.  The forward at head_dim 64, shared and crowd: fitted to 350 launches of each width (first
+// segments and behind prefixes, 10 to 2500 us), whose times the prediction then misses by 7 % instead of 14; with the
+// former numbers it preferred 192-row tiles where 128 rows were up to 16 % faster (32 heads, 5573 rows behind 48904 keys
+// 2957 -> 2543 us).
 struct StepUs {
   double alone0, alone_nc, shared0, shared_nc, crowd0, crowd_nc;
   double at(int nc, int64_t per_cu) const {
@@ -121,7 +124,7 @@ struct StepUs {
 };
 template <typename T, int D> struct Cost;   // forward, dQ (steps of 32 keys), dK/dV (steps of 32 rows, nc = 0)
 template <> struct Cost<bf16_t, 64> {
-  static constexpr StepUs fwd = {0.225, 0.11, 0.175, 0.23, 0.15, 0.065}, dq = {0.075, 0.16, 0.12, 0.31, 0.07, 0.12},
+  static constexpr StepUs fwd = {0.225, 0.11, 0.181, 0.18, 0.034, 0.119}, dq = {0.075, 0.16, 0.12, 0.31, 0.07, 0.12},
                           dkdv = {0.75, 0, 0.9, 0, 0.42, 0};
 };
 template <> struct Cost<bf16_t, 80> {
