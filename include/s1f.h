@@ -27,8 +27,8 @@
  *     the call returns without synchronising.  Arguments are validated before anything is enqueued: on
  *     S1F_EINVAL, S1F_EUNSUPPORTED or S1F_ERANGE nothing has been launched and no output was touched.
  *     S1F_EDEVICE reports that the HIP runtime refused a launch of THIS call (errors left behind by the
- *     caller's earlier HIP work are not picked up); a call made of several launches (s1f_seg_attn_bwd, the
- *     cache calls with batch > 1) may then have enqueued its earlier ones, so its outputs are undefined.
+ *     caller's earlier HIP work are not picked up); an attention call, which may be made of several
+ *     launches, may then have enqueued its earlier ones, so its outputs are undefined.
  *   - Every entry point returns an s1f_status; nothing throws or aborts across this boundary.
  */
 #ifndef S1F_H
@@ -190,10 +190,11 @@ size_t s1f_bwd_workspace_bytes(const s1f_desc *desc, int64_t seg_off, int64_t se
 
 /* s1f_seg_attn_bwd for callers that cannot allocate device memory or pass a workspace: code under HIP graph
  * capture, tight serving or training loops, harnesses that forbid hipMalloc.  Same arguments (without the
- * workspace), same kernels; dK/dV bit-identical, dQ identical up to the rounding order of the key-split (the
+ * workspace), same kernels; dK/dV are bit-identical to those of a call with a workspace of s1f_bwd_workspace_bytes
+ * (an fp32 call with a smaller one runs uncut and adds in another order), dQ identical up to the order of its sums (the
  * built-in scratch leaves room for 32 MiB of partial dQ rows, s1f_seg_attn_bwd's workspace for 512 MiB, so the
- * two may cut a launch differently); the row statistics go to a device array built into the
- * library (48 MiB per GPU: 16 MiB of row statistics and 32 MiB for partial dQ rows; held until the process ends)
+ * two may cut that launch differently); the scratch is a device array built into the
+ * library (48 MiB per GPU: 16 MiB of row statistics and 32 MiB of partial results; held until the process ends)
  * instead of a caller-owned workspace.  The call
  * allocates nothing and frees nothing.
  *   Limit: batch * n_q_heads * seg_len <= s1f_static_scratch_rows() (2^21); beyond it the call returns

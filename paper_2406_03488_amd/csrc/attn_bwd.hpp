@@ -34,7 +34,7 @@ template <typename T, int D, int NC> struct BwdDqCfg {
 //   B  dQ += K(k)^T dS(k)    ||  p(k+1) = exp2(c * S(k+1) - lse)
 //   C  dP(k+1)
 // The order is pinned matrix instruction by matrix instruction; LDS operands are read kDqRing operands ahead.
-// Bound by the matrix pipe at the clock the power limit leaves (head_dim 128, 56 heads: 77 % busy at 1.63 GHz), with 64 registers
+// Bound by the matrix pipe at the clock the power limit leaves (head_dim 128: 71-77 % busy at 1.73-1.78 GHz), with 64 registers
 // of accumulators and 64 of Q and dO per lane at NC = 2.  32 heads, 4096 rows behind 28672 keys: head_dim 128
 // 2.52 -> 2.29 ms (three products executed: 1230 -> 1350 TFLOP/s), 80 1.89 -> 1.57 ms and 64 1.54 -> 1.26 ms (NC = 3).
 // One wave per SIMD with 64 rows (half the LDS reads) ran 15 % slower: half of its registers are accumulator
@@ -284,7 +284,7 @@ __global__ void __launch_bounds__(256, OCC) seg_attn_bwd_dq_kernel(const AttnArg
   }
 }
 
-// Sums the chunks of the units that seg_attn_bwd_dq_kernel split along the keys: dq = scale * sum_c part_c.
+// Sums the chunks of the units that seg_attn_bwd_dq_kernel cut along the keys: dq = scale * sum_c part_c.
 // Thread and grid layout as in seg_attn_fwd_merge_kernel.
 template <typename T, int D, int MC>
 __global__ void __launch_bounds__(256) seg_attn_bwd_dq_merge_kernel(const AttnArgs a) {
@@ -340,7 +340,7 @@ template <typename T, int D> struct BwdDkdvCfg {
 // Vector work runs under the matrix instructions of the next product: the exponentials under dP, dS under dV; the order
 // is pinned matrix instruction by matrix instruction, LDS operands are read kDkdvRing operands ahead.  Two workgroups
 // share a compute unit, with barriers of their own: one's prologue, epilogue and waits overlap the other's products.
-// Bound by the matrix pipe at the clock the power limit leaves (head_dim 128: 69 % busy at 1.78 GHz).  32 heads, 4096
+// Bound by the matrix pipe at the clock the power limit leaves (head_dim 128: 62-68 % busy at 1.85-1.89 GHz).  32 heads, 4096
 // rows behind 28672 keys: head_dim 128 3.70 -> 3.41 ms (1114 -> 1210 TFLOP/s), 80 2.80 -> 2.54 ms; head_dim 64 with
 // three workgroups per compute unit 1.94 -> 1.74 ms (two: 1.89).  A ring of 6 operands measures the same, one of 8
 // 12 % slower.
@@ -603,7 +603,7 @@ __global__ void __launch_bounds__(256, WGS) seg_attn_bwd_dkdv_kernel(const AttnA
   }
 }
 
-// Adds the chunks of the units that seg_attn_bwd_dkdv_kernel split along the queries into the accumulators, which chunk
+// Adds the chunks of the units that seg_attn_bwd_dkdv_kernel cut along the queries into the accumulators, which chunk
 // 0 has updated itself: acc += sum_c part_c, c = 1 .. n_split - 1, in the order of the chunks.  A thread handles 4
 // consecutive head_dim elements of one key of one of the two accumulators (grid: split units x DkdvMerge<D>::GROUPS).
 template <int D> struct DkdvMerge {

@@ -103,13 +103,15 @@ S1F_DEV void decode_workgroup(int id, int n_tiles, int n_bh, int tile_major, int
   }
 }
 
-// Key-split.  The workgroups of a launch are handed to the chip's workgroup slots in id order; when the last
+// Cut launches.  The workgroups of a launch are handed to the chip's workgroup slots in id order; when the last
 // round of units fills only part of the slots, the launch ends with most of the chip idle for the length of one
-// unit (a row tile against its whole prefix).  The host may therefore cut each of the LAST units of a launch into
-// n_split chunks along the keys, which then run side by side; every chunk leaves a partial result in a workspace and a
-// small second kernel merges them.  The keys that every row of the unit sees in full (`full`, counted in pieces of the
-// kernel's step) are dealt out evenly; the last chunk also takes the pieces on the diagonal.
-// In: workgroup id.  Out: unit id, the chunk's piece range [begin, end) and its index in the workspace (-1: whole).
+// unit (forward and dQ: a row tile against its whole prefix; dK/dV: a key tile against the rows that see it).  The host may
+// therefore cut each of the LAST units of a launch into n_split chunks, along the keys or (dK/dV) along the query rows,
+// which then run side by side; a chunk leaves a partial result in a workspace (the first chunk of a dK/dV unit adds to the
+// accumulators itself) and a small second kernel merges them.  Row tiles deal out evenly the keys that every row of the
+// unit sees in full (`full`, counted in pieces of the kernel's step; see chunk_range); the last chunk also takes the pieces
+// on the diagonal.
+// In: workgroup id.  Out: unit id, the chunk's number and its index in the workspace (-1: whole).
 constexpr int kMaxChunks = 16;   // most chunks a unit is ever cut into
 struct UnitChunk {
   int unit, chunk, n_chunks, slot;
@@ -153,12 +155,12 @@ struct AttnArgs {
   int32_t n_tiles, n_bh;                 // launch shape: tiles per (batch, head) and number of (batch, head) pairs
   int32_t tile_major;                    // order of the workgroups within an XCD (see decode_workgroup)
   float scale;                           // 1/sqrt(head_dim)
-  // Key-split of the last units of a launch (forward and dQ kernels; see split_unit): workgroup ids below n_whole
-  // are whole units; the n_split_units units after them are cut into n_split chunks each.
+  // The cut of the last units of a launch (see split_unit): workgroup ids below n_whole are whole units; the
+  // n_split_units units after them are cut into n_split chunks each.
   int32_t n_whole, n_split, n_split_units;
   int32_t bm;                            // forward and dQ: rows per unit
   int32_t first_id;                      // forward: > 0 in a second launch, over the rows of the units from n_whole = first_id on
-  float *part;                           // partial results of the chunks: [chunk][split unit][rows per unit][head_dim]
+  float *part;                           // partial results of the chunks: [chunk][cut unit][rows per unit][head_dim]
   float *part_ml;                        // forward only: running maximum (log2 units) and row sum, [..][rows per unit][2]
 };
 

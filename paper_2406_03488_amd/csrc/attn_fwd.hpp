@@ -1,9 +1,9 @@
 // Forward of one segment: out = softmax(q k^T / sqrt(D), causal with the diagonal shifted by seg_off) v,
 // lse = log-sum-exp of the scaled scores (Section 3.1, Eq. 3, restricted to the segment's rows).
 //
-// One workgroup (4 waves) owns 128 query rows of one head; wave w owns rows 32*w .. +32, two column blocks of 16.
-// The transposed products are computed so that a lane always holds TWO queries (column n of either block) and the
-// keys run over registers:
+// One workgroup (4 waves) owns 64*NC query rows of one head (NC = 1, 2, 3); wave w owns rows 16*NC*w .. +16*NC, NC column
+// blocks of 16.  The transposed products are computed so that a lane always holds NC queries (column n of each block) and
+// the keys run over registers:
 //     S^T[key][q] = sum_d K[key][d] Q[q][d]        A = K from LDS, B = Q (registers)
 //     O^T[d][q]  += sum_key V[key][d] P^T[key][q]  A = V read transposed from LDS, B = P^T slab (registers)
 // Row maximum and sum are then in-lane reductions; the four lanes of a query meet at the end only.
@@ -12,11 +12,11 @@
 // barrier per tile.
 // The loop advances by one tile and is software-pipelined inside each wave: the score product of tile k+1 (matrix
 // pipe) is issued together with the operand packing of tile k's probabilities (vector pipe), then the PV product of
-// tile k together with the exponentials of tile k+1 (see fwd_step).  Tiles wholly above the shifted diagonal are never
-// visited; tiles wholly below it run a step without any masking code.
+// tile k together with the exponentials of tile k+1 (see fwd_step).  A wave walks to the last tile that one of its rows sees
+// (see own_tiles); tiles that all of them see run a step without any masking code.
 //
-// What bounds it: the matrix pipe, at the clock the power limit leaves (head_dim 128: 67 % busy at 1.77 GHz, two waves
-// per SIMD).  Per step and wave it runs 16 * NC matrix instructions of 16 cycles against about 12 * NC vector
+// What bounds it: the matrix pipe, at the clock the power limit leaves (head_dim 128: 63-68 % busy at 1.82-1.86 GHz, two
+// waves per SIMD).  Per step and wave it runs 16 * NC matrix instructions of 16 cycles against about 12 * NC vector
 // instructions and 8 * NC exponentials (two issue slots each), so both have to run under each other, and every operand
 // read from LDS should feed as many matrix instructions as registers allow: 48 rows per wave (NC = 3) read a third less
 // LDS per product than 32.  32 heads, 4096 rows behind 28672 keys: head_dim 128 1.86 -> 1.65 ms (1110 -> 1250
@@ -58,7 +58,7 @@ template <int NC> S1F_DEV void fwd_mask(f32x4 (&s)[2][NC], int rb, int ahead) {
       if (16 * rb + v > lim + 16 * cb) s[rb][cb][v] = hidden;
 }
 
-// Row maxima of a tile in log2 units (each lane gets the maxima of its two queries' 32 scores).
+// Row maxima of a tile in log2 units (each lane gets the maxima of its NC queries' 32 scores).
 template <int NC> S1F_DEV void fwd_row_max(const f32x4 (&s)[2][NC], float (&mx)[NC], float c) {
 #pragma unroll
   for (int cb = 0; cb < NC; ++cb) {
@@ -383,7 +383,7 @@ __global__ void __launch_bounds__(256, OCC) seg_attn_fwd_kernel(const AttnArgs a
   }
 }
 
-// Merges the chunks of the units that seg_attn_fwd_kernel split along the keys: with m_c, l_c, o_c the running
+// Merges the chunks of the units that seg_attn_fwd_kernel cut along the keys: with m_c, l_c, o_c the running
 // maximum (log2 units), row sum and unnormalised output row of chunk c,
 //   m = max_c m_c,  l = sum_c l_c 2^(m_c - m),  out = sum_c o_c 2^(m_c - m) / l,  lse = (m + log2 l) ln 2.
 // A thread handles 4 consecutive head_dim elements of one row; a workgroup MergeRows<D>::RG rows of one split unit

@@ -44,7 +44,7 @@ int check_desc(const s1f_desc *d) {
   for (int i = 0; i < 6; ++i)
     if (s[i] < 0 || s[i] % ce != 0) return S1F_EINVAL;
   if (d->q_stride_s < d->head_dim || d->kv_stride_s < d->head_dim) return S1F_EINVAL;
-  // the asynchronous tile copies address the rows of a tile (up to 64 rows) with 32-bit byte offsets
+  // the asynchronous tile copies address the 32 rows of a tile with 32-bit byte offsets
   if (d->q_stride_s >= (int64_t(1) << 23) || d->kv_stride_s >= (int64_t(1) << 23)) return S1F_EUNSUPPORTED;
   return S1F_OK;
 }
