@@ -19,58 +19,63 @@ struct CopyArgs {
   int32_t batch, rows, heads, chunks;                        // chunks of 8 elements per row
 };
 
-// One thread moves 8 consecutive head_dim elements of one row of both tensors of one (batch entry, head); the grid's y and
-// z run over heads and batch entries (in strides, should there be more than a grid holds): one launch per call, where
-// one per batch entry took 3 us each for two sequences of 340 rows.  Bound by memory: append and emit of 32 heads x 3652
+// One thread moves 8 consecutive head_dim elements of one row of both tensors of one batch entry; the grid's y runs over
+// batch entries (in strides, should there be more than a grid holds): one launch per call, where one per batch entry took
+// 3 us each for two sequences of 340 rows.  A batch entry's rows are numbered head after head without a gap, so that
+// workgroups copy aligned blocks of a dense cache (with heads in the grid's y, 56 heads x 58553 rows of head_dim 80 took 956
+// us for append and emit instead of 900).  Bound by memory: append and emit of 32 heads x 3652
 // rows (300 MB) take 60 us, 5.0 TB/s (a plain device copy reaches 4.8 TB/s).  Loading the rows past the caches took 57 us
 // there, but rows that are still in a cache, as they are when something has just produced them, are then fetched again
 // (append of the same rows 18.1 -> 21.8 us, emit 26.5 -> 31.6), and fp32 lost at every size (append of 32 heads x 30000 rows,
 // head_dim 64: 235 -> 285 us).
 // SRC/DST: element types (float or bf16_t); float -> bf16 rounds to nearest even.
 template <typename SRC, typename DST> __global__ void __launch_bounds__(256) rows_kernel(const CopyArgs a) {
-  const int64_t id = (int64_t)blockIdx.x * 256 + threadIdx.x;
-  if (id >= (int64_t)a.rows * a.chunks) return;
-  int64_t r;
+  const int64_t id = (int64_t)blockIdx.x * 256 + threadIdx.x, per_head = (int64_t)a.rows * a.chunks;
+  if (id >= per_head * a.heads) return;
+  int64_t h, r;
   int c;
-  if ((int64_t)a.rows * a.chunks <= 0x7fffffff) {
-    r = (int)id / a.chunks;
-    c = (int)id % a.chunks;
+  if (per_head * a.heads <= 0x7fffffff) {
+    const unsigned row = (unsigned)id / (unsigned)a.chunks;
+    c = (int)((unsigned)id % (unsigned)a.chunks);
+    h = row / (unsigned)a.rows;
+    r = row % (unsigned)a.rows;
   } else {
-    r = id / a.chunks;
+    const int64_t row = id / a.chunks;
     c = (int)(id % a.chunks);
+    h = row / a.rows;
+    r = row % a.rows;
   }
-  for (int b = blockIdx.z; b < a.batch; b += gridDim.z)
-    for (int h = blockIdx.y; h < a.heads; h += gridDim.y) {
-      const int64_t so = b * a.src_sb + h * a.src_sh + r * a.src_ss + 8 * c;
-      const int64_t dof = b * a.dst_sb + h * a.dst_sh + r * a.dst_ss + 8 * c;
+  const int64_t so0 = h * a.src_sh + r * a.src_ss + 8 * c, do0 = h * a.dst_sh + r * a.dst_ss + 8 * c;
+  for (int b = blockIdx.y; b < a.batch; b += gridDim.y) {
+    const int64_t so = b * a.src_sb + so0, dof = b * a.dst_sb + do0;
 #pragma unroll
-      for (int t = 0; t < 2; ++t) {
-        const SRC *s = reinterpret_cast<const SRC *>(t ? a.src1 : a.src0) + so;
-        DST *d = reinterpret_cast<DST *>(t ? a.dst1 : a.dst0) + dof;
-        if (sizeof(SRC) == sizeof(DST)) {
-          if (sizeof(SRC) == 2) {
-            *reinterpret_cast<u32x4 *>(d) = *reinterpret_cast<const u32x4 *>(s);
-          } else {
-            reinterpret_cast<u32x4 *>(d)[0] = reinterpret_cast<const u32x4 *>(s)[0];
-            reinterpret_cast<u32x4 *>(d)[1] = reinterpret_cast<const u32x4 *>(s)[1];
-          }
-        } else {   // fp32 -> bf16
-          const f32x4 x = reinterpret_cast<const f32x4 *>(s)[0], y = reinterpret_cast<const f32x4 *>(s)[1];
-          bf16x8 o;
-#pragma unroll
-          for (int e = 0; e < 4; ++e) { o[e] = (bf16_t)x[e]; o[4 + e] = (bf16_t)y[e]; }
-          *reinterpret_cast<bf16x8 *>(d) = o;
+    for (int t = 0; t < 2; ++t) {
+      const SRC *s = reinterpret_cast<const SRC *>(t ? a.src1 : a.src0) + so;
+      DST *d = reinterpret_cast<DST *>(t ? a.dst1 : a.dst0) + dof;
+      if (sizeof(SRC) == sizeof(DST)) {
+        if (sizeof(SRC) == 2) {
+          *reinterpret_cast<u32x4 *>(d) = *reinterpret_cast<const u32x4 *>(s);
+        } else {
+          reinterpret_cast<u32x4 *>(d)[0] = reinterpret_cast<const u32x4 *>(s)[0];
+          reinterpret_cast<u32x4 *>(d)[1] = reinterpret_cast<const u32x4 *>(s)[1];
         }
+      } else {   // fp32 -> bf16
+        const f32x4 x = reinterpret_cast<const f32x4 *>(s)[0], y = reinterpret_cast<const f32x4 *>(s)[1];
+        bf16x8 o;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) { o[e] = (bf16_t)x[e]; o[4 + e] = (bf16_t)y[e]; }
+        *reinterpret_cast<bf16x8 *>(d) = o;
       }
     }
+  }
 }
 
 template <typename SRC, typename DST> int launch_rows(const CopyArgs &a, hipStream_t st) {
-  const int64_t blocks = ((int64_t)a.rows * a.chunks + 255) / 256;
+  const int64_t blocks = ((int64_t)a.heads * a.rows * a.chunks + 255) / 256;
   if (blocks > 0x7fffffff) return S1F_EUNSUPPORTED;
   CopyArgs args = a;
   void *params[] = {&args};
-  const dim3 grid((unsigned)blocks, a.heads < 65535 ? a.heads : 65535, a.batch < 65535 ? a.batch : 65535);
+  const dim3 grid((unsigned)blocks, a.batch < 65535 ? a.batch : 65535);
   const hipError_t e = hipLaunchKernel(reinterpret_cast<const void *>(&rows_kernel<SRC, DST>), grid, dim3(256), params, 0, st);
   return e == hipSuccess ? S1F_OK : S1F_EDEVICE;
 }
