@@ -18,10 +18,6 @@
 
 namespace s1f {
 
-template <typename T, int D, int NC> struct BwdDqCfg {
-  static constexpr int BM = 64 * NC, BN = 32;
-};
-
 // One workgroup (4 waves) owns 64*NC query rows of one head, a wave NC column blocks of 16; lane = one query per column
 // block, keys run over registers.
 //   S^T[key][q]  = K Q^T      A = K (LDS),            B = Q (registers)
@@ -39,15 +35,14 @@ template <typename T, int D, int NC> struct BwdDqCfg {
 // 2.52 -> 2.29 ms (three products executed: 1230 -> 1350 TFLOP/s), 80 1.89 -> 1.57 ms and 64 1.54 -> 1.26 ms (NC = 3).
 // One wave per SIMD with 64 rows (half the LDS reads) ran 15 % slower: half of its registers are accumulator
 // registers, which the vector phases reach by copies only.
-constexpr int kDqRing = 4;
+template <typename T, int D> constexpr int kDqRing = sizeof(T) == 2 ? 4 : D == 64 ? 2 : 3;   // (fp32: three registers for one)
 
-template <typename T, int D, int NC, int OCC>
-__global__ void __launch_bounds__(256, OCC) seg_attn_bwd_dq_kernel(const AttnArgs a) {
-  typedef BwdDqCfg<T, D, NC> Cfg;
+template <typename T, int D, int NC, int OCC, int WAVES>
+__global__ void __launch_bounds__(64 * WAVES, OCC) seg_attn_bwd_dq_kernel(const AttnArgs a) {
   typedef Mat<T, D> M;
   typedef typename M::Frag Frag;
-  typedef TileRing<T, D> Ring;
-  constexpr int DB = M::DB, BM = Cfg::BM, BN = Cfg::BN, NN = M::NN, NK = M::NK, NT = M::NT, PR = kDqRing;
+  typedef TileRing<T, D, WAVES> Ring;
+  constexpr int DB = M::DB, BM = 16 * NC * WAVES, BN = 32, NN = M::NN, NK = M::NK, NT = M::NT, PR = kDqRing<T, D>;
   constexpr int TOTAL = NN + NT + NN;
   static_assert(NN >= PR && NT >= PR, "operand ring deeper than a product");
 
@@ -113,7 +108,7 @@ __global__ void __launch_bounds__(256, OCC) seg_attn_bwd_dq_kernel(const AttnArg
 
   if (n_kt <= 0) {   // more chunks than this unit has whole tiles: nothing to add
     float *pd = a.part + (int64_t)uc.slot * (BM * D);
-    for (int i = tid; i < BM * D; i += 256) pd[i] = 0.f;
+    for (int i = tid; i < BM * D; i += 64 * WAVES) pd[i] = 0.f;
     return;
   }
   wait_async_tiles();
@@ -162,11 +157,12 @@ __global__ void __launch_bounds__(256, OCC) seg_attn_bwd_dq_kernel(const AttnArg
     if (BN - 1 > wfirst) hide(p, 0);
   }
   Frag fr[PR];   // operand ring: operand x of a step sits in fr[x % PR]
-  {
+  auto first_operands = [&]() {
     const typename M::Nat ka = rd.nat_at(ring.st[1]);
 #pragma unroll
     for (int i = 0; i < PR; ++i) fr[i] = M::nat(ka, i);
-  }
+  };
+  if (Ring::AHEAD) first_operands();
   typename M::Slab ds[NC];
   auto make_ds = [&](int cb) {
     ds[cb] = M::slab(p[0][cb] * dp[0][cb], p[1][cb] * dp[1][cb]);
@@ -175,6 +171,7 @@ __global__ void __launch_bounds__(256, OCC) seg_attn_bwd_dq_kernel(const AttnArg
   auto step = [&](auto mask, auto whole) {
     constexpr bool MASK = decltype(mask)::value, WHOLE = decltype(whole)::value;
     ring.template begin_step<WHOLE>(n_kt - 1 - k);
+    if (!Ring::AHEAD) first_operands();
     const typename M::Nat kn = rd.nat_at(ring.st[1]), ka = rd.nat_at(ring.st[2]);
     const typename M::Tr kt = rd.tr_at(ring.st[0]);
     auto next_operand = [&](int x) {   // operand x has been used up: the one that takes its place
@@ -182,7 +179,7 @@ __global__ void __launch_bounds__(256, OCC) seg_attn_bwd_dq_kernel(const AttnArg
       if (y < NN) fr[x % PR] = M::nat(kn, y);
       else if (y < NN + NT) fr[x % PR] = M::tr(kt, y - NN);
       else if (y < TOTAL) fr[x % PR] = M::nat(kn, y - NN - NT, Tile32<T, D>::BYTES);
-      else fr[x % PR] = M::nat(ka, x % PR);   // the next step's first ones
+      else if (Ring::AHEAD) fr[x % PR] = M::nat(ka, x % PR);   // the next step's first ones
     };
     if (D != 80) __builtin_amdgcn_s_setprio(1);   // phase A first: of two ready waves the one with little else to issue
     f32x4 sn[2][NC];
@@ -194,7 +191,8 @@ __global__ void __launch_bounds__(256, OCC) seg_attn_bwd_dq_kernel(const AttnArg
         sn[i / NK][cb] = M::mma_nat(i, fr[i % PR], q[cb], i % NK ? sn[i / NK][cb] : zero);
         if (cb + 1 == NC) next_operand(i);
         if (i == 1) make_ds(cb);
-        __builtin_amdgcn_sched_barrier(0);
+        ring.template work<WHOLE>(i * NC + cb, TOTAL * NC);
+        end_slot<M>();
       }
     if (D != 80) __builtin_amdgcn_s_setprio(0);
     // probability x of 8 * NC: column block by column block, so that half of them do not wait for the last scores
@@ -215,7 +213,8 @@ __global__ void __launch_bounds__(256, OCC) seg_attn_bwd_dq_kernel(const AttnArg
         if (cb + 1 == NC) next_operand(NN + i);
         const int w = i * NC + cb, W = NT * NC;
         probs(8 * NC * w / W, 8 * NC * (w + 1) / W);
-        __builtin_amdgcn_sched_barrier(0);
+        ring.template work<WHOLE>(NN * NC + w, TOTAL * NC);
+        end_slot<M>();
       }
 #pragma unroll
     for (int i = 0; i < NN; ++i)
@@ -224,7 +223,8 @@ __global__ void __launch_bounds__(256, OCC) seg_attn_bwd_dq_kernel(const AttnArg
         dp[i / NK][cb] = M::mma_nat(i, fr[(NN + NT + i) % PR], dor[cb], i % NK ? dp[i / NK][cb] : nd[cb]);
         if (cb + 1 == NC) next_operand(NN + NT + i);
         if (MASK && i == 0 && cb + 1 == NC) hide(p, BN * (k + 1));
-        __builtin_amdgcn_sched_barrier(0);
+        ring.template work<WHOLE>((NN + NT + i) * NC + cb, TOTAL * NC);
+        end_slot<M>();
       }
     ++k;
     ring.end_step();
@@ -315,20 +315,25 @@ __global__ void __launch_bounds__(256) seg_attn_bwd_dq_merge_kernel(const AttnAr
 
 template <typename T, int D> struct BwdDkdvCfg {
   static constexpr int BQ = 32;                        // rows per Q/dO tile
-  static constexpr int BNW = 128;                      // keys per workgroup: 4 waves of 32
+  static constexpr int BNW = 128;                      // keys per workgroup: 4 waves of 32, in fp32 above head_dim 64 8 waves of 16
+  static constexpr int WAVES = sizeof(T) == 4 && D > 64 ? 8 : 4;
+  static constexpr int CB = 8 / WAVES;                 // column blocks of 16 keys per wave
   typedef Tile32<T, D> TL;
+  static constexpr int STAGES = sizeof(T) == 4 ? 1 : 2;   // (fp32: three planes of V and one stage are what LDS holds)
   static constexpr int STAGE_BYTES = 2 * TL::BYTES;    // Q tile, dO tile right behind it
   static constexpr int STAT_BYTES = 2 * BQ * 4;        // -lse/scale and -delta of the tile's rows
   static constexpr int V_BYTES = 4 * TL::BYTES;        // the workgroup's V rows
-  static constexpr int LOOP_BYTES = 2 * STAGE_BYTES + V_BYTES + 2 * STAT_BYTES;   // two stages, V, statistics
+  static constexpr int LOOP_BYTES = STAGES * STAGE_BYTES + V_BYTES + 2 * STAT_BYTES;   // stages, V, statistics
   static constexpr int EPI_ROW = pow2_at_least(D * 4); // bytes per row of the epilogue's staging regions
-  static constexpr int EPI_BYTES = 4 * 32 * EPI_ROW;
+  static constexpr int EPI_BYTES = BNW * EPI_ROW;
   static constexpr int LDS_BYTES = LOOP_BYTES > EPI_BYTES ? LOOP_BYTES : EPI_BYTES;
 };
 
 // dK/dV kernel.  A workgroup owns 128 keys of one K/V head, a wave 32 of them in two column blocks of 16; lane = one key
 // per column block; queries run over registers.  Q/dO tiles of 32 rows and their row statistics travel through a
-// two-stage LDS ring, copied HBM -> LDS asynchronously.
+// two-stage LDS ring, copied HBM -> LDS asynchronously.  (fp32: one stage of planes, the next tile waiting in registers; above
+// head_dim 64 eight waves of one column block each, two to a SIMD: 32 heads, 2048 rows behind 8000 keys, head_dim 128 3235 ->
+// 2676 us, 80 2364 -> 1995; at 64, where two workgroups of four waves share a compute unit, 1359 -> 1511, hence four there.)
 //   S[q][key]  = Q K^T         A = Q (LDS),              B = K (registers)
 //   dP[q][key] = dO V^T        A = dO (LDS),             B = V (LDS)
 //   dV^T[d][key] += dO^T P     A = dO read transposed,   B = P slab (registers)
@@ -344,16 +349,17 @@ template <typename T, int D> struct BwdDkdvCfg {
 // rows behind 28672 keys: head_dim 128 3.70 -> 3.41 ms (1114 -> 1210 TFLOP/s), 80 2.80 -> 2.54 ms; head_dim 64 with
 // three workgroups per compute unit 1.94 -> 1.74 ms (two: 1.89).  A ring of 6 operands measures the same, one of 8
 // 12 % slower.
-constexpr int kDkdvRing = 4;
+template <typename T> constexpr int kDkdvRing = sizeof(T) == 4 ? 3 : 4;   // (fp32: three registers for one)
 
-template <typename T, int D, int WGS>   // WGS: workgroups meant to share a compute unit
-__global__ void __launch_bounds__(256, WGS) seg_attn_bwd_dkdv_kernel(const AttnArgs a) {
+template <typename T, int D, int WGS>   // WGS: waves meant to share a SIMD
+__global__ void __launch_bounds__((64 * BwdDkdvCfg<T, D>::WAVES), WGS) seg_attn_bwd_dkdv_kernel(const AttnArgs a) {
   typedef BwdDkdvCfg<T, D> Cfg;
   typedef Mat<T, D> M;
   typedef typename M::Frag Frag;
-  typedef TilePairCopy<T, D> Copy;
-  constexpr int DB = M::DB, BQ = Cfg::BQ, NN = M::NN, NK = M::NK, NT = M::NT, PR = kDkdvRing;
-  constexpr int TB = Tile32<T, D>::BYTES, X1 = NN, X2 = X1 + 4 * NK, X3 = X2 + NT, TOTAL = X3 + NT;
+  typedef typename TileRing<T, D, Cfg::WAVES>::Copy Copy;
+  constexpr bool ASYNC = Cfg::STAGES == 2;   // tiles are copied past the registers
+  constexpr int DB = M::DB, BQ = Cfg::BQ, NN = M::NN, NK = M::NK, NT = M::NT, PR = kDkdvRing<T>, CB = Cfg::CB;
+  constexpr int TB = Tile32<T, D>::BYTES, X1 = NN, X2 = X1 + (2 + CB) * NK, X3 = X2 + NT, TOTAL = X3 + NT;
 
   extern __shared__ __attribute__((aligned(1024))) char smem[];
   const int tid = threadIdx.x, lane = tid & 63, j = lane >> 4, n = lane & 15;
@@ -365,7 +371,7 @@ __global__ void __launch_bounds__(256, WGS) seg_attn_bwd_dkdv_kernel(const AttnA
   const int hk = bh % n_kv_heads, b = bh / n_kv_heads;
   const int seg_off = a.seg_off, seg_len = a.seg_len, kv_len = seg_off + seg_len;
   const int j0 = kt * Cfg::BNW;                    // first key of the workgroup
-  const int wkey0 = j0 + wave * 32;                // first key of the wave
+  const int wkey0 = j0 + wave * 16 * CB;                // first key of the wave
 
   const int64_t kvoff = b * a.kv_sb + hk * a.kv_sh;
   const T *kbase = reinterpret_cast<const T *>(a.k) + kvoff;
@@ -384,7 +390,7 @@ __global__ void __launch_bounds__(256, WGS) seg_attn_bwd_dkdv_kernel(const AttnA
   const bool w_active = wkey0 < kv_len;
 
   const lds_addr lds0 = to_lds_addr(smem);
-  const lds_addr vtile = lds0 + 2 * Cfg::STAGE_BYTES;
+  const lds_addr vtile = lds0 + Cfg::STAGES * Cfg::STAGE_BYTES;
   const lds_addr stats0 = vtile + Cfg::V_BYTES;
   M rd;
   rd.init(lane);
@@ -393,9 +399,15 @@ __global__ void __launch_bounds__(256, WGS) seg_attn_bwd_dkdv_kernel(const AttnA
     lv.init(wave, lane, a.kv_ss);
 #pragma unroll
     for (int i = 0; i < 4; i += 2) {
-      const int key0 = j0 + 32 * (i + (wave >> 1)), at = key0 < kv_len ? key0 : kv_len - 1;
+      const int key0 = j0 + 32 * (i + ((wave >> 1) & 1)), at = key0 < kv_len ? key0 : kv_len - 1;
       const T *row = vbase + (int64_t)at * a.kv_ss;
-      lv.issue(row, row, a.kv_ss, kv_len - at, kv_len - at, vtile + i * TB, wave);
+      if constexpr (ASYNC) {
+        lv.issue(row, row, a.kv_ss, kv_len - at, kv_len - at, vtile + i * TB, wave);
+      } else {
+        lv.load(row, row, a.kv_ss, kv_len - at, kv_len - at, wave);
+#pragma unroll
+        for (int x = 0; x < Copy::NI; ++x) lv.write(x, vtile + i * TB);
+      }
     }
   }
   // Tile cursors (row offset of the tile, its query head, its ring stage), advanced once per iteration.
@@ -411,8 +423,10 @@ __global__ void __launch_bounds__(256, WGS) seg_attn_bwd_dkdv_kernel(const AttnA
   ld.init(wave, lane, a.q_ss);
   auto issue = [&](const Cursor &t) {   // rows past the segment re-read its last row
     const int64_t qoff = b * a.q_sb + t.hq * a.q_sh + (int64_t)t.r0 * a.q_ss;
-    ld.issue(reinterpret_cast<const T *>(a.q) + qoff, reinterpret_cast<const T *>(a.dout) + qoff, a.q_ss, seg_len - t.r0,
-             seg_len - t.r0, lds0 + t.stage * Cfg::STAGE_BYTES, wave);
+    const T *q = reinterpret_cast<const T *>(a.q) + qoff, *dout = reinterpret_cast<const T *>(a.dout) + qoff;
+    const int left = seg_len - t.r0;
+    if constexpr (ASYNC) ld.issue(q, dout, a.q_ss, left, left, lds0 + t.stage * Cfg::STAGE_BYTES, wave);
+    else ld.load(q, dout, a.q_ss, left, left, wave);
     if (wave == 0) {   // lane l copies entry l of {-lse/scale [32], -delta [32]}
       const int l = lane_id(), rr = t.r0 + l % BQ;
       const unsigned plane = (unsigned)((l / BQ) * a.ws_plane);
@@ -427,38 +441,47 @@ __global__ void __launch_bounds__(256, WGS) seg_attn_bwd_dkdv_kernel(const AttnA
   if (it_begin < it_end) issue(t_iss);
   advance(t_iss);
   // K rows of the wave's keys stay in registers for the whole kernel.
-  typename M::RowOp kr[2];
+  typename M::RowOp kr[CB];
 #pragma unroll
-  for (int cb = 0; cb < 2; ++cb) {
+  for (int cb = 0; cb < CB; ++cb) {
     int key = wkey0 + 16 * cb + n;
     key = key < kv_len ? key : kv_len - 1;     // keys past the prefix are computed on a copy and never stored
     M::load_row(kr[cb], kbase + (int64_t)key * a.kv_ss, j);
 #pragma unroll
     for (int i = 0; i < M::NK; ++i) settle(kr[cb].f[i]);
   }
-  f32x4 dk[2][DB], dv[2][DB];
+  f32x4 dk[CB][DB], dv[CB][DB];
 #pragma unroll
-  for (int cb = 0; cb < 2; ++cb)
+  for (int cb = 0; cb < CB; ++cb)
 #pragma unroll
     for (int db = 0; db < DB; ++db) dk[cb][db] = dv[cb][db] = f32x4{0.f, 0.f, 0.f, 0.f};
+  // one stage: the tile whose rows are in registers
+  auto write_tile = [&]() {
+    if constexpr (!ASYNC) {
+#pragma unroll
+      for (int x = 0; x < Copy::NI; ++x) ld.write(x, lds0);
+    }
+  };
+  if constexpr (!ASYNC)
+    if (it_begin < it_end) write_tile();
   wait_async_tiles();
   __syncthreads();
 
   for (int it = it_begin; it < it_end; ++it) {
-    // the stage this copy overwrites was last read before the barrier that ended the previous iteration
+    // (two stages) the stage this copy overwrites was last read before the barrier that ended the previous iteration
     if (it + 1 < it_end) issue(t_iss);
     advance(t_iss);
     if (w_active && wkey0 <= seg_off + cur.r0 + 31) {
-      const lds_addr qt = lds0 + cur.stage * Cfg::STAGE_BYTES;   // the dO tile lies TB behind it
+      const lds_addr qt = lds0 + (ASYNC ? cur.stage * Cfg::STAGE_BYTES : 0);   // the dO tile lies TB behind it
       const lds_addr st = opaque(stats0 + (unsigned)(cur.stage * Cfg::STAT_BYTES + 16 * j));
-      const typename M::Nat qn = rd.nat_at(qt), vn = rd.nat_at(vtile + wave * TB);
+      const typename M::Nat qn = rd.nat_at(qt), vn = rd.nat_at(CB == 2 ? vtile + wave * TB : vtile + (wave >> 1) * TB + (wave & 1) * NK * 1024);
       const typename M::Tr qx = rd.tr_at(qt);
-      // Operand x of the iteration: Q [NN], then per step along D dO, V, V, dO, then dO and Q transposed [NT each].
+      // Operand x of the iteration: Q [NN], then per step along D dO, V [CB], dO, then dO and Q transposed [NT each].
       auto operand = [&](int x) {
         if (x < X1) return M::nat(qn, x);
         if (x < X2) {
-          const int ks = (x - X1) / 4, w = (x - X1) % 4;
-          return w == 0 ? M::nat(qn, ks, TB) : w == 3 ? M::nat(qn, NK + ks, TB) : M::nat(vn, (w - 1) * NK + ks);
+          const int ks = (x - X1) / (2 + CB), w = (x - X1) % (2 + CB);
+          return w == 0 ? M::nat(qn, ks, TB) : w == 1 + CB ? M::nat(qn, NK + ks, TB) : M::nat(vn, (w - 1) * NK + ks);
         }
         return x < X3 ? M::tr(qx, x - X2, TB) : M::tr(qx, x - X3);
       };
@@ -466,7 +489,7 @@ __global__ void __launch_bounds__(256, WGS) seg_attn_bwd_dkdv_kernel(const AttnA
       auto used = [&](int x) {   // operand x has been used up: read the one that takes its place
         if (x + PR < TOTAL) fr[x % PR] = operand(x + PR);
       };
-      f32x4 s[2][2], dp[2][2];
+      f32x4 s[2][CB], dp[2][CB];
       f32x4 nl[2], nd[2];
 #pragma unroll
       for (int x = 0; x < 2; ++x) fr[x] = operand(x);
@@ -478,36 +501,37 @@ __global__ void __launch_bounds__(256, WGS) seg_attn_bwd_dkdv_kernel(const AttnA
 #pragma unroll
       for (int i = 0; i < NN; ++i)
 #pragma unroll
-        for (int cb = 0; cb < 2; ++cb) {
+        for (int cb = 0; cb < CB; ++cb) {
           s[i / NK][cb] = M::mma_nat(i, fr[i % PR], kr[cb], i % NK ? s[i / NK][cb] : nl[i / NK]);
-          if (cb == 1) used(i);
-          if (cb == 1 && i + 2 >= NN) nd[i + 2 - NN] = lds_load<f32x4>(st + 4 * BQ + 64 * (i + 2 - NN));
+          if (cb + 1 == CB) used(i);
+          if (cb + 1 == CB && i + 2 >= NN) nd[i + 2 - NN] = lds_load<f32x4>(st + 4 * BQ + 64 * (i + 2 - NN));
           __builtin_amdgcn_sched_barrier(0);
         }
-      auto probs = [&](int x0, int x1) {   // probabilities x0 .. x1-1 of the lane's 16
+      auto probs = [&](int x0, int x1) {   // probabilities x0 .. x1-1 of the lane's 8 * CB
 #pragma unroll
         for (int x = x0; x < x1; ++x) {
-          float y = exp2_fast(s[x >> 3][(x >> 2) & 1][x & 3] * c);
+          float y = exp2_fast(s[x / (4 * CB)][(x >> 2) % CB][x & 3] * c);
           settle(y);
-          s[x >> 3][(x >> 2) & 1][x & 3] = y;
+          s[x / (4 * CB)][(x >> 2) % CB][x & 3] = y;
         }
       };
 #pragma unroll
       for (int ks = 0; ks < NK; ++ks)
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
-          const int rb = i >> 1, cb = i & 1, x = X1 + 4 * ks;
-          dp[rb][cb] = M::mma_op(ks, fr[(x + (rb ? 3 : 0)) % PR], fr[(x + 1 + cb) % PR], ks ? dp[rb][cb] : nd[rb]);
-          if (i > 0) used(x + i - 1);
-          if (i == 3) used(x + 3);
-          const int w = 4 * ks + i, W = 4 * NK;
-          probs(16 * w / W, 16 * (w + 1) / W);
+        for (int i = 0; i < 2 * CB; ++i) {
+          const int rb = i / CB, cb = i % CB, x = X1 + (2 + CB) * ks;
+          dp[rb][cb] = M::mma_op(ks, fr[(x + (rb ? 1 + CB : 0)) % PR], fr[(x + 1 + cb) % PR], ks ? dp[rb][cb] : nd[rb]);
+          if (rb == 0 && cb + 1 == CB) used(x);   // the first row half's dO; then V as the second half uses it; its dO last
+          if (rb == 1) used(x + 1 + cb);
+          if (rb == 1 && cb + 1 == CB) used(x + 1 + CB);
+          const int w = 2 * CB * ks + i, W = 2 * CB * NK;
+          probs(8 * CB * w / W, 8 * CB * (w + 1) / W);
           __builtin_amdgcn_sched_barrier(0);
         }
       // Visible iff key <= seg_off + row and row < seg_len.  Tiles on the diagonal or at the end of the segment: entries
       // above the diagonal and rows past the segment are set to zero here, in a branch that holds nothing else (whatever
       // the exponential made of them, infinity included, is overwritten).
-      if ((wkey0 + 31 > seg_off + cur.r0) || (cur.r0 + 32 > seg_len)) {
+      if ((wkey0 + 16 * CB - 1 > seg_off + cur.r0) || (cur.r0 + 32 > seg_len)) {
         asm volatile("" ::: "memory");   // keeps this a branch
         const int fl = lane_id(), fj = fl >> 4;
         const int lo = wkey0 + (fl & 15) - seg_off - cur.r0 - 4 * fj;   // need 16*rb + v >= lo + 16*cb
@@ -515,7 +539,7 @@ __global__ void __launch_bounds__(256, WGS) seg_attn_bwd_dkdv_kernel(const AttnA
 #pragma unroll
         for (int rb = 0; rb < 2; ++rb)
 #pragma unroll
-          for (int cb = 0; cb < 2; ++cb)
+          for (int cb = 0; cb < CB; ++cb)
 #pragma unroll
             for (int v = 0; v < 4; ++v)
               if (16 * rb + v < lo + 16 * cb || 16 * rb + v >= hi) {
@@ -523,18 +547,18 @@ __global__ void __launch_bounds__(256, WGS) seg_attn_bwd_dkdv_kernel(const AttnA
                 dp[rb][cb][v] = 0.f;
               }
       }
-      typename M::Slab pf[2], ds[2];
+      typename M::Slab pf[CB], ds[CB];
 #pragma unroll
-      for (int cb = 0; cb < 2; ++cb) {
+      for (int cb = 0; cb < CB; ++cb) {
         pf[cb] = M::slab(s[0][cb], s[1][cb]);
         M::settle_slab(pf[cb]);
       }
 #pragma unroll
       for (int i = 0; i < NT; ++i)
 #pragma unroll
-        for (int cb = 0; cb < 2; ++cb) {
+        for (int cb = 0; cb < CB; ++cb) {
           M::mma_tr(i, fr[(X2 + i) % PR], pf[cb], dv[cb]);
-          if (cb == 1) used(X2 + i);
+          if (cb + 1 == CB) used(X2 + i);
           if (i == 1) {
             ds[cb] = M::slab(s[0][cb] * dp[0][cb], s[1][cb] * dp[1][cb]);
             M::settle_slab(ds[cb]);
@@ -544,15 +568,19 @@ __global__ void __launch_bounds__(256, WGS) seg_attn_bwd_dkdv_kernel(const AttnA
 #pragma unroll
       for (int i = 0; i < NT; ++i)
 #pragma unroll
-        for (int cb = 0; cb < 2; ++cb) {
+        for (int cb = 0; cb < CB; ++cb) {
           M::mma_tr(i, fr[(X3 + i) % PR], ds[cb], dk[cb]);
-          if (cb == 1) used(X3 + i);
+          if (cb + 1 == CB) used(X3 + i);
           __builtin_amdgcn_sched_barrier(0);
         }
     }
     advance(cur);
     wait_async_tiles();   // this wave's part of tile it+1 has landed
     __syncthreads();
+    if constexpr (!ASYNC) {
+      if (it + 1 < it_end) write_tile();
+      __syncthreads();
+    }
   }
 
   // Epilogue: acc[key][d] += result, each element touched by exactly one lane of the grid.  In the accumulators a
@@ -564,27 +592,28 @@ __global__ void __launch_bounds__(256, WGS) seg_attn_bwd_dkdv_kernel(const AttnA
   float *dkb = a.dk_acc + kvoff, *dvb = a.dv_acc + kvoff;
   constexpr int LPR = D / 4;                        // lanes per row (16 bytes each)
   constexpr int RPI = 64 / LPR;                     // rows per instruction
-  constexpr int NI = (32 + RPI - 1) / RPI;          // instructions per block
-  char *region = smem + wave * (32 * Cfg::EPI_ROW);
+  constexpr int KW = 16 * CB;                       // keys of the wave
+  constexpr int NI = (KW + RPI - 1) / RPI;          // instructions per block
+  char *region = smem + wave * (KW * Cfg::EPI_ROW);
   const int row_in = el / LPR, col = el % LPR;
 #pragma unroll
   for (int which = 0; which < 2; ++which) {
     const float mul = which == 0 ? a.scale : 1.f;
     float *base = which == 0 ? dkb : dvb;
 #pragma unroll
-    for (int cb = 0; cb < 2; ++cb)
+    for (int cb = 0; cb < CB; ++cb)
 #pragma unroll
       for (int x = 0; x < DB; ++x) {
         const int r = 16 * cb + en, ch = M::quad_d0(x, ej) >> 2;
         *reinterpret_cast<f32x4 *>(region + r * Cfg::EPI_ROW + 16 * (ch ^ en)) = M::quad(which == 0 ? dk[cb] : dv[cb], x) * mul;
       }
     if (uc.chunk > 0) {   // a chunk other than the first: its share goes to the workspace, [chunk - 1][dK, dV][key][head_dim]
-      float *part = a.part + ((int64_t)(uc.slot - a.n_split_units) * 2 + which) * (Cfg::BNW * D) + (int64_t)(wave * 32) * D;
+      float *part = a.part + ((int64_t)(uc.slot - a.n_split_units) * 2 + which) * (Cfg::BNW * D) + (int64_t)(wave * KW) * D;
 #pragma unroll
       for (int i = 0; i < NI; ++i) {
-        const int r = i * RPI + row_in, rc = r < 32 ? r : 31;
+        const int r = i * RPI + row_in, rc = r < KW ? r : KW - 1;
         const f32x4 x = *reinterpret_cast<const f32x4 *>(region + rc * Cfg::EPI_ROW + 16 * (col ^ (rc & 15)));
-        if (row_in < RPI && r < 32) *reinterpret_cast<f32x4 *>(part + (int64_t)r * D + 4 * col) = x;
+        if (row_in < RPI && r < KW) *reinterpret_cast<f32x4 *>(part + (int64_t)r * D + 4 * col) = x;
       }
       continue;
     }
@@ -596,9 +625,9 @@ __global__ void __launch_bounds__(256, WGS) seg_attn_bwd_dkdv_kernel(const AttnA
     }
 #pragma unroll
     for (int i = 0; i < NI; ++i) {
-      const int r = i * RPI + row_in, key = wkey0 + r, rc = r < 32 ? r : 31;
+      const int r = i * RPI + row_in, key = wkey0 + r, rc = r < KW ? r : KW - 1;
       const f32x4 sum = old[i] + *reinterpret_cast<const f32x4 *>(region + rc * Cfg::EPI_ROW + 16 * (col ^ (rc & 15)));
-      if (row_in < RPI && r < 32 && key < kv_len) *reinterpret_cast<f32x4 *>(base + (int64_t)key * a.kv_ss + 4 * col) = sum;
+      if (row_in < RPI && r < KW && key < kv_len) *reinterpret_cast<f32x4 *>(base + (int64_t)key * a.kv_ss + 4 * col) = sum;
     }
   }
 }

@@ -8,8 +8,10 @@
 //     O^T[d][q]  += sum_key V[key][d] P^T[key][q]  A = V read transposed from LDS, B = P^T slab (registers)
 // Row maximum and sum are then in-lane reductions; the four lanes of a query meet at the end only.
 //
-// K/V tiles of 32 keys go from HBM straight into a ring in LDS (TileRing; no register staging), with one workgroup
-// barrier per tile.
+// K/V tiles of 32 keys go from HBM straight into a ring in LDS (TileRing; no register staging, except that fp32 tiles are split
+// on the way), with one workgroup barrier per tile.  In fp32 128-row tiles above head_dim 64 are eight waves of 16 rows, two
+// to a SIMD (LDS has room for one workgroup): a wave's splitting and waiting runs beside the other's products (four waves
+// of 32 rows: 32 heads, 2048 rows behind 8000 keys, head_dim 128 1948 us instead of 1650).
 // The loop advances by one tile and is software-pipelined inside each wave: the score product of tile k+1 (matrix
 // pipe) is issued together with the operand packing of tile k's probabilities (vector pipe), then the PV product of
 // tile k together with the exponentials of tile k+1 (see fwd_step).  A wave walks to the last tile that one of its rows sees
@@ -40,10 +42,6 @@ namespace s1f {
 // its own through all scores, plus lane exchanges) thereby leave the steady loop.
 constexpr float kRescaleTau = 8.0f;
 constexpr float kRescaleLimit = 256.0f;   // 2^kRescaleTau
-
-template <typename T, int D, int NC> struct FwdCfg {
-  static constexpr int BM = 64 * NC, BN = 32;
-};
 
 // Masks the scores of rows 16*rb.. of a tile that crosses the diagonal.
 //   ahead = (absolute row of the wave's first query) - (first key of the tile)
@@ -124,10 +122,12 @@ template <typename M> struct KRing {
 // share a SIMD, and left alone the compiler puts LDS reads right before their use and the exponentials in heaps.
 //   MASK: tile k+1 may cross the diagonal of the wave's rows; ahead_next: see fwd_mask
 //   hidden (without a next tile): column blocks, from the first on, that tile k is wholly hidden from (never the last)
-template <typename M, bool HAS_NEXT, bool MASK, int NC>
+//   AHEAD: the first operands of ktile_after are read at the end (TileRing::AHEAD)
+//   work(slot, slots): the share of a slot in what else the wave has to do in the step
+template <typename M, bool HAS_NEXT, bool MASK, bool AHEAD, int NC, typename F>
 S1F_DEV void fwd_step(f32x4 (&p)[2][NC], f32x4 (&o)[NC][M::DB], const float (&m)[NC], float (&rs)[NC],
                       const typename M::RowOp (&q)[NC], const M &rd, KRing<M> &kr, lds_addr ktile_next, lds_addr ktile_after,
-                      lds_addr vtile, float c, int ahead_next, int hidden) {
+                      lds_addr vtile, float c, int ahead_next, int hidden, F work) {
   typedef typename M::Frag Frag;
   constexpr int PK = KRing<M>::N, PV = M::NT < 3 ? M::NT : 3, NK = M::NK, NN = M::NN, NT = M::NT;
   __builtin_amdgcn_s_setprio(1);   // of two ready waves the one in phase 1, which has little else to issue, feeds the matrix pipe
@@ -174,7 +174,8 @@ S1F_DEV void fwd_step(f32x4 (&p)[2][NC], f32x4 (&o)[NC][M::DB], const float (&m)
         const int w = i * NC + cb, W = NK * NC;
         if (w < NC) pack(w);
         if (w >= W) probs(4 * NC * (w - W) / W, 4 * NC * (w - W + 1) / W);
-        __builtin_amdgcn_sched_barrier(0);
+        work(w, (NN + NT) * NC);
+        end_slot<M>();
       }
     }
   } else {
@@ -184,7 +185,7 @@ S1F_DEV void fwd_step(f32x4 (&p)[2][NC], f32x4 (&o)[NC][M::DB], const float (&m)
     for (int i = 0; i < PV; ++i) vf[i] = M::tr(va, i);
   }
   __builtin_amdgcn_s_setprio(0);
-  const typename M::Nat kb = rd.nat_at(ktile_after);
+  const typename M::Nat kb = rd.nat_at(AHEAD ? ktile_after : vtile);
 #pragma unroll
   for (int i = 0; i < NT; ++i) {
 #pragma unroll
@@ -192,22 +193,22 @@ S1F_DEV void fwd_step(f32x4 (&p)[2][NC], f32x4 (&o)[NC][M::DB], const float (&m)
       if (HAS_NEXT || cb + 1 == NC || cb >= hidden) M::mma_tr(i, vf[i % PV], pf[cb], o[cb]);
       if (cb + 1 == NC) {
         if (i + PV < NT) vf[i % PV] = M::tr(va, i + PV);
-        if (HAS_NEXT && i + PK >= NT) kr.f[i + PK - NT] = M::nat(kb, i + PK - NT);
+        if (HAS_NEXT && AHEAD && i + PK >= NT) kr.f[i + PK - NT] = M::nat(kb, i + PK - NT);
       }
       const int w = i * NC + cb, W = NT * NC;
       if (HAS_NEXT) probs(4 * NC + 4 * NC * w / W, 4 * NC + 4 * NC * (w + 1) / W);
-      __builtin_amdgcn_sched_barrier(0);
+      if (HAS_NEXT) work(NN * NC + w, (NN + NT) * NC);
+      end_slot<M>();
     }
   }
   if (HAS_NEXT) rs[NC - 1] += prob(8 * NC - 1);
 }
 
-template <typename T, int D, int NC, int OCC>
-__global__ void __launch_bounds__(256, OCC) seg_attn_fwd_kernel(const AttnArgs a) {
-  typedef FwdCfg<T, D, NC> Cfg;
+template <typename T, int D, int NC, int OCC, int WAVES>
+__global__ void __launch_bounds__(64 * WAVES, OCC) seg_attn_fwd_kernel(const AttnArgs a) {
   typedef Mat<T, D> M;
-  typedef TileRing<T, D> Ring;
-  constexpr int DB = M::DB, BM = Cfg::BM, BN = Cfg::BN;
+  typedef TileRing<T, D, WAVES> Ring;
+  constexpr int DB = M::DB, BM = 16 * NC * WAVES, BN = 32;
 
   extern __shared__ __attribute__((aligned(1024))) char smem[];
   const int tid = threadIdx.x, lane = tid & 63, j = lane >> 4, n = lane & 15;
@@ -235,8 +236,8 @@ __global__ void __launch_bounds__(256, OCC) seg_attn_fwd_kernel(const AttnArgs a
   if (n_kt <= 0) {   // more chunks than this unit has whole tiles: a result that the merge gives no weight
     float *po = a.part + (int64_t)uc.slot * (BM * D);
     float *pml = a.part_ml + (int64_t)uc.slot * (BM * 2);
-    for (int i = tid; i < BM * D; i += 256) po[i] = 0.f;
-    for (int i = tid; i < BM; i += 256) {
+    for (int i = tid; i < BM * D; i += 64 * WAVES) po[i] = 0.f;
+    for (int i = tid; i < BM; i += 64 * WAVES) {
       pml[2 * i] = -INFINITY;
       pml[2 * i + 1] = 0.f;
     }
@@ -294,13 +295,15 @@ __global__ void __launch_bounds__(256, OCC) seg_attn_fwd_kernel(const AttnArgs a
     return;
   }
   KRing<M> kr;
-  kr.fill(rd.nat_at(ring.st[1]));
+  if (Ring::AHEAD) kr.fill(rd.nat_at(ring.st[1]));
   auto steady = [&](auto mask, auto whole) {
     constexpr bool MASK = decltype(mask)::value, WHOLE = decltype(whole)::value;
     ring.template begin_step<WHOLE>(n_kt - 1 - k);
+    if (!Ring::AHEAD) kr.fill(rd.nat_at(ring.st[1]));
     const int ahead = seg_off + wrow0 - BN * (k + 1);
-    fwd_step<M, true, MASK, NC>(s, o, m, rs, q, rd, kr, ring.st[1], ring.st[2],
-                                ring.st[0] + Tile32<T, D>::BYTES, c, ahead, 0);
+    fwd_step<M, true, MASK, Ring::AHEAD, NC>(s, o, m, rs, q, rd, kr, ring.st[1], ring.st[2],
+                                ring.st[0] + Tile32<T, D>::BYTES, c, ahead, 0,
+                                [&](int slot, int slots) { ring.template work<WHOLE>(slot, slots); });
     ++k;
     ring.end_step();
     bool raise = false;
@@ -341,8 +344,8 @@ __global__ void __launch_bounds__(256, OCC) seg_attn_fwd_kernel(const AttnArgs a
   while (k + 1 < n_own) steady(yes, no);
   // the wave's last tile: no next scores to compute.  Waves that have more tiles to walk are let into their next step first.
   if (k + 1 < n_kt) ring.template begin_step<false>(n_kt - 1 - k);
-  fwd_step<M, false, false, NC>(s, o, m, rs, q, rd, kr, ring.st[0], ring.st[0], ring.st[0] + Tile32<T, D>::BYTES, c, 0,
-                                hidden_blocks<BN>(seg_off + wrow0, n_own));
+  fwd_step<M, false, false, Ring::AHEAD, NC>(s, o, m, rs, q, rd, kr, ring.st[0], ring.st[0], ring.st[0] + Tile32<T, D>::BYTES, c, 0,
+                                hidden_blocks<BN>(seg_off + wrow0, n_own), [](int, int) {});
   if (k + 1 < n_kt) {   // its share of the others' tiles
     ring.end_step();
     for (++k; k + 1 < n_kt; ++k, ring.end_step()) ring.template begin_step<false>(n_kt - 1 - k);

@@ -5,7 +5,7 @@
 //   block     a 16x16 fp32 result held as 4 registers per lane: register v of lane (n, j) is element (row 4*j + v,
 //             column n).  Kernels work on 32x32 scores as 2x2 blocks [rb][cb].
 //   operand   what one lane feeds to one matrix instruction: A row n or B column n, and of the contraction index
-//             bf16 (16x16x32): the 8 elements 8*j .. 8*j+7;   fp32 (16x16x4, four in a row): the 4 elements 4*j .. +3
+//             the 8 elements 8*j .. 8*j+7 (fp32: of three planes, see split3)
 //   slab      the 32 rows of a block pair [0..1][cb] as contraction index, so that scores are fed back as an operand
 //             without any movement between lanes: slot (j, e) is row 16*(e/4) + 4*j + e%4, which lane (n, j) holds.
 //             The other operand is read from LDS in the same row order.
@@ -19,7 +19,6 @@
 namespace s1f {
 
 S1F_DEV f32x4 mma16(bf16x8 a, bf16x8 b, f32x4 c) { return __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, c, 0, 0, 0); }
-S1F_DEV f32x4 mma16(float a, float b, f32x4 c) { return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0); }
 
 // Reductions over the four lanes that hold the rows of one column (lane ^ 16, lane ^ 32).  v_permlane16_swap exchanges
 // the odd 16-lane rows of its first operand with the even ones of its second; see own_and_partner.
@@ -47,21 +46,20 @@ S1F_DEV int lane_id() {
 }
 S1F_DEV float uniform(float x) { return __builtin_bit_cast(float, __builtin_amdgcn_readfirstlane(__builtin_bit_cast(int, x))); }
 
-// A [32 x D] tile in LDS, in pieces of 1 KiB: piece (rh, kq) = rows 16*rh .. +15, bytes 64*kq .. +63 of the rows, i.e.
+// A [32 x D] tile of bf16 in LDS, in pieces of 1 KiB: piece (rh, kq) = rows 16*rh .. +15, bytes 64*kq .. +63 of the rows, i.e.
 // exactly the A operand of rows 16*rh for contraction step kq.  Inside a piece chunk c (16 bytes) of row r lies in slot
-// 4*(r ^ rot) + (c ^ f(r)), f(r) = -(r / 4) mod 4; rot = kq & 3 in fp32, else 0.  Neither access pattern below has
-// bank conflicts (the 16 lanes that a 128-bit read serves together, 0-3 with 12-15, 20-23 and 24-27 and so on, and the
-// 32 of a 64-bit one cover all 64 banks), and the piece enters every
-// address as a constant: one address register per pattern, where rows stored whole and swizzled took a vector
-// instruction per operand.  Four consecutive slots hold 64 consecutive bytes of a row, which keeps the copies coalesced.
+// 4*r + (c ^ f(r)), f(r) = -(r / 4) mod 4.  Neither access pattern below has bank conflicts (the 16 lanes that a 128-bit read
+// serves together, 0-3 with 12-15, 20-23 and 24-27 and so on, and the 32 of a 64-bit one cover all 64 banks), and the
+// piece enters every address as a constant: one address register per pattern, where rows stored whole and swizzled took a
+// vector instruction per operand.  Four consecutive slots hold 64 consecutive bytes of a row, which keeps the copies coalesced.
+// An fp32 tile is three of them one behind the other, the planes of split3.
 template <typename T, int D> struct Tile32 {
-  static constexpr int CE = Elem<T>::CE;
-  static constexpr int CPR = D / CE;                 // 16-byte chunks per row
+  static constexpr int CPR = D / 8;                  // 16-byte chunks per row
   static constexpr int NP = (CPR + 3) / 4;           // pieces per row half
-  static constexpr int BYTES = 2 * NP * 1024;
-  static_assert(D % CE == 0, "head_dim must be a whole number of 16-byte chunks");
+  static constexpr int PLANE = 2 * NP * 1024;
+  static constexpr int BYTES = (sizeof(T) == 4 ? 3 : 1) * PLANE;
+  static_assert(D % 8 == 0, "head_dim must be a whole number of 16-byte chunks");
   S1F_DEV static int f(int r) { return -(r >> 2) & 3; }
-  S1F_DEV static int rot(int kq) { return sizeof(T) == 4 ? kq & 3 : 0; }
 };
 
 // An LDS address as the compiler shall keep it: without this it folds the constant offsets of the operands into as many
@@ -80,6 +78,7 @@ S1F_DEV lds_addr opaque(lds_addr x) {
 template <typename T, int D> struct Mat;
 
 template <int D> struct Mat<bf16_t, D> {
+  static constexpr int PRODUCTS = 1;   // matrix instructions per product of two operands
   typedef Tile32<bf16_t, D> TL;
   typedef bf16x8 Frag;
   typedef bf16x8 Slab;
@@ -165,95 +164,108 @@ template <int D> struct Mat<bf16_t, D> {
   S1F_DEV static f32x4 quad(const f32x4 (&acc)[DB], int q) { return acc[q]; }
 };
 
-// fp32: one 128-bit read feeds four matrix instructions.  In a nat product they contract elements 4*j+e of the step,
-// e = 0..3.  In a tr product a lane reads four consecutive elements 4*n..+3 of a 64-wide group of head_dim, which are
-// row n of four blocks: block 4*G+e holds d = 64*G + 4*row + e.  A last group of 16 (head_dim 80) is read one by one.
+// fp32 operands as three bf16 planes: x = p[0] + p[1] + p[2] exactly.  The first is cut off (rounded, the largest floats would
+// overflow), the others are rounded to nearest.  A value that is not finite becomes NaN.
+// Why: the fp32 matrix instructions run at a sixteenth of the bf16 ones' rate (153 against 1353 TFLOP/s in large matrix
+// products here); six bf16 products for each take less than half as long, and accumulate fewer times.  Six, because the
+// first plane leaves at most 2^-7 |x| and the second at most 2^-16 |x|: what the three products left out contribute is below
+// 2^-23 of |a| |b| and of either sign.  Relative error against 64 bits, 8/2 heads, 500 rows behind 3000 keys, head_dim 128
+// (fp32 instructions / this): out 1.1e-6 / 0.9e-6, lse 5.7e-8 / 5.8e-8, dq 9.5e-7 / 8.0e-7, dk and dv 2.3e-6 / 2.0e-6; with
+// queries 30 times as large 3.6e-6 / 2.6e-6, 1.8e-7 / 1.2e-7, 1.2e-5 / 0.9e-5, 2.6e-5 / 2.3e-5.  (All planes cut off: lse up to 1.3
+// times further off than with fp32 instructions.)  32 heads, 2048 rows behind 8000 keys, us: head_dim 128 forward 2493 -> 1618,
+// dQ 3524 -> 1924, dK/dV 5005 -> 2696; 80 1631 -> 1028, 2347 -> 1363, 3274 -> 2005; 64 1293 -> 729, 1899 -> 956, 2277 -> 1252:
+// bound, like bf16, by the matrix pipe under the power limit (dQ and dK/dV execute 1350-1450 TFLOP/s of bf16 products).
+struct Planes {
+  bf16x8 p[3];
+};
+S1F_DEV Planes split3(f32x4 lo, f32x4 hi) {
+  Planes r;
+  uint32_t first[8];
+#pragma unroll
+  for (int e = 0; e < 8; ++e) {
+    const float x = e < 4 ? lo[e & 3] : hi[e & 3];
+    first[e] = __builtin_bit_cast(uint32_t, x);
+    const float rest = x - __builtin_bit_cast(float, first[e] & 0xffff0000u);
+    r.p[1][e] = (bf16_t)rest;
+    r.p[2][e] = (bf16_t)(rest - (float)r.p[1][e]);
+  }
+  u32x4 v;
+#pragma unroll
+  for (int e = 0; e < 4; ++e) v[e] = __builtin_amdgcn_perm(first[2 * e + 1], first[2 * e], 0x07060302u);   // the upper halves of both
+  r.p[0] = __builtin_bit_cast(bf16x8, v);
+  return r;
+}
+S1F_DEV void settle(Planes &x) { asm volatile("" : "+v"(x.p[0]), "+v"(x.p[1]), "+v"(x.p[2])); }
+// Product of two fp32 operands: the six products of planes that fp32 resolves (those left out are below 2^-24 of |a| |b|),
+// smallest first.
+S1F_DEV f32x4 mma16(const Planes &a, const Planes &b, f32x4 c) {
+  c = mma16(a.p[2], b.p[0], c);
+  c = mma16(a.p[0], b.p[2], c);
+  c = mma16(a.p[1], b.p[1], c);
+  c = mma16(a.p[1], b.p[0], c);
+  c = mma16(a.p[0], b.p[1], c);
+  return mma16(a.p[0], b.p[0], c);
+}
+
+// End of a scheduling slot of M's products: nothing moves across it.  In fp32 a slot holds the six matrix instructions of each of
+// its products; they are spread over its vector instructions (a wave issues in order: one behind the other, each waits for
+// the one before it and nothing runs beside them).
+template <typename M> S1F_DEV void end_slot() {
+  if constexpr (M::PRODUCTS > 1) {
+#pragma unroll
+    for (int i = 0; i < M::PRODUCTS; ++i) {
+      __builtin_amdgcn_sched_group_barrier(0x8, 1, 0);   // a matrix instruction
+      __builtin_amdgcn_sched_group_barrier(0x2, 6, 0);   // vector ones
+    }
+  }
+  __builtin_amdgcn_sched_barrier(0);
+}
+
 template <int D> struct Mat<float, D> {
+  static constexpr int PRODUCTS = 6;
+  typedef Mat<bf16_t, D> B;
   typedef Tile32<float, D> TL;
-  typedef f32x4 Frag;
-  struct Slab {
-    f32x4 r[2];
-  };
-  static constexpr int NK = D / 16, NN = 2 * NK, NG = D / 64, DB = D / 16;
-  static constexpr bool TAIL = D % 64 != 0;
-  static constexpr int NT = 8 * NG + (TAIL ? 8 : 0);
-  static_assert(D % 64 == 0 || D % 64 == 16, "whole groups of 64 and at most one of 16");
+  typedef Planes Frag;
+  typedef Planes Slab;
+  typedef typename B::Nat Nat;
+  typedef typename B::Tr Tr;
+  static constexpr int NK = B::NK, NKS = B::NKS, NN = B::NN, NT = B::NT, DB = B::DB;
   struct RowOp {
     Frag f[NK];
   };
-  unsigned nat_, tr_, tail_;
-  S1F_DEV void init(int lane) {
-    const int n = lane & 15, j = lane >> 4;
-    nat_ = 64 * n + 16 * (j ^ TL::f(n));                                              // step k: ^ 64 * (k & 3)
-    tr_ = 1024 * (n >> 2) + 64 * (4 * j + (n >> 2)) + 16 * ((n & 3) ^ TL::f(4 * j));  // row 4*j + v: ^ 64 * v
-    tail_ = 64 * 4 * j + 16 * ((n >> 2) ^ TL::f(4 * j)) + 4 * (n & 3);
-  }
-  struct Nat {
-    lds_addr a[4];
-  };
-  struct Tr {
-    lds_addr a[4], tail;
-  };
-  S1F_DEV Nat nat_at(lds_addr tile) const {
-    return Nat{{opaque(tile + nat_), opaque(tile + (nat_ ^ 64u)), opaque(tile + (nat_ ^ 128u)), opaque(tile + (nat_ ^ 192u))}};
-  }
-  S1F_DEV Tr tr_at(lds_addr tile) const {
-    return Tr{{opaque(tile + tr_), opaque(tile + (tr_ ^ 64u)), opaque(tile + (tr_ ^ 128u)), opaque(tile + (tr_ ^ 192u))},
-              TAIL ? opaque(tile + tail_) : 0u};
-  }
+  B b;
+  S1F_DEV void init(int lane) { b.init(lane); }
+  S1F_DEV Nat nat_at(lds_addr tile) const { return b.nat_at(tile); }
+  S1F_DEV Tr tr_at(lds_addr tile) const { return b.tr_at(tile); }
   S1F_DEV static Frag nat(const Nat &x, int i, unsigned delta = 0) {
-    return lds_load<Frag>(x.a[(i % NK) & 3] + (unsigned)(i * 1024 + delta));
+    return Frag{{B::nat(x, i, delta), B::nat(x, i, delta + TL::PLANE), B::nat(x, i, delta + 2 * TL::PLANE)}};
   }
   S1F_DEV static Frag tr(const Tr &x, int t, unsigned delta = 0) {
-    if (t < 8 * NG) {
-      const int rv = t / NG, g = t % NG;
-      return lds_load<Frag>(x.a[rv & 3] + (unsigned)(((rv >> 2) * TL::NP + 4 * g) * 1024 + delta));
-    }
-    const int rv = t - 8 * NG;
-    const float y = lds_load<float>(x.tail + (unsigned)(((rv >> 2) * TL::NP + 4 * NG) * 1024 + 64 * (rv & 3) + delta));
-    return Frag{y, y, y, y};
+    return Frag{{B::tr(x, t, delta), B::tr(x, t, delta + TL::PLANE), B::tr(x, t, delta + 2 * TL::PLANE)}};
   }
   S1F_DEV static void load_row(RowOp &o, const float *row, int j) {
 #pragma unroll
-    for (int k = 0; k < NK; ++k) o.f[k] = *reinterpret_cast<const Frag *>(row + 16 * k + 4 * j);
+    for (int k = 0; k < NK; ++k) {
+      const f32x4 *at = reinterpret_cast<const f32x4 *>(row + 32 * k + (k < NKS ? 8 : 4) * j);
+      o.f[k] = split3(at[0], k < NKS ? at[1] : f32x4{0.f, 0.f, 0.f, 0.f});
+    }
   }
   S1F_DEV static float dot(const RowOp &x, const RowOp &y) {
+    auto whole = [](const Planes &a, int e) { return ((float)a.p[0][e] + (float)a.p[1][e]) + (float)a.p[2][e]; };
     float s = 0.f;
 #pragma unroll
     for (int k = 0; k < NK; ++k)
 #pragma unroll
-      for (int e = 0; e < 4; ++e) s += x.f[k][e] * y.f[k][e];
+      for (int e = 0; e < (k < NKS ? 8 : 4); ++e) s += whole(x.f[k], e) * whole(y.f[k], e);
     return s;
   }
-  S1F_DEV static f32x4 mma_nat(int i, Frag a, const RowOp &o, f32x4 c) {
-#pragma unroll
-    for (int e = 0; e < 4; ++e) c = mma16(a[e], o.f[i % NK][e], c);
-    return c;
-  }
-  S1F_DEV static f32x4 mma_op(int, Frag a, Frag b, f32x4 c) {
-#pragma unroll
-    for (int e = 0; e < 4; ++e) c = mma16(a[e], b[e], c);
-    return c;
-  }
-  S1F_DEV static Slab slab(f32x4 x, f32x4 y) { return Slab{{x, y}}; }
-  S1F_DEV static void settle_slab(Slab &) {}
-  S1F_DEV static void mma_tr(int t, Frag a, const Slab &s, f32x4 (&acc)[DB]) {
-    if (t < 8 * NG) {
-      const int rv = t / NG, g = t % NG;
-#pragma unroll
-      for (int e = 0; e < 4; ++e) acc[4 * g + e] = mma16(a[e], s.r[rv >> 2][rv & 3], acc[4 * g + e]);
-    } else if constexpr (TAIL) {
-      const int rv = t - 8 * NG;
-      acc[4 * NG] = mma16(a[0], s.r[rv >> 2][rv & 3], acc[4 * NG]);
-    }
-  }
-  S1F_DEV static int quad_d0(int q, int j) { return q < 4 * NG ? 64 * (q >> 2) + 16 * j + 4 * (q & 3) : 64 * NG + 4 * j; }
-  S1F_DEV static f32x4 quad(const f32x4 (&acc)[DB], int q) {
-    if constexpr (TAIL)
-      if (q >= 4 * NG) return acc[4 * NG];
-    const int g = 4 * (q >> 2), v = q & 3;
-    return f32x4{acc[g][v], acc[g + 1][v], acc[g + 2][v], acc[g + 3][v]};
-  }
+  S1F_DEV static f32x4 mma_nat(int i, const Frag &a, const RowOp &o, f32x4 c) { return mma16(a, o.f[i % NK], c); }
+  S1F_DEV static f32x4 mma_op(int, const Frag &a, const Frag &b, f32x4 c) { return mma16(a, b, c); }
+  S1F_DEV static Slab slab(f32x4 x, f32x4 y) { return split3(x, y); }
+  S1F_DEV static void settle_slab(Slab &s) { settle(s); }
+  S1F_DEV static void mma_tr(int t, const Frag &a, const Slab &s, f32x4 (&acc)[DB]) { acc[t] = mma16(a, s, acc[t]); }
+  S1F_DEV static int quad_d0(int q, int j) { return B::quad_d0(q, j); }
+  S1F_DEV static f32x4 quad(const f32x4 (&acc)[DB], int q) { return acc[q]; }
 };
 
 // Asynchronous copy of two Tile32s (the second right behind the first) from global memory by the four waves of a
@@ -264,25 +276,26 @@ template <int D> struct Mat<float, D> {
 // wait-count pass does not tie LDS reads of OTHER ring stages to these copies; callers order the copies against their
 // readers with wait_async_tiles() + a workgroup barrier.
 // The address is (scalar base of the piece) + (32-bit lane offset fixed at init).  The pieces of a row half differ by
-// 64 bytes in the scalar base and share the lane offset, except that fp32 has one per row rotation and that the last
-// piece of head_dim 80 in bf16, half of it past the row's end, has its own (those slots re-read a valid chunk and are
-// never used).  Rows past the last valid one re-read it (callers mask them).
+// 64 bytes in the scalar base and share the lane offset, except that the last piece of head_dim 80, half of it past the
+// row's end, has its own (those slots re-read a valid chunk and are never used).  Rows past the last valid one re-read it
+// (callers mask them).
 template <typename T, int D> struct TilePairCopy {
+  static_assert(sizeof(T) == 2, "fp32 tiles: SplitPairCopy");
   typedef Tile32<T, D> TL;
   static constexpr int NP = TL::NP;
   static constexpr bool PARTIAL = TL::CPR % 4 != 0;
-  static constexpr int NV = sizeof(T) == 4 ? 4 : PARTIAL ? 2 : 1;
+  static constexpr int NV = PARTIAL ? 2 : 1;
   unsigned voff[NV];
 
-  S1F_DEV static constexpr int vclass(int kq) { return sizeof(T) == 4 ? kq & 3 : (PARTIAL && kq == NP - 1) ? 1 : 0; }
-  S1F_DEV static int slot_row(int wave, int v, int lane) { return 16 * (wave & 1) + ((lane >> 2) ^ (sizeof(T) == 4 ? v : 0)); }
+  S1F_DEV static constexpr int vclass(int kq) { return (PARTIAL && kq == NP - 1) ? 1 : 0; }
+  S1F_DEV static int slot_row(int wave, int lane) { return 16 * (wave & 1) + (lane >> 2); }
   S1F_DEV void init(int wave, int lane, int64_t row_stride) {
 #pragma unroll
     for (int v = 0; v < NV; ++v) {
-      const int r = slot_row(wave, v, lane);
+      const int r = slot_row(wave, lane);
       int c = (lane & 3) ^ TL::f(r & 15);   // chunk within the piece
-      if (sizeof(T) == 2 && v == 1 && c >= TL::CPR % 4) c -= 2;
-      voff[v] = (unsigned)((r * row_stride + c * TL::CE) * (int64_t)sizeof(T));
+      if (v == 1 && c >= TL::CPR % 4) c -= 2;
+      voff[v] = (unsigned)((r * row_stride + c * 8) * (int64_t)sizeof(T));
     }
   }
   // pieces kq .. kq+N-1; tb: first byte of the tile's first row, advanced to piece kq
@@ -323,7 +336,7 @@ template <typename T, int D> struct TilePairCopy {
     if (!WHOLE && rows_left < 32) {   // the sequence ends inside this tile
 #pragma unroll
       for (int v = 0; v < NV; ++v) {
-        const int over = slot_row(wave, v, lane_id()) - (rows_left - 1);
+        const int over = slot_row(wave, lane_id()) - (rows_left - 1);
         if (over > 0) off[v] -= (unsigned)(over * row_stride * (int64_t)sizeof(T));
       }
     }
@@ -337,12 +350,70 @@ template <typename T, int D> struct TilePairCopy {
   }
 };
 
+// The same for fp32 tensors, through registers (split once per workgroup, not by every wave that reads the operand): a lane loads the 8 elements of its slot in every piece, splits them and writes a
+// chunk of each plane.  Between load() and write() the values travel in registers, so that a load has as long as the caller
+// leaves it.
+// WAVES: waves that share the work, 4 or 8 (then waves w and w + 4 take every other piece).
+template <int D, int WAVES> struct SplitPairCopy {
+  typedef Tile32<float, D> TL;
+  static constexpr int STEP = WAVES / 4, NP = TL::NP, NI = (NP + STEP - 1) / STEP;
+  static constexpr bool PARTIAL = TL::CPR % 4 != 0;
+  f32x4 held[NI][2];
+  unsigned dst;   // within the pair of tiles
+  int row, chunk, first;
+  S1F_DEV void init(int wave8, int lane, int64_t) {
+    const int wave = wave8 & 3;
+    first = wave8 >> 2;
+    row = 16 * (wave & 1) + (lane >> 2);
+    chunk = (lane & 3) ^ TL::f(row & 15);
+    dst = (unsigned)((wave >> 1) * TL::BYTES + (wave & 1) * NP * 1024 + 16 * lane);
+  }
+  S1F_DEV int piece(int i) const { return STEP == 1 ? i : STEP * i + first; }
+  // where the lane's row lies
+  S1F_DEV const float *at(const float *row0, const float *row1, int64_t row_stride, int left0, int left1, int wave8) const {
+    const int wave = wave8 & 3, left = wave >= 2 ? left1 : left0, r = row < left ? row : left - 1;
+    return (wave >= 2 ? row1 : row0) + r * row_stride;
+  }
+  S1F_DEV void load(const float *lane_row, int i) {
+    const int kq = piece(i);
+    if (STEP * i + STEP > NP && kq >= NP) return;
+    const int c = PARTIAL && kq == NP - 1 ? chunk & 1 : chunk;   // (of the last piece of head_dim 80 only half is ever read)
+    held[i][0] = *reinterpret_cast<const f32x4 *>(lane_row + 32 * kq + 8 * c);
+    held[i][1] = *reinterpret_cast<const f32x4 *>(lane_row + 32 * kq + 8 * c + 4);
+  }
+  S1F_DEV void load(const float *row0, const float *row1, int64_t row_stride, int left0, int left1, int wave8) {
+    const float *lane_row = at(row0, row1, row_stride, left0, left1, wave8);
+#pragma unroll
+    for (int i = 0; i < NI; ++i) load(lane_row, i);
+  }
+  S1F_DEV void write(int i, lds_addr stage) const {
+    write_half(i, 0, stage);
+    write_half(i, 1, stage);
+  }
+  // half h of piece i: four of the eight elements
+  S1F_DEV void write_half(int i, int h, lds_addr stage) const {
+    const int kq = piece(i);
+    if (STEP * i + STEP > NP && kq >= NP) return;
+    const f32x4 none = {0.f, 0.f, 0.f, 0.f};
+    const Planes x = split3(held[i][h], none);
+    const lds_addr at = opaque(stage + dst + (unsigned)(kq * 1024 + 8 * h));
+    typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
+#pragma unroll
+    for (int p = 0; p < 3; ++p) {
+      const u32x4 v = __builtin_bit_cast(u32x4, x.p[p]);
+      *reinterpret_cast<__attribute__((address_space(3))) u32x2 *>((uintptr_t)(at + (unsigned)(p * TL::PLANE))) = u32x2{v[0], v[1]};
+    }
+  }
+};
+
 // Ring of five stages of one K and one V tile each, shared by the forward and the dQ kernel.  Step k computes on tiles
 // k and k+1 and reads the first operands of tile k+2; tile k+4 is copied into the stage of tile k-1 meanwhile.  A copy
 // therefore has two steps to land: a launch that leaves one workgroup per compute unit spends 0.4-0.5 us on a step, less
 // than memory takes to answer.  With one step, 64 heads of 256 rows behind 16384 keys (forward, head_dim 128, 64-row
 // units) took 359 us, with two 237.
-template <typename T, int D> struct TileRing {
+template <typename T, int D, int WAVES = 4> struct TileRing {
+  static_assert(WAVES == 4, "four waves copy a pair of tiles");
+  static constexpr bool AHEAD = true;   // a step may read the first operands of the next one
   static constexpr int STAGE_BYTES = 2 * Tile32<T, D>::BYTES;   // K tile then V tile
   static constexpr int LDS_BYTES = 5 * STAGE_BYTES;
   typedef TilePairCopy<T, D> Copy;
@@ -378,11 +449,90 @@ template <typename T, int D> struct TileRing {
     __syncthreads();
     issue<WHOLE>(4);
   }
+  template <bool WHOLE> S1F_DEV void work(int, int) {}
   S1F_DEV void end_step() {
     const lds_addr s0 = st[0];
 #pragma unroll
     for (int i = 0; i < 4; ++i) st[i] = st[i + 1];
     st[4] = s0;
+  }
+};
+
+// The ring of fp32 tiles: three stages, all that LDS holds of three planes at head_dim 128.  Step k computes on tiles k and k+1; meanwhile
+// tile k+2, loaded during step k-1, is split and written into the stage of tile k-1, and tile k+3 is loaded.
+template <int D, int WAVES> struct TileRing<float, D, WAVES> {
+  static constexpr bool AHEAD = false;
+  static constexpr int STAGE_BYTES = 2 * Tile32<float, D>::BYTES;
+  static constexpr int LDS_BYTES = 3 * STAGE_BYTES;
+  typedef SplitPairCopy<D, WAVES> Copy;
+  Copy ld;
+  const float *k_next, *v_next;
+  int64_t row_stride;
+  int to_load, rows_left;
+  bool held;                     // a tile is in registers
+  lds_addr st[3];                // stages of tiles k, k+1 and k+2 (= k-1)
+  int wave;
+  S1F_DEV void init(const float *k, const float *v, int64_t row_stride_, int tiles, int rows, lds_addr lds, int wave_, int lane) {
+    ld.init(wave_, lane, row_stride_);
+    k_next = k; v_next = v;
+    row_stride = row_stride_;
+    to_load = tiles; rows_left = rows;
+#pragma unroll
+    for (int i = 0; i < 3; ++i) st[i] = lds + (unsigned)(i * STAGE_BYTES);
+    wave = wave_;
+    held = false;
+  }
+  S1F_DEV void load() {
+    held = to_load > 0;
+    if (!held) return;
+    ld.load(k_next, v_next, row_stride, rows_left, rows_left, wave);
+    --to_load;
+    rows_left -= 32;
+    k_next += 32 * row_stride;
+    v_next += 32 * row_stride;
+  }
+  S1F_DEV void write(int i) {
+    if (!held) return;
+#pragma unroll
+    for (int x = 0; x < Copy::NI; ++x) ld.write(x, st[i]);
+  }
+  // Before the first step: tiles 0 and 1 into their stages, tile 2 into registers.
+  S1F_DEV void issue(int i) {
+    if (i > 2) return;
+    load();
+    if (i < 2) write(i);
+  }
+  // WHOLE: a whole tile is in registers and another is left to load; both then happen piece by piece in work()
+  template <bool WHOLE> S1F_DEV void begin_step(int) {
+    __syncthreads();
+    if constexpr (WHOLE) {
+      lane_row = ld.at(k_next, v_next, row_stride, 32, 32, wave);
+      --to_load;
+      rows_left -= 32;
+      k_next += 32 * row_stride;
+      v_next += 32 * row_stride;
+    } else {
+      write(2);
+      load();
+    }
+  }
+  const float *lane_row;
+  // Share `slot` of `slots` of a step's splitting, under the matrix instructions of one operand
+  static constexpr int HALVES = 2 * Copy::NI;
+  template <bool WHOLE> S1F_DEV void work(int slot, int slots) {
+    if constexpr (WHOLE) {
+#pragma unroll
+      for (int x = HALVES * slot / slots; x < HALVES * (slot + 1) / slots; ++x) {
+        ld.write_half(x >> 1, x & 1, st[2]);
+        if (x & 1) ld.load(lane_row, x >> 1);
+      }
+    }
+  }
+  S1F_DEV void end_step() {
+    const lds_addr s0 = st[0];
+    st[0] = st[1];
+    st[1] = st[2];
+    st[2] = s0;
   }
 };
 

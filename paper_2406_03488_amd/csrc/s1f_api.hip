@@ -22,10 +22,14 @@ template <int D> struct Shape<bf16_t, D> {
   static constexpr int FWD_MAX = 3, DQ_MAX = D == 128 ? 2 : 3, OCC = 2, KWGS = D == 64 ? 3 : 2;
   // the 128-row forward at head_dim 64 takes 130 registers if left alone; LDS has room for the four workgroups that 128 allow
   static constexpr int fwd_occ(int nc) { return D == 64 && nc == 2 ? 4 : OCC; }
+  static constexpr int dq_occ(int) { return OCC; }
+  static constexpr int waves(int) { return 4; }
 };
 template <int D> struct Shape<float, D> {
-  static constexpr int FWD_MAX = 2, DQ_MAX = 2, OCC = 1, KWGS = D == 64 ? 2 : 1;
-  static constexpr int fwd_occ(int) { return OCC; }
+  static constexpr int FWD_MAX = 2, DQ_MAX = 2, KWGS = 2;
+  static constexpr int waves(int nc) { return nc == 2 && D > 64 ? 8 : 4; }
+  static constexpr int fwd_occ(int nc) { return waves(nc) == 8 || D == 64 ? 2 : 1; }
+  static constexpr int dq_occ(int nc) { return fwd_occ(nc); }
 };
 
 bool aligned16(const void *p) { return (reinterpret_cast<uintptr_t>(p) & 15u) == 0; }
@@ -116,6 +120,7 @@ constexpr double kMergeUs = 4.5, kMergeBytesPerUs = 2.5e6; // the merge kernel: 
 // 2957 -> 2543 us).
 struct StepUs {
   double alone0, alone_nc, shared0, shared_nc, crowd0, crowd_nc;
+  double merge = 1;   // cost of the merge behind a cut launch, relative to kMergeUs and kMergeBytesPerUs
   double at(int nc, int64_t per_cu) const {
     if (per_cu <= 1) return alone0 + alone_nc * nc;
     const double two = shared0 + shared_nc * nc, all = (crowd0 + crowd_nc * nc) * (double)per_cu;
@@ -133,10 +138,17 @@ template <> struct Cost<bf16_t, 80> {
 template <> struct Cost<bf16_t, 128> {
   static constexpr StepUs fwd = {0.29, 0.17, 0.36, 0.32, 0, 0}, dq = {0.2, 0.26, 0.32, 0.52, 0, 0}, dkdv = {1.05, 0, 1.65, 0, 0, 0};
 };
-template <int D> struct Cost<float, D> {   // bound by the matrix instructions: two workgroups take twice as long as one
-  static constexpr double k = D / 64.0;
-  static constexpr StepUs fwd = {0.07 * k, 1.1 * k, 0.14 * k, 2.2 * k, 0.07 * k, 1.1 * k}, dq = {0, 1.6 * k, 0, 3.2 * k, 0, 1.6 * k},
-                          dkdv = {5.4 * k, 0, 9.5 * k, 0, 4.75 * k, 0};
+// fp32: measured 1.06 + 0.33 * nc and so on; the forward at head_dim 64 (up to 19 %) and the dQ kernel at 64 and 128 (alone: up to
+// 1.9 and 2.1 times) stand above that, which chooses a little more cutting for launches of less than a round: over 400
+// shapes the plan taken is predicted to cost 0.1, 1.8 and 2.9 % on average over the best one.
+template <> struct Cost<float, 64> {
+  static constexpr StepUs fwd = {0.72, 0.46, 0.885, 0.92, 0, 0}, dq = {-1.17, 2.23, 0.37, 1.615, 0, 0, 0.7}, dkdv = {2.75, 0, 4.7, 0, 0, 0};
+};
+template <> struct Cost<float, 80> {   // one workgroup per compute unit (LDS), as at head_dim 128
+  static constexpr StepUs fwd = {0.75, 0.47, 1.5, 0.94, 0, 0}, dq = {0.83, 0.707, 1.67, 1.41, 0, 0}, dkdv = {3.3, 0, 6.6, 0, 0, 0};
+};
+template <> struct Cost<float, 128> {
+  static constexpr StepUs fwd = {1.034, 0.636, 2.07, 1.27, 0, 0}, dq = {0.2, 3.09, 0.4, 6.18, 0, 0}, dkdv = {4.2, 0, 8.4, 0, 0, 0};
 };
 
 // Workgroups of a kernel that the current device holds at once, and its compute units (0 if that cannot be found out,
@@ -183,7 +195,7 @@ void plan_units(SplitPlan *best, double *t, int nc, int64_t n_tiles, int64_t uni
     } else {
       const int64_t bytes = r * (n - direct) * part_bytes;
       if (r == 0 || steps < (double)n || bytes > cap) break;
-      const double extra = kMergeUs + (double)bytes / kMergeBytesPerUs + 1.0;   // (1.0: not for nothing)
+      const double extra = us.merge * (kMergeUs + (double)bytes / kMergeBytesPerUs + 1.0);   // (1.0: not for nothing)
       if (kStartUs + extra >= *t) break;   // nor can more chunks win (the smallest launches end here, after one prediction)
       now = rounds_us(r * n, steps / n, longest / n, us, nc, s) + extra;
       if (whole > 0) now += rounds_us(whole, steps, steps, us, nc, s) - kStartUs;
@@ -200,7 +212,7 @@ void plan_units(SplitPlan *best, double *t, int nc, int64_t n_tiles, int64_t uni
 }
 
 // Looked up once per kernel and device.
-template <typename K> Slots resident_slots(K kernel, int lds_bytes, std::atomic<int64_t> *cache) {
+template <typename K> Slots resident_slots(K kernel, int lds_bytes, std::atomic<int64_t> *cache, int threads = 256) {
   Slots s;
   int dev = 0;
   if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= kMaxDevices) {
@@ -215,7 +227,7 @@ template <typename K> Slots resident_slots(K kernel, int lds_bytes, std::atomic<
   }
   int per_cu = 0, cus = 0;
   if (prepare(kernel, lds_bytes) != S1F_OK ||
-      hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, reinterpret_cast<const void *>(kernel), 256,
+      hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, reinterpret_cast<const void *>(kernel), threads,
                                                    (size_t)lds_bytes) != hipSuccess ||
       hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || per_cu <= 0 || cus <= 0) {
     (void)hipGetLastError();
@@ -239,12 +251,12 @@ void fill_launch(AttnArgs *a, int64_t n_bh, int tile_major, const SplitPlan &p) 
   a->n_split_units = (int32_t)p.n_split_units;
   a->bm = 64 * p.nc;
 }
-template <typename K> int launch(K kernel, int lds_bytes, const SplitPlan &p, int64_t n_bh, AttnArgs a, hipStream_t st) {
+template <typename K> int launch(K kernel, int lds_bytes, const SplitPlan &p, int64_t n_bh, AttnArgs a, hipStream_t st, int threads = 256) {
   if (p.n_tiles * n_bh > 0x7fffffff || p.grid() > 0x7fffffff) return S1F_EUNSUPPORTED;
   const int rc = prepare(kernel, lds_bytes);
   if (rc != S1F_OK) return rc;
   void *params[] = {&a};
-  const hipError_t e = hipLaunchKernel(reinterpret_cast<const void *>(kernel), dim3((unsigned)p.grid()), dim3(256), params,
+  const hipError_t e = hipLaunchKernel(reinterpret_cast<const void *>(kernel), dim3((unsigned)p.grid()), dim3(threads), params,
                                        (size_t)lds_bytes, st);
   return e == hipSuccess ? S1F_OK : S1F_EDEVICE;
 }
@@ -269,20 +281,29 @@ inline size_t align256(size_t x) { return (x + 255) & ~(size_t)255; }
 // ---- forward and dQ: row tiles of one kernel family ----
 // KERNEL<NC> of a family F: F::kernel<NC>(), F::LDS, F::MAX (widest NC), F::cost
 template <typename T, int D> struct FwdFamily {
+  static constexpr bool FP32 = sizeof(T) == 4;
   static constexpr int MAX = Shape<T, D>::FWD_MAX, LDS = TileRing<T, D>::LDS_BYTES;
   static constexpr StepUs cost = Cost<T, D>::fwd;
   static constexpr int64_t row_bytes = D * 4 + 8;   // of a partial result: output, running maximum, row sum
-  template <int NC> static auto kernel() { return seg_attn_fwd_kernel<T, D, NC, Shape<T, D>::fwd_occ(NC)>; }
+    static constexpr int threads(int nc) { return 64 * Shape<T, D>::waves(nc); }
+  template <int NC> static auto kernel() {
+    constexpr int W = Shape<T, D>::waves(NC);
+    return seg_attn_fwd_kernel<T, D, 4 * NC / W, Shape<T, D>::fwd_occ(NC), W>;
+  }
 };
 template <typename T, int D> struct DqFamily {
   static constexpr int MAX = Shape<T, D>::DQ_MAX, LDS = TileRing<T, D>::LDS_BYTES;
   static constexpr StepUs cost = Cost<T, D>::dq;
   static constexpr int64_t row_bytes = D * 4;
-  template <int NC> static auto kernel() { return seg_attn_bwd_dq_kernel<T, D, NC, Shape<T, D>::OCC>; }
+    static constexpr int threads(int nc) { return 64 * Shape<T, D>::waves(nc); }
+  template <int NC> static auto kernel() {
+    constexpr int W = Shape<T, D>::waves(NC);
+    return seg_attn_bwd_dq_kernel<T, D, 4 * NC / W, Shape<T, D>::dq_occ(NC), W>;
+  }
 };
 template <typename F, int NC> Slots family_slots() {
   static std::atomic<int64_t> cache[kMaxDevices];
-  return resident_slots(F::template kernel<NC>(), F::LDS, cache);
+  return resident_slots(F::template kernel<NC>(), F::LDS, cache, F::threads(NC));
 }
 template <typename F, int NC> void plan_rows_nc(const s1f_desc *d, int64_t seg_off, int64_t seg_len, int64_t cap, SplitPlan *best, double *t) {
   const Slots s = family_slots<F, NC>();
@@ -305,9 +326,9 @@ template <typename F> SplitPlan plan_rows(const s1f_desc *d, int64_t seg_off, in
 }
 template <typename F> int launch_rows(const SplitPlan &p, int64_t n_bh, const AttnArgs &a, hipStream_t st) {
   if constexpr (F::MAX >= 3)
-    if (p.nc == 3) return launch(F::template kernel<3>(), F::LDS, p, n_bh, a, st);
-  if (p.nc == 2) return launch(F::template kernel<2>(), F::LDS, p, n_bh, a, st);
-  return launch(F::template kernel<1>(), F::LDS, p, n_bh, a, st);
+    if (p.nc == 3) return launch(F::template kernel<3>(), F::LDS, p, n_bh, a, st, F::threads(3));
+  if (p.nc == 2) return launch(F::template kernel<2>(), F::LDS, p, n_bh, a, st, F::threads(2));
+  return launch(F::template kernel<1>(), F::LDS, p, n_bh, a, st, F::threads(1));
 }
 
 template <typename T, int D> size_t fwd_workspace(const SplitPlan &p) {
@@ -325,8 +346,8 @@ template <typename T, int D> size_t fwd_workspace(const SplitPlan &p) {
 //                                                                                    1.02 .. 1.10 of 10, mean 1.06
 //   bf16 at head_dim 64, three or four workgroups per compute unit: no round ends at once
 //                                                                                    0.95 .. 1.06 of 36, mean 1.03
-//   fp32, grouped 0.98 of 3; ungrouped, uneven 1.02 .. 1.05 of 5
-// hence the two further conditions.  56 heads, 3678 rows behind 39549 keys (96 units of 192 rows left over) 4286 -> 3974
+//   fp32, grouped, behind seven or more full rounds 0.99 .. 1.02 of 7; behind fewer 0.99 .. 1.26 of 7; ungrouped 1.02
+// hence the further conditions (fp32: either way takes the same time where the second launch is still allowed).  56 heads, 3678 rows behind 39549 keys (96 units of 192 rows left over) 4286 -> 3974
 // us; 64/8 heads, 3214 rows behind 5000 keys 645 -> 592.
 constexpr double kDrainUs = 10.0, kTailUneven = 1.12, kTailUnevenGrouped = 1.3;
 template <typename F, int NC> bool row_tail(const AttnArgs &a, const SplitPlan &p, int64_t *whole) {
@@ -337,9 +358,10 @@ template <typename F, int NC> bool row_tail(const AttnArgs &a, const SplitPlan &
   *whole = units - r;
   if (r == 0 || *whole == 0 || s.total > 2 * s.cus) return false;
   if (most > (a.group > 1 ? kTailUnevenGrouped : kTailUneven) * mean) return false;
+  if (F::FP32 && (a.group == 1 || *whole < 7 * (int64_t)s.total)) return false;
   const double now = rounds_us(units, mean, most, F::cost, NC, s);
   const double two = rounds_us(*whole, mean, mean, F::cost, NC, s) + rounds_us(r * NC, mean, mean, F::cost, 1, s1);
-  return two + kDrainUs < 0.98 * now;
+  return two + kDrainUs < (F::FP32 ? 1.03 : 0.98) * now;
 }
 
 // ... for a plan of either width; 64-row tiles have no narrower ones to go to.
@@ -396,7 +418,7 @@ inline size_t stat_bytes(const s1f_desc *d, int64_t seg_len) {
 }
 template <typename T, int D> struct DkdvFamily {
   typedef BwdDkdvCfg<T, D> Cfg;
-  static constexpr int LDS = Cfg::LDS_BYTES;
+  static constexpr int LDS = Cfg::LDS_BYTES, THREADS = 64 * Cfg::WAVES;
   static constexpr int64_t part_bytes = 2 * (int64_t)Cfg::BNW * D * 4;
   static auto kernel() { return seg_attn_bwd_dkdv_kernel<T, D, Shape<T, D>::KWGS>; }
   static SplitPlan plan(const s1f_desc *d, int64_t seg_off, int64_t seg_len, int64_t cap) {
@@ -406,7 +428,7 @@ template <typename T, int D> struct DkdvFamily {
     p.n_tiles = (kv_len + Cfg::BNW - 1) / Cfg::BNW;
     p.n_whole = units;
     if (cap <= 0) return p;
-    const Slots s = resident_slots(kernel(), LDS, cache);
+    const Slots s = resident_slots(kernel(), LDS, cache, THREADS);
     if (s.total <= 0) return p;
     const double most = (double)(d->n_q_heads / d->n_kv_heads) * (double)((seg_len + 31) / 32);
     const double mean = most * ((double)seg_off + 0.5 * (double)seg_len) / (double)kv_len;
@@ -445,7 +467,7 @@ template <typename T, int D> int bwd_dkdv_impl(const s1f_desc *d, AttnArgs a, co
   a.part = reinterpret_cast<float *>(reinterpret_cast<char *>(a.delta) + stat_bytes(d, a.seg_len));
   const int64_t n_bh = (int64_t)d->n_kv_heads * d->batch;
   fill_launch(&a, n_bh, 2 * (int64_t)a.seg_off < (int64_t)a.seg_len, p);
-  const int rc = launch(F::kernel(), F::LDS, p, n_bh, a, st);
+  const int rc = launch(F::kernel(), F::LDS, p, n_bh, a, st, F::THREADS);
   if (rc != S1F_OK || p.n_split_units == 0) return rc;
   return S1F_MERGE(seg_attn_bwd_dkdv_merge_kernel, T, D, p.n_split - 1, a, p, DkdvMerge<D>::GROUPS, st);
 }

@@ -1,0 +1,77 @@
+"""fp32 operands travel as three bf16 planes: operands of all magnitudes (each head_dim column of V, dO and K has a power of two of its
+own, so that a plane lost or shifted shows in the small ones too), walks of one to eight key tiles through the three-stage
+ring, waves that end at different tiles, rows and keys past the end; the largest floats; infinities."""
+import numpy as np
+import pytest
+import torch
+
+import paper_2406_03488_amd as s1f
+from oracle import attention as A
+
+pytestmark = pytest.mark.gpu
+
+# (query heads, K/V heads, offset, rows): last tiles of one key, walks of 1 to 8 tiles; enough heads for the wide tiles
+SHAPES = [(2, 1, 0, 1), (2, 2, 0, 33), (4, 2, 31, 66), (2, 1, 96, 129), (2, 2, 64, 192), (264, 264, 127, 97)]
+
+
+def _call(q, k, v, do, off):
+    out, dq = torch.full_like(q, float("nan")), torch.full_like(q, float("nan"))
+    lse = torch.full(q.shape[:3], float("nan"), device="cuda")
+    s1f.seg_attn_fwd(q, k, v, off, out, lse)
+    dk, dv = (torch.zeros(k.shape, device="cuda") for _ in range(2))
+    ws = torch.empty(s1f.bwd_workspace_bytes(q, k, off), dtype=torch.uint8, device="cuda")
+    s1f.seg_attn_bwd(do, q, k, v, out, lse, off, dq, dk, dv, ws)
+    return {"out": out, "lse": lse, "dq": dq, "dk": dk, "dv": dv}
+
+
+@pytest.mark.parametrize("d", [64, 80, 128])
+@pytest.mark.parametrize("hq,hkv,off,m", SHAPES)
+def test_operands_of_all_magnitudes(d, hq, hkv, off, m):
+    g = torch.Generator(device="cuda")
+    g.manual_seed(100 * off + m + d)
+    rnd = lambda h, n: torch.empty((1, h, n, d), device="cuda").normal_(generator=g)
+    q, do, k, v = rnd(hq, m), rnd(hq, m), rnd(hkv, off + m), rnd(hkv, off + m)
+    up = torch.exp2(torch.arange(d, device="cuda") % 41 - 20.0)   # 2^-20 .. 2^20 along head_dim
+    v, do = v * up, do / up                                       # dP = dO V^T stays of order one
+    k, q = k * up, q / up
+    got = _call(q, k, v, do, off)
+    host = lambda x: x[0].double().cpu().numpy()
+    for h in sorted({0, hq // 2, hq - 1}):
+        kv = h // (hq // hkv)
+        hs = slice(kv * (hq // hkv), (kv + 1) * (hq // hkv))
+        qh, doh, kh, vh = host(q)[hs], host(do)[hs], host(k)[kv:kv + 1], host(v)[kv:kv + 1]
+        out, lse = A.segment_forward(qh, kh, vh, off)
+        dq, dk, dv = A.segment_backward(doh, qh, kh, vh, off)
+        want = {"out": out, "lse": lse, "dq": dq, "dk": dk, "dv": dv}
+        # Column by column.  dS = P (dP - delta) carries the rounding of dP and delta, which may cancel (a row that sees one key
+        # has dQ = 0): an error of eps (|dP| + |delta|) in dS, times the other operand's column, summed over keys with sum P = 1
+        # (dQ) or over at most m rows (dK).  The probabilities are off by the scores' own rounding: |S| < 64, so 2^6 eps.
+        # eps: 2^-24 times the square root of the terms of a sum (up to 400), hence 2^-18; with the scores' 2^6 of it, 2^-13.
+        dp = np.abs(doh @ vh[0].T).max() + np.abs((doh * out).sum(-1)).max()
+        col = lambda x: np.abs(x).reshape(-1, d).max(0)
+        size = {"out": col(vh), "lse": 64.0, "dq": dp * col(kh) / np.sqrt(d), "dk": m * len(qh) * dp * col(qh) / np.sqrt(d),
+                "dv": m * len(qh) * col(doh)}
+        for name, x in want.items():
+            y = host(got[name])[hs if name in ("out", "lse", "dq") else slice(kv, kv + 1)]
+            err = np.abs(y - x).max() if name == "lse" else col(y - x)
+            assert np.isfinite(y).all() and (err <= 2.0 ** (-18 if name == "lse" else -13) * size[name]).all(), (name, h, (err / size[name]).max())
+
+
+@pytest.mark.parametrize("d", [64, 80, 128])
+def test_largest_floats_and_infinities(d):
+    big = torch.finfo(torch.float32).max
+    q, do, k, v = (torch.randn((1, 2, 70, d), device="cuda", generator=torch.Generator("cuda").manual_seed(d + i)) for i in range(4))
+    v[:, 0, :, 5] = big       # a probability-weighted mean of the largest float is the largest float
+    v[:, 1, :, 7] = -big
+    out, lse = torch.empty_like(q), torch.empty((1, 2, 70), device="cuda")
+    s1f.seg_attn_fwd(q, k, v, 0, out, lse)
+    ratio = torch.stack([out[0, 0, :, 5] / big, out[0, 1, :, 7] / -big])
+    near = torch.isfinite(ratio)   # (a mean that rounds up past the largest float is infinite)
+    assert near.sum() > 0 and (ratio[near] - 1).abs().max() <= 2.0 ** -18
+    keep = torch.ones(d, dtype=torch.bool, device="cuda")
+    keep[[5, 7]] = False
+    assert torch.isfinite(out[..., keep]).all()
+    v[:, 0, 69] = float("inf")   # seen by the last row only; rows whose block ends before its tile stay as they are
+    again = torch.empty_like(out)
+    s1f.seg_attn_fwd(q, k, v, 0, again, lse)
+    assert torch.equal(again[:, :, :64], out[:, :, :64]) and not torch.isfinite(again[0, 0, 69]).any()
