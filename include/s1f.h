@@ -155,11 +155,12 @@ size_t s1f_fwd_workspace_bytes(const s1f_desc *desc, int64_t seg_off, int64_t se
  *             [seg_off, seg_off+seg_len) hold final gradients.
  *   workspace device scratch of at least s1f_bwd_workspace_bytes(desc, seg_off, seg_len) bytes
  *             (two fp32 values per query row and head: -lse/scale and -rowsum(dout * out), the row
- *             statistics the dK/dV kernel starts its products from; behind them up to 512 MiB of partial dQ
- *             rows when the dQ kernel cuts its last row tiles into chunks along the keys, as
- *             s1f_seg_attn_fwd_ws does, and, once those have been merged, up to 32 MiB of partial dK/dV when the
- *             last key tiles of that launch are cut along the queries); contents are undefined afterwards.
- *             An fp32 call accepts any workspace that holds the statistics and then runs uncut.
+ *             statistics the dK/dV half starts its products from; behind them up to 512 MiB of partial dQ
+ *             rows when the dQ half cuts its last row tiles into chunks along the keys, as
+ *             s1f_seg_attn_fwd_ws does, and up to 32 MiB of partial dK/dV when the last key tiles of that half are
+ *             cut along the queries); contents are undefined afterwards.  The halves run in one launch where that is
+ *             faster; a workspace that holds the partial results of only one of them at a time is accepted as well, and
+ *             they then run one after the other, with the same results.  An fp32 call accepts any workspace that holds the statistics and then runs uncut.
  * Errors as above, plus S1F_EINVAL if workspace is NULL or workspace_bytes is too small, and
  * S1F_EUNSUPPORTED if batch * n_q_heads * seg_len > 2^28 (the kernels' asynchronous copies use 32-bit byte
  * offsets inside the workspace). */
@@ -195,7 +196,7 @@ size_t s1f_bwd_workspace_bytes(const s1f_desc *desc, int64_t seg_off, int64_t se
  * (an fp32 call with a smaller one runs uncut and adds in another order), dQ identical up to the order of its sums (the
  * built-in scratch leaves room for 32 MiB of partial dQ rows, s1f_seg_attn_bwd's workspace for 512 MiB, so the
  * two may cut that launch differently); the scratch is a device array built into the
- * library (48 MiB per GPU: 16 MiB of row statistics and 32 MiB of partial results; held until the process ends)
+ * library (80 MiB per GPU: 16 MiB of row statistics and 32 MiB of partial results of either half; held until the process ends)
  * instead of a caller-owned workspace.  The call
  * allocates nothing and frees nothing.
  *   Limit: batch * n_q_heads * seg_len <= s1f_static_scratch_rows() (2^21); beyond it the call returns

@@ -2,14 +2,16 @@
 //   p_ij = exp(s_ij - lse_i),  delta_i = dO_i . O_i,  dp_ij = dO_i . v_j,  ds_ij = p_ij (dp_ij - delta_i)
 //   dq_i = scale * sum_j ds_ij k_j      dk_j += scale * sum_i ds_ij q_i      dv_j += sum_i p_ij dO_i
 //
-// Two kernels, neither uses atomics:
-//   seg_attn_bwd_dq_kernel    owns query rows (same decomposition as the forward), loops over key tiles,
-//                             also writes delta for the second kernel;
-//   seg_attn_bwd_dkdv_kernel  owns key rows, loops over the query heads of its K/V group and over the
-//                             segment's query tiles, and adds its result into the fp32 prefix accumulators
-//                             (each accumulator element is touched by exactly one lane of one workgroup).
+// Two bodies, neither uses atomics:
+//   bwd_dq_body    owns query rows (same decomposition as the forward), loops over key tiles, and, by itself, first computes
+//                  the row statistics of the other;
+//   bwd_dkdv_body  owns key rows, loops over the query heads of its K/V group and over the
+//                  segment's query tiles, and adds its result into the fp32 prefix accumulators
+//                  (each accumulator element is touched by exactly one lane of one workgroup).
 // The probabilities are recomputed in both (7 matrix products in total instead of 5) in exchange for
-// deterministic sums and no dQ workspace.
+// deterministic sums and no dQ workspace.  seg_attn_bwd_dq_kernel and
+// seg_attn_bwd_dkdv_kernel run one of them; seg_attn_bwd_kernel runs the units of both in one launch, behind
+// seg_attn_bwd_stats_kernel, which then computes the row statistics.
 #pragma once
 #include <type_traits>
 
@@ -17,6 +19,36 @@
 
 
 namespace s1f {
+
+// Row statistics of 16 rows, one per lane in row order: lane (n, j) returns -lse and -delta = -rowsum(dO * O) of row n and,
+// with `write`, leaves -lse/scale and -delta in the two planes of the workspace.  dor: the rows of dO
+template <typename T, int D>
+S1F_DEV void bwd_row_stats(const AttnArgs &a, const typename Mat<T, D>::RowOp &dor, int64_t off, int64_t at, bool write, int j, float &nlse,
+                           float &nd) {
+  typedef Mat<T, D> M;
+  typename M::RowOp o;
+  M::load_row(o, reinterpret_cast<const T *>(a.out) + off, j);
+  nd = -sum_over_rows(M::dot(dor, o));
+  const float lse = a.lse[at];
+  nlse = -lse;
+  if (write && j == 0) {
+    a.delta[at] = -lse / a.scale;
+    a.delta[a.ws_plane + at] = nd;
+  }
+}
+// ... of all rows, for halves of the backward that run in one launch: a wave per 16 rows of one (batch, head).  The same sums as
+// in the dQ kernel's own prologue.  Bound by its launch (3 us of small calls) or by memory (67 MB of out and dout: 15 us).
+template <typename T, int D> __global__ void __launch_bounds__(256) seg_attn_bwd_stats_kernel(const AttnArgs a) {
+  typedef Mat<T, D> M;
+  const int groups = (a.seg_len + 63) / 64, bh = (int)blockIdx.x / groups, lane = threadIdx.x & 63, j = lane >> 4;
+  const int r = ((int)blockIdx.x - bh * groups) * 64 + ((int)threadIdx.x >> 6) * 16 + (lane & 15), rc = r < a.seg_len ? r : a.seg_len - 1;
+  const int h = bh % a.n_q_heads, b = bh / a.n_q_heads;
+  const int64_t off = b * a.q_sb + h * a.q_sh + (int64_t)rc * a.q_ss;
+  typename M::RowOp dor;
+  M::load_row(dor, reinterpret_cast<const T *>(a.dout) + off, j);
+  float nlse, nd;
+  bwd_row_stats<T, D>(a, dor, off, (int64_t)bh * a.seg_len + rc, r < a.seg_len, j, nlse, nd);
+}
 
 // One workgroup (4 waves) owns 64*NC query rows of one head, a wave NC column blocks of 16; lane = one query per column
 // block, keys run over registers.
@@ -37,8 +69,9 @@ namespace s1f {
 // registers, which the vector phases reach by copies only.
 template <typename T, int D> constexpr int kDqRing = sizeof(T) == 2 ? 4 : D == 64 ? 2 : 3;   // (fp32: three registers for one)
 
-template <typename T, int D, int NC, int OCC, int WAVES>
-__global__ void __launch_bounds__(64 * WAVES, OCC) seg_attn_bwd_dq_kernel(const AttnArgs a) {
+// id: number of the workgroup among those of this half; smem: TileRing::LDS_BYTES
+// STATS: computes the row statistics and leaves them for the dK/dV half, instead of reading them
+template <typename T, int D, int NC, int WAVES, bool STATS> S1F_DEV void bwd_dq_body(const AttnArgs &a, int id, char *smem) {
   typedef Mat<T, D> M;
   typedef typename M::Frag Frag;
   typedef TileRing<T, D, WAVES> Ring;
@@ -46,10 +79,9 @@ __global__ void __launch_bounds__(64 * WAVES, OCC) seg_attn_bwd_dq_kernel(const 
   constexpr int TOTAL = NN + NT + NN;
   static_assert(NN >= PR && NT >= PR, "operand ring deeper than a product");
 
-  extern __shared__ __attribute__((aligned(1024))) char smem[];
   const int tid = threadIdx.x, lane = tid & 63, j = lane >> 4, n = lane & 15;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const UnitChunk uc = split_unit(blockIdx.x, a.n_whole, a.n_split, a.n_split_units);
+  const UnitChunk uc = split_unit(id, a.n_whole, a.n_split, a.n_split_units);
   int qt, bh;
   decode_workgroup(uc.unit, a.n_tiles, a.n_bh, a.tile_major, qt, bh);
   qt = a.n_tiles - 1 - qt;   // later (heavier) row tiles are scheduled first
@@ -81,17 +113,16 @@ __global__ void __launch_bounds__(64 * WAVES, OCC) seg_attn_bwd_dq_kernel(const 
     const int64_t off = qoff + (int64_t)rc * a.q_ss;
     M::load_row(q[cb], reinterpret_cast<const T *>(a.q) + off, j);
     M::load_row(dor[cb], reinterpret_cast<const T *>(a.dout) + off, j);
-    typename M::RowOp o;
-    M::load_row(o, reinterpret_cast<const T *>(a.out) + off, j);
-    const float d = -sum_over_rows(M::dot(dor[cb], o));
-    nd[cb] = f32x4{d, d, d, d};
     const int64_t at = ((int64_t)b * a.n_q_heads + h) * seg_len + rc;
-    const float lse = a.lse[at];
-    nl[cb] = -lse * kLog2e;
-    if (r < seg_len && j == 0 && uc.chunk == 0) {   // row statistics for the dK/dV kernel
-      a.delta[at] = -lse / a.scale;
-      a.delta[a.ws_plane + at] = d;
+    float nlse, d;
+    if constexpr (STATS) {
+      bwd_row_stats<T, D>(a, dor[cb], off, at, r < seg_len && uc.chunk == 0, j, nlse, d);
+    } else {
+      nlse = -a.lse[at];
+      d = a.delta[a.ws_plane + at];
     }
+    nd[cb] = f32x4{d, d, d, d};
+    nl[cb] = nlse * kLog2e;
   }
   f32x4 dq[NC][DB];
 #pragma unroll
@@ -284,13 +315,12 @@ __global__ void __launch_bounds__(64 * WAVES, OCC) seg_attn_bwd_dq_kernel(const 
   }
 }
 
-// Sums the chunks of the units that seg_attn_bwd_dq_kernel cut along the keys: dq = scale * sum_c part_c.
+// Sums the chunks of the units that were cut along the keys: dq = scale * sum_c part_c.
 // Thread and grid layout as in seg_attn_fwd_merge_kernel.
-template <typename T, int D, int MC>
-__global__ void __launch_bounds__(256) seg_attn_bwd_dq_merge_kernel(const AttnArgs a) {
+template <typename T, int D, int MC> S1F_DEV void bwd_dq_merge_body(const AttnArgs &a, int id) {
   constexpr int C4 = D / 4, RG = 256 / C4;
   const int BM = a.bm, GROUPS = (BM + RG - 1) / RG;
-  const int unit = (int)blockIdx.x / GROUPS, rg = (int)blockIdx.x % GROUPS;
+  const int unit = id / GROUPS, rg = id % GROUPS;
   const int rl = rg * RG + (int)threadIdx.x / C4, c4 = (int)threadIdx.x % C4;
   int qt, bh;
   decode_workgroup(a.n_whole + unit, a.n_tiles, a.n_bh, a.tile_major, qt, bh);
@@ -351,8 +381,8 @@ template <typename T, int D> struct BwdDkdvCfg {
 // 12 % slower.
 template <typename T> constexpr int kDkdvRing = sizeof(T) == 4 ? 3 : 4;   // (fp32: three registers for one)
 
-template <typename T, int D, int WGS>   // WGS: waves meant to share a SIMD
-__global__ void __launch_bounds__((64 * BwdDkdvCfg<T, D>::WAVES), WGS) seg_attn_bwd_dkdv_kernel(const AttnArgs a) {
+// id: number of the workgroup among those of this half; smem: BwdDkdvCfg::LDS_BYTES
+template <typename T, int D> S1F_DEV void bwd_dkdv_body(const AttnArgs &a, int id, char *smem) {
   typedef BwdDkdvCfg<T, D> Cfg;
   typedef Mat<T, D> M;
   typedef typename M::Frag Frag;
@@ -361,10 +391,9 @@ __global__ void __launch_bounds__((64 * BwdDkdvCfg<T, D>::WAVES), WGS) seg_attn_
   constexpr int DB = M::DB, BQ = Cfg::BQ, NN = M::NN, NK = M::NK, NT = M::NT, PR = kDkdvRing<T>, CB = Cfg::CB;
   constexpr int TB = Tile32<T, D>::BYTES, X1 = NN, X2 = X1 + (2 + CB) * NK, X3 = X2 + NT, TOTAL = X3 + NT;
 
-  extern __shared__ __attribute__((aligned(1024))) char smem[];
   const int tid = threadIdx.x, lane = tid & 63, j = lane >> 4, n = lane & 15;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const UnitChunk uc = split_unit(blockIdx.x, a.n_whole, a.n_split, a.n_split_units);
+  const UnitChunk uc = split_unit(id, a.n_whole, a.n_split, a.n_split_units);
   int kt, bh;
   decode_workgroup(uc.unit, a.n_tiles, a.n_bh, a.tile_major, kt, bh);   // early key tiles see every query row: heaviest first
   const int n_kv_heads = a.n_q_heads / a.group;
@@ -632,7 +661,7 @@ __global__ void __launch_bounds__((64 * BwdDkdvCfg<T, D>::WAVES), WGS) seg_attn_
   }
 }
 
-// Adds the chunks of the units that seg_attn_bwd_dkdv_kernel cut along the queries into the accumulators, which chunk
+// Adds the chunks of the units that were cut along the queries into the accumulators, which chunk
 // 0 has updated itself: acc += sum_c part_c, c = 1 .. n_split - 1, in the order of the chunks.  A thread handles 4
 // consecutive head_dim elements of one key of one of the two accumulators (grid: split units x DkdvMerge<D>::GROUPS).
 template <int D> struct DkdvMerge {
@@ -640,9 +669,9 @@ template <int D> struct DkdvMerge {
   static constexpr int GROUPS = 2 * PER / 256;
   static_assert(PER % 256 == 0, "whole workgroups per accumulator");
 };
-template <typename T, int D, int MC> __global__ void __launch_bounds__(256) seg_attn_bwd_dkdv_merge_kernel(const AttnArgs a) {
+template <typename T, int D, int MC> S1F_DEV void bwd_dkdv_merge_body(const AttnArgs &a, int id) {
   typedef DkdvMerge<D> DM;
-  const int unit = (int)blockIdx.x / DM::GROUPS, g = (int)blockIdx.x % DM::GROUPS;
+  const int unit = id / DM::GROUPS, g = id % DM::GROUPS;
   const int which = g / (DM::GROUPS / 2), t = (g % (DM::GROUPS / 2)) * 256 + (int)threadIdx.x;
   int kt, bh;
   decode_workgroup(a.n_whole + unit, a.n_tiles, a.n_bh, a.tile_major, kt, bh);
@@ -662,6 +691,35 @@ template <typename T, int D, int MC> __global__ void __launch_bounds__(256) seg_
   for (int c = 1; c < MC; ++c)
     if (c < S) sum += pc[c];
   *reinterpret_cast<f32x4 *>(acc) = *reinterpret_cast<const f32x4 *>(acc) + sum;
+}
+
+// ---- the kernels: one half by itself, and both ----
+template <typename T, int D, int NC, int OCC, int WAVES>
+__global__ void __launch_bounds__(64 * WAVES, OCC) seg_attn_bwd_dq_kernel(const AttnArgs a) {
+  extern __shared__ __attribute__((aligned(1024))) char smem[];
+  bwd_dq_body<T, D, NC, WAVES, true>(a, blockIdx.x, smem);
+}
+template <typename T, int D, int WGS>   // WGS: waves meant to share a SIMD
+__global__ void __launch_bounds__((64 * BwdDkdvCfg<T, D>::WAVES), WGS) seg_attn_bwd_dkdv_kernel(const AttnArgs a) {
+  extern __shared__ __attribute__((aligned(1024))) char smem[];
+  bwd_dkdv_body<T, D>(a, blockIdx.x, smem);
+}
+// Both halves in one launch, first `first` workgroups of the one with the longer units, then those of the other: small calls,
+// chains of launches that each leave most of the chip idle, get shorter by one, and the last round of the first half
+// is filled by units of the second.
+template <typename T, int D, int NC, int OCC, int WAVES>
+__global__ void __launch_bounds__(64 * WAVES, OCC) seg_attn_bwd_kernel(const AttnArgs aq, const AttnArgs ak, int first, int dq_first) {
+  static_assert(WAVES == BwdDkdvCfg<T, D>::WAVES, "both halves run in workgroups of one size");
+  extern __shared__ __attribute__((aligned(1024))) char smem[];
+  const int id = blockIdx.x < first ? blockIdx.x : blockIdx.x - first;
+  if ((blockIdx.x < first) == (dq_first != 0)) bwd_dq_body<T, D, NC, WAVES, false>(aq, id, smem);
+  else bwd_dkdv_body<T, D>(ak, id, smem);
+}
+// The merges of either half or both: `q_groups` workgroups of the dQ half, then those of the dK/dV half.
+template <typename T, int D, int MC>
+__global__ void __launch_bounds__(256) seg_attn_bwd_merge_kernel(const AttnArgs aq, const AttnArgs ak, int q_groups) {
+  if (blockIdx.x < q_groups) bwd_dq_merge_body<T, D, MC>(aq, blockIdx.x);
+  else bwd_dkdv_merge_body<T, D, MC>(ak, blockIdx.x - q_groups);
 }
 
 }  // namespace s1f

@@ -24,12 +24,17 @@ template <int D> struct Shape<bf16_t, D> {
   static constexpr int fwd_occ(int nc) { return D == 64 && nc == 2 ? 4 : OCC; }
   static constexpr int dq_occ(int) { return OCC; }
   static constexpr int waves(int) { return 4; }
+  // both halves of the backward in one launch: as many workgroups per compute unit as the dK/dV kernel has alone
+  static constexpr int BOTH_OCC = KWGS;
+  static constexpr bool both(int nc) { return nc <= (D == 64 ? 2 : DQ_MAX); }
 };
 template <int D> struct Shape<float, D> {
   static constexpr int FWD_MAX = 2, DQ_MAX = 2, KWGS = 2;
   static constexpr int waves(int nc) { return nc == 2 && D > 64 ? 8 : 4; }
   static constexpr int fwd_occ(int nc) { return waves(nc) == 8 || D == 64 ? 2 : 1; }
   static constexpr int dq_occ(int nc) { return fwd_occ(nc); }
+  static constexpr int BOTH_OCC = 2;
+  static constexpr bool both(int nc) { return nc <= DQ_MAX && (D == 64 || waves(nc) == 8); }   // (workgroups of the dK/dV kernel's size)
 };
 
 bool aligned16(const void *p) { return (reinterpret_cast<uintptr_t>(p) & 15u) == 0; }
@@ -269,7 +274,7 @@ template <typename K> int launch_merge(K kernel, AttnArgs a, const SplitPlan &pl
   return e == hipSuccess ? S1F_OK : S1F_EDEVICE;
 }
 
-// The instance of a merge kernel for a number of partial results per unit.
+// The instance of the forward's merge kernel for a number of partial results per unit.
 #define S1F_MERGE(KERNEL, T, D, parts, ...)                                                                       \
   ((parts) <= 2   ? launch_merge(KERNEL<T, D, 2>, __VA_ARGS__)                                                    \
    : (parts) <= 4 ? launch_merge(KERNEL<T, D, 4>, __VA_ARGS__)                                                    \
@@ -411,8 +416,8 @@ template <typename T, int D> size_t fwd_ws_impl(const s1f_desc *d, int64_t seg_o
 }
 
 // ---- backward ----
-// Workspace: the two planes of row statistics, then (256-byte aligned) the partial results of a cut launch, first those
-// of the dQ kernel, then (its merge kernel has read them) those of the dK/dV kernel.
+// Workspace: the two planes of row statistics, then (256-byte aligned) the partial results of the dQ half, then those of the
+// dK/dV half (in the same place if the halves run one after the other).
 inline size_t stat_bytes(const s1f_desc *d, int64_t seg_len) {
   return align256(2 * (size_t)d->batch * (size_t)d->n_q_heads * (size_t)seg_len * sizeof(float));
 }
@@ -439,39 +444,123 @@ template <typename T, int D> struct DkdvFamily {
     return p;
   }
 };
-// The plans of both launches of a backward, made once per call: the size check and the launches use the same ones.
+// The plans of both halves of a backward, made once per call: the size check and the launches use the same ones.
 struct BwdPlans {
   SplitPlan q, k;
-  size_t bytes = 0;   // of the workspace they need
+  bool both = false;        // in one launch, if the workspace holds the partial results of both halves at once
+  size_t bytes = 0;         // of the workspace that needs
+  size_t apart_bytes = 0;   // of the workspace the halves need one after the other
+  size_t k_part = 0;        // in one launch: where the partial results of the dK/dV half begin, behind those of the dQ half
 };
+// Both halves in one launch: where there is a kernel for the dQ half's tile width, and unless the call is long and the dQ half's
+// last round is cut to fill the chip anyway.  One launch / two, backward of a segment, us:
+//   tiny and small     4 heads fp32, 256 rows behind 768 keys, head_dim 64 32 -> 24; 8/2 heads, 1051 rows behind 1391 112 -> 94
+//   a few rounds       32 heads, 1757 rows behind 6435 keys, head_dim 80 480 -> 453; 64/8 heads, 533 behind 5649, 128 374 -> 327
+//   long, dQ uncut     32 heads, head_dim 128, 3983 behind 15556 3166 -> 3129; 80, 2782 behind 29986 2989 -> 2865
+//   long, dQ cut       32 heads, head_dim 128, 3652 behind 19539 3599 -> 3547, 3181 behind 26583 4078 -> 4097; 56 heads, 4897 behind
+//                      17918 7768 -> 7829, 2898 behind 62638 14797 -> 14859; 64/8 heads, 3606 behind 79334 same: workgroups of the
+//                      second half start one by one and no longer walk the same rows side by side
+constexpr double kBothUs = 3000.0;
+template <typename T, int D> bool both_halves(const s1f_desc *d, int64_t seg_off, int64_t seg_len, const BwdPlans &p) {
+  if (!Shape<T, D>::both(p.q.nc) || p.q.grid() + p.k.grid() > 0x7fffffff) return false;
+  if (p.q.n_split_units == 0) return true;
+  const double cells = ((double)seg_off + 0.5 * (double)seg_len) * (double)seg_len * d->n_q_heads * d->batch;   // (query, key) pairs
+  const double step_us = Cost<T, D>::dq.at(p.q.nc, 2) / (64 * p.q.nc) + Cost<T, D>::dkdv.at(0, 2) / 128;        // per 32 of them
+  return cells / 32 * step_us / 512 < kBothUs;   // (two workgroups on each of 256 compute units, as the step times presume)
+}
 template <typename T, int D> int bwd_plans_impl(const s1f_desc *d, int64_t seg_off, int64_t seg_len, int64_t cap, BwdPlans *p) {
   p->q = plan_rows<DqFamily<T, D>>(d, seg_off, seg_len, cap);
   p->k = DkdvFamily<T, D>::plan(d, seg_off, seg_len, cap);
-  const int64_t qb = p->q.chunks() * 64 * p->q.nc * D * 4, kb = (p->k.chunks() - p->k.n_split_units) * DkdvFamily<T, D>::part_bytes;
-  p->bytes = stat_bytes(d, seg_len) + (size_t)(qb > kb ? qb : kb);
+  const size_t qb = (size_t)(p->q.chunks() * 64 * p->q.nc * D * 4);
+  const size_t kb = (size_t)((p->k.chunks() - p->k.n_split_units) * DkdvFamily<T, D>::part_bytes);
+  p->both = both_halves<T, D>(d, seg_off, seg_len, *p);
+  p->k_part = p->both ? align256(qb) : 0;
+  p->apart_bytes = stat_bytes(d, seg_len) + (qb > kb ? qb : kb);
+  p->bytes = p->both && kb > 0 ? stat_bytes(d, seg_len) + p->k_part + kb : p->apart_bytes;
   return S1F_OK;
 }
 
-template <typename T, int D> int bwd_dq_impl(const s1f_desc *d, AttnArgs a, const SplitPlan &p, hipStream_t st) {
-  typedef DqFamily<T, D> F;
+template <typename T, int D> int launch_stats(const s1f_desc *d, AttnArgs a, hipStream_t st) {
+  const int64_t grid = ((int64_t)a.seg_len + 63) / 64 * d->n_q_heads * d->batch;   // (at most 2^28: bwd_prepare)
+  void *params[] = {&a};
+  const hipError_t e = hipLaunchKernel(reinterpret_cast<const void *>(seg_attn_bwd_stats_kernel<T, D>), dim3((unsigned)grid), dim3(256),
+                                       params, 0, st);
+  return e == hipSuccess ? S1F_OK : S1F_EDEVICE;
+}
+// The merges of the dQ half's `q_units` and the dK/dV half's `k_units` cut units, in one launch.
+template <typename T, int D, int MC>
+int launch_bwd_merge_of(AttnArgs aq, AttnArgs ak, int64_t q_groups, int64_t k_groups, hipStream_t st) {
+  int n = (int)q_groups;
+  void *params[] = {&aq, &ak, &n};
+  const hipError_t e = hipLaunchKernel(reinterpret_cast<const void *>(seg_attn_bwd_merge_kernel<T, D, MC>),
+                                       dim3((unsigned)(q_groups + k_groups)), dim3(256), params, 0, st);
+  return e == hipSuccess ? S1F_OK : S1F_EDEVICE;
+}
+template <typename T, int D>
+int launch_bwd_merge(const AttnArgs &aq, const AttnArgs &ak, int64_t q_units, int64_t k_units, hipStream_t st) {
+  if (q_units + k_units == 0) return S1F_OK;
+  const int64_t q_groups = q_units * MergeRows<D>::groups(aq.bm), k_groups = k_units * DkdvMerge<D>::GROUPS;
+  const int pq = q_units > 0 ? aq.n_split : 0, pk = k_units > 0 ? ak.n_split - 1 : 0, parts = pq > pk ? pq : pk;
+  return parts <= 2   ? launch_bwd_merge_of<T, D, 2>(aq, ak, q_groups, k_groups, st)
+         : parts <= 4 ? launch_bwd_merge_of<T, D, 4>(aq, ak, q_groups, k_groups, st)
+         : parts <= 8 ? launch_bwd_merge_of<T, D, 8>(aq, ak, q_groups, k_groups, st)
+                      : launch_bwd_merge_of<T, D, kMaxChunks>(aq, ak, q_groups, k_groups, st);
+}
+// The arguments of either half's launch; k_part: see BwdPlans.
+template <typename T, int D> AttnArgs dq_args(const s1f_desc *d, AttnArgs a, const SplitPlan &p) {
   a.part = reinterpret_cast<float *>(reinterpret_cast<char *>(a.delta) + stat_bytes(d, a.seg_len));
-  const int64_t n_bh = (int64_t)d->n_q_heads * d->batch;
-  fill_launch(&a, n_bh, row_tile_order(d, a), p);
-  const int rc = launch_rows<F>(p, n_bh, a, st);
-  if (rc != S1F_OK || p.n_split_units == 0) return rc;
-  return S1F_MERGE(seg_attn_bwd_dq_merge_kernel, T, D, p.n_split, a, p, MergeRows<D>::groups(a.bm), st);
+  fill_launch(&a, (int64_t)d->n_q_heads * d->batch, row_tile_order(d, a), p);
+  return a;
+}
+template <typename T, int D> AttnArgs dkdv_args(const s1f_desc *d, AttnArgs a, const SplitPlan &p, size_t k_part) {
+  a.part = reinterpret_cast<float *>(reinterpret_cast<char *>(a.delta) + stat_bytes(d, a.seg_len) + k_part);
+  fill_launch(&a, (int64_t)d->n_kv_heads * d->batch, 2 * (int64_t)a.seg_off < (int64_t)a.seg_len, p);
+  return a;
 }
 
-template <typename T, int D> int bwd_dkdv_impl(const s1f_desc *d, AttnArgs a, const SplitPlan &p, hipStream_t st) {
+template <typename T, int D> int bwd_dq_impl(const s1f_desc *d, const AttnArgs &a0, const SplitPlan &p, hipStream_t st) {
+  const AttnArgs a = dq_args<T, D>(d, a0, p);
+  const int rc = launch_rows<DqFamily<T, D>>(p, a.n_bh, a, st);
+  return rc == S1F_OK ? launch_bwd_merge<T, D>(a, a, p.n_split_units, 0, st) : rc;
+}
+
+template <typename T, int D> int bwd_dkdv_impl(const s1f_desc *d, const AttnArgs &a0, const SplitPlan &p, hipStream_t st) {
   typedef DkdvFamily<T, D> F;
-  a.part = reinterpret_cast<float *>(reinterpret_cast<char *>(a.delta) + stat_bytes(d, a.seg_len));
-  const int64_t n_bh = (int64_t)d->n_kv_heads * d->batch;
-  fill_launch(&a, n_bh, 2 * (int64_t)a.seg_off < (int64_t)a.seg_len, p);
-  const int rc = launch(F::kernel(), F::LDS, p, n_bh, a, st, F::THREADS);
-  if (rc != S1F_OK || p.n_split_units == 0) return rc;
-  return S1F_MERGE(seg_attn_bwd_dkdv_merge_kernel, T, D, p.n_split - 1, a, p, DkdvMerge<D>::GROUPS, st);
+  const AttnArgs a = dkdv_args<T, D>(d, a0, p, 0);
+  const int rc = launch(F::kernel(), F::LDS, p, a.n_bh, a, st, F::THREADS);
+  return rc == S1F_OK ? launch_bwd_merge<T, D>(a, a, 0, p.n_split_units, st) : rc;
 }
 
+template <typename T, int D, int NC> auto both_kernel() {
+  constexpr int W = Shape<T, D>::waves(NC);
+  return seg_attn_bwd_kernel<T, D, 4 * NC / W, Shape<T, D>::BOTH_OCC, W>;
+}
+template <typename T, int D> constexpr int kBothLds =
+    TileRing<T, D>::LDS_BYTES > BwdDkdvCfg<T, D>::LDS_BYTES ? TileRing<T, D>::LDS_BYTES : BwdDkdvCfg<T, D>::LDS_BYTES;
+template <typename T, int D, int NC>
+int launch_both(const BwdPlans &p, AttnArgs aq, AttnArgs ak, int dq_first, hipStream_t st) {
+  const int rc = prepare(both_kernel<T, D, NC>(), kBothLds<T, D>);
+  if (rc != S1F_OK) return rc;
+  int first = (int)(dq_first ? p.q.grid() : p.k.grid());
+  void *params[] = {&aq, &ak, &first, &dq_first};
+  const hipError_t e = hipLaunchKernel(reinterpret_cast<const void *>(both_kernel<T, D, NC>()), dim3((unsigned)(p.q.grid() + p.k.grid())),
+                                       dim3(DkdvFamily<T, D>::THREADS), params, (size_t)kBothLds<T, D>, st);
+  return e == hipSuccess ? S1F_OK : S1F_EDEVICE;
+}
+// The longer units first: those of the other half then fill the gaps at the end.
+template <typename T, int D> int bwd_both_impl(const s1f_desc *d, const AttnArgs &a, const BwdPlans &p, hipStream_t st) {
+  const AttnArgs aq = dq_args<T, D>(d, a, p.q), ak = dkdv_args<T, D>(d, a, p.k, p.k_part);
+  const double q_us = ((double)a.seg_off + 0.5 * a.seg_len) / 32 * Cost<T, D>::dq.at(p.q.nc, 2) / (p.q.n_whole > 0 ? 1 : p.q.n_split);
+  const double k_us = (double)a.group * ((a.seg_len + 31) / 32) * Cost<T, D>::dkdv.at(0, 2) / (p.k.n_whole > 0 ? 1 : p.k.n_split);
+  const int dq_first = q_us >= k_us;
+  int rc = launch_stats<T, D>(d, a, st);
+  if (rc != S1F_OK) return rc;
+  rc = S1F_EUNSUPPORTED;
+  if constexpr (Shape<T, D>::both(3)) { if (p.q.nc == 3) rc = launch_both<T, D, 3>(p, aq, ak, dq_first, st); }
+  if constexpr (Shape<T, D>::both(2)) { if (p.q.nc == 2) rc = launch_both<T, D, 2>(p, aq, ak, dq_first, st); }
+  if constexpr (Shape<T, D>::both(1)) { if (p.q.nc == 1) rc = launch_both<T, D, 1>(p, aq, ak, dq_first, st); }
+  return rc == S1F_OK ? launch_bwd_merge<T, D>(aq, ak, p.q.n_split_units, p.k.n_split_units, st) : rc;
+}
 
 // What a launch of either backward kernel could be refused for before it reaches the runtime.
 template <typename F, int NC> int prepare_rows() {
@@ -479,10 +568,17 @@ template <typename F, int NC> int prepare_rows() {
   if constexpr (NC > 1) return rc != S1F_OK ? rc : prepare_rows<F, NC - 1>();
   return rc;
 }
-template <typename T, int D> int bwd_ready_impl(const s1f_desc *d, const AttnArgs &a) {
+template <typename T, int D, int NC> int prepare_both() {
+  int rc = S1F_OK;
+  if constexpr (Shape<T, D>::both(NC)) rc = prepare(both_kernel<T, D, NC>(), kBothLds<T, D>);
+  if constexpr (NC > 1) return rc != S1F_OK ? rc : prepare_both<T, D, NC - 1>();
+  return rc;
+}
+template <typename T, int D> int bwd_ready_impl(const s1f_desc *d, const AttnArgs &a, bool both) {
   const int64_t kv_tiles = ((int64_t)a.seg_off + a.seg_len + DkdvFamily<T, D>::Cfg::BNW - 1) / DkdvFamily<T, D>::Cfg::BNW;
   const int64_t row_tiles = ((int64_t)a.seg_len + 63) / 64;
   if (kv_tiles * d->n_kv_heads * d->batch > 0x7fffffff || row_tiles * d->n_q_heads * d->batch > 0x7fffffff) return S1F_EUNSUPPORTED;
+  if (both) return prepare_both<T, D, DqFamily<T, D>::MAX>();
   const int rc = prepare_rows<DqFamily<T, D>, DqFamily<T, D>::MAX>();
   return rc != S1F_OK ? rc : prepare(DkdvFamily<T, D>::kernel(), DkdvFamily<T, D>::LDS);
 }
@@ -579,7 +675,10 @@ int bwd_dkdv_dispatch(const s1f_desc *d, const AttnArgs &a, const BwdPlans &p, h
   S1F_DISPATCH(bwd_dkdv_impl, d, d, a, p.k, st);
 }
 
-int bwd_ready_dispatch(const s1f_desc *d, const AttnArgs &a) { S1F_DISPATCH(bwd_ready_impl, d, d, a); }
+int bwd_both_dispatch(const s1f_desc *d, const AttnArgs &a, const BwdPlans &p, hipStream_t st) {
+  S1F_DISPATCH(bwd_both_impl, d, d, a, p, st);
+}
+int bwd_ready_dispatch(const s1f_desc *d, const AttnArgs &a, bool both) { S1F_DISPATCH(bwd_ready_impl, d, d, a, both); }
 
 // Validation shared by the backward entry points; fills `a` and `plans` on success.
 int bwd_prepare(const s1f_desc *desc, const void *dout, const void *q_seg, const void *k_prefix, const void *v_prefix,
@@ -593,7 +692,8 @@ int bwd_prepare(const s1f_desc *desc, const void *dout, const void *q_seg, const
   rc = check_seg(desc, seg_off, seg_len);
   if (rc != S1F_OK) return rc;
   bwd_plans_dispatch(desc, seg_off, seg_len, part_cap, plans);
-  if (workspace_bytes < plans->bytes) {
+  if (workspace_bytes < plans->bytes) plans->both = false;
+  if (workspace_bytes < plans->apart_bytes) {
     // fp32 runs with any workspace that holds the row statistics; its launches are then left whole
     if (desc->dtype == S1F_BF16 || workspace_bytes < stat_bytes(desc, seg_len)) return S1F_EINVAL;
     bwd_plans_dispatch(desc, seg_off, seg_len, 0, plans);
@@ -623,7 +723,8 @@ int bwd_entry(const s1f_desc *desc, const void *dout, const void *q_seg, const v
   a.out = out; a.dq = dq; a.dk_acc = dk_prefix_acc; a.dv_acc = dv_prefix_acc;
   hipStream_t st = reinterpret_cast<hipStream_t>(hip_stream);
   // everything that can fail short of the launches themselves happens before the first kernel is enqueued
-  int rc2 = bwd_ready_dispatch(desc, a);
+  int rc2 = bwd_ready_dispatch(desc, a, p.both);
+  if (rc2 == S1F_OK && p.both) return bwd_both_dispatch(desc, a, p, st);
   if (rc2 == S1F_OK) rc2 = bwd_dq_dispatch(desc, a, p, st);
   return rc2 == S1F_OK ? bwd_dkdv_dispatch(desc, a, p, st) : rc2;
 }
@@ -669,8 +770,8 @@ extern "C" int s1f_seg_attn_bwd(const s1f_desc *desc, const void *dout, const vo
 // (each device holds its own copy) and that address is what the kernels receive.
 namespace {
 constexpr int64_t kStaticStatRows = int64_t(1) << 21;            // batch * n_q_heads * seg_len the array holds
-// two planes of row statistics (16 MiB), then the partial dQ rows of a split dQ launch (at most kStaticPartBytes)
-constexpr size_t kStaticScratchBytes = 2 * (size_t)kStaticStatRows * sizeof(float) + (size_t)kStaticPartBytes;
+// two planes of row statistics (16 MiB), then the partial results of either half (at most kStaticPartBytes each)
+constexpr size_t kStaticScratchBytes = 2 * (size_t)kStaticStatRows * sizeof(float) + 2 * (size_t)kStaticPartBytes;
 static __device__ __align__(256) float scratch[kStaticScratchBytes / sizeof(float)];
 
 std::mutex scratch_mutex;
