@@ -267,6 +267,36 @@ def _stream_ptr():
     return _raw_stream(torch.cuda.current_device())
 
 
+_calls, _calls_of = None, None
+
+
+def _native():
+    """The compiled forms of the tensor calls below (csrc/torch_calls.cpp), bound to the loaded library.  They return a status,
+    or -1 for arguments that are not the plain case, which the Python code then handles or refuses."""
+    global _calls, _calls_of
+    lib = _lib or load_library()
+    if _calls_of is not lib:
+        import torch
+        try:
+            from . import _torch_calls
+        except ImportError as e:
+            raise ImportError(f"{e}: build it with `python -m paper_2406_03488_amd.build`") from e
+        entry = (lib.s1f_seg_attn_fwd, lib.s1f_seg_attn_fwd_ws, lib.s1f_seg_attn_bwd, lib.s1f_seg_attn_bwd_noalloc,
+                 lib.s1f_kv_append, lib.s1f_kv_grad_emit)
+        _torch_calls.bind(*[ctypes.cast(f, ctypes.c_void_p).value for f in entry], torch.cuda.current_device,
+                          getattr(torch._C, "_cuda_getCurrentRawStream", None) or (
+                              lambda device: torch.cuda.current_stream(device).cuda_stream))
+        _calls, _calls_of = _torch_calls, lib
+    return _calls
+
+
+def _done(rc, name):
+    """True if the call has been made."""
+    if rc > 0:
+        raise S1FError(rc, name)
+    return rc == 0
+
+
 def _same_layout(ref, *others):
     shape, stride, dtype = ref.shape, ref.stride(), ref.dtype
     for t in others:
@@ -280,6 +310,8 @@ def seg_attn_fwd(q_seg, k_prefix, v_prefix, seg_off: int, out, lse):
     q_seg/out [B, Hq, seg_len, D]; k_prefix/v_prefix [B, Hkv, capacity, D] (row 0 of the cache);
     lse [B, Hq, seg_len] fp32 contiguous.  Enqueued on torch's current stream.
     """
+    if _done(_native().fwd(q_seg, k_prefix, v_prefix, seg_off, out, lse), "s1f_seg_attn_fwd"):
+        return
     lib = load_library()
     _same_layout(q_seg, out)
     _same_layout(k_prefix, v_prefix)
@@ -312,6 +344,8 @@ def launch_plan(q_seg, k_prefix, seg_off: int, launch: int):
 def seg_attn_fwd_ws(q_seg, k_prefix, v_prefix, seg_off: int, out, lse, workspace):
     """s1f_seg_attn_fwd_ws on torch device tensors: seg_attn_fwd with a device workspace of at least
     fwd_workspace_bytes(...) bytes (None is accepted when that is 0)."""
+    if _done(_native().fwd_ws(q_seg, k_prefix, v_prefix, seg_off, out, lse, workspace), "s1f_seg_attn_fwd_ws"):
+        return
     lib = load_library()
     _same_layout(q_seg, out)
     _same_layout(k_prefix, v_prefix)
@@ -361,6 +395,9 @@ def seg_attn_bwd(dout, q_seg, k_prefix, v_prefix, out, lse, seg_off: int, dq, dk
     dk_prefix_acc/dv_prefix_acc are fp32 tensors with the shape and strides of k_prefix; workspace is any
     device tensor of at least bwd_workspace_bytes(...) bytes.
     """
+    if _done(_native().bwd(dout, q_seg, k_prefix, v_prefix, out, lse, seg_off,
+                           dq, dk_prefix_acc, dv_prefix_acc, workspace), "s1f_seg_attn_bwd"):
+        return
     lib = load_library()
     _check_bwd_tensors(dout, q_seg, k_prefix, v_prefix, out, lse, dq, dk_prefix_acc, dv_prefix_acc)
     desc = make_desc(q_seg, k_prefix)
@@ -378,6 +415,9 @@ def static_scratch_rows() -> int:
 
 def seg_attn_bwd_noalloc(dout, q_seg, k_prefix, v_prefix, out, lse, seg_off: int, dq, dk_prefix_acc, dv_prefix_acc):
     """s1f_seg_attn_bwd_noalloc on torch device tensors: s1f_seg_attn_bwd without a workspace argument."""
+    if _done(_native().bwd_noalloc(dout, q_seg, k_prefix, v_prefix, out, lse, seg_off,
+                                   dq, dk_prefix_acc, dv_prefix_acc), "s1f_seg_attn_bwd_noalloc"):
+        return
     lib = load_library()
     _check_bwd_tensors(dout, q_seg, k_prefix, v_prefix, out, lse, dq, dk_prefix_acc, dv_prefix_acc)
     desc = make_desc(q_seg, k_prefix)
@@ -430,6 +470,8 @@ def _kv_desc(cache) -> Desc:
 
 def kv_append(k_seg, v_seg, seg_off: int, k_cache, v_cache):
     """s1f_kv_append: rows of the segment -> rows [seg_off, seg_off + seg_len) of the caches."""
+    if _done(_native().append(k_seg, v_seg, seg_off, k_cache, v_cache), "s1f_kv_append"):
+        return
     lib = load_library()
     _same_layout(k_seg, v_seg)
     _same_layout(k_cache, v_cache)
@@ -446,6 +488,8 @@ def kv_append(k_seg, v_seg, seg_off: int, k_cache, v_cache):
 
 def kv_grad_emit(dk_prefix_acc, dv_prefix_acc, seg_off: int, dk_seg, dv_seg):
     """s1f_kv_grad_emit: final rows [seg_off, seg_off + seg_len) of the fp32 accumulators -> dk_seg, dv_seg."""
+    if _done(_native().emit(dk_prefix_acc, dv_prefix_acc, seg_off, dk_seg, dv_seg), "s1f_kv_grad_emit"):
+        return
     import torch
     lib = load_library()
     _same_layout(dk_prefix_acc, dv_prefix_acc)
