@@ -447,6 +447,7 @@ template <typename T, int D> struct DkdvFamily {
 // The plans of both halves of a backward, made once per call: the size check and the launches use the same ones.
 struct BwdPlans {
   SplitPlan q, k;
+  SplitPlan q_both;         // the dQ half in one launch with the other
   bool both = false;        // in one launch, if the workspace holds the partial results of both halves at once
   size_t bytes = 0;         // of the workspace that needs
   size_t apart_bytes = 0;   // of the workspace the halves need one after the other
@@ -462,7 +463,7 @@ struct BwdPlans {
 //                      second half start one by one and no longer walk the same rows side by side
 constexpr double kBothUs = 3000.0;
 template <typename T, int D> bool both_halves(const s1f_desc *d, int64_t seg_off, int64_t seg_len, const BwdPlans &p) {
-  if (!Shape<T, D>::both(p.q.nc) || p.q.grid() + p.k.grid() > 0x7fffffff) return false;
+  if (!Shape<T, D>::both(p.q_both.nc) || p.q_both.grid() + p.k.grid() > 0x7fffffff) return false;
   if (p.q.n_split_units == 0) return true;
   const double cells = ((double)seg_off + 0.5 * (double)seg_len) * (double)seg_len * d->n_q_heads * d->batch;   // (query, key) pairs
   const double step_us = Cost<T, D>::dq.at(p.q.nc, 2) / (64 * p.q.nc) + Cost<T, D>::dkdv.at(0, 2) / 128;        // per 32 of them
@@ -473,6 +474,15 @@ template <typename T, int D> int bwd_plans_impl(const s1f_desc *d, int64_t seg_o
   p->k = DkdvFamily<T, D>::plan(d, seg_off, seg_len, cap);
   const size_t qb = (size_t)(p->q.chunks() * 64 * p->q.nc * D * 4);
   const size_t kb = (size_t)((p->k.chunks() - p->k.n_split_units) * DkdvFamily<T, D>::part_bytes);
+  p->q_both = p->q;
+  // Whole units give the same bits in tiles of any width.  fp32 above head_dim 64: the 64-row tiles run in workgroups of another
+  // size than the dK/dV half, and 128 rows in eight waves are faster next to it: 32 heads, head_dim 128, backward of 1020 rows 221
+  // -> 160 us, of 980 rows behind 1020 keys 518 -> 450
+  if (sizeof(T) == 4 && !Shape<T, D>::both(p->q.nc) && p->q.n_split_units == 0) {
+    p->q_both.nc = DqFamily<T, D>::MAX;
+    p->q_both.n_tiles = (seg_len + 64 * p->q_both.nc - 1) / (64 * p->q_both.nc);
+    p->q_both.n_whole = p->q_both.n_tiles * d->n_q_heads * d->batch;
+  }
   p->both = both_halves<T, D>(d, seg_off, seg_len, *p);
   p->k_part = p->both ? align256(qb) : 0;
   p->apart_bytes = stat_bytes(d, seg_len) + (qb > kb ? qb : kb);
@@ -541,25 +551,25 @@ template <typename T, int D, int NC>
 int launch_both(const BwdPlans &p, AttnArgs aq, AttnArgs ak, int dq_first, hipStream_t st) {
   const int rc = prepare(both_kernel<T, D, NC>(), kBothLds<T, D>);
   if (rc != S1F_OK) return rc;
-  int first = (int)(dq_first ? p.q.grid() : p.k.grid());
+  int first = (int)(dq_first ? p.q_both.grid() : p.k.grid());
   void *params[] = {&aq, &ak, &first, &dq_first};
-  const hipError_t e = hipLaunchKernel(reinterpret_cast<const void *>(both_kernel<T, D, NC>()), dim3((unsigned)(p.q.grid() + p.k.grid())),
+  const hipError_t e = hipLaunchKernel(reinterpret_cast<const void *>(both_kernel<T, D, NC>()), dim3((unsigned)(p.q_both.grid() + p.k.grid())),
                                        dim3(DkdvFamily<T, D>::THREADS), params, (size_t)kBothLds<T, D>, st);
   return e == hipSuccess ? S1F_OK : S1F_EDEVICE;
 }
 // The longer units first: those of the other half then fill the gaps at the end.
 template <typename T, int D> int bwd_both_impl(const s1f_desc *d, const AttnArgs &a, const BwdPlans &p, hipStream_t st) {
-  const AttnArgs aq = dq_args<T, D>(d, a, p.q), ak = dkdv_args<T, D>(d, a, p.k, p.k_part);
-  const double q_us = ((double)a.seg_off + 0.5 * a.seg_len) / 32 * Cost<T, D>::dq.at(p.q.nc, 2) / (p.q.n_whole > 0 ? 1 : p.q.n_split);
+  const AttnArgs aq = dq_args<T, D>(d, a, p.q_both), ak = dkdv_args<T, D>(d, a, p.k, p.k_part);
+  const double q_us = ((double)a.seg_off + 0.5 * a.seg_len) / 32 * Cost<T, D>::dq.at(p.q_both.nc, 2) / (p.q_both.n_whole > 0 ? 1 : p.q_both.n_split);
   const double k_us = (double)a.group * ((a.seg_len + 31) / 32) * Cost<T, D>::dkdv.at(0, 2) / (p.k.n_whole > 0 ? 1 : p.k.n_split);
   const int dq_first = q_us >= k_us;
   int rc = launch_stats<T, D>(d, a, st);
   if (rc != S1F_OK) return rc;
   rc = S1F_EUNSUPPORTED;
-  if constexpr (Shape<T, D>::both(3)) { if (p.q.nc == 3) rc = launch_both<T, D, 3>(p, aq, ak, dq_first, st); }
-  if constexpr (Shape<T, D>::both(2)) { if (p.q.nc == 2) rc = launch_both<T, D, 2>(p, aq, ak, dq_first, st); }
-  if constexpr (Shape<T, D>::both(1)) { if (p.q.nc == 1) rc = launch_both<T, D, 1>(p, aq, ak, dq_first, st); }
-  return rc == S1F_OK ? launch_bwd_merge<T, D>(aq, ak, p.q.n_split_units, p.k.n_split_units, st) : rc;
+  if constexpr (Shape<T, D>::both(3)) { if (p.q_both.nc == 3) rc = launch_both<T, D, 3>(p, aq, ak, dq_first, st); }
+  if constexpr (Shape<T, D>::both(2)) { if (p.q_both.nc == 2) rc = launch_both<T, D, 2>(p, aq, ak, dq_first, st); }
+  if constexpr (Shape<T, D>::both(1)) { if (p.q_both.nc == 1) rc = launch_both<T, D, 1>(p, aq, ak, dq_first, st); }
+  return rc == S1F_OK ? launch_bwd_merge<T, D>(aq, ak, p.q_both.n_split_units, p.k.n_split_units, st) : rc;
 }
 
 // What a launch of either backward kernel could be refused for before it reaches the runtime.
