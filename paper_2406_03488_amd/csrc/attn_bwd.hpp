@@ -423,21 +423,17 @@ template <typename T, int D> S1F_DEV void bwd_dkdv_body(const AttnArgs &a, int i
   const lds_addr stats0 = vtile + Cfg::V_BYTES;
   M rd;
   rd.init(lane);
-  {   // V rows of the workgroup's keys -> LDS (keys past the prefix: copies of its last row, products never stored)
-    Copy lv;
-    lv.init(wave, lane, a.kv_ss);
+  // V rows of the workgroup's keys -> LDS (keys past the prefix: copies of its last row, products never stored).  fp32: through
+  // registers, written when the first tile and the K rows are on their way as well
+  Copy lv[ASYNC ? 1 : 2];
 #pragma unroll
-    for (int i = 0; i < 4; i += 2) {
-      const int key0 = j0 + 32 * (i + ((wave >> 1) & 1)), at = key0 < kv_len ? key0 : kv_len - 1;
-      const T *row = vbase + (int64_t)at * a.kv_ss;
-      if constexpr (ASYNC) {
-        lv.issue(row, row, a.kv_ss, kv_len - at, kv_len - at, vtile + i * TB, wave);
-      } else {
-        lv.load(row, row, a.kv_ss, kv_len - at, kv_len - at, wave);
-#pragma unroll
-        for (int x = 0; x < Copy::NI; ++x) lv.write(x, vtile + i * TB);
-      }
-    }
+  for (int i = 0; i < 4; i += 2) {
+    const int key0 = j0 + 32 * (i + ((wave >> 1) & 1)), at = key0 < kv_len ? key0 : kv_len - 1;
+    const T *row = vbase + (int64_t)at * a.kv_ss;
+    Copy &l = lv[ASYNC ? 0 : i / 2];
+    if (!ASYNC || i == 0) l.init(wave, lane, a.kv_ss);
+    if constexpr (ASYNC) l.issue(row, row, a.kv_ss, kv_len - at, kv_len - at, vtile + i * TB, wave);
+    else l.load(row, row, a.kv_ss, kv_len - at, kv_len - at, wave);
   }
   // Tile cursors (row offset of the tile, its query head, its ring stage), advanced once per iteration.
   struct Cursor {
@@ -491,8 +487,13 @@ template <typename T, int D> S1F_DEV void bwd_dkdv_body(const AttnArgs &a, int i
       for (int x = 0; x < Copy::NI; ++x) ld.write(x, lds0);
     }
   };
-  if constexpr (!ASYNC)
+  if constexpr (!ASYNC) {
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+#pragma unroll
+      for (int x = 0; x < Copy::NI; ++x) lv[i].write(x, vtile + 2 * i * TB);
     if (it_begin < it_end) write_tile();
+  }
   wait_async_tiles();
   __syncthreads();
 

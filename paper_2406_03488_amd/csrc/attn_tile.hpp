@@ -496,11 +496,27 @@ template <int D, int WAVES> struct TileRing<float, D, WAVES> {
 #pragma unroll
     for (int x = 0; x < Copy::NI; ++x) ld.write(x, st[i]);
   }
-  // Before the first step: tiles 0 and 1 into their stages, tile 2 into registers.
+  // Before the first step: tiles 0 and 1 into their stages, tile 2 into registers.  Tiles 0 and 1 are both loaded before either
+  // is written, and the caller loads its own rows in between: one wait for memory instead of three (8/8 heads, head_dim 80, 947 rows
+  // behind 4053 keys, backward 232 -> 228 us; 32/8 heads, 64, 1675 behind 6325 1477 -> 1436, forward 488 -> 479; the
+  // same in the dK/dV kernel is part of that).  Four waves above head_dim 64 have no registers for two tiles next to their rows (backward of
+  // 8/2 heads, 128, 941 behind 2300: 253 -> 261).
+  static constexpr bool TWO = WAVES == 8 || D == 64;
+  Copy ld0;
   S1F_DEV void issue(int i) {
     if (i > 2) return;
-    load();
-    if (i < 2) write(i);
+    if constexpr (TWO) {
+      if (i == 2) {
+#pragma unroll
+        for (int x = 0; x < Copy::NI; ++x) ld0.write(x, st[0]);   // (there always is a first tile)
+        write(1);
+      }
+      load();
+      if (i == 0) ld0 = ld;
+    } else {
+      load();
+      if (i < 2) write(i);
+    }
   }
   // WHOLE: a whole tile is in registers and another is left to load; both then happen piece by piece in work()
   template <bool WHOLE> S1F_DEV void begin_step(int) {
