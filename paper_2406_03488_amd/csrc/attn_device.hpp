@@ -160,6 +160,7 @@ struct AttnArgs {
   int32_t n_whole, n_split, n_split_units;
   int32_t bm;                            // forward and dQ: rows per unit
   int32_t first_id;                      // forward: > 0 in a second launch, over the rows of the units from n_whole = first_id on
+  int32_t rag_tiles;                     // in it: tiles per (batch, head) over the rows behind the n_tiles whole units
   float *part;                           // partial results of the chunks: [chunk][cut unit][rows per unit][head_dim]
   float *part_ml;                        // forward only: running maximum (log2 units) and row sum, [..][rows per unit][2]
 };

@@ -213,18 +213,27 @@ __global__ void __launch_bounds__(64 * WAVES, OCC) seg_attn_fwd_kernel(const Att
   extern __shared__ __attribute__((aligned(1024))) char smem[];
   const int tid = threadIdx.x, lane = tid & 63, j = lane >> 4, n = lane & 15;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  UnitChunk uc = split_unit(blockIdx.x + a.first_id, a.n_whole, a.n_split, a.n_split_units);
-  int qt, bh;
-  decode_workgroup(uc.unit, a.n_tiles, a.n_bh, a.tile_major, qt, bh);
-  qt = a.n_tiles - 1 - qt;   // later (heavier) row tiles are scheduled first
-  const int h = bh % a.n_q_heads, b = bh / a.n_q_heads, hk = h / a.group;
   const int seg_len = a.seg_len;
-  int row0 = qt * BM;
-  if (a.first_id > 0) {   // the launch of the last units' rows: a chunk is a tile of BM of the unit's a.bm rows
-    row0 = qt * a.bm + uc.chunk * BM;
+  UnitChunk uc;
+  int qt, bh, row0;
+  if (BM == 64 && a.first_id > 0) {   // the launch of the last units' rows: a chunk is a tile of 64 of the unit's a.bm rows
+    const int cut = a.n_split * a.n_split_units;
+    if ((int)blockIdx.x < cut) {
+      uc = split_unit(blockIdx.x + a.first_id, a.first_id, a.n_split, a.n_split_units);
+      decode_workgroup(uc.unit, a.n_tiles, a.n_bh, a.tile_major, qt, bh);
+      row0 = (a.n_tiles - 1 - qt) * a.bm + uc.chunk * BM;
+    } else {
+      decode_workgroup(blockIdx.x - cut, a.rag_tiles, a.n_bh, 1, qt, bh);
+      row0 = a.n_tiles * a.bm + qt * BM;
+    }
     if (row0 >= seg_len) return;
-    uc = UnitChunk{uc.unit, 0, 1, -1};
+    uc = UnitChunk{0, 0, 1, -1};
+  } else {
+    uc = split_unit(blockIdx.x, a.n_whole, a.n_split, a.n_split_units);
+    decode_workgroup(uc.unit, a.n_tiles, a.n_bh, a.tile_major, qt, bh);
+    row0 = (a.n_tiles - 1 - qt) * BM;   // later (heavier) row tiles are scheduled first
   }
+  const int h = bh % a.n_q_heads, b = bh / a.n_q_heads, hk = h / a.group;
   const int wrow0 = row0 + wave * 16 * NC;
   const int last_row = (row0 + BM < seg_len ? row0 + BM : seg_len) - 1;
   // This workgroup's 32-key tiles: all that hold keys 0 .. seg_off+last_row, or one chunk of them.  From here on

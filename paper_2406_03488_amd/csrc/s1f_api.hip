@@ -399,6 +399,18 @@ int fwd_impl(const s1f_desc *d, AttnArgs a, hipStream_t st, void *workspace, siz
     rest.n_whole = 0;
     rest.n_split_units = p.n_whole - whole;
     rest.n_split = p.nc;
+    // The last unit of every (batch, head) may hold rows for fewer 64-row tiles than the others; where that leaves fewer tiles to the
+    // busiest compute unit, it is those that run in the second launch.  56 heads, 3678 rows behind 39549 keys: 56 units of 30 rows and
+    // 40 whole ones are 176 tiles, 96 whole ones 288: 3903 -> 3746 us; 3669 rows behind 40380 4010 -> 3835.  Not for grouped
+    // heads, whose units left over are the ones with the fewest keys (64/8 heads, 3110 rows behind 4612: 524 -> 561).
+    const int64_t rag = (a.seg_len - (p.n_tiles - 1) * 64 * p.nc + 63) / 64, cus = family_slots<F, 1>().cus;
+    const int64_t tiles = rest.n_split_units * p.nc, fewer = tiles - (p.nc - rag) * n_bh;
+    if (a.group == 1 && rest.n_split_units >= n_bh && (fewer + cus - 1) / cus < (tiles + cus - 1) / cus) {
+      head.n_tiles = rest.n_tiles = p.n_tiles - 1;
+      rest.n_split_units -= n_bh;
+      rest.n_whole = rag * n_bh;
+      a.rag_tiles = (int32_t)rag;
+    }
     fill_launch(&a, n_bh, row_tile_order(d, a), head);
     const int rc = launch_rows<F>(head, n_bh, a, st);
     if (rc != S1F_OK) return rc;
