@@ -204,7 +204,9 @@ S1F_DEV void fwd_step(f32x4 (&p)[2][NC], f32x4 (&o)[NC][M::DB], const float (&m)
   if (HAS_NEXT) rs[NC - 1] += prob(8 * NC - 1);
 }
 
-template <typename T, int D, int NC, int OCC, int WAVES>
+// REST: the second launch, over the rows of units that the first left over (an instance of its own: in the 64-row kernel itself
+// the decision cost 2 to 6 % of launches of 30 to 300 us)
+template <typename T, int D, int NC, int OCC, int WAVES, bool REST = false>
 __global__ void __launch_bounds__(64 * WAVES, OCC) seg_attn_fwd_kernel(const AttnArgs a) {
   typedef Mat<T, D> M;
   typedef TileRing<T, D, WAVES> Ring;
@@ -216,7 +218,7 @@ __global__ void __launch_bounds__(64 * WAVES, OCC) seg_attn_fwd_kernel(const Att
   const int seg_len = a.seg_len;
   UnitChunk uc;
   int qt, bh, row0;
-  if (BM == 64 && a.first_id > 0) {   // the launch of the last units' rows: a chunk is a tile of 64 of the unit's a.bm rows
+  if constexpr (REST) {   // a chunk is a tile of BM of the unit's a.bm rows
     const int cut = a.n_split * a.n_split_units;
     if ((int)blockIdx.x < cut) {
       uc = split_unit(blockIdx.x + a.first_id, a.first_id, a.n_split, a.n_split_units);

@@ -295,6 +295,7 @@ template <typename T, int D> struct FwdFamily {
     constexpr int W = Shape<T, D>::waves(NC);
     return seg_attn_fwd_kernel<T, D, 4 * NC / W, Shape<T, D>::fwd_occ(NC), W>;
   }
+  static auto rest_kernel() { return seg_attn_fwd_kernel<T, D, 1, Shape<T, D>::fwd_occ(1), 4, true>; }
 };
 template <typename T, int D> struct DqFamily {
   static constexpr int MAX = Shape<T, D>::DQ_MAX, LDS = TileRing<T, D>::LDS_BYTES;
@@ -417,7 +418,7 @@ int fwd_impl(const s1f_desc *d, AttnArgs a, hipStream_t st, void *workspace, siz
     a.first_id = (int32_t)whole;
     a.n_split = p.nc;
     a.n_split_units = (int32_t)rest.n_split_units;
-    return launch_rows<F>(rest, n_bh, a, st);
+    return launch(F::rest_kernel(), F::LDS, rest, n_bh, a, st, F::threads(1));
   }
   const int rc = launch_rows<F>(p, n_bh, a, st);
   if (rc != S1F_OK || p.n_split_units == 0) return rc;
