@@ -74,6 +74,32 @@ AttnArgs make_args(const s1f_desc *d, int64_t seg_off, int64_t seg_len) {
   return a;
 }
 
+// A launch counts its threads in 32 bits, and the runtime takes a larger one all the same and runs what its size is past 2^32: fewer
+// workgroups, without an error (two backwards of 129 x 65535 heads of one row, in one launch: half of dK and dV missing).
+bool one_launch(int64_t grid, int threads) { return grid * threads <= 0xffffffffll; }
+// The arguments of a call over the batch entries from b0 on.
+template <typename T> AttnArgs from_entry(AttnArgs a, int64_t b0) {
+  auto tensor = [&](const void *p, int64_t stride) { return p ? reinterpret_cast<const T *>(p) + b0 * stride : nullptr; };
+  auto ours = [&](void *p) { return const_cast<T *>(tensor(p, a.q_sb)); };
+  auto floats = [&](float *p, int64_t stride) { return p ? p + b0 * stride : nullptr; };
+  const int64_t rows = (int64_t)a.n_q_heads * a.seg_len;
+  a.q = tensor(a.q, a.q_sb); a.out = tensor(a.out, a.q_sb); a.dout = tensor(a.dout, a.q_sb);
+  a.k = tensor(a.k, a.kv_sb); a.v = tensor(a.v, a.kv_sb);
+  a.out_w = ours(a.out_w); a.dq = ours(a.dq);
+  a.lse = floats(a.lse, rows); a.delta = floats(a.delta, rows);
+  a.dk_acc = floats(a.dk_acc, a.kv_sb); a.dv_acc = floats(a.dv_acc, a.kv_sb);
+  return a;
+}
+// Runs a call that is too large for one launch as two, over the halves of its batch entries.
+template <typename T, typename F> int in_halves(const s1f_desc *d, const AttnArgs &a, F call) {
+  if (d->batch < 2) return S1F_EUNSUPPORTED;
+  s1f_desc lo = *d, hi = *d;
+  lo.batch = d->batch / 2;
+  hi.batch = d->batch - lo.batch;
+  const int rc = call(&lo, a);
+  return rc == S1F_OK ? call(&hi, from_entry<T>(a, lo.batch)) : rc;
+}
+
 // Kernels that need more than 64 KiB of LDS have to be told so once per device; `prepare` does that the first time
 // a kernel instantiation is used on the current device (a template: one flag set per instantiation).
 constexpr int kMaxDevices = 64;
@@ -186,6 +212,7 @@ struct SplitPlan {
   int n_split = 1;            // chunks per split unit
   int64_t grid() const { return n_whole + n_split_units * n_split; }
   int64_t chunks() const { return n_split_units * n_split; }
+  SplitPlan uncut(int64_t n_bh) const { return SplitPlan{nc, n_tiles, n_tiles * n_bh, 0, 1}; }
 };
 
 // Chooses between whole units and, with cap > 0, each number of chunks for those of the last round, of which `direct` per
@@ -257,7 +284,7 @@ void fill_launch(AttnArgs *a, int64_t n_bh, int tile_major, const SplitPlan &p) 
   a->bm = 64 * p.nc;
 }
 template <typename K> int launch(K kernel, int lds_bytes, const SplitPlan &p, int64_t n_bh, AttnArgs a, hipStream_t st, int threads = 256) {
-  if (p.n_tiles * n_bh > 0x7fffffff || p.grid() > 0x7fffffff) return S1F_EUNSUPPORTED;
+  if (p.n_tiles * n_bh > 0x7fffffff || !one_launch(p.grid(), threads)) return S1F_EUNSUPPORTED;
   const int rc = prepare(kernel, lds_bytes);
   if (rc != S1F_OK) return rc;
   void *params[] = {&a};
@@ -379,17 +406,16 @@ template <typename F> bool row_tail_of(const AttnArgs &a, const SplitPlan &p, in
   return false;
 }
 
-template <typename T, int D>
-int fwd_impl(const s1f_desc *d, AttnArgs a, hipStream_t st, void *workspace, size_t workspace_bytes, bool split) {
+template <typename T, int D> int fwd_run(const s1f_desc *d, AttnArgs a, const SplitPlan &p, hipStream_t st, void *workspace) {
   typedef FwdFamily<T, D> F;
-  SplitPlan p = plan_rows<F>(d, a.seg_off, a.seg_len, split ? kMaxPartBytes : 0);
-  if (fwd_workspace<T, D>(p) > workspace_bytes) {
-    if (sizeof(T) == 2) return S1F_EINVAL;
-    p = plan_rows<F>(d, a.seg_off, a.seg_len, 0);   // fp32 runs with any workspace
-  }
+  const int64_t n_bh = (int64_t)d->n_q_heads * d->batch;
+  if (p.n_tiles * n_bh > 0x7fffffff) return S1F_EUNSUPPORTED;
+  if (!one_launch(p.grid(), F::threads(p.nc)))
+    return in_halves<T>(d, a, [&](const s1f_desc *half, const AttnArgs &x) {
+      return fwd_run<T, D>(half, x, p.uncut((int64_t)d->n_q_heads * half->batch), st, nullptr);
+    });
   a.part = reinterpret_cast<float *>(workspace);
   a.part_ml = reinterpret_cast<float *>(reinterpret_cast<char *>(workspace) + align256((size_t)(p.chunks() * 64 * p.nc * D * 4)));
-  const int64_t n_bh = (int64_t)d->n_q_heads * d->batch;
   fill_launch(&a, n_bh, row_tile_order(d, a), p);
   a.first_id = 0;
   int64_t whole = 0;
@@ -423,6 +449,15 @@ int fwd_impl(const s1f_desc *d, AttnArgs a, hipStream_t st, void *workspace, siz
   const int rc = launch_rows<F>(p, n_bh, a, st);
   if (rc != S1F_OK || p.n_split_units == 0) return rc;
   return S1F_MERGE(seg_attn_fwd_merge_kernel, T, D, p.n_split, a, p, MergeRows<D>::groups(a.bm), st);
+}
+template <typename T, int D>
+int fwd_impl(const s1f_desc *d, const AttnArgs &a, hipStream_t st, void *workspace, size_t workspace_bytes, bool split) {
+  SplitPlan p = plan_rows<FwdFamily<T, D>>(d, a.seg_off, a.seg_len, split ? kMaxPartBytes : 0);
+  if (fwd_workspace<T, D>(p) > workspace_bytes) {
+    if (sizeof(T) == 2) return S1F_EINVAL;
+    p = plan_rows<FwdFamily<T, D>>(d, a.seg_off, a.seg_len, 0);   // fp32 runs with any workspace
+  }
+  return fwd_run<T, D>(d, a, p, st, workspace);
 }
 template <typename T, int D> size_t fwd_ws_impl(const s1f_desc *d, int64_t seg_off, int64_t seg_len) {
   return fwd_workspace<T, D>(plan_rows<FwdFamily<T, D>>(d, seg_off, seg_len, kMaxPartBytes));
@@ -476,7 +511,7 @@ struct BwdPlans {
 //                      second half start one by one and no longer walk the same rows side by side
 constexpr double kBothUs = 3000.0;
 template <typename T, int D> bool both_halves(const s1f_desc *d, int64_t seg_off, int64_t seg_len, const BwdPlans &p) {
-  if (!Shape<T, D>::both(p.q_both.nc) || p.q_both.grid() + p.k.grid() > 0x7fffffff) return false;
+  if (!Shape<T, D>::both(p.q_both.nc) || !one_launch(p.q_both.grid() + p.k.grid(), DkdvFamily<T, D>::THREADS)) return false;
   if (p.q.n_split_units == 0) return true;
   const double cells = ((double)seg_off + 0.5 * (double)seg_len) * (double)seg_len * d->n_q_heads * d->batch;   // (query, key) pairs
   const double step_us = Cost<T, D>::dq.at(p.q.nc, 2) / (64 * p.q.nc) + Cost<T, D>::dkdv.at(0, 2) / 128;        // per 32 of them
@@ -504,7 +539,9 @@ template <typename T, int D> int bwd_plans_impl(const s1f_desc *d, int64_t seg_o
 }
 
 template <typename T, int D> int launch_stats(const s1f_desc *d, AttnArgs a, hipStream_t st) {
-  const int64_t grid = ((int64_t)a.seg_len + 63) / 64 * d->n_q_heads * d->batch;   // (at most 2^28: bwd_prepare)
+  // (within one launch wherever both halves are: more than 2^24 workgroups of 64 rows and still fewer than that of wider tiles need
+  // 65 rows each, 2^30 in all, and bwd_prepare allows 2^28)
+  const int64_t grid = ((int64_t)a.seg_len + 63) / 64 * d->n_q_heads * d->batch;
   void *params[] = {&a};
   const hipError_t e = hipLaunchKernel(reinterpret_cast<const void *>(seg_attn_bwd_stats_kernel<T, D>), dim3((unsigned)grid), dim3(256),
                                        params, 0, st);
@@ -542,6 +579,10 @@ template <typename T, int D> AttnArgs dkdv_args(const s1f_desc *d, AttnArgs a, c
 }
 
 template <typename T, int D> int bwd_dq_impl(const s1f_desc *d, const AttnArgs &a0, const SplitPlan &p, hipStream_t st) {
+  if (!one_launch(p.grid(), DqFamily<T, D>::threads(p.nc)))
+    return in_halves<T>(d, a0, [&](const s1f_desc *half, const AttnArgs &x) {
+      return bwd_dq_impl<T, D>(half, x, p.uncut((int64_t)d->n_q_heads * half->batch), st);
+    });
   const AttnArgs a = dq_args<T, D>(d, a0, p);
   const int rc = launch_rows<DqFamily<T, D>>(p, a.n_bh, a, st);
   return rc == S1F_OK ? launch_bwd_merge<T, D>(a, a, p.n_split_units, 0, st) : rc;
@@ -549,6 +590,10 @@ template <typename T, int D> int bwd_dq_impl(const s1f_desc *d, const AttnArgs &
 
 template <typename T, int D> int bwd_dkdv_impl(const s1f_desc *d, const AttnArgs &a0, const SplitPlan &p, hipStream_t st) {
   typedef DkdvFamily<T, D> F;
+  if (!one_launch(p.grid(), F::THREADS))
+    return in_halves<T>(d, a0, [&](const s1f_desc *half, const AttnArgs &x) {
+      return bwd_dkdv_impl<T, D>(half, x, p.uncut((int64_t)d->n_kv_heads * half->batch), st);
+    });
   const AttnArgs a = dkdv_args<T, D>(d, a0, p, 0);
   const int rc = launch(F::kernel(), F::LDS, p, a.n_bh, a, st, F::THREADS);
   return rc == S1F_OK ? launch_bwd_merge<T, D>(a, a, 0, p.n_split_units, st) : rc;
@@ -597,11 +642,14 @@ template <typename T, int D, int NC> int prepare_both() {
   if constexpr (NC > 1) return rc != S1F_OK ? rc : prepare_both<T, D, NC - 1>();
   return rc;
 }
-template <typename T, int D> int bwd_ready_impl(const s1f_desc *d, const AttnArgs &a, bool both) {
+template <typename T, int D> int bwd_ready_impl(const s1f_desc *d, const AttnArgs &a, const BwdPlans &p) {
   const int64_t kv_tiles = ((int64_t)a.seg_off + a.seg_len + DkdvFamily<T, D>::Cfg::BNW - 1) / DkdvFamily<T, D>::Cfg::BNW;
   const int64_t row_tiles = ((int64_t)a.seg_len + 63) / 64;
   if (kv_tiles * d->n_kv_heads * d->batch > 0x7fffffff || row_tiles * d->n_q_heads * d->batch > 0x7fffffff) return S1F_EUNSUPPORTED;
-  if (both) return prepare_both<T, D, DqFamily<T, D>::MAX>();
+  if (!one_launch(p.q.n_tiles * d->n_q_heads, DqFamily<T, D>::threads(p.q.nc)) ||
+      !one_launch(p.k.n_tiles * d->n_kv_heads, DkdvFamily<T, D>::THREADS))   // one batch entry: not to be halved further
+    return S1F_EUNSUPPORTED;
+  if (p.both) return prepare_both<T, D, DqFamily<T, D>::MAX>();
   const int rc = prepare_rows<DqFamily<T, D>, DqFamily<T, D>::MAX>();
   return rc != S1F_OK ? rc : prepare(DkdvFamily<T, D>::kernel(), DkdvFamily<T, D>::LDS);
 }
@@ -701,7 +749,7 @@ int bwd_dkdv_dispatch(const s1f_desc *d, const AttnArgs &a, const BwdPlans &p, h
 int bwd_both_dispatch(const s1f_desc *d, const AttnArgs &a, const BwdPlans &p, hipStream_t st) {
   S1F_DISPATCH(bwd_both_impl, d, d, a, p, st);
 }
-int bwd_ready_dispatch(const s1f_desc *d, const AttnArgs &a, bool both) { S1F_DISPATCH(bwd_ready_impl, d, d, a, both); }
+int bwd_ready_dispatch(const s1f_desc *d, const AttnArgs &a, const BwdPlans &p) { S1F_DISPATCH(bwd_ready_impl, d, d, a, p); }
 
 // Validation shared by the backward entry points; fills `a` and `plans` on success.
 int bwd_prepare(const s1f_desc *desc, const void *dout, const void *q_seg, const void *k_prefix, const void *v_prefix,
@@ -746,7 +794,7 @@ int bwd_entry(const s1f_desc *desc, const void *dout, const void *q_seg, const v
   a.out = out; a.dq = dq; a.dk_acc = dk_prefix_acc; a.dv_acc = dv_prefix_acc;
   hipStream_t st = reinterpret_cast<hipStream_t>(hip_stream);
   // everything that can fail short of the launches themselves happens before the first kernel is enqueued
-  int rc2 = bwd_ready_dispatch(desc, a, p.both);
+  int rc2 = bwd_ready_dispatch(desc, a, p);
   if (rc2 == S1F_OK && p.both) return bwd_both_dispatch(desc, a, p, st);
   if (rc2 == S1F_OK) rc2 = bwd_dq_dispatch(desc, a, p, st);
   return rc2 == S1F_OK ? bwd_dkdv_dispatch(desc, a, p, st) : rc2;
