@@ -304,6 +304,19 @@ def _same_layout(ref, *others):
             raise ValueError("tensors sharing a stride set must have identical shape, strides and dtype")
 
 
+def _check_covers(big, small, what):
+    """The kernels take the number of batch entries and head_dim from `small` and address `big` with them; one that has more
+    of either is read in part."""
+    if big.shape[0] < small.shape[0] or big.shape[3] < small.shape[3]:
+        raise ValueError(f"{what}: fewer batch entries or a smaller head_dim than the tensors it goes with")
+
+
+def _check_prefix(k_prefix, q_seg):
+    if k_prefix.dtype != q_seg.dtype:
+        raise TypeError("queries and prefix must share the element type")
+    _check_covers(k_prefix, q_seg, "k_prefix")
+
+
 def seg_attn_fwd(q_seg, k_prefix, v_prefix, seg_off: int, out, lse):
     """s1f_seg_attn_fwd on torch device tensors.
 
@@ -315,9 +328,9 @@ def seg_attn_fwd(q_seg, k_prefix, v_prefix, seg_off: int, out, lse):
     lib = load_library()
     _same_layout(q_seg, out)
     _same_layout(k_prefix, v_prefix)
-    if not lse.is_contiguous() or lse.shape != q_seg.shape[:3]:
-        raise ValueError("lse must be a contiguous [B, Hq, seg_len] fp32 tensor")
+    _check_lse(lse, q_seg)
     desc = make_desc(q_seg, k_prefix)
+    _check_prefix(k_prefix, q_seg)
     rc = lib.s1f_seg_attn_fwd(ctypes.byref(desc), q_seg.data_ptr(), k_prefix.data_ptr(), v_prefix.data_ptr(),
                               int(seg_off), int(q_seg.shape[2]), out.data_ptr(), lse.data_ptr(), _stream_ptr())
     if rc != 0:
@@ -351,6 +364,7 @@ def seg_attn_fwd_ws(q_seg, k_prefix, v_prefix, seg_off: int, out, lse, workspace
     _same_layout(k_prefix, v_prefix)
     _check_lse(lse, q_seg)
     desc = make_desc(q_seg, k_prefix)
+    _check_prefix(k_prefix, q_seg)
     ws_ptr = workspace.data_ptr() if workspace is not None else None
     ws_bytes = workspace.numel() * workspace.element_size() if workspace is not None else 0
     rc = lib.s1f_seg_attn_fwd_ws(ctypes.byref(desc), q_seg.data_ptr(), k_prefix.data_ptr(), v_prefix.data_ptr(),
@@ -401,6 +415,7 @@ def seg_attn_bwd(dout, q_seg, k_prefix, v_prefix, out, lse, seg_off: int, dq, dk
     lib = load_library()
     _check_bwd_tensors(dout, q_seg, k_prefix, v_prefix, out, lse, dq, dk_prefix_acc, dv_prefix_acc)
     desc = make_desc(q_seg, k_prefix)
+    _check_prefix(k_prefix, q_seg)
     rc = lib.s1f_seg_attn_bwd(ctypes.byref(desc), dout.data_ptr(), q_seg.data_ptr(), k_prefix.data_ptr(),
                               v_prefix.data_ptr(), out.data_ptr(), lse.data_ptr(), int(seg_off), int(q_seg.shape[2]),
                               dq.data_ptr(), dk_prefix_acc.data_ptr(), dv_prefix_acc.data_ptr(),
@@ -421,6 +436,7 @@ def seg_attn_bwd_noalloc(dout, q_seg, k_prefix, v_prefix, out, lse, seg_off: int
     lib = load_library()
     _check_bwd_tensors(dout, q_seg, k_prefix, v_prefix, out, lse, dq, dk_prefix_acc, dv_prefix_acc)
     desc = make_desc(q_seg, k_prefix)
+    _check_prefix(k_prefix, q_seg)
     rc = lib.s1f_seg_attn_bwd_noalloc(ctypes.byref(desc), dout.data_ptr(), q_seg.data_ptr(), k_prefix.data_ptr(),
                                       v_prefix.data_ptr(), out.data_ptr(), lse.data_ptr(), int(seg_off),
                                       int(q_seg.shape[2]), dq.data_ptr(), dk_prefix_acc.data_ptr(),
@@ -436,6 +452,7 @@ def seg_attn_bwd_dq(dout, q_seg, k_prefix, v_prefix, out, lse, seg_off: int, dq,
     _same_layout(k_prefix, v_prefix)
     _check_lse(lse, q_seg)
     desc = make_desc(q_seg, k_prefix)
+    _check_prefix(k_prefix, q_seg)
     rc = lib.s1f_seg_attn_bwd_dq(ctypes.byref(desc), dout.data_ptr(), q_seg.data_ptr(), k_prefix.data_ptr(),
                                  v_prefix.data_ptr(), out.data_ptr(), lse.data_ptr(), int(seg_off),
                                  int(q_seg.shape[2]), dq.data_ptr(), workspace.data_ptr(),
@@ -451,6 +468,7 @@ def seg_attn_bwd_dkdv(dout, q_seg, k_prefix, v_prefix, lse, seg_off: int, dk_pre
     _check_acc(k_prefix, v_prefix, dk_prefix_acc, dv_prefix_acc)
     _check_lse(lse, q_seg)
     desc = make_desc(q_seg, k_prefix)
+    _check_prefix(k_prefix, q_seg)
     rc = lib.s1f_seg_attn_bwd_dkdv(ctypes.byref(desc), dout.data_ptr(), q_seg.data_ptr(), k_prefix.data_ptr(),
                                    v_prefix.data_ptr(), lse.data_ptr(), int(seg_off), int(q_seg.shape[2]),
                                    dk_prefix_acc.data_ptr(), dv_prefix_acc.data_ptr(), workspace.data_ptr(),
@@ -468,6 +486,12 @@ def _kv_desc(cache) -> Desc:
     return Desc(b, h, h, d, 0, 0, 0, 0, d, s[0], s[1], s[2], cap)
 
 
+def _check_segment(seg, cache):
+    _check_covers(seg, cache, "segment")
+    if seg.shape[1] < cache.shape[1]:
+        raise ValueError("segment: fewer heads than the cache")
+
+
 def kv_append(k_seg, v_seg, seg_off: int, k_cache, v_cache):
     """s1f_kv_append: rows of the segment -> rows [seg_off, seg_off + seg_len) of the caches."""
     if _done(_native().append(k_seg, v_seg, seg_off, k_cache, v_cache), "s1f_kv_append"):
@@ -480,6 +504,7 @@ def kv_append(k_seg, v_seg, seg_off: int, k_cache, v_cache):
     s = k_seg.stride()
     if k_seg.dtype != k_cache.dtype or s[3] != 1:
         raise ValueError("segment and cache must share the element type; head_dim must be contiguous")
+    _check_segment(k_seg, k_cache)
     rc = lib.s1f_kv_append(ctypes.byref(desc), k_seg.data_ptr(), v_seg.data_ptr(), s[0], s[1], s[2], int(seg_off),
                            k_seg.shape[2], k_cache.data_ptr(), v_cache.data_ptr(), _stream_ptr())
     if rc != 0:
@@ -498,6 +523,7 @@ def kv_grad_emit(dk_prefix_acc, dv_prefix_acc, seg_off: int, dk_seg, dv_seg):
     if dk_prefix_acc.dtype != torch.float32 or s[3] != 1:
         raise ValueError("accumulators must be fp32; head_dim must be contiguous")
     desc = _kv_desc(dk_prefix_acc)
+    _check_segment(dk_seg, dk_prefix_acc)
     desc.dtype = _dtype_code(dk_seg)
     rc = lib.s1f_kv_grad_emit(ctypes.byref(desc), dk_prefix_acc.data_ptr(), dv_prefix_acc.data_ptr(), int(seg_off),
                               dk_seg.shape[2], dk_seg.data_ptr(), dv_seg.data_ptr(), s[0], s[1], s[2], _stream_ptr())

@@ -77,9 +77,12 @@ bool dtype_of(const at::Tensor &t, int32_t *code) {
 }
 bool fits(int64_t x) { return x >= 0 && x <= 0x7fffffff; }
 
+// Batch entries and head_dim of `small` are what the kernels address `big` with.
+bool covers(const at::Tensor &big, const at::Tensor &small) { return big.size(0) >= small.size(0) && big.size(3) >= small.size(3); }
+
 bool desc_of(const at::Tensor &q, const at::Tensor &kv, s1f_desc *d) {
   *d = {};
-  if (!rows_of(q) || !rows_of(kv) || !dtype_of(q, &d->dtype)) return false;
+  if (!rows_of(q) || !rows_of(kv) || !dtype_of(q, &d->dtype) || kv.scalar_type() != q.scalar_type() || !covers(kv, q)) return false;
   if (!fits(q.size(0)) || !fits(q.size(1)) || !fits(kv.size(1)) || !fits(q.size(3))) return false;
   d->batch = (int32_t)q.size(0); d->n_q_heads = (int32_t)q.size(1); d->n_kv_heads = (int32_t)kv.size(1); d->head_dim = (int32_t)q.size(3);
   d->q_stride_b = q.stride(0); d->q_stride_h = q.stride(1); d->q_stride_s = q.stride(2);
@@ -95,6 +98,9 @@ bool cache_desc_of(const at::Tensor &cache, const at::Tensor &typed, s1f_desc *d
   d->kv_stride_b = cache.stride(0); d->kv_stride_h = cache.stride(1); d->kv_stride_s = cache.stride(2);
   d->kv_capacity = cache.size(2);
   return true;
+}
+bool segment_ok(const at::Tensor &seg, const at::Tensor &cache) {
+  return rows_of(seg) && covers(seg, cache) && seg.size(1) >= cache.size(1);
 }
 bool lse_ok(const at::Tensor &lse, const at::Tensor &q) {
   return lse.scalar_type() == at::kFloat && lse.is_contiguous() && lse.sizes() == q.sizes().slice(0, 3);
@@ -174,7 +180,7 @@ PyObject *append(PyObject *, PyObject *const *args, Py_ssize_t n) {
     s1f_desc d;
     if (!x.read(args, n, 5, 2, -1)) return kPython;
     auto &[ks, vs, kc, vc] = reinterpret_cast<const at::Tensor *(&)[4]>(x.t);
-    if (!same_layout(*ks, *vs) || !same_layout(*kc, *vc) || !cache_desc_of(*kc, *kc, &d) || !rows_of(*ks) ||
+    if (!same_layout(*ks, *vs) || !same_layout(*kc, *vc) || !cache_desc_of(*kc, *kc, &d) || !segment_ok(*ks, *kc) ||
         ks->scalar_type() != kc->scalar_type() || !x.read_stream())
       return kPython;
     void *const p[] = {ptr(ks), ptr(vs), ptr(kc), ptr(vc)};
@@ -189,8 +195,8 @@ PyObject *emit(PyObject *, PyObject *const *args, Py_ssize_t n) {
     s1f_desc d;
     if (!x.read(args, n, 5, 2, -1)) return kPython;
     auto &[dk, dv, ks, vs] = reinterpret_cast<const at::Tensor *(&)[4]>(x.t);
-    if (!same_layout(*dk, *dv) || !same_layout(*ks, *vs) || dk->scalar_type() != at::kFloat || !rows_of(*ks) ||
-        !cache_desc_of(*dk, *ks, &d) || !x.read_stream())
+    if (!same_layout(*dk, *dv) || !same_layout(*ks, *vs) || dk->scalar_type() != at::kFloat || !cache_desc_of(*dk, *ks, &d) ||
+        !segment_ok(*ks, *dk) || !x.read_stream())
       return kPython;
     void *const p[] = {ptr(dk), ptr(dv), ptr(ks), ptr(vs)};
     Unlocked u;

@@ -93,3 +93,22 @@ def test_same_refusals():
     out = q.as_subclass(Sub)   # a subclass goes through its own methods
     s1f.seg_attn_fwd(out, k, k, 0, out, lse)
     torch.cuda.synchronize()
+
+
+def test_compiled_forms_leave_mismatched_tensors_to_the_python_forms():
+    """-1: nothing has been launched (tests/test_host_tensor_calls.py: the Python forms refuse them)."""
+    native = binding._native()
+    e = lambda *shape, t=torch.bfloat16: torch.zeros(shape, dtype=t, device="cuda")
+    q, lse, ws = e(2, 2, 32, 64), e(2, 2, 32, t=torch.float32), e(1 << 16, t=torch.uint8)
+    for k in (e(1, 2, 32, 64), e(2, 2, 32, 32), e(2, 2, 32, 64, t=torch.float32)):
+        acc = torch.zeros_like(k, dtype=torch.float32)
+        assert native.fwd(q, k, k, 0, q, lse) == -1 and native.fwd_ws(q, k, k, 0, q, lse, ws) == -1
+        assert native.bwd(q, q, k, k, q, lse, 0, q, acc, acc, ws) == -1
+        assert native.bwd_noalloc(q, q, k, k, q, lse, 0, q, acc, acc) == -1
+    assert native.fwd(q, q, q, 0, q, lse.bfloat16()) == -1
+    cache, acc = e(2, 2, 64, 64), e(2, 2, 64, 64, t=torch.float32)
+    for seg in (e(1, 2, 8, 64), e(2, 1, 8, 64), e(2, 2, 8, 32)):
+        assert native.append(seg, seg, 0, cache, cache) == -1 and native.emit(acc, acc, 0, seg, seg) == -1
+    wide = e(3, 4, 8, 128)   # more than the cache takes: read in part, as ever
+    assert native.append(wide, wide, 0, cache, cache) == 0 and native.emit(acc, acc, 0, wide, wide) == 0
+    torch.cuda.synchronize()
