@@ -52,7 +52,8 @@ typedef enum {
 
 typedef enum {
   S1F_F32 = 0, /* q, k, v, out, dout, dq are fp32; products to fp32 precision (operands as three exact bf16 parts each,
-                  accumulated in fp32); a row that sees an operand that is not finite becomes NaN */
+                  accumulated in fp32).  Operands and products that are not finite give what fp32 arithmetic gives; rows
+                  (dK/dV: keys) whose result is not finite, and up to 31 beside each, then take far longer */
   S1F_BF16 = 1 /* q, k, v, out, dout, dq are bf16; bf16 MFMA with fp32 accumulation; probabilities and
                   score gradients are rounded to bf16 before their second product */
 } s1f_dtype;

@@ -15,8 +15,7 @@
 #pragma once
 #include <type_traits>
 
-#include "attn_tile.hpp"
-
+#include "attn_plain.hpp"
 
 namespace s1f {
 
@@ -25,10 +24,7 @@ namespace s1f {
 template <typename T, int D>
 S1F_DEV void bwd_row_stats(const AttnArgs &a, const typename Mat<T, D>::RowOp &dor, int64_t off, int64_t at, bool write, int j, float &nlse,
                            float &nd) {
-  typedef Mat<T, D> M;
-  typename M::RowOp o;
-  M::load_row(o, reinterpret_cast<const T *>(a.out) + off, j);
-  nd = -sum_over_rows(M::dot(dor, o));
+  nd = -sum_over_rows(Mat<T, D>::row_dot(dor, reinterpret_cast<const T *>(a.dout) + off, reinterpret_cast<const T *>(a.out) + off, j));
   const float lse = a.lse[at];
   nlse = -lse;
   if (write && j == 0) {
@@ -104,6 +100,14 @@ template <typename T, int D, int NC, int WAVES, bool STATS> S1F_DEV void bwd_dq_
   ring.issue(0);
   ring.issue(1);
 
+  auto row_stats = [&](const typename M::RowOp &dor, int64_t off, int64_t at, bool write, int j, float &nlse, float &d) {
+    if constexpr (STATS) {
+      bwd_row_stats<T, D>(a, dor, off, at, write, j, nlse, d);
+    } else {
+      nlse = -a.lse[at];
+      d = a.delta[a.ws_plane + at];
+    }
+  };
   typename M::RowOp q[NC], dor[NC];
   float nl[NC];    // -lse in log2 units
   f32x4 nd[NC];    // -delta
@@ -115,12 +119,7 @@ template <typename T, int D, int NC, int WAVES, bool STATS> S1F_DEV void bwd_dq_
     M::load_row(dor[cb], reinterpret_cast<const T *>(a.dout) + off, j);
     const int64_t at = ((int64_t)b * a.n_q_heads + h) * seg_len + rc;
     float nlse, d;
-    if constexpr (STATS) {
-      bwd_row_stats<T, D>(a, dor[cb], off, at, r < seg_len && uc.chunk == 0, j, nlse, d);
-    } else {
-      nlse = -a.lse[at];
-      d = a.delta[a.ws_plane + at];
-    }
+    row_stats(dor[cb], off, at, r < seg_len && uc.chunk == 0, j, nlse, d);
     nd[cb] = f32x4{d, d, d, d};
     nl[cb] = nlse * kLog2e;
   }
@@ -290,6 +289,26 @@ template <typename T, int D, int NC, int WAVES, bool STATS> S1F_DEV void bwd_dq_
     for (++k; k + 1 < n_kt; ++k, ring.end_step()) ring.template begin_step<false>(n_kt - 1 - k);
   }
 
+  if constexpr (sizeof(T) == 4) {
+    float bad = 0.f;
+#pragma unroll
+    for (int cb = 0; cb < NC; ++cb)
+#pragma unroll
+      for (int db = 0; db < DB; ++db) bad = add_if_not_finite(dq[cb][db], bad);
+    if (__builtin_expect(any_not_finite(bad), 0)) {
+      const T *k0 = reinterpret_cast<const T *>(a.k) + kv_first, *v0 = reinterpret_cast<const T *>(a.v) + kv_first;
+#pragma unroll
+      for (int cb = 0; cb < NC; ++cb) {
+        const int r_last = wrow0 + 16 * cb + 15, last = seg_off + (r_last < seg_len ? r_last : seg_len - 1);
+        const int pl = lane_id(), r = wrow0 + 16 * cb + (pl & 15), rc = r < seg_len ? r : seg_len - 1;
+        const int64_t off = qoff + (int64_t)rc * a.q_ss;
+        float nlse, d;   // (anew: not kept in registers across the loop)
+        row_stats(dor[cb], off, ((int64_t)b * a.n_q_heads + h) * seg_len + rc, false, pl >> 4, nlse, d);
+        dq_plain<D>(reinterpret_cast<const T *>(a.q) + off, reinterpret_cast<const T *>(a.dout) + off, k0, v0, a.kv_ss, seg_off + rc,
+                    last < BN * n_kt ? last + 1 : BN * n_kt, c, nlse * kLog2e, d, pl >> 4, dq[cb]);
+      }
+    }
+  }
   if (uc.slot >= 0) {   // a chunk: its unscaled share of the unit's dQ rows goes to the workspace
     float *pd = a.part + (int64_t)uc.slot * (BM * D);
 #pragma unroll
@@ -610,6 +629,32 @@ template <typename T, int D> S1F_DEV void bwd_dkdv_body(const AttnArgs &a, int i
     if constexpr (!ASYNC) {
       if (it + 1 < it_end) write_tile();
       __syncthreads();
+    }
+  }
+
+  if constexpr (sizeof(T) == 4) {
+    float bad = 0.f;
+#pragma unroll
+    for (int cb = 0; cb < CB; ++cb)
+#pragma unroll
+      for (int db = 0; db < DB; ++db) bad = add_if_not_finite(dv[cb][db], add_if_not_finite(dk[cb][db], bad));
+    if (__builtin_expect(any_not_finite(bad), 0)) {
+#pragma unroll
+      for (int cb = 0; cb < CB; ++cb) {
+        const int pl = lane_id(), pj = pl >> 4, key = wkey0 + 16 * cb + (pl & 15), kc = key < kv_len ? key : kv_len - 1;
+        PlainRow<D> k_row, v_row;
+        k_row.load(kbase + (int64_t)kc * a.kv_ss, pj);
+        v_row.load(vbase + (int64_t)kc * a.kv_ss, pj);
+#pragma unroll
+        for (int db = 0; db < DB; ++db) dk[cb][db] = dv[cb][db] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll 1
+        for (int it = it_begin; it < it_end; ++it) {
+          const int hq = hk * a.group + it / per_head, r0 = (qt_first + it % per_head) * BQ, r1 = r0 + BQ < seg_len ? r0 + BQ : seg_len;
+          const int64_t qoff = b * a.q_sb + hq * a.q_sh;
+          dkdv_plain<D>(k_row, v_row, reinterpret_cast<const T *>(a.q) + qoff, reinterpret_cast<const T *>(a.dout) + qoff, a.q_ss,
+                        a.delta + ((int64_t)b * a.n_q_heads + hq) * seg_len, a.ws_plane, r0, r1, kc - seg_off, c, pj, dk[cb], dv[cb]);
+        }
+      }
     }
   }
 

@@ -27,7 +27,7 @@
 #pragma once
 #include <type_traits>
 
-#include "attn_tile.hpp"
+#include "attn_plain.hpp"
 
 namespace s1f {
 
@@ -362,6 +362,25 @@ __global__ void __launch_bounds__(64 * WAVES, OCC) seg_attn_fwd_kernel(const Att
     for (++k; k + 1 < n_kt; ++k, ring.end_step()) ring.template begin_step<false>(n_kt - 1 - k);
   }
 
+  if constexpr (sizeof(T) == 4) {
+    float bad = 0.f;
+#pragma unroll
+    for (int cb = 0; cb < NC; ++cb) {
+      bad = fmaf(l[cb], 0.f, bad);
+#pragma unroll
+      for (int db = 0; db < DB; ++db) bad = add_if_not_finite(o[cb][db], bad);
+    }
+    if (__builtin_expect(any_not_finite(bad), 0)) {
+#pragma unroll
+      for (int cb = 0; cb < NC; ++cb) {
+        const int r_last = wrow0 + 16 * cb + 15, last = seg_off + (r_last < seg_len ? r_last : seg_len - 1);
+        const int pl = lane_id(), r = wrow0 + 16 * cb + (pl & 15), rc = r < seg_len ? r : seg_len - 1;
+        fwd_plain<D>(qb + (int64_t)rc * a.q_ss, kbase, vbase, a.kv_ss, seg_off + rc, last < BN * n_kt ? last + 1 : BN * n_kt, c, pl >> 4,
+                     o[cb], m[cb], l[cb]);
+        if (pl >= 16) l[cb] = 0.f;   // (the sum over the row's four lanes follows)
+      }
+    }
+  }
   if (uc.slot >= 0) {   // a chunk: unnormalised output rows, running maximum and row sum go to the workspace
     float *po = a.part + (int64_t)uc.slot * (BM * D);
     float *pml = a.part_ml + (int64_t)uc.slot * (BM * 2);

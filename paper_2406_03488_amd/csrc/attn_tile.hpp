@@ -139,7 +139,10 @@ template <int D> struct Mat<bf16_t, D> {
       o.f[k] = k < NKS ? *reinterpret_cast<const Frag *>(row + 32 * k + 8 * j)
                        : padded(*reinterpret_cast<const s16x4 *>(row + 32 * k + 4 * j));
   }
-  S1F_DEV static float dot(const RowOp &x, const RowOp &y) {
+  // the lane's share of the dot product of two rows, the first of which it has loaded
+  S1F_DEV static float row_dot(const RowOp &x, const bf16_t *, const bf16_t *y_row, int j) {
+    RowOp y;
+    load_row(y, y_row, j);
     float s = 0.f;
 #pragma unroll
     for (int k = 0; k < NK; ++k)
@@ -165,7 +168,8 @@ template <int D> struct Mat<bf16_t, D> {
 };
 
 // fp32 operands as three bf16 planes: x = p[0] + p[1] + p[2] exactly.  The first is cut off (rounded, the largest floats would
-// overflow), the others are rounded to nearest.  A value that is not finite becomes NaN.
+// overflow), the others are rounded to nearest.  The planes of a value that is not finite have a NaN among them, which every
+// product with them turns into: attn_plain.hpp computes what has become of such rows.
 // Why: the fp32 matrix instructions run at a sixteenth of the bf16 ones' rate (153 against 1353 TFLOP/s in large matrix
 // products here); six bf16 products for each take less than half as long, and accumulate fewer times.  Six, because the
 // first plane leaves at most 2^-7 |x| and the second at most 2^-16 |x|: what the three products left out contribute is below
@@ -250,13 +254,18 @@ template <int D> struct Mat<float, D> {
       o.f[k] = split3(at[0], k < NKS ? at[1] : f32x4{0.f, 0.f, 0.f, 0.f});
     }
   }
-  S1F_DEV static float dot(const RowOp &x, const RowOp &y) {
-    auto whole = [](const Planes &a, int e) { return ((float)a.p[0][e] + (float)a.p[1][e]) + (float)a.p[2][e]; };
+  // (from the values themselves: those that have no planes count as well)
+  S1F_DEV static float row_dot(const RowOp &, const float *x_row, const float *y_row, int j) {
     float s = 0.f;
 #pragma unroll
     for (int k = 0; k < NK; ++k)
 #pragma unroll
-      for (int e = 0; e < (k < NKS ? 8 : 4); ++e) s += whole(x.f[k], e) * whole(y.f[k], e);
+      for (int h = 0; h < (k < NKS ? 2 : 1); ++h) {
+        const int at = 32 * k + (k < NKS ? 8 : 4) * j + 4 * h;
+        const f32x4 x = *reinterpret_cast<const f32x4 *>(x_row + at), y = *reinterpret_cast<const f32x4 *>(y_row + at);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) s += x[e] * y[e];
+      }
     return s;
   }
   S1F_DEV static f32x4 mma_nat(int i, const Frag &a, const RowOp &o, f32x4 c) { return mma16(a, o.f[i % NK], c); }
