@@ -167,41 +167,41 @@ template <int D> struct Mat<bf16_t, D> {
   S1F_DEV static f32x4 quad(const f32x4 (&acc)[DB], int q) { return acc[q]; }
 };
 
-// fp32 operands as three bf16 planes: x = p[0] + p[1] + p[2] exactly.  The first is cut off (rounded, the largest floats would
-// overflow), the others are rounded to nearest.  The planes of a value that is not finite have a NaN among them, which every
-// product with them turns into: attn_plain.hpp computes what has become of such rows.
+// fp32 operands as three bf16 planes: x = p[0] + p[1] + p[2] exactly (above 2^-110), each what remains, rounded to nearest.  The
+// planes of a value that is not finite, or that rounds up past the largest float, have a NaN or an infinity among them, which
+// every product with them turns into: attn_plain.hpp computes what has become of such rows.
 // Why: the fp32 matrix instructions run at a sixteenth of the bf16 ones' rate (153 against 1353 TFLOP/s in large matrix
 // products here); six bf16 products for each take less than half as long, and accumulate fewer times.  Six, because the
-// first plane leaves at most 2^-7 |x| and the second at most 2^-16 |x|: what the three products left out contribute is below
-// 2^-23 of |a| |b| and of either sign.  Relative error against 64 bits, 8/2 heads, 500 rows behind 3000 keys, head_dim 128
-// (fp32 instructions / this): out 1.1e-6 / 0.9e-6, lse 5.7e-8 / 5.8e-8, dq 9.5e-7 / 8.0e-7, dk and dv 2.3e-6 / 2.0e-6; with
-// queries 30 times as large 3.6e-6 / 2.6e-6, 1.8e-7 / 1.2e-7, 1.2e-5 / 0.9e-5, 2.6e-5 / 2.3e-5.  (All planes cut off: lse up to 1.3
-// times further off than with fp32 instructions.)  32 heads, 2048 rows behind 8000 keys, us: head_dim 128 forward 2493 -> 1618,
-// dQ 3524 -> 1924, dK/dV 5005 -> 2696; 80 1631 -> 1028, 2347 -> 1363, 3274 -> 2005; 64 1293 -> 729, 1899 -> 956, 2277 -> 1252:
-// bound, like bf16, by the matrix pipe under the power limit (dQ and dK/dV execute 1350-1450 TFLOP/s of bf16 products).
+// first plane leaves at most 2^-8 |x| and the second at most 2^-17 |x|: what the three products left out contribute is at most
+// 2^-24 (1 + 2^-9) of |a| |b|, the rounding of one fp32 product, and of either sign.  (With a first plane cut off instead of rounded it
+// is 2^-22, and of one sign where operands fill their bits: scores of operands just below 1 + 2^-7 were 1.9e-7 off on average.)  Relative error against 64 bits, 8/2 heads, 500 rows behind 3000 keys, head_dim 128
+// (fp32 instructions / this): out 6.5e-7 / 4.3e-7, lse 5.60e-8 / 5.57e-8, dq 9.4e-7 / 8.3e-7, dk and dv 2.3e-6 / 2.0e-6; with
+// queries 30 times as large 3.4e-6 / 2.5e-6, 1.7e-7 / 1.3e-7, 1.2e-5 / 0.9e-5, 2.8e-5 / 2.4e-5.  32 heads, 2048 rows behind 8000
+// keys, us: head_dim 128 forward 2449 -> 1422, dQ 3500 -> 1909, dK/dV 4967 -> 2638; 80 1622 -> 1030, 2329 -> 1401, 3233 -> 1977; 64
+// 1289 -> 700, 1885 -> 968, 2253 -> 1260: bound, like bf16, by the matrix pipe under the power limit (dQ and dK/dV execute 1350-1450 TFLOP/s of bf16 products).
 struct Planes {
   bf16x8 p[3];
 };
+// two rounded values as one register; what is left of them
+S1F_DEV uint32_t round_pair(float &x, float &y) {
+  uint32_t w = __builtin_bit_cast(uint32_t, __builtin_convertvector((f32x2{x, y}), bf16x2));
+  asm("" : "+v"(w));   // (one conversion for both, which the compiler does anew for each to subtract it: f32 step of 8/2 heads 1078 -> 1043 us)
+  x -= __builtin_bit_cast(float, w << 16);
+  y -= __builtin_bit_cast(float, w & 0xffff0000u);
+  return w;
+}
 S1F_DEV Planes split3(f32x4 lo, f32x4 hi) {
-  Planes r;
-  uint32_t first[8];
+  u32x4 v[3];
 #pragma unroll
-  for (int e = 0; e < 8; ++e) {
-    const float x = e < 4 ? lo[e & 3] : hi[e & 3];
-    first[e] = __builtin_bit_cast(uint32_t, x);
-    const float rest = x - __builtin_bit_cast(float, first[e] & 0xffff0000u);
-    r.p[1][e] = (bf16_t)rest;
-    r.p[2][e] = (bf16_t)(rest - (float)r.p[1][e]);
+  for (int e = 0; e < 4; ++e) {
+    float x = e < 2 ? lo[2 * e] : hi[2 * e - 4], y = e < 2 ? lo[2 * e + 1] : hi[2 * e - 3];
+#pragma unroll
+    for (int p = 0; p < 3; ++p) v[p][e] = round_pair(x, y);
   }
-  u32x4 v;
-#pragma unroll
-  for (int e = 0; e < 4; ++e) v[e] = __builtin_amdgcn_perm(first[2 * e + 1], first[2 * e], 0x07060302u);   // the upper halves of both
-  r.p[0] = __builtin_bit_cast(bf16x8, v);
-  return r;
+  return Planes{{__builtin_bit_cast(bf16x8, v[0]), __builtin_bit_cast(bf16x8, v[1]), __builtin_bit_cast(bf16x8, v[2])}};
 }
 S1F_DEV void settle(Planes &x) { asm volatile("" : "+v"(x.p[0]), "+v"(x.p[1]), "+v"(x.p[2])); }
-// Product of two fp32 operands: the six products of planes that fp32 resolves (those left out are below 2^-24 of |a| |b|),
-// smallest first.
+// Product of two fp32 operands: the six products of planes that fp32 resolves (see Planes), smallest first.
 S1F_DEV f32x4 mma16(const Planes &a, const Planes &b, f32x4 c) {
   c = mma16(a.p[2], b.p[0], c);
   c = mma16(a.p[0], b.p[2], c);

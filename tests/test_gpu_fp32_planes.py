@@ -75,3 +75,21 @@ def test_largest_floats_and_infinities(d):
     again = torch.empty_like(out)
     s1f.seg_attn_fwd(q, k, v, 0, again, lse)
     assert torch.equal(again[:, :, :64], out[:, :, :64]) and not torch.isfinite(again[0, 0, 69]).any()
+
+
+@pytest.mark.parametrize("d", [64, 80, 128])
+def test_products_left_out_do_not_add_up(d):
+    """Scores of one product each, of operands just below a step of the second plane.  With planes cut off, a1 * b2 + a2 * b1 of
+    all of them is 2^-22 of the product and of one sign; rounded to nearest, what is left out is at most 2^-24 (each of the first two
+    planes leaves 2^-8, then 2^-9 of itself), of either sign here.  Read from lse = s of rows that see one key."""
+    heads = 4096
+    up = 1 + 2.0 ** -7 - 2.0 ** -16 + torch.arange(64, device="cuda", dtype=torch.float64) * 2.0 ** -23
+    x, y = up.repeat(64), up.repeat_interleave(64)
+    q, k = torch.zeros((1, heads, 1, d), device="cuda"), torch.zeros((1, heads, 1, d), device="cuda")
+    q[0, :, 0, 5], k[0, :, 0, 5] = x.float(), y.float()
+    out, lse = torch.empty_like(q), torch.empty((1, heads, 1), device="cuda")
+    s1f.seg_attn_fwd(q, k, torch.ones_like(k), 0, out, lse)
+    f = lambda v: float(np.float32(v))
+    unit = f(f(f(1 / d ** 0.5) * f(1.4426950408889634)) * 1.0) * f(0.6931471805599453)   # lse of a score of one, in the kernel's constants
+    err = lse[0, :, 0].double() / (x * y * unit) - 1
+    assert abs(err.mean().item()) <= 2.0 ** -24 and err.abs().max().item() <= 2.0 ** -21   # (single ones: three roundings as well)
