@@ -120,6 +120,7 @@ template <typename T, int D, int NC, int WAVES, bool STATS> S1F_DEV void bwd_dq_
     const int64_t at = ((int64_t)b * a.n_q_heads + h) * seg_len + rc;
     float nlse, d;
     row_stats(dor[cb], off, at, r < seg_len && uc.chunk == 0, j, nlse, d);
+    d *= M::UP * M::UP;
     nd[cb] = f32x4{d, d, d, d};
     nl[cb] = nlse * kLog2e;
   }
@@ -128,7 +129,7 @@ template <typename T, int D, int NC, int WAVES, bool STATS> S1F_DEV void bwd_dq_
   for (int cb = 0; cb < NC; ++cb)
 #pragma unroll
     for (int db = 0; db < DB; ++db) dq[cb][db] = f32x4{0.f, 0.f, 0.f, 0.f};
-  const float c = uniform(a.scale * kLog2e);
+  const float c = uniform(a.scale * kLog2e / (M::UP * M::UP));
   M rd;
   rd.init(lane);
 #pragma unroll
@@ -294,7 +295,10 @@ template <typename T, int D, int NC, int WAVES, bool STATS> S1F_DEV void bwd_dq_
 #pragma unroll
     for (int cb = 0; cb < NC; ++cb)
 #pragma unroll
-      for (int db = 0; db < DB; ++db) bad = add_if_not_finite(dq[cb][db], bad);
+      for (int db = 0; db < DB; ++db) {
+        bad = add_if_not_finite(dq[cb][db], bad);
+        dq[cb][db] *= 1.f / (M::UP * M::UP * M::UP);
+      }
     if (__builtin_expect(any_not_finite(bad), 0)) {
       const T *k0 = reinterpret_cast<const T *>(a.k) + kv_first, *v0 = reinterpret_cast<const T *>(a.v) + kv_first;
 #pragma unroll
@@ -305,7 +309,7 @@ template <typename T, int D, int NC, int WAVES, bool STATS> S1F_DEV void bwd_dq_
         float nlse, d;   // (anew: not kept in registers across the loop)
         row_stats(dor[cb], off, ((int64_t)b * a.n_q_heads + h) * seg_len + rc, false, pl >> 4, nlse, d);
         dq_plain<D>(reinterpret_cast<const T *>(a.q) + off, reinterpret_cast<const T *>(a.dout) + off, k0, v0, a.kv_ss, seg_off + rc,
-                    last < BN * n_kt ? last + 1 : BN * n_kt, c, nlse * kLog2e, d, pl >> 4, dq[cb]);
+                    last < BN * n_kt ? last + 1 : BN * n_kt, c * (M::UP * M::UP), nlse * kLog2e, d, pl >> 4, dq[cb]);
       }
     }
   }
@@ -434,7 +438,7 @@ template <typename T, int D> S1F_DEV void bwd_dkdv_body(const AttnArgs &a, int i
   // All iterations, or one chunk of them.
   const int it_begin = (int)((int64_t)uc.chunk * per_head * a.group / uc.n_chunks);
   const int it_end = (int)((int64_t)(uc.chunk + 1) * per_head * a.group / uc.n_chunks);
-  const float c = uniform(a.scale * kLog2e);
+  const float c = uniform(a.scale * kLog2e / (M::UP * M::UP));
   const bool w_active = wkey0 < kv_len;
 
   const lds_addr lds0 = to_lds_addr(smem);
@@ -543,7 +547,7 @@ template <typename T, int D> S1F_DEV void bwd_dkdv_body(const AttnArgs &a, int i
 #pragma unroll
       for (int x = 0; x < 2; ++x) fr[x] = operand(x);
 #pragma unroll
-      for (int rb = 0; rb < 2; ++rb) nl[rb] = lds_load<f32x4>(st + 64 * rb);
+      for (int rb = 0; rb < 2; ++rb) nl[rb] = lds_load<f32x4>(st + 64 * rb) * (M::UP * M::UP);
 #pragma unroll
       for (int x = 2; x < PR; ++x) fr[x] = operand(x);
       __builtin_amdgcn_sched_barrier(0);
@@ -553,7 +557,7 @@ template <typename T, int D> S1F_DEV void bwd_dkdv_body(const AttnArgs &a, int i
         for (int cb = 0; cb < CB; ++cb) {
           s[i / NK][cb] = M::mma_nat(i, fr[i % PR], kr[cb], i % NK ? s[i / NK][cb] : nl[i / NK]);
           if (cb + 1 == CB) used(i);
-          if (cb + 1 == CB && i + 2 >= NN) nd[i + 2 - NN] = lds_load<f32x4>(st + 4 * BQ + 64 * (i + 2 - NN));
+          if (cb + 1 == CB && i + 2 >= NN) nd[i + 2 - NN] = lds_load<f32x4>(st + 4 * BQ + 64 * (i + 2 - NN)) * (M::UP * M::UP);
           __builtin_amdgcn_sched_barrier(0);
         }
       auto probs = [&](int x0, int x1) {   // probabilities x0 .. x1-1 of the lane's 8 * CB
@@ -599,7 +603,7 @@ template <typename T, int D> S1F_DEV void bwd_dkdv_body(const AttnArgs &a, int i
       typename M::Slab pf[CB], ds[CB];
 #pragma unroll
       for (int cb = 0; cb < CB; ++cb) {
-        pf[cb] = M::slab(s[0][cb], s[1][cb]);
+        pf[cb] = M::slab_up(s[0][cb], s[1][cb]);
         M::settle_slab(pf[cb]);
       }
 #pragma unroll
@@ -637,7 +641,11 @@ template <typename T, int D> S1F_DEV void bwd_dkdv_body(const AttnArgs &a, int i
 #pragma unroll
     for (int cb = 0; cb < CB; ++cb)
 #pragma unroll
-      for (int db = 0; db < DB; ++db) bad = add_if_not_finite(dv[cb][db], add_if_not_finite(dk[cb][db], bad));
+      for (int db = 0; db < DB; ++db) {
+        bad = add_if_not_finite(dv[cb][db], add_if_not_finite(dk[cb][db], bad));
+        dv[cb][db] *= 1.f / (M::UP * M::UP);
+        dk[cb][db] *= 1.f / (M::UP * M::UP * M::UP);
+      }
     if (__builtin_expect(any_not_finite(bad), 0)) {
 #pragma unroll
       for (int cb = 0; cb < CB; ++cb) {
@@ -652,7 +660,8 @@ template <typename T, int D> S1F_DEV void bwd_dkdv_body(const AttnArgs &a, int i
           const int hq = hk * a.group + it / per_head, r0 = (qt_first + it % per_head) * BQ, r1 = r0 + BQ < seg_len ? r0 + BQ : seg_len;
           const int64_t qoff = b * a.q_sb + hq * a.q_sh;
           dkdv_plain<D>(k_row, v_row, reinterpret_cast<const T *>(a.q) + qoff, reinterpret_cast<const T *>(a.dout) + qoff, a.q_ss,
-                        a.delta + ((int64_t)b * a.n_q_heads + hq) * seg_len, a.ws_plane, r0, r1, kc - seg_off, c, pj, dk[cb], dv[cb]);
+                        a.delta + ((int64_t)b * a.n_q_heads + hq) * seg_len, a.ws_plane, r0, r1, kc - seg_off,
+                        c * (M::UP * M::UP), pj, dk[cb], dv[cb]);
         }
       }
     }

@@ -282,7 +282,7 @@ __global__ void __launch_bounds__(64 * WAVES, OCC) seg_attn_fwd_kernel(const Att
   for (int cb = 0; cb < NC; ++cb)
 #pragma unroll
     for (int db = 0; db < DB; ++db) o[cb][db] = f32x4{0.f, 0.f, 0.f, 0.f};
-  const float c = uniform(a.scale * kLog2e);
+  const float c = uniform(a.scale * kLog2e / (M::UP * M::UP));
   M rd;
   rd.init(lane);
 
@@ -368,15 +368,18 @@ __global__ void __launch_bounds__(64 * WAVES, OCC) seg_attn_fwd_kernel(const Att
     for (int cb = 0; cb < NC; ++cb) {
       bad = fmaf(l[cb], 0.f, bad);
 #pragma unroll
-      for (int db = 0; db < DB; ++db) bad = add_if_not_finite(o[cb][db], bad);
+      for (int db = 0; db < DB; ++db) {
+        bad = add_if_not_finite(o[cb][db], bad);
+        o[cb][db] *= 1.f / M::UP;
+      }
     }
     if (__builtin_expect(any_not_finite(bad), 0)) {
 #pragma unroll
       for (int cb = 0; cb < NC; ++cb) {
         const int r_last = wrow0 + 16 * cb + 15, last = seg_off + (r_last < seg_len ? r_last : seg_len - 1);
         const int pl = lane_id(), r = wrow0 + 16 * cb + (pl & 15), rc = r < seg_len ? r : seg_len - 1;
-        fwd_plain<D>(qb + (int64_t)rc * a.q_ss, kbase, vbase, a.kv_ss, seg_off + rc, last < BN * n_kt ? last + 1 : BN * n_kt, c, pl >> 4,
-                     o[cb], m[cb], l[cb]);
+        fwd_plain<D>(qb + (int64_t)rc * a.q_ss, kbase, vbase, a.kv_ss, seg_off + rc, last < BN * n_kt ? last + 1 : BN * n_kt,
+                     c * (M::UP * M::UP), pl >> 4, o[cb], m[cb], l[cb]);
         if (pl >= 16) l[cb] = 0.f;   // (the sum over the row's four lanes follows)
       }
     }

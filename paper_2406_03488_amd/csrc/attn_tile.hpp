@@ -79,6 +79,7 @@ template <typename T, int D> struct Mat;
 
 template <int D> struct Mat<bf16_t, D> {
   static constexpr int PRODUCTS = 1;   // matrix instructions per product of two operands
+  static constexpr float UP = 1.f;     // what operands are multiplied by (fp32: kUp)
   typedef Tile32<bf16_t, D> TL;
   typedef bf16x8 Frag;
   typedef bf16x8 Slab;
@@ -161,13 +162,14 @@ template <int D> struct Mat<bf16_t, D> {
     for (int e = 0; e < 4; ++e) { r[e] = (bf16_t)x[e]; r[4 + e] = (bf16_t)y[e]; }
     return r;
   }
+  S1F_DEV static Slab slab_up(f32x4 x, f32x4 y) { return slab(x, y); }
   S1F_DEV static void settle_slab(Slab &s) { settle(s); }
   S1F_DEV static void mma_tr(int t, Frag a, const Slab &s, f32x4 (&acc)[DB]) { acc[t] = mma16(a, s, acc[t]); }
   S1F_DEV static int quad_d0(int q, int j) { return 16 * q + 4 * j; }
   S1F_DEV static f32x4 quad(const f32x4 (&acc)[DB], int q) { return acc[q]; }
 };
 
-// fp32 operands as three bf16 planes: x = p[0] + p[1] + p[2] exactly (above 2^-110), each what remains, rounded to nearest.  The
+// fp32 operands as three bf16 planes: x = p[0] + p[1] + p[2] exactly (from 2^-110 on; see kUp), each what remains, rounded to nearest.  The
 // planes of a value that is not finite, or that rounds up past the largest float, have a NaN or an infinity among them, which
 // every product with them turns into: attn_plain.hpp computes what has become of such rows.
 // Why: the fp32 matrix instructions run at a sixteenth of the bf16 ones' rate (153 against 1353 TFLOP/s in large matrix
@@ -182,6 +184,13 @@ template <int D> struct Mat<bf16_t, D> {
 struct Planes {
   bf16x8 p[3];
 };
+// Operands are split 2^16 times as large as they are (score gradients, which come out of a product of two such operands, as they
+// come: 2^32 times), and accumulators divided in the end.  The last plane of a value below 2^-110 would lie under the smallest
+// bf16 number: values of 2^-120 alone gave results 3.5e-5 off, of 2^-125 1e-3.  Nothing changes for the others, up to what then no
+// longer has planes (operands and outputs from 2^112 on, scores and dV from 2^96, dQ and dK from 2^80: see attn_plain.hpp).  Not the
+// forward's probabilities, of which a row has one of at least 1: the bits of 2^-134 that those below 2^-110 lose are nothing beside
+// it.  Costs up to one vector instruction per operand element, 2 % of the forward at head_dim 64 and less elsewhere.
+constexpr float kUp = 65536.f;
 // two rounded values as one register; what is left of them
 S1F_DEV uint32_t round_pair(float &x, float &y) {
   uint32_t w = __builtin_bit_cast(uint32_t, __builtin_convertvector((f32x2{x, y}), bf16x2));
@@ -227,6 +236,7 @@ template <typename M> S1F_DEV void end_slot() {
 
 template <int D> struct Mat<float, D> {
   static constexpr int PRODUCTS = 6;
+  static constexpr float UP = kUp;
   typedef Mat<bf16_t, D> B;
   typedef Tile32<float, D> TL;
   typedef Planes Frag;
@@ -251,7 +261,7 @@ template <int D> struct Mat<float, D> {
 #pragma unroll
     for (int k = 0; k < NK; ++k) {
       const f32x4 *at = reinterpret_cast<const f32x4 *>(row + 32 * k + (k < NKS ? 8 : 4) * j);
-      o.f[k] = split3(at[0], k < NKS ? at[1] : f32x4{0.f, 0.f, 0.f, 0.f});
+      o.f[k] = split3(at[0] * kUp, k < NKS ? at[1] * kUp : f32x4{0.f, 0.f, 0.f, 0.f});
     }
   }
   // (from the values themselves: those that have no planes count as well)
@@ -271,6 +281,7 @@ template <int D> struct Mat<float, D> {
   S1F_DEV static f32x4 mma_nat(int i, const Frag &a, const RowOp &o, f32x4 c) { return mma16(a, o.f[i % NK], c); }
   S1F_DEV static f32x4 mma_op(int, const Frag &a, const Frag &b, f32x4 c) { return mma16(a, b, c); }
   S1F_DEV static Slab slab(f32x4 x, f32x4 y) { return split3(x, y); }
+  S1F_DEV static Slab slab_up(f32x4 x, f32x4 y) { return split3(x * kUp, y * kUp); }
   S1F_DEV static void settle_slab(Slab &s) { settle(s); }
   S1F_DEV static void mma_tr(int t, const Frag &a, const Slab &s, f32x4 (&acc)[DB]) { acc[t] = mma16(a, s, acc[t]); }
   S1F_DEV static int quad_d0(int q, int j) { return B::quad_d0(q, j); }
@@ -404,7 +415,7 @@ template <int D, int WAVES> struct SplitPairCopy {
     const int kq = piece(i);
     if (STEP * i + STEP > NP && kq >= NP) return;
     const f32x4 none = {0.f, 0.f, 0.f, 0.f};
-    const Planes x = split3(held[i][h], none);
+    const Planes x = split3(held[i][h] * kUp, none);
     const lds_addr at = opaque(stage + dst + (unsigned)(kq * 1024 + 8 * h));
     typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
 #pragma unroll

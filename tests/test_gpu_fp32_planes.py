@@ -93,3 +93,32 @@ def test_products_left_out_do_not_add_up(d):
     unit = f(f(f(1 / d ** 0.5) * f(1.4426950408889634)) * 1.0) * f(0.6931471805599453)   # lse of a score of one, in the kernel's constants
     err = lse[0, :, 0].double() / (x * y * unit) - 1
     assert abs(err.mean().item()) <= 2.0 ** -24 and err.abs().max().item() <= 2.0 ** -21   # (single ones: three roundings as well)
+
+
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("power", [-125, -115, 60, 100])
+@pytest.mark.parametrize("small", ["v", "do", "q", "k"])
+def test_operands_at_the_ends_of_the_range(d, power, small):
+    """One operand 2^power times as large (of large queries or keys the other as much smaller): the same relative errors of what is
+    linear in it.  At 2^-125 one value in three is a subnormal number, with the bits that it has."""
+    g = torch.Generator(device="cuda")
+    g.manual_seed(d + power)
+    x = {n: torch.empty((1, 2, 150, d), device="cuda").normal_(generator=g) for n in ("q", "k", "v", "do")}
+    x[small] = x[small] * 2.0 ** power
+    if small in ("q", "k") and power > 0:
+        other = "k" if small == "q" else "q"
+        x[other] = x[other] * 2.0 ** -power
+    got = _call(x["q"], x["k"], x["v"], x["do"], 0)
+    names = {"v": ("out",), "do": ("dv",), "q": ("dk", "out", "lse"), "k": ("dq", "out", "lse")}[small]
+    _relative_errors_of(names, got, x)
+
+
+def _relative_errors_of(names, got, x):
+    host = lambda t: t[0].double().cpu().numpy()
+    out, lse = A.segment_forward(host(x["q"]), host(x["k"]), host(x["v"]), 0)
+    dq, dk, dv = A.segment_backward(host(x["do"]), host(x["q"]), host(x["k"]), host(x["v"]), 0)
+    want = {"out": out, "lse": lse, "dq": dq, "dk": dk, "dv": dv}
+    for name in names:
+        y = host(got[name])
+        top = np.abs(want[name]).max()
+        assert np.linalg.norm(y / top - want[name] / top) <= 2e-6 * np.linalg.norm(want[name] / top), name   # (a last plane lost: 1e-3, 1e-6 at 2^-115)
