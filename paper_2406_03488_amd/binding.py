@@ -3,6 +3,7 @@ from __future__ import annotations
 
 import ctypes
 import os
+import warnings
 
 _HERE = os.path.dirname(os.path.abspath(__file__))
 _LIB_PATH = os.path.join(_HERE, "libs1f.so")
@@ -270,6 +271,26 @@ def _stream_ptr():
 _calls, _calls_of = None, None
 
 
+class _PythonForms:
+    """In place of the compiled forms where they cannot be loaded: every call is left to the Python code."""
+    fwd = fwd_ws = bwd = bwd_noalloc = append = emit = staticmethod(lambda *args: -1)
+
+
+def _load_calls():
+    """The module of the compiled forms.  It reads tensors by the layout that they have in the torch it was built against."""
+    import torch
+    try:
+        from . import _torch_calls
+        built_for = getattr(_torch_calls, "torch_version", None)
+        if built_for != torch.__version__.split("+")[0]:
+            raise ImportError(f"_torch_calls was built for torch {built_for}, this is {torch.__version__}")
+        return _torch_calls
+    except ImportError as e:
+        warnings.warn(f"tensor calls in their Python forms, 8 to 12 us of host time each: {e}; "
+                      "build with `python -m paper_2406_03488_amd.build`", RuntimeWarning, stacklevel=4)
+        return None
+
+
 def _native():
     """The compiled forms of the tensor calls below (csrc/torch_calls.cpp), bound to the loaded library.  They return a status,
     or -1 for arguments that are not the plain case, which the Python code then handles or refuses."""
@@ -277,10 +298,10 @@ def _native():
     lib = _lib or load_library()
     if _calls_of is not lib:
         import torch
-        try:
-            from . import _torch_calls
-        except ImportError as e:
-            raise ImportError(f"{e}: build it with `python -m paper_2406_03488_amd.build`") from e
+        _torch_calls = _load_calls()
+        if _torch_calls is None:
+            _calls, _calls_of = _PythonForms, lib
+            return _calls
         entry = (lib.s1f_seg_attn_fwd, lib.s1f_seg_attn_fwd_ws, lib.s1f_seg_attn_bwd, lib.s1f_seg_attn_bwd_noalloc,
                  lib.s1f_kv_append, lib.s1f_kv_grad_emit)
         _torch_calls.bind(*[ctypes.cast(f, ctypes.c_void_p).value for f in entry], torch.cuda.current_device,

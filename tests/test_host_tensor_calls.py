@@ -1,5 +1,6 @@
 """What the Python forms of the tensor calls refuse before the library is called: tensors that its kernels would read or write past.  The
 library is replaced by one that only counts its calls, so that nothing reaches a device."""
+import sys
 import types
 
 import pytest
@@ -87,3 +88,26 @@ def test_segment_smaller_than_the_cache_is_refused(library, seg_shape, taken):
             with pytest.raises(ValueError):
                 call()
     assert len(library.calls) == (2 if taken else 0)
+
+
+@pytest.mark.parametrize("broken", ["missing", "of another torch"])
+def test_without_the_compiled_forms_the_python_forms_serve(monkeypatch, broken):
+    """Only libs1f.so is needed: a module of the compiled forms that is missing, or was built against another torch, costs a warning."""
+    name = "paper_2406_03488_amd._torch_calls"
+    module = None if broken == "missing" else types.SimpleNamespace(torch_version="1.0.0")
+    monkeypatch.setitem(sys.modules, name, module)
+    if module is None:
+        monkeypatch.delattr(s1f, "_torch_calls", raising=False)
+    else:
+        monkeypatch.setattr(s1f, "_torch_calls", module, raising=False)
+    monkeypatch.setattr(binding, "_calls_of", None)
+    monkeypatch.setattr(binding, "_calls", None)
+    with pytest.warns(RuntimeWarning, match="Python forms"):
+        native = binding._native()
+    assert all(getattr(native, n)(None) == -1 for n in NAMES)
+    lib = Library()
+    monkeypatch.setattr(binding, "load_library", lambda: lib)
+    monkeypatch.setattr(binding, "_stream_ptr", lambda: 0)
+    q, lse = bf16(2, 2, 32, 64), torch.zeros(2, 2, 32)
+    s1f.seg_attn_fwd(q, q, q, 0, q, lse)   # (and no second warning)
+    assert lib.calls == ["s1f_seg_attn_fwd"]
