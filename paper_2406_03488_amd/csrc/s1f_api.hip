@@ -101,16 +101,17 @@ template <typename T, typename F> int in_halves(const s1f_desc *d, const AttnArg
 }
 
 // Kernels that need more than 64 KiB of LDS have to be told so once per device; `prepare` does that the first time
-// a kernel instantiation is used on the current device (a template: one flag set per instantiation).
+// a kernel is used on the current device (a template over the kernel itself, not its type, which all of them share: one set of
+// flags each).
 constexpr int kMaxDevices = 64;
-template <typename K> int prepare(K kernel, int lds_bytes) {
+template <auto KERNEL> int prepare(int lds_bytes) {
   if (lds_bytes <= 64 * 1024) return S1F_OK;
   static std::atomic<bool> done[kMaxDevices];
   int dev = 0;
   if (hipGetDevice(&dev) != hipSuccess) return S1F_EDEVICE;
   const bool cached = dev >= 0 && dev < kMaxDevices;
   if (cached && done[dev].load(std::memory_order_acquire)) return S1F_OK;
-  if (hipFuncSetAttribute(reinterpret_cast<const void *>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize,
+  if (hipFuncSetAttribute(reinterpret_cast<const void *>(KERNEL), hipFuncAttributeMaxDynamicSharedMemorySize,
                           lds_bytes) != hipSuccess)
     return S1F_EDEVICE;
   if (cached) done[dev].store(true, std::memory_order_release);
@@ -244,7 +245,7 @@ void plan_units(SplitPlan *best, double *t, int nc, int64_t n_tiles, int64_t uni
 }
 
 // Looked up once per kernel and device.
-template <typename K> Slots resident_slots(K kernel, int lds_bytes, std::atomic<int64_t> *cache, int threads = 256) {
+template <auto KERNEL> Slots resident_slots(int lds_bytes, std::atomic<int64_t> *cache, int threads) {
   Slots s;
   int dev = 0;
   if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= kMaxDevices) {
@@ -258,8 +259,8 @@ template <typename K> Slots resident_slots(K kernel, int lds_bytes, std::atomic<
     return s;
   }
   int per_cu = 0, cus = 0;
-  if (prepare(kernel, lds_bytes) != S1F_OK ||
-      hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, reinterpret_cast<const void *>(kernel), threads,
+  if (prepare<KERNEL>(lds_bytes) != S1F_OK ||
+      hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, reinterpret_cast<const void *>(KERNEL), threads,
                                                    (size_t)lds_bytes) != hipSuccess ||
       hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || per_cu <= 0 || cus <= 0) {
     (void)hipGetLastError();
@@ -283,12 +284,12 @@ void fill_launch(AttnArgs *a, int64_t n_bh, int tile_major, const SplitPlan &p) 
   a->n_split_units = (int32_t)p.n_split_units;
   a->bm = 64 * p.nc;
 }
-template <typename K> int launch(K kernel, int lds_bytes, const SplitPlan &p, int64_t n_bh, AttnArgs a, hipStream_t st, int threads = 256) {
+template <auto KERNEL> int launch(int lds_bytes, const SplitPlan &p, int64_t n_bh, AttnArgs a, hipStream_t st, int threads) {
   if (p.n_tiles * n_bh > 0x7fffffff || !one_launch(p.grid(), threads)) return S1F_EUNSUPPORTED;
-  const int rc = prepare(kernel, lds_bytes);
+  const int rc = prepare<KERNEL>(lds_bytes);
   if (rc != S1F_OK) return rc;
   void *params[] = {&a};
-  const hipError_t e = hipLaunchKernel(reinterpret_cast<const void *>(kernel), dim3((unsigned)p.grid()), dim3(threads), params,
+  const hipError_t e = hipLaunchKernel(reinterpret_cast<const void *>(KERNEL), dim3((unsigned)p.grid()), dim3(threads), params,
                                        (size_t)lds_bytes, st);
   return e == hipSuccess ? S1F_OK : S1F_EDEVICE;
 }
@@ -318,25 +319,25 @@ template <typename T, int D> struct FwdFamily {
   static constexpr StepUs cost = Cost<T, D>::fwd;
   static constexpr int64_t row_bytes = D * 4 + 8;   // of a partial result: output, running maximum, row sum
     static constexpr int threads(int nc) { return 64 * Shape<T, D>::waves(nc); }
-  template <int NC> static auto kernel() {
+  template <int NC> static constexpr auto kernel() {
     constexpr int W = Shape<T, D>::waves(NC);
     return seg_attn_fwd_kernel<T, D, 4 * NC / W, Shape<T, D>::fwd_occ(NC), W>;
   }
-  static auto rest_kernel() { return seg_attn_fwd_kernel<T, D, 1, Shape<T, D>::fwd_occ(1), 4, true>; }
+  static constexpr auto rest_kernel() { return seg_attn_fwd_kernel<T, D, 1, Shape<T, D>::fwd_occ(1), 4, true>; }
 };
 template <typename T, int D> struct DqFamily {
   static constexpr int MAX = Shape<T, D>::DQ_MAX, LDS = TileRing<T, D>::LDS_BYTES;
   static constexpr StepUs cost = Cost<T, D>::dq;
   static constexpr int64_t row_bytes = D * 4;
     static constexpr int threads(int nc) { return 64 * Shape<T, D>::waves(nc); }
-  template <int NC> static auto kernel() {
+  template <int NC> static constexpr auto kernel() {
     constexpr int W = Shape<T, D>::waves(NC);
     return seg_attn_bwd_dq_kernel<T, D, 4 * NC / W, Shape<T, D>::dq_occ(NC), W>;
   }
 };
 template <typename F, int NC> Slots family_slots() {
   static std::atomic<int64_t> cache[kMaxDevices];
-  return resident_slots(F::template kernel<NC>(), F::LDS, cache, F::threads(NC));
+  return resident_slots<F::template kernel<NC>()>(F::LDS, cache, F::threads(NC));
 }
 template <typename F, int NC> void plan_rows_nc(const s1f_desc *d, int64_t seg_off, int64_t seg_len, int64_t cap, SplitPlan *best, double *t) {
   const Slots s = family_slots<F, NC>();
@@ -359,9 +360,9 @@ template <typename F> SplitPlan plan_rows(const s1f_desc *d, int64_t seg_off, in
 }
 template <typename F> int launch_rows(const SplitPlan &p, int64_t n_bh, const AttnArgs &a, hipStream_t st) {
   if constexpr (F::MAX >= 3)
-    if (p.nc == 3) return launch(F::template kernel<3>(), F::LDS, p, n_bh, a, st, F::threads(3));
-  if (p.nc == 2) return launch(F::template kernel<2>(), F::LDS, p, n_bh, a, st, F::threads(2));
-  return launch(F::template kernel<1>(), F::LDS, p, n_bh, a, st, F::threads(1));
+    if (p.nc == 3) return launch<F::template kernel<3>()>(F::LDS, p, n_bh, a, st, F::threads(3));
+  if (p.nc == 2) return launch<F::template kernel<2>()>(F::LDS, p, n_bh, a, st, F::threads(2));
+  return launch<F::template kernel<1>()>(F::LDS, p, n_bh, a, st, F::threads(1));
 }
 
 template <typename T, int D> size_t fwd_workspace(const SplitPlan &p) {
@@ -444,7 +445,7 @@ template <typename T, int D> int fwd_run(const s1f_desc *d, AttnArgs a, const Sp
     a.first_id = (int32_t)whole;
     a.n_split = p.nc;
     a.n_split_units = (int32_t)rest.n_split_units;
-    return launch(F::rest_kernel(), F::LDS, rest, n_bh, a, st, F::threads(1));
+    return launch<F::rest_kernel()>(F::LDS, rest, n_bh, a, st, F::threads(1));
   }
   const int rc = launch_rows<F>(p, n_bh, a, st);
   if (rc != S1F_OK || p.n_split_units == 0) return rc;
@@ -473,7 +474,7 @@ template <typename T, int D> struct DkdvFamily {
   typedef BwdDkdvCfg<T, D> Cfg;
   static constexpr int LDS = Cfg::LDS_BYTES, THREADS = 64 * Cfg::WAVES;
   static constexpr int64_t part_bytes = 2 * (int64_t)Cfg::BNW * D * 4;
-  static auto kernel() { return seg_attn_bwd_dkdv_kernel<T, D, Shape<T, D>::KWGS>; }
+  static constexpr auto kernel() { return seg_attn_bwd_dkdv_kernel<T, D, Shape<T, D>::KWGS>; }
   static SplitPlan plan(const s1f_desc *d, int64_t seg_off, int64_t seg_len, int64_t cap) {
     static std::atomic<int64_t> cache[kMaxDevices];
     const int64_t kv_len = seg_off + seg_len, units = (kv_len + Cfg::BNW - 1) / Cfg::BNW * d->n_kv_heads * d->batch;
@@ -481,7 +482,7 @@ template <typename T, int D> struct DkdvFamily {
     p.n_tiles = (kv_len + Cfg::BNW - 1) / Cfg::BNW;
     p.n_whole = units;
     if (cap <= 0) return p;
-    const Slots s = resident_slots(kernel(), LDS, cache, THREADS);
+    const Slots s = resident_slots<kernel()>(LDS, cache, THREADS);
     if (s.total <= 0) return p;
     const double most = (double)(d->n_q_heads / d->n_kv_heads) * (double)((seg_len + 31) / 32);
     const double mean = most * ((double)seg_off + 0.5 * (double)seg_len) / (double)kv_len;
@@ -595,11 +596,11 @@ template <typename T, int D> int bwd_dkdv_impl(const s1f_desc *d, const AttnArgs
       return bwd_dkdv_impl<T, D>(half, x, p.uncut((int64_t)d->n_kv_heads * half->batch), st);
     });
   const AttnArgs a = dkdv_args<T, D>(d, a0, p, 0);
-  const int rc = launch(F::kernel(), F::LDS, p, a.n_bh, a, st, F::THREADS);
+  const int rc = launch<F::kernel()>(F::LDS, p, a.n_bh, a, st, F::THREADS);
   return rc == S1F_OK ? launch_bwd_merge<T, D>(a, a, 0, p.n_split_units, st) : rc;
 }
 
-template <typename T, int D, int NC> auto both_kernel() {
+template <typename T, int D, int NC> constexpr auto both_kernel() {
   constexpr int W = Shape<T, D>::waves(NC);
   return seg_attn_bwd_kernel<T, D, 4 * NC / W, Shape<T, D>::BOTH_OCC, W>;
 }
@@ -607,7 +608,7 @@ template <typename T, int D> constexpr int kBothLds =
     TileRing<T, D>::LDS_BYTES > BwdDkdvCfg<T, D>::LDS_BYTES ? TileRing<T, D>::LDS_BYTES : BwdDkdvCfg<T, D>::LDS_BYTES;
 template <typename T, int D, int NC>
 int launch_both(const BwdPlans &p, AttnArgs aq, AttnArgs ak, int dq_first, hipStream_t st) {
-  const int rc = prepare(both_kernel<T, D, NC>(), kBothLds<T, D>);
+  const int rc = prepare<both_kernel<T, D, NC>()>(kBothLds<T, D>);
   if (rc != S1F_OK) return rc;
   int first = (int)(dq_first ? p.q_both.grid() : p.k.grid());
   void *params[] = {&aq, &ak, &first, &dq_first};
@@ -632,13 +633,13 @@ template <typename T, int D> int bwd_both_impl(const s1f_desc *d, const AttnArgs
 
 // What a launch of either backward kernel could be refused for before it reaches the runtime.
 template <typename F, int NC> int prepare_rows() {
-  const int rc = prepare(F::template kernel<NC>(), F::LDS);
+  const int rc = prepare<F::template kernel<NC>()>(F::LDS);
   if constexpr (NC > 1) return rc != S1F_OK ? rc : prepare_rows<F, NC - 1>();
   return rc;
 }
 template <typename T, int D, int NC> int prepare_both() {
   int rc = S1F_OK;
-  if constexpr (Shape<T, D>::both(NC)) rc = prepare(both_kernel<T, D, NC>(), kBothLds<T, D>);
+  if constexpr (Shape<T, D>::both(NC)) rc = prepare<both_kernel<T, D, NC>()>(kBothLds<T, D>);
   if constexpr (NC > 1) return rc != S1F_OK ? rc : prepare_both<T, D, NC - 1>();
   return rc;
 }
@@ -651,7 +652,7 @@ template <typename T, int D> int bwd_ready_impl(const s1f_desc *d, const AttnArg
     return S1F_EUNSUPPORTED;
   if (p.both) return prepare_both<T, D, DqFamily<T, D>::MAX>();
   const int rc = prepare_rows<DqFamily<T, D>, DqFamily<T, D>::MAX>();
-  return rc != S1F_OK ? rc : prepare(DkdvFamily<T, D>::kernel(), DkdvFamily<T, D>::LDS);
+  return rc != S1F_OK ? rc : prepare<DkdvFamily<T, D>::kernel()>(DkdvFamily<T, D>::LDS);
 }
 
 // What s1f_launch_plan reports.

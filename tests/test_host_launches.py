@@ -1,0 +1,58 @@
+"""What the library asks of the runtime, recorded by one that runs nothing (recording_runtime.c): in a process of its own, without torch."""
+import os
+import subprocess
+import sys
+
+import pytest
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+MAX_DYNAMIC_LDS = 8   # hipFuncAttributeMaxDynamicSharedMemorySize
+
+DRIVER = """
+import ctypes, sys
+ctypes.CDLL(sys.argv[1], mode=ctypes.RTLD_GLOBAL)
+import paper_2406_03488_amd as s1f
+from paper_2406_03488_amd.binding import Desc
+lib = s1f.load_library()
+p = 4096   # (no address is looked at)
+for dtype in (0, 1):
+    for d in (64, 80, 128):
+        for hq, hk, off, m in eval(sys.argv[2]):
+            desc = ctypes.byref(Desc(1, hq, hk, d, dtype, 0, hq * m * d, m * d, d, hk * (off + m) * d, (off + m) * d, d, off + m))
+            big = 1 << 40
+            rc = [lib.s1f_seg_attn_fwd(desc, p, p, p, off, m, p, p, None), lib.s1f_seg_attn_fwd_ws(desc, p, p, p, off, m, p, p, p, big, None),
+                  lib.s1f_seg_attn_bwd(desc, p, p, p, p, p, p, off, m, p, p, p, p, big, None),
+                  lib.s1f_seg_attn_bwd_noalloc(desc, p, p, p, p, p, p, off, m, p, p, p, None),
+                  lib.s1f_seg_attn_bwd_dq(desc, p, p, p, p, p, p, off, m, p, p, big, None),
+                  lib.s1f_seg_attn_bwd_dkdv(desc, p, p, p, p, p, off, m, p, p, p, big, None)]
+            assert rc == [0] * 6, rc
+"""
+
+
+@pytest.fixture(scope="module")
+def runtime(tmp_path_factory):
+    so = str(tmp_path_factory.mktemp("runtime") / "recording.so")
+    subprocess.run(["gcc", "-O1", "-shared", "-fPIC", "-Wall", "-Werror", "-o", so, os.path.join(ROOT, "tests", "recording_runtime.c")], check=True)
+    return so
+
+
+def record(runtime, tmp_path, shapes):
+    path = str(tmp_path / "record")
+    env = dict(os.environ, RECORD=path, PYTHONPATH=ROOT)
+    run = subprocess.run([sys.executable, "-c", DRIVER, runtime, repr(shapes)], env=env, capture_output=True, text=True, cwd=ROOT)
+    assert run.returncode == 0, run.stderr
+    return [line.split() for line in open(path)]
+
+
+def test_every_kernel_is_told_of_its_lds_before_it_runs(runtime, tmp_path):
+    lines = record(runtime, tmp_path, [(2, 1, 0, 40), (32, 32, 700, 321), (64, 8, 5000, 3214), (56, 56, 9203, 5220), (112, 112, 0, 193)])
+    told, launched = {}, set()
+    for what, name, *rest in lines:
+        if what == "attribute":
+            assert int(rest[0]) == MAX_DYNAMIC_LDS
+            told[name] = int(rest[1])
+        else:
+            lds = int(rest[2])
+            launched.add((name, lds))
+            assert lds <= 64 * 1024 or told.get(name, 0) >= lds, name
+    assert sum(lds > 64 * 1024 for _, lds in launched) >= 25   # (one flag per type of kernel told two of them)
