@@ -216,13 +216,22 @@ size_t s1f_static_scratch_rows(void);
 /* How a call of this shape is launched on the current device: a question about speed only, for tests and measurements.
  * HOST function; nothing is enqueued.  `launch` names the call: the forward without and with a workspace, and the two
  * kernels of the backward (s1f_seg_attn_bwd and its halves).  Writes
- *   plan[0]  rows (dK/dV: keys) per unit, the work of one workgroup
+ *   plan[0]  rows (dK/dV: keys) per unit, the work of one workgroup (S1F_PLAN_DQ: of the half by itself, see s1f_launch_paths)
  *   plan[1]  units that are left whole
  *   plan[2]  units cut along the keys (dK/dV: along the queries), plan[3] the chunks per cut unit
  *   plan[4]  forward: units whose rows run in a second launch of 64-row tiles
  * Errors: S1F_EINVAL, S1F_EUNSUPPORTED, S1F_ERANGE as for the calls themselves. */
 typedef enum { S1F_PLAN_FWD = 0, S1F_PLAN_FWD_WS = 1, S1F_PLAN_DQ = 2, S1F_PLAN_DKDV = 3 } s1f_launch;
 int s1f_launch_plan(const s1f_desc *desc, int32_t launch, int64_t seg_off, int64_t seg_len, int64_t *plan);
+/* ... and what the plans do not say; a question of the same kind, with the same errors.  Writes
+ *   paths[0]  1 if s1f_seg_attn_bwd, given the workspace that it asks for, runs its halves in one launch (else in two, as
+ *             s1f_seg_attn_bwd_dq and _dkdv do)
+ *   paths[1]  rows per unit of its dQ half (in one launch this may be more than the plan of S1F_PLAN_DQ: same results)
+ *   paths[2]  1 if they run in one launch and the units of the dQ half come first
+ *   paths[3]  1 if s1f_seg_attn_bwd_noalloc runs them in one launch
+ *   paths[4]  forward without a workspace: 64-row tiles per (batch, head) that the partly filled last units have in the second
+ *             launch (0: those units stay in the first) */
+int s1f_launch_paths(const s1f_desc *desc, int64_t seg_off, int64_t seg_len, int64_t *paths);
 
 /* The two data movements on either side of a segment's attention calls (Section 3.2: the keys and values of
  * all preceding tokens are retained; gradients of earlier tokens are accumulated until the backward passes

@@ -6,7 +6,7 @@ memory and the current stream.  There is no fallback: if the shared library is m
 compute entry points raises.
 """
 from .binding import (COST_ADDITIVE, COST_LITERAL, PLAN_DKDV, PLAN_DQ, PLAN_FWD, PLAN_FWD_WS, Desc, S1FError,
-                      bwd_workspace_bytes, fwd_workspace_bytes, launch_plan,
+                      bwd_workspace_bytes, fwd_workspace_bytes, launch_paths, launch_plan,
                       kv_append, kv_grad_emit, seg_attn_fwd_ws,
                       library_path, load_library, partition, partition_ex, partition_rebalance, pipeline_simulate,
                       seq1f1b_interleaved_order, seq1f1b_interleaved_warmup, seg_attn_bwd, seg_attn_bwd_dkdv, seg_attn_bwd_dq,
@@ -14,7 +14,7 @@ from .binding import (COST_ADDITIVE, COST_LITERAL, PLAN_DKDV, PLAN_DQ, PLAN_FWD,
                       seq1f1b_warmup, strerror, version)
 
 __all__ = ["COST_ADDITIVE", "COST_LITERAL", "PLAN_DKDV", "PLAN_DQ", "PLAN_FWD", "PLAN_FWD_WS", "Desc", "S1FError",
-           "bwd_workspace_bytes", "fwd_workspace_bytes", "launch_plan",
+           "bwd_workspace_bytes", "fwd_workspace_bytes", "launch_paths", "launch_plan",
            "kv_append", "kv_grad_emit", "seg_attn_fwd_ws",
            "library_path", "load_library", "partition", "partition_ex", "partition_rebalance", "pipeline_simulate",
            "seq1f1b_interleaved_order", "seq1f1b_interleaved_warmup",

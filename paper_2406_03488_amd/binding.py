@@ -86,6 +86,8 @@ def load_library():
     lib.s1f_bwd_workspace_bytes.restype = sz
     lib.s1f_launch_plan.argtypes = [dp, i32, i64, i64, ctypes.POINTER(i64)]
     lib.s1f_launch_plan.restype = ctypes.c_int
+    lib.s1f_launch_paths.argtypes = [dp, i64, i64, ctypes.POINTER(i64)]
+    lib.s1f_launch_paths.restype = ctypes.c_int
     lib.s1f_kv_append.argtypes = [dp, vp, vp, i64, i64, i64, i64, i64, vp, vp, vp]
     lib.s1f_kv_append.restype = ctypes.c_int
     lib.s1f_kv_grad_emit.argtypes = [dp, vp, vp, i64, i64, vp, vp, i64, i64, i64, vp]
@@ -373,6 +375,16 @@ def launch_plan(q_seg, k_prefix, seg_off: int, launch: int):
     if rc != 0:
         raise S1FError(rc, "s1f_launch_plan")
     return tuple(plan)
+
+
+def launch_paths(q_seg, k_prefix, seg_off: int):
+    """s1f_launch_paths: (backward in one launch, rows per unit of its dQ half, dQ half first, one launch without a workspace,
+    forward's tiles per head of partly filled units in the second launch)."""
+    desc, paths = make_desc(q_seg, k_prefix), (ctypes.c_int64 * 5)()
+    rc = load_library().s1f_launch_paths(ctypes.byref(desc), int(seg_off), int(q_seg.shape[2]), paths)
+    if rc != 0:
+        raise S1FError(rc, "s1f_launch_paths")
+    return tuple(paths)
 
 
 def seg_attn_fwd_ws(q_seg, k_prefix, v_prefix, seg_off: int, out, lse, workspace):

@@ -407,6 +407,38 @@ template <typename F> bool row_tail_of(const AttnArgs &a, const SplitPlan &p, in
   return false;
 }
 
+// How the rows of a forward whose last round goes to a second launch are shared out: `head` the first launch, `rest` the second (units
+// of the first cut into 64-row tiles, and `rag` such tiles of the partly filled last unit of every (batch, head)).
+struct Tail {
+  SplitPlan head, rest;
+  int64_t rag = 0;
+};
+template <typename F> bool fwd_tail(const AttnArgs &a, const SplitPlan &p, int64_t n_bh, Tail *t) {
+  int64_t whole = 0;
+  if (!row_tail_of<F>(a, p, &whole)) return false;
+  t->head = t->rest = p;
+  t->head.n_whole = whole;
+  t->rest.nc = 1;
+  t->rest.n_whole = 0;
+  t->rest.n_split_units = p.n_whole - whole;
+  t->rest.n_split = p.nc;
+  // The last unit of every (batch, head) may hold rows for fewer 64-row tiles than the others; where that leaves fewer tiles to the
+  // busiest compute unit, it is those that run in the second launch.  56 heads, 3678 rows behind 39549 keys: 56 units of 30 rows and
+  // 40 whole ones are 176 tiles, 96 whole ones 288: 3903 -> 3746 us; 3669 rows behind 40380 4010 -> 3835.  Over 40 random calls that
+  // it moves rows in (24 to 130 heads, 0.9 to 6 ms), time against leaving the last units of the launch: head_dim 128 0.947 .. 1.030, mean
+  // 0.969; 80 0.956 .. 1.009, mean 0.990.  Not for grouped heads, whose units left over are the ones with the fewest keys (64/8 heads, 3110
+  // rows behind 4612: 524 -> 561).
+  const int64_t rag = (a.seg_len - (p.n_tiles - 1) * 64 * p.nc + 63) / 64, cus = family_slots<F, 1>().cus;
+  const int64_t tiles = t->rest.n_split_units * p.nc, fewer = tiles - (p.nc - rag) * n_bh;
+  if (a.group == 1 && t->rest.n_split_units >= n_bh && (fewer + cus - 1) / cus < (tiles + cus - 1) / cus) {
+    t->head.n_tiles = t->rest.n_tiles = p.n_tiles - 1;
+    t->rest.n_split_units -= n_bh;
+    t->rest.n_whole = rag * n_bh;
+    t->rag = rag;
+  }
+  return true;
+}
+
 template <typename T, int D> int fwd_run(const s1f_desc *d, AttnArgs a, const SplitPlan &p, hipStream_t st, void *workspace) {
   typedef FwdFamily<T, D> F;
   const int64_t n_bh = (int64_t)d->n_q_heads * d->batch;
@@ -419,33 +451,16 @@ template <typename T, int D> int fwd_run(const s1f_desc *d, AttnArgs a, const Sp
   a.part_ml = reinterpret_cast<float *>(reinterpret_cast<char *>(workspace) + align256((size_t)(p.chunks() * 64 * p.nc * D * 4)));
   fill_launch(&a, n_bh, row_tile_order(d, a), p);
   a.first_id = 0;
-  int64_t whole = 0;
-  if (row_tail_of<F>(a, p, &whole)) {
-    SplitPlan head = p, rest = p;
-    head.n_whole = whole;
-    rest.nc = 1;
-    rest.n_whole = 0;
-    rest.n_split_units = p.n_whole - whole;
-    rest.n_split = p.nc;
-    // The last unit of every (batch, head) may hold rows for fewer 64-row tiles than the others; where that leaves fewer tiles to the
-    // busiest compute unit, it is those that run in the second launch.  56 heads, 3678 rows behind 39549 keys: 56 units of 30 rows and
-    // 40 whole ones are 176 tiles, 96 whole ones 288: 3903 -> 3746 us; 3669 rows behind 40380 4010 -> 3835.  Not for grouped
-    // heads, whose units left over are the ones with the fewest keys (64/8 heads, 3110 rows behind 4612: 524 -> 561).
-    const int64_t rag = (a.seg_len - (p.n_tiles - 1) * 64 * p.nc + 63) / 64, cus = family_slots<F, 1>().cus;
-    const int64_t tiles = rest.n_split_units * p.nc, fewer = tiles - (p.nc - rag) * n_bh;
-    if (a.group == 1 && rest.n_split_units >= n_bh && (fewer + cus - 1) / cus < (tiles + cus - 1) / cus) {
-      head.n_tiles = rest.n_tiles = p.n_tiles - 1;
-      rest.n_split_units -= n_bh;
-      rest.n_whole = rag * n_bh;
-      a.rag_tiles = (int32_t)rag;
-    }
-    fill_launch(&a, n_bh, row_tile_order(d, a), head);
-    const int rc = launch_rows<F>(head, n_bh, a, st);
+  Tail t;
+  if (fwd_tail<F>(a, p, n_bh, &t)) {
+    a.rag_tiles = (int32_t)t.rag;
+    fill_launch(&a, n_bh, row_tile_order(d, a), t.head);
+    const int rc = launch_rows<F>(t.head, n_bh, a, st);
     if (rc != S1F_OK) return rc;
-    a.first_id = (int32_t)whole;
-    a.n_split = p.nc;
-    a.n_split_units = (int32_t)rest.n_split_units;
-    return launch<F::rest_kernel()>(F::LDS, rest, n_bh, a, st, F::threads(1));
+    a.first_id = (int32_t)t.head.n_whole;
+    a.n_split = t.rest.n_split;
+    a.n_split_units = (int32_t)t.rest.n_split_units;
+    return launch<F::rest_kernel()>(F::LDS, t.rest, n_bh, a, st, F::threads(1));
   }
   const int rc = launch_rows<F>(p, n_bh, a, st);
   if (rc != S1F_OK || p.n_split_units == 0) return rc;
@@ -617,11 +632,14 @@ int launch_both(const BwdPlans &p, AttnArgs aq, AttnArgs ak, int dq_first, hipSt
   return e == hipSuccess ? S1F_OK : S1F_EDEVICE;
 }
 // The longer units first: those of the other half then fill the gaps at the end.
-template <typename T, int D> int bwd_both_impl(const s1f_desc *d, const AttnArgs &a, const BwdPlans &p, hipStream_t st) {
-  const AttnArgs aq = dq_args<T, D>(d, a, p.q_both), ak = dkdv_args<T, D>(d, a, p.k, p.k_part);
+template <typename T, int D> bool dq_half_first(const AttnArgs &a, const BwdPlans &p) {
   const double q_us = ((double)a.seg_off + 0.5 * a.seg_len) / 32 * Cost<T, D>::dq.at(p.q_both.nc, 2) / (p.q_both.n_whole > 0 ? 1 : p.q_both.n_split);
   const double k_us = (double)a.group * ((a.seg_len + 31) / 32) * Cost<T, D>::dkdv.at(0, 2) / (p.k.n_whole > 0 ? 1 : p.k.n_split);
-  const int dq_first = q_us >= k_us;
+  return q_us >= k_us;
+}
+template <typename T, int D> int bwd_both_impl(const s1f_desc *d, const AttnArgs &a, const BwdPlans &p, hipStream_t st) {
+  const AttnArgs aq = dq_args<T, D>(d, a, p.q_both), ak = dkdv_args<T, D>(d, a, p.k, p.k_part);
+  const int dq_first = dq_half_first<T, D>(a, p);
   int rc = launch_stats<T, D>(d, a, st);
   if (rc != S1F_OK) return rc;
   rc = S1F_EUNSUPPORTED;
@@ -668,6 +686,22 @@ template <typename T, int D> int plan_impl(const s1f_desc *d, const AttnArgs &a,
   out[2] = p.n_split_units;
   out[3] = p.n_split;
   out[4] = tail ? p.n_whole - whole : 0;
+  return S1F_OK;
+}
+
+// What s1f_launch_paths reports.
+template <typename T, int D> int paths_impl(const s1f_desc *d, const AttnArgs &a, int64_t *out) {
+  BwdPlans p, small;
+  bwd_plans_impl<T, D>(d, a.seg_off, a.seg_len, kMaxPartBytes, &p);
+  bwd_plans_impl<T, D>(d, a.seg_off, a.seg_len, kStaticPartBytes, &small);
+  Tail t;
+  typedef FwdFamily<T, D> F;
+  fwd_tail<F>(a, plan_rows<F>(d, a.seg_off, a.seg_len, 0), (int64_t)d->n_q_heads * d->batch, &t);
+  out[0] = p.both;
+  out[1] = 64 * (p.both ? p.q_both.nc : p.q.nc);
+  out[2] = p.both && dq_half_first<T, D>(a, p);
+  out[3] = small.both;
+  out[4] = t.rag;
   return S1F_OK;
 }
 
@@ -877,7 +911,8 @@ extern "C" int s1f_seg_attn_bwd_noalloc(const s1f_desc *desc, const void *dout, 
   float *ws = nullptr;
   rc = static_scratch(&ws);
   if (rc != S1F_OK) return rc;
-  // every plane entry the dK/dV kernel reads is written by the dQ kernel of the same call: nothing to clear
+  // every plane entry that is read is written by the same call before (by the statistics kernel, or by the dQ kernel where the halves
+  // run one after the other): nothing to clear
   return bwd_entry(desc, dout, q_seg, k_prefix, v_prefix, out, lse, seg_off, seg_len, dq, dk_prefix_acc, dv_prefix_acc, ws,
                    kStaticScratchBytes, kStaticPartBytes, hip_stream);
 }
@@ -890,6 +925,16 @@ extern "C" int s1f_launch_plan(const s1f_desc *desc, int32_t launch, int64_t seg
   if (rc != S1F_OK) return rc;
   const AttnArgs a = make_args(desc, seg_off, seg_len);
   S1F_DISPATCH(plan_impl, desc, desc, a, launch, launch == S1F_PLAN_FWD ? 0 : kMaxPartBytes, plan);
+}
+
+extern "C" int s1f_launch_paths(const s1f_desc *desc, int64_t seg_off, int64_t seg_len, int64_t *paths) {
+  int rc = check_desc(desc);
+  if (rc != S1F_OK) return rc;
+  if (paths == nullptr) return S1F_EINVAL;
+  rc = check_seg(desc, seg_off, seg_len);
+  if (rc != S1F_OK) return rc;
+  const AttnArgs a = make_args(desc, seg_off, seg_len);
+  S1F_DISPATCH(paths_impl, desc, desc, a, paths);
 }
 
 extern "C" const char *s1f_strerror(int status) {

@@ -6,14 +6,20 @@ import paper_2406_03488_amd as s1f
 
 pytestmark = pytest.mark.gpu
 
-# dtype, head_dim, batch, query heads, K/V heads, offset, rows, storage: each tile width of the dQ half, whole and cut, next to a
-# whole and a cut dK/dV half, either of them first; one row, ends of tiles and one past them; several workgroups of statistics
+# dtype, head_dim, batch, query heads, K/V heads, offset, rows, storage, rows per unit of the dQ half in the one launch (0: there is none
+# for this width) and whether its units come first: each width whole and cut, next to a whole and a cut dK/dV half, either of them
+# first; one row, ends of tiles and one past them; several workgroups of statistics
 SHAPES = [
-    ("bf16", 64, 1, 1, 1, 0, 1, "bhsd"), ("bf16", 64, 2, 8, 2, 1000, 357, "bshd"), ("bf16", 64, 1, 32, 8, 4600, 1882, "bhsd"),
-    ("bf16", 80, 3, 3, 3, 31, 65, "bshd"), ("bf16", 80, 1, 32, 32, 2406, 513, "bhsd"), ("bf16", 80, 1, 32, 32, 4522, 1913, "bhsd"),
-    ("bf16", 128, 1, 2, 1, 63, 64, "bhsd"), ("bf16", 128, 1, 64, 8, 2901, 561, "bshd"), ("bf16", 128, 1, 32, 32, 0, 1500, "bhsd"),
-    ("f32", 64, 1, 4, 4, 768, 256, "bhsd"), ("f32", 64, 2, 3, 1, 5, 129, "bshd"), ("f32", 80, 1, 4, 4, 300, 193, "bshd"),
-    ("f32", 128, 1, 8, 2, 1240, 1060, "bhsd"), ("f32", 128, 1, 2, 1, 0, 33, "bhsd"),
+    ("bf16", 64, 1, 1, 1, 0, 1, "bhsd", 64, 0), ("bf16", 64, 2, 8, 2, 1000, 357, "bshd", 64, 1), ("bf16", 64, 1, 32, 8, 4600, 1882, "bhsd", 128, 0),
+    ("bf16", 64, 3, 32, 32, 2585, 129, "bhsd", 64, 1), ("bf16", 64, 1, 56, 56, 4772, 65, "bshd", 128, 1), ("bf16", 64, 3, 56, 56, 196, 554, "bhsd", 0, 0),
+    ("bf16", 80, 3, 3, 3, 31, 65, "bshd", 64, 0), ("bf16", 80, 1, 32, 32, 2406, 513, "bhsd", 192, 1), ("bf16", 80, 1, 32, 32, 4522, 1913, "bhsd", 128, 1),
+    ("bf16", 80, 3, 64, 8, 0, 129, "bshd", 192, 0), ("bf16", 80, 1, 32, 32, 1500, 577, "bhsd", 128, 0),
+    ("bf16", 128, 1, 2, 1, 63, 64, "bhsd", 64, 0), ("bf16", 128, 1, 64, 8, 2901, 561, "bshd", 64, 0), ("bf16", 128, 1, 32, 32, 0, 1500, "bhsd", 64, 0),
+    ("bf16", 128, 1, 112, 112, 1500, 769, "bhsd", 64, 1), ("bf16", 128, 1, 32, 32, 1500, 577, "bshd", 128, 0),
+    ("f32", 64, 1, 4, 4, 768, 256, "bhsd", 64, 0), ("f32", 64, 2, 3, 1, 5, 129, "bshd", 64, 0), ("f32", 64, 3, 56, 56, 333, 65, "bhsd", 128, 0),
+    ("f32", 80, 1, 4, 4, 300, 193, "bshd", 0, 0), ("f32", 80, 1, 64, 8, 300, 200, "bhsd", 128, 1), ("f32", 80, 1, 32, 32, 700, 321, "bshd", 128, 0),
+    ("f32", 128, 1, 8, 2, 1240, 1060, "bhsd", 128, 0), ("f32", 128, 1, 2, 1, 0, 33, "bhsd", 128, 0), ("f32", 128, 1, 32, 32, 700, 321, "bhsd", 0, 0),
+    ("f32", 128, 1, 64, 8, 300, 200, "bshd", 128, 1),
 ]
 
 
@@ -39,15 +45,19 @@ def _apart_bytes(q, k, off, e=4):
     return stats + max(units * chunks * rows * d * e, k_units * (k_chunks - 1) * 2 * 128 * d * e)
 
 
-@pytest.mark.parametrize("dtype,d,nb,hq,hk,off,m,layout", SHAPES)
-def test_one_launch_equals_two(dtype, d, nb, hq, hk, off, m, layout):
+@pytest.mark.parametrize("dtype,d,nb,hq,hk,off,m,layout,rows,dq_first", SHAPES)
+def test_one_launch_equals_two(dtype, d, nb, hq, hk, off, m, layout, rows, dq_first):
     q, do, k, v = _data(70 + off + m, dtype, d, nb, hq, hk, off, m, layout)
     out, lse = torch.empty_like(q), torch.empty((nb, hq, m), device="cuda")
     s1f.seg_attn_fwd(q, k, v, off, out, lse)
     like_k = torch.empty_like(k, dtype=torch.float32)
     assert like_k.stride() == k.stride()
     need, apart = s1f.bwd_workspace_bytes(q, k, off), _apart_bytes(q, k, off)
-    assert need >= apart
+    both, dq_rows, first, _, _ = s1f.launch_paths(q, k, off)
+    assert (both * dq_rows, first) == (rows, dq_first), "the shape no longer takes the path it is here for"
+    # a workspace for one half's partial results only, which "one call, smaller workspace" brings, makes a difference where both are cut
+    cut = [s1f.launch_plan(q, k, off, i)[2] > 0 for i in (s1f.PLAN_DQ, s1f.PLAN_DKDV)]
+    assert (need > apart) == (both and all(cut))
     got = {}
     for how, size in (("one call", need), ("one call, smaller workspace", apart), ("halves", need), ("no workspace", 0)):
         dq = torch.full_like(q, float("nan"))

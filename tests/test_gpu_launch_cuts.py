@@ -263,3 +263,27 @@ def test_every_tile_width_whole_and_cut(dtype, d, shape, plans, rising):
                    where + how + " ")
         _close({"dq": host(dq[b, hs]), "dk": host(dk[b, g:g + 1]), "dv": host(dv[b, g:g + 1])},
                {"dq": wdq, "dk": wdk, "dv": wdv}, dtype, where)
+
+
+@pytest.mark.parametrize("dtype,d,shape,plans", WIDTHS)
+def test_every_tile_width_in_halves(dtype, d, shape, plans):
+    """The kernels of one half each, which most calls above do not run: the same bits as the one call, which is compared with the
+    oracle there."""
+    nb, hq, hkv, off, m = shape
+    q, do, k, v = _device_data(9000 + off + m + d, dtype, d, *shape, False)
+    out, lse = torch.empty_like(q), torch.empty(q.shape[:3], device="cuda")
+    s1f.seg_attn_fwd(q, k, v, off, out, lse)
+    ws = torch.empty(s1f.bwd_workspace_bytes(q, k, off), dtype=torch.uint8, device="cuda")
+    res = []
+    for halves in (False, True):
+        dq = torch.full_like(q, float("nan"))
+        dk, dv = (torch.full(k.shape, 0.5, device="cuda") for _ in range(2))
+        ws.fill_(0xff)
+        if halves:
+            s1f.seg_attn_bwd_dq(do, q, k, v, out, lse, off, dq, ws)
+            s1f.seg_attn_bwd_dkdv(do, q, k, v, lse, off, dk, dv, ws)
+        else:
+            s1f.seg_attn_bwd(do, q, k, v, out, lse, off, dq, dk, dv, ws)
+        res.append((dq, dk, dv))
+    for name, x, y in zip(("dq", "dk", "dv"), *res):
+        assert torch.isfinite(x).all() and torch.equal(x, y), name

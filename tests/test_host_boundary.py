@@ -223,6 +223,11 @@ def test_launch_plan_validates_and_is_whole_without_a_device():
     assert ask(_desc(), -1, 0, 64) == 1 and ask(_desc(), 4, 0, 64) == 1 and ask(_desc(), 0, 0, 64, None) == 1
     assert ask(_desc(head_dim=96), 0, 0, 64) == 2 and ask(_desc(), 0, 500, 64) == 3
     assert lib.s1f_launch_plan(None, 0, 0, 64, plan) == 1
+    paths = (ctypes.c_int64 * 5)()
+    assert lib.s1f_launch_paths(ctypes.byref(_desc()), 100, 200, paths) == 0 and paths[1] in (64, 128, 192) and paths[4] == 0
+    assert lib.s1f_launch_paths(ctypes.byref(_desc()), 100, 200, None) == 1 and lib.s1f_launch_paths(None, 0, 64, paths) == 1
+    assert lib.s1f_launch_paths(ctypes.byref(_desc(head_dim=96)), 0, 64, paths) == 2
+    assert lib.s1f_launch_paths(ctypes.byref(_desc()), 500, 64, paths) == 3
 
 
 def test_noalloc_backward_rejects_more_rows_than_the_array_holds():

@@ -26,6 +26,9 @@ for dtype in (0, 1):
                   lib.s1f_seg_attn_bwd_dq(desc, p, p, p, p, p, p, off, m, p, p, big, None),
                   lib.s1f_seg_attn_bwd_dkdv(desc, p, p, p, p, p, off, m, p, p, p, big, None)]
             assert rc == [0] * 6, rc
+            paths, plan = (ctypes.c_int64 * 5)(), (ctypes.c_int64 * 5)()
+            assert lib.s1f_launch_paths(desc, off, m, paths) == 0 and lib.s1f_launch_plan(desc, 0, off, m, plan) == 0
+            print(*paths, plan[4], hq)
 """
 
 
@@ -41,11 +44,12 @@ def record(runtime, tmp_path, shapes):
     env = dict(os.environ, RECORD=path, PYTHONPATH=ROOT)
     run = subprocess.run([sys.executable, "-c", DRIVER, runtime, repr(shapes)], env=env, capture_output=True, text=True, cwd=ROOT)
     assert run.returncode == 0, run.stderr
-    return [line.split() for line in open(path)]
+    lines = [line.split() for line in open(path)]
+    return lines, [[int(x) for x in line.split()] for line in run.stdout.splitlines()]
 
 
 def test_every_kernel_is_told_of_its_lds_before_it_runs(runtime, tmp_path):
-    lines = record(runtime, tmp_path, [(2, 1, 0, 40), (32, 32, 700, 321), (64, 8, 5000, 3214), (56, 56, 9203, 5220), (112, 112, 0, 193)])
+    lines, _ = record(runtime, tmp_path, [(2, 1, 0, 40), (32, 32, 700, 321), (64, 8, 5000, 3214), (56, 56, 9203, 5220), (112, 112, 0, 193)])
     told, launched = {}, set()
     for what, name, *rest in lines:
         if what == "attribute":
@@ -56,3 +60,33 @@ def test_every_kernel_is_told_of_its_lds_before_it_runs(runtime, tmp_path):
             launched.add((name, lds))
             assert lds <= 64 * 1024 or told.get(name, 0) >= lds, name
     assert sum(lds > 64 * 1024 for _, lds in launched) >= 25   # (one flag per type of kernel told two of them)
+
+
+def test_paths_are_the_ones_that_calls_take(runtime, tmp_path):
+    shapes = [(2, 1, 0, 40), (32, 32, 700, 321), (56, 56, 17918, 4897), (64, 8, 5000, 3214), (56, 56, 39549, 3678), (130, 130, 8808, 1600)]
+    lines, paths = record(runtime, tmp_path, shapes)
+    launches = [(name, int(rest[0])) for what, name, *rest in lines if what == "launch"]
+
+    def take(kernel):
+        """The next launch, if it is one of that kernel: its workgroups."""
+        return launches.pop(0)[1] if launches and kernel in launches[0][0] else 0
+
+    seen = set()
+    for one_bwd, _, _, one_noalloc, tiles, second, heads in paths:
+        assert take("seg_attn_fwd_kernel")
+        assert second == 0 or take("seg_attn_fwd_kernel") >= tiles * heads
+        assert take("seg_attn_fwd_kernel")
+        take("fwd_merge")
+        for one in (one_bwd, one_noalloc):
+            if one:
+                assert take("bwd_stats") and take("seg_attn_bwd_kernel")
+            else:
+                assert take("bwd_dq_kernel")
+                take("bwd_merge")
+                assert take("bwd_dkdv_kernel")
+            take("bwd_merge")
+        for half in ("dq", "dkdv"):
+            assert take(f"bwd_{half}_kernel")
+            take("bwd_merge")
+        seen |= {("one launch", one_bwd), ("second launch", second > 0), ("partly filled units", tiles > 0)}
+    assert not launches and len(seen) == 6
