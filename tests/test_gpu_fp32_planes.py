@@ -95,6 +95,37 @@ def test_products_left_out_do_not_add_up(d):
     assert abs(err.mean().item()) <= 2.0 ** -24 and err.abs().max().item() <= 2.0 ** -21   # (single ones: three roundings as well)
 
 
+@pytest.mark.parametrize("d", [64, 80, 128])
+def test_every_bit_of_an_operand_counts(d):
+    """A row that sees one key: out = v and dv = dout, all 24 bits of them (the last plane alone is 2^-17 of a value and less)."""
+    g = torch.Generator(device="cuda")
+    g.manual_seed(d)
+    q, k = (torch.zeros((3, 50, 1, d), device="cuda") for _ in range(2))
+    v, do = (torch.empty_like(q).normal_(generator=g) for _ in range(2))
+    got = _call(q, k, v, do, 0)
+    assert torch.equal(got["out"], v) and torch.equal(got["dv"], do) and not got["lse"].any()
+
+
+@pytest.mark.parametrize("d", [64, 80, 128])
+def test_every_product_of_planes_counts(d):
+    """Heads of one row that sees two keys, with so few elements that are not zero that every result is one product, of scores, dP or
+    dS among its factors: p1 = P(key 1), dS = p1 p2 (dO . v1), dQ = dS k1, dK = dS q, dV = p dO.  Relative errors are a few times 2^-24,
+    with one of the six products or the last plane of one operand missing 2e-6 and more (tests/test_host_fp32_planes.py)."""
+    heads = 2048
+    g = torch.Generator(device="cuda")
+    g.manual_seed(d)
+    q, do = (torch.zeros((1, heads, 1, d), device="cuda") for _ in range(2))
+    k, v = (torch.zeros((1, heads, 2, d), device="cuda") for _ in range(2))
+    rnd = lambda: torch.empty((1, heads), device="cuda").normal_(generator=g)
+    do[:, :, 0, 3], v[:, :, 0, 3], k[:, :, 0, 7], k[:, :, 0, d - 1], q[:, :, 0, d - 1] = (rnd() for _ in range(5))
+    got = _call(q, k, v, do, 1)
+    host = lambda x: x[0].double().cpu().numpy()
+    out, lse = A.segment_forward(host(q), host(k), host(v), 1)
+    dq, dk, dv = A.segment_backward(host(do), host(q), host(k), host(v), 1)
+    for name, x in {"out": out, "lse": lse, "dq": dq, "dk": dk, "dv": dv}.items():
+        assert np.linalg.norm(host(got[name]) - x) <= 1e-6 * np.linalg.norm(x), (name, np.linalg.norm(host(got[name]) - x) / np.linalg.norm(x))
+
+
 @pytest.mark.parametrize("d", [64, 128])
 @pytest.mark.parametrize("power", [-125, -115, 60, 100])
 @pytest.mark.parametrize("small", ["v", "do", "q", "k"])
