@@ -53,7 +53,7 @@ typedef enum {
 typedef enum {
   S1F_F32 = 0, /* q, k, v, out, dout, dq are fp32; products to fp32 precision (operands as three exact bf16 parts each,
                   accumulated in fp32).  Operands and products that are not finite give what fp32 arithmetic gives, and rows
-                  (dK/dV: keys) that they touch, and up to 31 beside each, take far longer; so do operands and outputs
+                  (dK/dV: keys) that they touch, and up to 31 beside each, take up to 13 times as long; so do operands and outputs
                   from 2^112 on, scores and dV from 2^96 and dQ and dK from 2^80 on */
   S1F_BF16 = 1 /* q, k, v, out, dout, dq are bf16; bf16 MFMA with fp32 accumulation; probabilities and
                   score gradients are rounded to bf16 before their second product */

@@ -655,13 +655,14 @@ template <typename T, int D> S1F_DEV void bwd_dkdv_body(const AttnArgs &a, int i
         v_row.load(vbase + (int64_t)kc * a.kv_ss, pj);
 #pragma unroll
         for (int db = 0; db < DB; ++db) dk[cb][db] = dv[cb][db] = f32x4{0.f, 0.f, 0.f, 0.f};
+        float met = 0.f;
 #pragma unroll 1
-        for (int it = it_begin; it < it_end; ++it) {
+        for (int it = it_begin; it < it_end && !all_nan(met); ++it) {
           const int hq = hk * a.group + it / per_head, r0 = (qt_first + it % per_head) * BQ, r1 = r0 + BQ < seg_len ? r0 + BQ : seg_len;
           const int64_t qoff = b * a.q_sb + hq * a.q_sh;
           dkdv_plain<D>(k_row, v_row, reinterpret_cast<const T *>(a.q) + qoff, reinterpret_cast<const T *>(a.dout) + qoff, a.q_ss,
                         a.delta + ((int64_t)b * a.n_q_heads + hq) * seg_len, a.ws_plane, r0, r1, kc - seg_off,
-                        c * (M::UP * M::UP), pj, dk[cb], dv[cb]);
+                        c * (M::UP * M::UP), pj, dk[cb], dv[cb], met);
         }
       }
     }

@@ -11,7 +11,7 @@ pytestmark = pytest.mark.gpu
 # (query heads, K/V heads, offset, rows, heads looked at): one tile; several, with waves that end at different ones; launches that are cut
 # along the keys (or queries); enough heads for tiles of 128 rows
 SHAPES = [(2, 2, 0, 70, (0,)), (4, 2, 31, 130, (0, 2)), (4, 4, 1200, 150, (3,)), (264, 264, 127, 97, (0, 263))]
-INF = float("inf")
+INF, NAN = float("inf"), float("nan")
 
 
 def exact(q, k, v, do, off):
@@ -57,7 +57,7 @@ def kind(x):
 
 
 @pytest.mark.parametrize("how", ["plain", "workspace"])
-@pytest.mark.parametrize("which,value", [("v", INF), ("k", -INF), ("q", INF), ("do", INF), ("do", float("nan")), ("v", 1e37), ("v", -1e37)])
+@pytest.mark.parametrize("which,value", [("v", INF), ("k", -INF), ("q", INF), ("do", INF), ("do", NAN), ("q", NAN), ("k", NAN), ("v", NAN), ("v", 1e37), ("v", -1e37)])
 @pytest.mark.parametrize("d", [64, 80, 128])
 @pytest.mark.parametrize("hq,hkv,off,m,heads", SHAPES)
 def test_elements_that_are_not_finite(hq, hkv, off, m, heads, d, which, value, how):
