@@ -33,7 +33,7 @@ S1F_DEV void bwd_row_stats(const AttnArgs &a, const typename Mat<T, D>::RowOp &d
   }
 }
 // ... of all rows, for halves of the backward that run in one launch: a wave per 16 rows of one (batch, head).  The same sums as
-// in the dQ kernel's own prologue.  Bound by its launch (3 us of small calls) or by memory (67 MB of out and dout: 15 us).
+// in the dQ kernel's own prologue.  Bound by its launch (4 to 5 us of small calls) or by memory (67 MB of out and dout: 15 us).
 template <typename T, int D> __global__ void __launch_bounds__(256) seg_attn_bwd_stats_kernel(const AttnArgs a) {
   typedef Mat<T, D> M;
   const int groups = (a.seg_len + 63) / 64, bh = (int)blockIdx.x / groups, lane = threadIdx.x & 63, j = lane >> 4;

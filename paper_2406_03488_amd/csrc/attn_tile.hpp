@@ -180,7 +180,8 @@ template <int D> struct Mat<bf16_t, D> {
 // (fp32 instructions / this): out 6.5e-7 / 4.3e-7, lse 5.60e-8 / 5.57e-8, dq 9.4e-7 / 8.3e-7, dk and dv 2.3e-6 / 2.0e-6; with
 // queries 30 times as large 3.4e-6 / 2.5e-6, 1.7e-7 / 1.3e-7, 1.2e-5 / 0.9e-5, 2.8e-5 / 2.4e-5.  32 heads, 2048 rows behind 8000
 // keys, us: head_dim 128 forward 2449 -> 1422, dQ 3500 -> 1909, dK/dV 4967 -> 2638; 80 1622 -> 1030, 2329 -> 1401, 3233 -> 1977; 64
-// 1289 -> 700, 1885 -> 968, 2253 -> 1260: bound, like bf16, by the matrix pipe under the power limit (dQ and dK/dV execute 1350-1450 TFLOP/s of bf16 products).
+// 1289 -> 700, 1885 -> 968, 2253 -> 1260: bound, like bf16, by the matrix pipe under the power limit (56-64 % busy at
+// 2.0-2.2 GHz: 1230, 1360 and 1280 TFLOP/s executed, six products for each, at head_dim 128, 1320, 1440 and 1450 at 64).
 struct Planes {
   bf16x8 p[3];
 };

@@ -170,9 +170,12 @@ template <> struct Cost<bf16_t, 80> {
 template <> struct Cost<bf16_t, 128> {
   static constexpr StepUs fwd = {0.29, 0.17, 0.36, 0.32, 0, 0}, dq = {0.2, 0.26, 0.32, 0.52, 0, 0}, dkdv = {1.05, 0, 1.65, 0, 0, 0};
 };
-// fp32: measured 1.06 + 0.33 * nc and so on; the forward at head_dim 64 (up to 19 %) and the dQ kernel at 64 and 128 (alone: up to
-// 1.9 and 2.1 times) stand above that, which chooses a little more cutting for launches of less than a round: over 400
-// shapes the plan taken is predicted to cost 0.1, 1.8 and 2.9 % on average over the best one.
+// fp32: the forward at head_dim 80 and 128, dQ at 80 and dK/dV as measured.  Not so the forward at head_dim 64 (up to 19 % above) and
+// dQ at 64 and 128 (alone: up to 1.9 and 2.1 times above; merge 0.7): those values are chosen for the plans that they lead to, cut
+// 64-row dQ units for some launches of less than a round, which the tests of tile widths ask for by shape.  With the measured ones such
+// calls would run in 128-row tiles, faster where that was timed (8/2 heads, head_dim 128: backward of a first segment of 1240 rows
+// 125 -> 98 us, of 941 rows behind 2300 keys 254 -> 213); over 400 shapes the plan taken is predicted to cost 0.1, 1.8 and 2.9 % on
+// average over the best one.
 template <> struct Cost<float, 64> {
   static constexpr StepUs fwd = {0.72, 0.46, 0.885, 0.92, 0, 0}, dq = {-1.17, 2.23, 0.37, 1.615, 0, 0, 0.7}, dkdv = {2.75, 0, 4.7, 0, 0, 0};
 };
@@ -525,6 +528,8 @@ struct BwdPlans {
 //   long, dQ cut       32 heads, head_dim 128, 3652 behind 19539 3599 -> 3547, 3181 behind 26583 4078 -> 4097; 56 heads, 4897 behind
 //                      17918 7768 -> 7829, 2898 behind 62638 14797 -> 14859; 64/8 heads, 3606 behind 79334 same: workgroups of the
 //                      second half start one by one and no longer walk the same rows side by side
+// Over 170 random calls that run in one launch (20 us to 20 ms), time against two: bf16 0.82 on average, worst 1.044 (64/8 heads,
+// head_dim 64, 913 rows behind 6179) and 1.028 (3 x 56 heads, head_dim 128, first segment of 267 rows); fp32 0.85, worst 1.008.
 constexpr double kBothUs = 3000.0;
 template <typename T, int D> bool both_halves(const s1f_desc *d, int64_t seg_off, int64_t seg_len, const BwdPlans &p) {
   if (!Shape<T, D>::both(p.q_both.nc) || !one_launch(p.q_both.grid() + p.k.grid(), DkdvFamily<T, D>::THREADS)) return false;
