@@ -216,7 +216,8 @@ size_t s1f_static_scratch_rows(void);
 /* How a call of this shape is launched on the current device: a question about speed only, for tests and measurements.
  * HOST function; nothing is enqueued.  `launch` names the call: the forward without and with a workspace, and the two
  * kernels of the backward (s1f_seg_attn_bwd and its halves).  Writes
- *   plan[0]  rows (dK/dV: keys) per unit, the work of one workgroup (S1F_PLAN_DQ: of the half by itself, see s1f_launch_paths)
+ *   plan[0]  rows (dK/dV: keys) per unit, the work of one workgroup (S1F_PLAN_DQ: of the half by itself, see s1f_launch_paths; forward:
+ *            16 or 32 where the waves of a workgroup share the keys of the unit, else 64 and more)
  *   plan[1]  units that are left whole
  *   plan[2]  units cut along the keys (dK/dV: along the queries), plan[3] the chunks per cut unit
  *   plan[4]  forward: units whose rows run in a second launch of 64-row tiles

@@ -204,6 +204,37 @@ S1F_DEV void fwd_step(f32x4 (&p)[2][NC], f32x4 (&o)[NC][M::DB], const float (&m)
   if (HAS_NEXT) rs[NC - 1] += prob(8 * NC - 1);
 }
 
+// fp32: the factor of the planes is taken out of a wave's accumulators; if they are not all finite, its rows (16*NC from row0 on) are
+// computed again in plain arithmetic.  qb: row 0 of the segment; kbase, vbase: first of the `keys` keys that the wave has walked, from
+// which seg_off counts.
+template <typename T, int D, int NC>
+S1F_DEV void fwd_finish_fp32(const AttnArgs &a, const T *qb, const T *kbase, const T *vbase, int row0, int seg_off, int keys, float c,
+                             f32x4 (&o)[NC][Mat<T, D>::DB], float (&m)[NC], float (&l)[NC]) {
+  typedef Mat<T, D> M;
+  if constexpr (sizeof(T) == 4) {
+    float bad = 0.f;
+#pragma unroll
+    for (int cb = 0; cb < NC; ++cb) {
+      bad = fmaf(l[cb], 0.f, bad);
+#pragma unroll
+      for (int db = 0; db < M::DB; ++db) {
+        bad = add_if_not_finite(o[cb][db], bad);
+        o[cb][db] *= 1.f / M::UP;
+      }
+    }
+    if (__builtin_expect(any_not_finite(bad), 0)) {
+#pragma unroll
+      for (int cb = 0; cb < NC; ++cb) {
+        const int r_last = row0 + 16 * cb + 15, last = seg_off + (r_last < a.seg_len ? r_last : a.seg_len - 1);
+        const int pl = lane_id(), r = row0 + 16 * cb + (pl & 15), rc = r < a.seg_len ? r : a.seg_len - 1;
+        fwd_plain<D>(qb + (int64_t)rc * a.q_ss, kbase, vbase, a.kv_ss, seg_off + rc, last < keys ? last + 1 : keys,
+                     c * (M::UP * M::UP), pl >> 4, o[cb], m[cb], l[cb]);
+        if (pl >= 16) l[cb] = 0.f;   // (the sum over the row's four lanes follows)
+      }
+    }
+  }
+}
+
 // REST: the second launch, over the rows of units that the first left over (an instance of its own: in the 64-row kernel itself
 // the decision cost 2 to 6 % of launches of 30 to 300 us)
 template <typename T, int D, int NC, int OCC, int WAVES, bool REST = false>
@@ -362,28 +393,7 @@ __global__ void __launch_bounds__(64 * WAVES, OCC) seg_attn_fwd_kernel(const Att
     for (++k; k + 1 < n_kt; ++k, ring.end_step()) ring.template begin_step<false>(n_kt - 1 - k);
   }
 
-  if constexpr (sizeof(T) == 4) {
-    float bad = 0.f;
-#pragma unroll
-    for (int cb = 0; cb < NC; ++cb) {
-      bad = fmaf(l[cb], 0.f, bad);
-#pragma unroll
-      for (int db = 0; db < DB; ++db) {
-        bad = add_if_not_finite(o[cb][db], bad);
-        o[cb][db] *= 1.f / M::UP;
-      }
-    }
-    if (__builtin_expect(any_not_finite(bad), 0)) {
-#pragma unroll
-      for (int cb = 0; cb < NC; ++cb) {
-        const int r_last = wrow0 + 16 * cb + 15, last = seg_off + (r_last < seg_len ? r_last : seg_len - 1);
-        const int pl = lane_id(), r = wrow0 + 16 * cb + (pl & 15), rc = r < seg_len ? r : seg_len - 1;
-        fwd_plain<D>(qb + (int64_t)rc * a.q_ss, kbase, vbase, a.kv_ss, seg_off + rc, last < BN * n_kt ? last + 1 : BN * n_kt,
-                     c * (M::UP * M::UP), pl >> 4, o[cb], m[cb], l[cb]);
-        if (pl >= 16) l[cb] = 0.f;   // (the sum over the row's four lanes follows)
-      }
-    }
-  }
+  fwd_finish_fp32<T, D, NC>(a, qb, kbase, vbase, wrow0, seg_off, BN * n_kt, c, o, m, l);
   if (uc.slot >= 0) {   // a chunk: unnormalised output rows, running maximum and row sum go to the workspace
     float *po = a.part + (int64_t)uc.slot * (BM * D);
     float *pml = a.part_ml + (int64_t)uc.slot * (BM * 2);

@@ -8,6 +8,7 @@
 
 #include "attn_bwd.hpp"
 #include "attn_fwd.hpp"
+#include "attn_fwd_keys.hpp"
 #include "s1f.h"
 
 namespace {
@@ -352,13 +353,14 @@ template <typename F, int NC> void plan_rows_nc(const s1f_desc *d, int64_t seg_o
   plan_units(best, t, NC, tiles, units, (double)(seg_off + (seg_len + 1) / 2) / 32 + 1, (double)(seg_off + seg_len) / 32 + 1, F::cost,
              s, F::row_bytes * 64 * NC, 0, cap);
 }
-// Wide tiles first: a narrower one has to be faster.
-template <typename F> SplitPlan plan_rows(const s1f_desc *d, int64_t seg_off, int64_t seg_len, int64_t cap) {
+// Wide tiles first: a narrower one has to be faster.  us: the time predicted for the plan
+template <typename F> SplitPlan plan_rows(const s1f_desc *d, int64_t seg_off, int64_t seg_len, int64_t cap, double *us = nullptr) {
   SplitPlan p;
   double t = 1e300;
   if constexpr (F::MAX >= 3) plan_rows_nc<F, 3>(d, seg_off, seg_len, cap, &p, &t);
   plan_rows_nc<F, 2>(d, seg_off, seg_len, cap, &p, &t);
   plan_rows_nc<F, 1>(d, seg_off, seg_len, cap, &p, &t);
+  if (us != nullptr) *us = t;
   return p;
 }
 template <typename F> int launch_rows(const SplitPlan &p, int64_t n_bh, const AttnArgs &a, hipStream_t st) {
@@ -442,6 +444,71 @@ template <typename F> bool fwd_tail(const AttnArgs &a, const SplitPlan &p, int64
   return true;
 }
 
+// The forward whose waves share the keys of a unit (seg_attn_fwd_kernel_by_keys).  Its time in microseconds, fitted to calls of 4 to 500
+// us: base + step per 32 keys (which a workgroup's waves walk side by side), for units of 16 and of 32 rows with a compute unit each.
+struct KeysUs {
+  double base1, step1, base2, step2;
+};
+template <typename T, int D> struct KeysCost;
+template <> struct KeysCost<bf16_t, 64> { static constexpr KeysUs us = {4.0, 0.073, 5.0, 0.105}; };
+template <> struct KeysCost<bf16_t, 80> { static constexpr KeysUs us = {4.2, 0.103, 6.3, 0.125}; };
+template <> struct KeysCost<bf16_t, 128> { static constexpr KeysUs us = {4.8, 0.146, 8.0, 0.17}; };
+template <> struct KeysCost<float, 64> { static constexpr KeysUs us = {6.0, 0.33, 10.0, 0.45}; };
+template <> struct KeysCost<float, 80> { static constexpr KeysUs us = {6.5, 0.45, 10.0, 0.75}; };
+template <> struct KeysCost<float, 128> { static constexpr KeysUs us = {8.0, 0.85, 17.0, 1.0}; };
+template <typename T, int D, int NC> struct KeysShape {
+  // fp32 at head_dim 80: eight waves of two column blocks spill; 128: LDS
+  static constexpr int W = sizeof(T) == 2 || D == 64 || (D == 80 && NC == 1) ? 8 : 4;
+  static constexpr int PER_CU = sizeof(T) == 2 && D == 64 && NC == 1 ? 2 : 1;   // workgroups that a compute unit takes without longer steps
+};
+// Column blocks of its waves (1 or 2), if such a launch is predicted to take less than `plan_us`, the plan of row tiles' time; else 0.
+//   few units only    (each has a compute unit to itself): beyond, every unit reading all keys costs more than idle compute units
+//   not fp32 with a workspace   its steps are bound by the splitting of operands, which waves of row tiles share: 4 heads, 256 rows behind
+//                     768 keys, D 64 cut into chunks 13.4 us, by keys 17.7; without a workspace 34.9, by keys 17.7
+//   with a workspace, up to 48 steps, or up to 80 if units take more than half of the chip   chunks use the compute units that few units
+//                     leave idle: 2/1 heads, 839 rows behind 2668, D 80 14.6 us in chunks, 15.1 by keys; 4 heads, 368 behind 2578, 13.4 and
+//                     13.6 (few units of 50 to 80 steps would still gain up to 25 %; tests ask for chunks there)
+//   fewer than 32 (batch, head) pairs   with a workspace there is nothing in it beyond (32 heads, 129 rows behind 4011 keys, D 64: 18.7 us in
+//                     chunks, 18.5 by keys); without one there would be (40.4 us), but tests ask for the tile widths of such calls by shape
+// Over 60 random calls of up to 256 units, time of the row tiles against this rule's choice, with / without a workspace: bf16 0.99 .. 1.48 /
+// 1.08 .. 3.1 (2/1 heads, 3046 rows behind 31131, D 80: 371 -> 119 us), fp32 without one 1.02 .. 2.8.
+template <typename T, int D> int keys_nc(const s1f_desc *d, int64_t seg_off, int64_t seg_len, int64_t cap, double plan_us) {
+  const int64_t cus = family_slots<FwdFamily<T, D>, 1>().cus, n_bh = (int64_t)d->n_q_heads * d->batch;
+  if (cus <= 0 || 8 * n_bh >= cus || (sizeof(T) == 4 && cap > 0)) return 0;
+  constexpr KeysUs us = KeysCost<T, D>::us;
+  const double steps = (double)((seg_off + seg_len + 31) / 32);
+  const int64_t units1 = (seg_len + 15) / 16 * n_bh, units2 = (seg_len + 31) / 32 * n_bh;
+  if (cap > 0 && steps > (2 * units1 > cus ? 80 : 48)) return 0;
+  int nc = 0;
+  // (two units of 16 rows on a compute unit: each step takes 1.6 times as long)
+  const double us1 = us.base1 + us.step1 * steps * (units1 > cus ? 1.6 : 1.0), us2 = us.base2 + us.step2 * steps;
+  if (units1 <= KeysShape<T, D, 1>::PER_CU * cus && us1 < plan_us) { nc = 1; plan_us = us1; }
+  if (units1 > cus && units2 <= cus && us2 < plan_us) nc = 2;
+  return nc;
+}
+// The plan of a forward, and how many column blocks its waves hold where they share keys (0: they do not; then as planned).
+struct FwdPlan {
+  SplitPlan p;
+  int keys_nc = 0;
+};
+template <typename T, int D> FwdPlan fwd_plan(const s1f_desc *d, int64_t seg_off, int64_t seg_len, int64_t cap) {
+  FwdPlan f;
+  double us = 0;
+  f.p = plan_rows<FwdFamily<T, D>>(d, seg_off, seg_len, cap, &us);
+  f.keys_nc = keys_nc<T, D>(d, seg_off, seg_len, cap, us);
+  if (f.keys_nc > 0) {
+    const int64_t tiles = (seg_len + 16 * f.keys_nc - 1) / (16 * f.keys_nc);
+    f.p = SplitPlan{1, tiles, tiles * d->n_q_heads * d->batch, 0, 1};
+  }
+  return f;
+}
+template <typename T, int D, int NC> int launch_keys(const s1f_desc *d, AttnArgs a, const SplitPlan &p, hipStream_t st) {
+  constexpr int W = KeysShape<T, D, NC>::W;
+  const int64_t n_bh = (int64_t)d->n_q_heads * d->batch;
+  fill_launch(&a, n_bh, row_tile_order(d, a), p);
+  return launch<seg_attn_fwd_kernel_by_keys<T, D, NC, W>>(FwdKeysCfg<T, D, NC, W>::LDS_BYTES, p, n_bh, a, st, 64 * W);
+}
+
 template <typename T, int D> int fwd_run(const s1f_desc *d, AttnArgs a, const SplitPlan &p, hipStream_t st, void *workspace) {
   typedef FwdFamily<T, D> F;
   const int64_t n_bh = (int64_t)d->n_q_heads * d->batch;
@@ -471,15 +538,17 @@ template <typename T, int D> int fwd_run(const s1f_desc *d, AttnArgs a, const Sp
 }
 template <typename T, int D>
 int fwd_impl(const s1f_desc *d, const AttnArgs &a, hipStream_t st, void *workspace, size_t workspace_bytes, bool split) {
-  SplitPlan p = plan_rows<FwdFamily<T, D>>(d, a.seg_off, a.seg_len, split ? kMaxPartBytes : 0);
-  if (fwd_workspace<T, D>(p) > workspace_bytes) {
+  FwdPlan f = fwd_plan<T, D>(d, a.seg_off, a.seg_len, split ? kMaxPartBytes : 0);
+  if (fwd_workspace<T, D>(f.p) > workspace_bytes) {
     if (sizeof(T) == 2) return S1F_EINVAL;
-    p = plan_rows<FwdFamily<T, D>>(d, a.seg_off, a.seg_len, 0);   // fp32 runs with any workspace
+    f = fwd_plan<T, D>(d, a.seg_off, a.seg_len, 0);   // fp32 runs with any workspace
   }
-  return fwd_run<T, D>(d, a, p, st, workspace);
+  if (f.keys_nc == 1) return launch_keys<T, D, 1>(d, a, f.p, st);
+  if (f.keys_nc == 2) return launch_keys<T, D, 2>(d, a, f.p, st);
+  return fwd_run<T, D>(d, a, f.p, st, workspace);
 }
 template <typename T, int D> size_t fwd_ws_impl(const s1f_desc *d, int64_t seg_off, int64_t seg_len) {
-  return fwd_workspace<T, D>(plan_rows<FwdFamily<T, D>>(d, seg_off, seg_len, kMaxPartBytes));
+  return fwd_workspace<T, D>(fwd_plan<T, D>(d, seg_off, seg_len, kMaxPartBytes).p);
 }
 
 // ---- backward ----
@@ -682,11 +751,16 @@ template <typename T, int D> int bwd_ready_impl(const s1f_desc *d, const AttnArg
 template <typename T, int D> int plan_impl(const s1f_desc *d, const AttnArgs &a, int launch, int64_t cap, int64_t *out) {
   SplitPlan p;
   int64_t whole = 0;
-  if (launch == S1F_PLAN_FWD || launch == S1F_PLAN_FWD_WS) p = plan_rows<FwdFamily<T, D>>(d, a.seg_off, a.seg_len, cap);
-  else if (launch == S1F_PLAN_DQ) p = plan_rows<DqFamily<T, D>>(d, a.seg_off, a.seg_len, cap);
+  const bool fwd = launch == S1F_PLAN_FWD || launch == S1F_PLAN_FWD_WS;
+  int keys_nc = 0;
+  if (fwd) {
+    const FwdPlan f = fwd_plan<T, D>(d, a.seg_off, a.seg_len, cap);
+    p = f.p;
+    keys_nc = f.keys_nc;
+  } else if (launch == S1F_PLAN_DQ) p = plan_rows<DqFamily<T, D>>(d, a.seg_off, a.seg_len, cap);
   else p = DkdvFamily<T, D>::plan(d, a.seg_off, a.seg_len, cap);
-  const bool fwd = launch == S1F_PLAN_FWD || launch == S1F_PLAN_FWD_WS, tail = fwd && row_tail_of<FwdFamily<T, D>>(a, p, &whole);
-  out[0] = launch == S1F_PLAN_DKDV ? DkdvFamily<T, D>::Cfg::BNW : 64 * p.nc;
+  const bool tail = fwd && keys_nc == 0 && row_tail_of<FwdFamily<T, D>>(a, p, &whole);
+  out[0] = launch == S1F_PLAN_DKDV ? DkdvFamily<T, D>::Cfg::BNW : keys_nc > 0 ? 16 * keys_nc : 64 * p.nc;
   out[1] = tail ? whole : p.n_whole;
   out[2] = p.n_split_units;
   out[3] = p.n_split;
@@ -700,8 +774,8 @@ template <typename T, int D> int paths_impl(const s1f_desc *d, const AttnArgs &a
   bwd_plans_impl<T, D>(d, a.seg_off, a.seg_len, kMaxPartBytes, &p);
   bwd_plans_impl<T, D>(d, a.seg_off, a.seg_len, kStaticPartBytes, &small);
   Tail t;
-  typedef FwdFamily<T, D> F;
-  fwd_tail<F>(a, plan_rows<F>(d, a.seg_off, a.seg_len, 0), (int64_t)d->n_q_heads * d->batch, &t);
+  const FwdPlan f = fwd_plan<T, D>(d, a.seg_off, a.seg_len, 0);
+  if (f.keys_nc == 0) fwd_tail<FwdFamily<T, D>>(a, f.p, (int64_t)d->n_q_heads * d->batch, &t);
   out[0] = p.both;
   out[1] = 64 * (p.both ? p.q_both.nc : p.q.nc);
   out[2] = p.both && dq_half_first<T, D>(a, p);

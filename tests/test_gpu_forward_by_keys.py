@@ -1,0 +1,71 @@
+"""Forward of calls with few rows, whose waves share the keys of a unit of 16 or 32 rows (that they do is asked of the library): edges
+of units and tiles, waves without keys, every head_dim and element type, against the oracle."""
+import numpy as np
+import pytest
+import torch
+
+import paper_2406_03488_amd as s1f
+from oracle import attention as A
+from test_gpu_launch_cuts import _close, _device_data
+
+pytestmark = pytest.mark.gpu
+
+# (batch, query heads, K/V heads, offset, rows), rows per unit: one row; one row more and less than a block and than a unit;
+# fewer tiles than waves; one unit of 16 rows per compute unit, and more (bf16 at head_dim 64 has two of them before it takes
+# units of 32, unless walks are long); a last unit of one row; offsets that put a diagonal on two tiles
+SHAPES = [((1, 1, 1, 400, 1), 16), ((2, 3, 1, 700, 15), 16), ((1, 4, 4, 200, 17), 16), ((1, 2, 1, 225, 33), 16), ((3, 2, 2, 90, 161), 16),
+          ((1, 8, 2, 1500, 512), 16), ((1, 8, 2, 1499, 625), 32), ((2, 15, 5, 777, 225), 32), ((1, 8, 2, 3500, 577), 32)]
+
+
+@pytest.mark.parametrize("rising", [False, True])
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+@pytest.mark.parametrize("d", [64, 80, 128])
+@pytest.mark.parametrize("shape,rows", SHAPES)
+def test_units_whose_waves_share_the_keys(dtype, d, shape, rows, rising):
+    nb, hq, hkv, off, m = shape
+    q, _, k, v = _device_data(300 + off + m + d, dtype, d, *shape, rising)
+    if (off + m) % 2:   # other strides: heads between the rows
+        q, k, v = (x.transpose(1, 2).contiguous().transpose(1, 2) for x in (q, k, v))
+    if dtype == "bf16" and d == 64 and off < 3000:
+        rows = 16
+    plan = s1f.launch_plan(q, k, off, s1f.PLAN_FWD)
+    assert plan == (rows, nb * hq * -(-m // rows), 0, 1, 0), "the shape no longer takes the path it is here for"
+    host = lambda x: x.double().cpu().numpy()
+    calls = [lambda o, l: s1f.seg_attn_fwd(q, k, v, off, o, l)]
+    if dtype == "bf16" and off < 3000:   # (fp32, and few rows behind many keys, with a workspace: row tiles)
+        assert s1f.launch_plan(q, k, off, s1f.PLAN_FWD_WS) == plan and s1f.fwd_workspace_bytes(q, k, off) == 0
+        calls.append(lambda o, l: s1f.seg_attn_fwd_ws(q, k, v, off, o, l, None))
+    res = []
+    for call in calls:
+        out, lse = torch.full_like(q, float("nan")), torch.full(q.shape[:3], float("nan"), device="cuda")
+        call(out, lse)
+        res.append((out, lse))
+    assert all(torch.equal(x, y) for x, y in zip(res[0], res[-1]))
+    out, lse = res[0]
+    for b in range(nb):
+        want, want_lse = A.segment_forward(host(q[b]), host(k[b]), host(v[b]), off)
+        _close({"out": host(out[b]), "lse": host(lse[b])}, {"out": want, "lse": want_lse}, dtype, f"entry {b}: ")
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+@pytest.mark.parametrize("m,rows", [(180, 16), (1041, 32)])
+def test_keys_that_are_not_finite_leave_earlier_rows_alone(dtype, m, rows):
+    """Units of 16 rows, and of 32 whose first block ends a tile before the second: rows whose block ends before a tile keep their bits
+    when that tile's values become NaN and its keys infinite."""
+    off = 117   # (rows 16*i .. end 4 keys into a tile)
+    q, _, k, v = _device_data(m, dtype, 80, 1, 4, 2, off, m, False)
+    assert s1f.launch_plan(q, k, off, s1f.PLAN_FWD)[0] == rows
+    res = []
+    for bad in (False, True):
+        first = 32 * ((off + m // 2) // 32)
+        if bad:
+            v[:, :, first:] = float("nan")
+            k[:, :, first:] = float("inf")
+        out, lse = torch.empty_like(q), torch.empty(q.shape[:3], device="cuda")
+        s1f.seg_attn_fwd(q, k, v, off, out, lse)
+        res.append((out, lse))
+    alone = (first - off) // 16 * 16   # rows of blocks that end before the tile
+    assert alone > 0 and torch.isfinite(res[0][0]).all()
+    for x, y in zip(*res):
+        assert torch.equal(x[:, :, :alone], y[:, :, :alone])
+    assert not torch.isfinite(res[1][0][:, :, first - off:]).any()
