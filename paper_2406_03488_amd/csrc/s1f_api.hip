@@ -562,17 +562,24 @@ template <typename T, int D> struct DkdvFamily {
   static constexpr int LDS = Cfg::LDS_BYTES, THREADS = 64 * Cfg::WAVES;
   static constexpr int64_t part_bytes = 2 * (int64_t)Cfg::BNW * D * 4;
   static constexpr auto kernel() { return seg_attn_bwd_dkdv_kernel<T, D, Shape<T, D>::KWGS>; }
-  static SplitPlan plan(const s1f_desc *d, int64_t seg_off, int64_t seg_len, int64_t cap) {
+  static Slots slots() {
     static std::atomic<int64_t> cache[kMaxDevices];
+    return resident_slots<kernel()>(LDS, cache, THREADS);
+  }
+  // iterations of a unit: of one that every row sees, and on average
+  static double most_steps(const s1f_desc *d, int64_t seg_len) { return (double)(d->n_q_heads / d->n_kv_heads) * (double)((seg_len + 31) / 32); }
+  static double mean_steps(const s1f_desc *d, int64_t seg_off, int64_t seg_len) {
+    return most_steps(d, seg_len) * ((double)seg_off + 0.5 * (double)seg_len) / (double)(seg_off + seg_len);
+  }
+  static SplitPlan plan(const s1f_desc *d, int64_t seg_off, int64_t seg_len, int64_t cap) {
     const int64_t kv_len = seg_off + seg_len, units = (kv_len + Cfg::BNW - 1) / Cfg::BNW * d->n_kv_heads * d->batch;
     SplitPlan p;
     p.n_tiles = (kv_len + Cfg::BNW - 1) / Cfg::BNW;
     p.n_whole = units;
     if (cap <= 0) return p;
-    const Slots s = resident_slots<kernel()>(LDS, cache, THREADS);
+    const Slots s = slots();
     if (s.total <= 0) return p;
-    const double most = (double)(d->n_q_heads / d->n_kv_heads) * (double)((seg_len + 31) / 32);
-    const double mean = most * ((double)seg_off + 0.5 * (double)seg_len) / (double)kv_len;
+    const double most = most_steps(d, seg_len), mean = mean_steps(d, seg_off, seg_len);
     double t = 1e300;
     // never more partial results than the built-in scratch holds: s1f_seg_attn_bwd and its _noalloc form then cut alike
     // and add in the same order
@@ -607,20 +614,130 @@ template <typename T, int D> bool both_halves(const s1f_desc *d, int64_t seg_off
   const double step_us = Cost<T, D>::dq.at(p.q.nc, 2) / (64 * p.q.nc) + Cost<T, D>::dkdv.at(0, 2) / 128;        // per 32 of them
   return cells / 32 * step_us / 512 < kBothUs;   // (two workgroups on each of 256 compute units, as the step times presume)
 }
-template <typename T, int D> int bwd_plans_impl(const s1f_desc *d, int64_t seg_off, int64_t seg_len, int64_t cap, BwdPlans *p) {
-  p->q = plan_rows<DqFamily<T, D>>(d, seg_off, seg_len, cap);
-  p->k = DkdvFamily<T, D>::plan(d, seg_off, seg_len, cap);
-  const size_t qb = (size_t)(p->q.chunks() * 64 * p->q.nc * D * 4);
-  const size_t kb = (size_t)((p->k.chunks() - p->k.n_split_units) * DkdvFamily<T, D>::part_bytes);
+// Time of both halves in one launch: groups of workgroups of equal length, handed to the slots in the order of their ids.
+struct Group {
+  int64_t count;
+  double us;
+};
+double groups_us(const Group *g, int n, int64_t slots) {
+  struct { double at; int64_t count; } ends[64];   // when slots become free, in order
+  int n_ends = 1;
+  ends[0] = {0, slots};
+  double last = 0;
+  for (int i = 0; i < n; ++i)
+    for (int64_t left = g[i].count; left > 0;) {
+      const double end = ends[0].at + g[i].us;
+      const int64_t now = left < ends[0].count ? left : ends[0].count;
+      left -= now;
+      last = end > last ? end : last;
+      if ((ends[0].count -= now) == 0) {
+        for (int x = 1; x < n_ends; ++x) ends[x - 1] = ends[x];
+        --n_ends;
+      }
+      int x = n_ends;
+      while (x > 0 && ends[x - 1].at > end) --x;
+      if (n_ends == 64) return 1e300;
+      for (int y = n_ends; y > x; --y) ends[y] = ends[y - 1];
+      ends[x] = {end, now};
+      ++n_ends;
+    }
+  return last;
+}
+// The cut of the dK/dV half, and the number of chunks of the dQ half where all of its units are cut, for the one launch of a segment
+// behind a prefix: its slots and its merge are shared, and as long as there is a compute unit for every workgroup, steps are short.  Each
+// half cut as if it ran alone / so, backward of a segment, us: 2 x 8/2 heads, D 64, 340 rows behind 1017 29.0 / 27.4 (228 workgroups instead
+// of 316); 4 heads fp32, D 64, 256 behind 768 26.2 / 24.6 (256 instead of 416); 4 heads, D 128, 427 behind 2318 35.5 / 31.0; 8/2 heads, D
+// 128, 645 behind 8640 126 / 100.  The prediction is good for about 10 %, hence the margins; of first segments, whose units differ in
+// length, it is not (1.25 times slower at worst).  Of 320 random calls 26 get another plan: 0.86 to 1.04 of the time, 0.955 on average.
+// A function of the plan that the dQ half has with the built-in scratch, so that dK and dV do not depend on the workspace.
+constexpr int64_t kJointRounds = 8;   // (longer launches: as alone)
+template <typename T, int D> void plan_together(const s1f_desc *d, int64_t seg_off, int64_t seg_len, BwdPlans *p) {
+  typedef DkdvFamily<T, D> K;
+  const Slots s = K::slots();
+  SplitPlan q = p->q_both, k = p->k;
+  const int64_t n_qh = (int64_t)d->n_q_heads * d->batch, uq = q.n_tiles * n_qh, uk = k.n_tiles * d->n_kv_heads * d->batch;
+  if (s.total <= 0 || uq + uk > kJointRounds * s.total || seg_off < seg_len) return;
+  const double q_mean = (double)seg_off / 32 + (double)(seg_len + 1) / 64 + 1, q_most = (double)(seg_off + seg_len) / 32 + 1;
+  const double k_mean = K::mean_steps(d, seg_off, seg_len), k_most = K::most_steps(d, seg_len);
+  const int64_t q_bytes = DqFamily<T, D>::row_bytes * 64 * q.nc;
+  const bool cut_q = q.n_whole == 0 && q.n_split_units > 0, whole_k = k.n_split_units == 0;
+  double best = 1e300;
+  auto consider = [&]() {
+    const int64_t part = (k.chunks() - k.n_split_units) * K::part_bytes;
+    if (part > kStaticPartBytes) return;
+    const int64_t n = q.grid() + k.grid(), per_cu = n >= s.total ? s.total / s.cus : (n + s.cus - 1) / s.cus;
+    const double q_step = Cost<T, D>::dq.at(q.nc, per_cu), k_step = Cost<T, D>::dkdv.at(0, per_cu);
+    const double q_one = q_step * q_most / (q.n_whole > 0 ? 1 : q.n_split), k_one = k_step * k_most / (k.n_whole > 0 ? 1 : k.n_split);
+    double us = (q_one > k_one ? q_one : k_one) + kRoundUs;   // side by side
+    if (n > s.total) {
+      const double lq = q_step * q_mean, lk = k_step * k_mean;
+      const Group groups[4] = {{q.n_whole, lq + kRoundUs}, {q.chunks(), lq / q.n_split + kRoundUs},
+                               {k.n_whole, lk + kRoundUs}, {k.chunks(), lk / k.n_split + kRoundUs}};
+      const int a = q_one >= k_one ? 0 : 2;
+      const Group in_order[4] = {groups[a], groups[a + 1], groups[2 - a], groups[3 - a]};
+      const double all = groups_us(in_order, 4, s.total);
+      us = all > 0.75 * us ? all : 0.75 * us;   // (the longest unit shares its compute unit for about half of its life)
+    }
+    if (q.n_split_units + k.n_split_units > 0) us += kMergeUs + (double)(q.chunks() * q_bytes + part) / kMergeBytesPerUs;
+    // The first is the plan as alone; others have to be better by more than the prediction is good for.
+    if (best == 1e300) best = 0.88 * us;
+    if (us >= (whole_k && k.n_split > 1 ? 0.9 : 1.0) * best) return;
+    best = us;
+    p->k = k;
+    if (cut_q) p->q.n_split = p->q_both.n_split = q.n_split;
+  };
+  consider();
+  const double over = (double)uq * q_mean * Cost<T, D>::dq.at(q.nc, 2) / (k_mean * Cost<T, D>::dkdv.at(0, 2)) + (double)uk;
+  // units to cut: all, those of the last, partial round if all ran in rounds of the dK/dV half's, and if there were no other half
+  const int64_t rests[3] = {uk, ((int64_t)over % s.total + 7) / 8 * 8, uk % s.total};
+  const int planned = q.n_split;
+  for (int nq : {planned, 8, 6, 4, 3}) {
+    if (nq != planned && (!cut_q || nq > planned)) continue;
+    q.n_split = nq;
+    for (int n : {1, 2, 3, 4, 6, 8}) {
+      if (n > 1 && k_mean < n) break;
+      for (int64_t r : rests) {
+        if (r == 0 || r > uk || (r < uk && uq + uk < s.total)) continue;
+        k.n_split = n;
+        k.n_split_units = n == 1 ? 0 : r;
+        k.n_whole = uk - k.n_split_units;
+        consider();
+        if (n == 1) break;
+      }
+    }
+  }
+}
+// The dQ half's plan in one launch with the other.  Whole units give the same bits in tiles of any width.  fp32 above head_dim 64: the
+// 64-row tiles run in workgroups of another size than the dK/dV half, and 128 rows in eight waves are faster next to it: 32 heads,
+// head_dim 128, backward of 1020 rows 221 -> 160 us, of 980 rows behind 1020 keys 518 -> 450
+template <typename T, int D> void one_launch_dq(const s1f_desc *d, int64_t seg_len, BwdPlans *p) {
   p->q_both = p->q;
-  // Whole units give the same bits in tiles of any width.  fp32 above head_dim 64: the 64-row tiles run in workgroups of another
-  // size than the dK/dV half, and 128 rows in eight waves are faster next to it: 32 heads, head_dim 128, backward of 1020 rows 221
-  // -> 160 us, of 980 rows behind 1020 keys 518 -> 450
   if (sizeof(T) == 4 && !Shape<T, D>::both(p->q.nc) && p->q.n_split_units == 0) {
     p->q_both.nc = DqFamily<T, D>::MAX;
     p->q_both.n_tiles = (seg_len + 64 * p->q_both.nc - 1) / (64 * p->q_both.nc);
     p->q_both.n_whole = p->q_both.n_tiles * d->n_q_heads * d->batch;
   }
+}
+template <typename T, int D> int bwd_plans_impl(const s1f_desc *d, int64_t seg_off, int64_t seg_len, int64_t cap, BwdPlans *p) {
+  p->q = plan_rows<DqFamily<T, D>>(d, seg_off, seg_len, cap);
+  p->k = DkdvFamily<T, D>::plan(d, seg_off, seg_len, cap);
+  one_launch_dq<T, D>(d, seg_len, p);
+  if (cap > 0) {
+    BwdPlans c = *p;   // as with the built-in scratch
+    const bool same = cap <= kStaticPartBytes || p->q.chunks() * 64 * p->q.nc * D * 4 <= kStaticPartBytes;
+    if (!same) {
+      c.q = plan_rows<DqFamily<T, D>>(d, seg_off, seg_len, kStaticPartBytes);
+      one_launch_dq<T, D>(d, seg_len, &c);
+    }
+    if (both_halves<T, D>(d, seg_off, seg_len, c)) plan_together<T, D>(d, seg_off, seg_len, &c);
+    p->k = c.k;
+    if (same) {
+      p->q = c.q;
+      p->q_both = c.q_both;
+    }
+  }
+  const size_t qb = (size_t)(p->q.chunks() * 64 * p->q.nc * D * 4);
+  const size_t kb = (size_t)((p->k.chunks() - p->k.n_split_units) * DkdvFamily<T, D>::part_bytes);
   p->both = both_halves<T, D>(d, seg_off, seg_len, *p);
   p->k_part = p->both ? align256(qb) : 0;
   p->apart_bytes = stat_bytes(d, seg_len) + (qb > kb ? qb : kb);
@@ -757,8 +874,11 @@ template <typename T, int D> int plan_impl(const s1f_desc *d, const AttnArgs &a,
     const FwdPlan f = fwd_plan<T, D>(d, a.seg_off, a.seg_len, cap);
     p = f.p;
     keys_nc = f.keys_nc;
-  } else if (launch == S1F_PLAN_DQ) p = plan_rows<DqFamily<T, D>>(d, a.seg_off, a.seg_len, cap);
-  else p = DkdvFamily<T, D>::plan(d, a.seg_off, a.seg_len, cap);
+  } else {
+    BwdPlans b;
+    bwd_plans_impl<T, D>(d, a.seg_off, a.seg_len, cap, &b);
+    p = launch == S1F_PLAN_DQ ? b.q : b.k;
+  }
   const bool tail = fwd && keys_nc == 0 && row_tail_of<FwdFamily<T, D>>(a, p, &whole);
   out[0] = launch == S1F_PLAN_DKDV ? DkdvFamily<T, D>::Cfg::BNW : keys_nc > 0 ? 16 * keys_nc : 64 * p.nc;
   out[1] = tail ? whole : p.n_whole;
