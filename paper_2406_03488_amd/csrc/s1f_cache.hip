@@ -28,6 +28,10 @@ struct CopyArgs {
 // there, but rows that are still in a cache, as they are when something has just produced them, are then fetched again
 // (append of the same rows 18.1 -> 21.8 us, emit 26.5 -> 31.6), and fp32 lost at every size (append of 32 heads x 30000 rows,
 // head_dim 64: 235 -> 285 us).
+// fp32 rows: 16 bytes of either half of a row per lane, so that each access takes whole lines, from both tensors before either is
+// stored, since a store in between holds back the loads behind it.  Append of 32 heads x 20000 rows, head_dim 64, 157 -> 124 us (32
+// bytes side by side, both tensors first: 121), of 8 heads x 1000, 128, 4.5 -> 4.1 (4.6).  bf16, whose loads take whole lines as they are,
+// loses with both tensors first (56 heads x 10000, 80: 62 -> 65).
 // SRC/DST: element types (float or bf16_t); float -> bf16 rounds to nearest even.
 template <typename SRC, typename DST> __global__ void __launch_bounds__(256) rows_kernel(const CopyArgs a) {
   const int64_t id = (int64_t)blockIdx.x * 256 + threadIdx.x, per_head = (int64_t)a.rows * a.chunks;
@@ -48,17 +52,22 @@ template <typename SRC, typename DST> __global__ void __launch_bounds__(256) row
   const int64_t so0 = h * a.src_sh + r * a.src_ss + 8 * c, do0 = h * a.dst_sh + r * a.dst_ss + 8 * c;
   for (int b = blockIdx.y; b < a.batch; b += gridDim.y) {
     const int64_t so = b * a.src_sb + so0, dof = b * a.dst_sb + do0;
+    if constexpr (sizeof(DST) == 4) {   // both rows first, then their copies; a lane has the chunks c of both halves of a row
+      u32x4 x[2][2];
+#pragma unroll
+      for (int t = 0; t < 4; ++t)
+        x[t / 2][t % 2] = *reinterpret_cast<const u32x4 *>(reinterpret_cast<const SRC *>(t / 2 ? a.src1 : a.src0) + so + 4 * (t % 2 * a.chunks - c));
+#pragma unroll
+      for (int t = 0; t < 4; ++t)
+        *reinterpret_cast<u32x4 *>(reinterpret_cast<DST *>(t / 2 ? a.dst1 : a.dst0) + dof + 4 * (t % 2 * a.chunks - c)) = x[t / 2][t % 2];
+      continue;
+    }
 #pragma unroll
     for (int t = 0; t < 2; ++t) {
       const SRC *s = reinterpret_cast<const SRC *>(t ? a.src1 : a.src0) + so;
       DST *d = reinterpret_cast<DST *>(t ? a.dst1 : a.dst0) + dof;
-      if (sizeof(SRC) == sizeof(DST)) {
-        if (sizeof(SRC) == 2) {
-          *reinterpret_cast<u32x4 *>(d) = *reinterpret_cast<const u32x4 *>(s);
-        } else {
-          reinterpret_cast<u32x4 *>(d)[0] = reinterpret_cast<const u32x4 *>(s)[0];
-          reinterpret_cast<u32x4 *>(d)[1] = reinterpret_cast<const u32x4 *>(s)[1];
-        }
+      if (sizeof(SRC) == 2) {
+        *reinterpret_cast<u32x4 *>(d) = *reinterpret_cast<const u32x4 *>(s);
       } else {   // fp32 -> bf16
         const f32x4 x = reinterpret_cast<const f32x4 *>(s)[0], y = reinterpret_cast<const f32x4 *>(s)[1];
         bf16x8 o;
