@@ -36,9 +36,12 @@ S1F_DEV void bwd_row_stats(const AttnArgs &a, const typename Mat<T, D>::RowOp &d
 // in the dQ kernel's own prologue.  Bound by its launch (4 to 5 us of small calls) or by memory (67 MB of out and dout: 15 us).
 template <typename T, int D> __global__ void __launch_bounds__(256) seg_attn_bwd_stats_kernel(const AttnArgs a) {
   typedef Mat<T, D> M;
-  const int groups = (a.seg_len + 63) / 64, bh = (int)blockIdx.x / groups, lane = threadIdx.x & 63, j = lane >> 4;
-  const int r = ((int)blockIdx.x - bh * groups) * 64 + ((int)threadIdx.x >> 6) * 16 + (lane & 15), rc = r < a.seg_len ? r : a.seg_len - 1;
-  const int h = bh % a.n_q_heads, b = bh / a.n_q_heads;
+  int bh, group64;
+  div_mod(blockIdx.x, a.by_groups, bh, group64);
+  const int lane = threadIdx.x & 63, j = lane >> 4;
+  const int r = group64 * 64 + ((int)threadIdx.x >> 6) * 16 + (lane & 15), rc = r < a.seg_len ? r : a.seg_len - 1;
+  int b, h;
+  div_mod(bh, a.by_heads, b, h);
   const int64_t off = b * a.q_sb + h * a.q_sh + (int64_t)rc * a.q_ss;
   typename M::RowOp dor;
   M::load_row(dor, reinterpret_cast<const T *>(a.dout) + off, j);
@@ -77,18 +80,20 @@ template <typename T, int D, int NC, int WAVES, bool STATS> S1F_DEV void bwd_dq_
 
   const int tid = threadIdx.x, lane = tid & 63, j = lane >> 4, n = lane & 15;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const UnitChunk uc = split_unit(id, a.n_whole, a.n_split, a.n_split_units);
+  const UnitChunk uc = split_unit(id, a.n_whole, a.n_split, a.n_split_units, a.by_split_units);
   int qt, bh;
-  decode_workgroup(uc.unit, a.n_tiles, a.n_bh, a.tile_major, qt, bh);
+  decode_workgroup(uc.unit, a.by_tiles, a.n_bh, a.by_xcd, a.tile_major, qt, bh);
   qt = a.n_tiles - 1 - qt;   // later (heavier) row tiles are scheduled first
-  const int h = bh % a.n_q_heads, b = bh / a.n_q_heads, hk = h / a.group;
+  int b, h;
+  div_mod(bh, a.by_heads, b, h);
+  const int hk = div(h, a.by_group);
   const int seg_len = a.seg_len;
   const int row0 = qt * BM, wrow0 = row0 + wave * 16 * NC;
   const int last_row = (row0 + BM < seg_len ? row0 + BM : seg_len) - 1;
   // This workgroup's key tiles: all that hold keys 0 .. seg_off+last_row, or one chunk of them.  From here on keys
   // are counted from the chunk's first key: seg_off and kv_len are relative to it.
   int kt0, kt1;
-  chunk_range(uc, (a.seg_off + row0) / BN, (a.seg_off + last_row) / BN + 1, kt0, kt1);
+  chunk_range(uc, a.by_split, (a.seg_off + row0) / BN, (a.seg_off + last_row) / BN + 1, kt0, kt1);
   const int seg_off = a.seg_off - BN * kt0, kv_len = seg_off + seg_len;
   const int n_kt = kt1 - kt0;
 
@@ -342,13 +347,15 @@ template <typename T, int D, int NC, int WAVES, bool STATS> S1F_DEV void bwd_dq_
 // Thread and grid layout as in seg_attn_fwd_merge_kernel.
 template <typename T, int D, int MC> S1F_DEV void bwd_dq_merge_body(const AttnArgs &a, int id) {
   constexpr int C4 = D / 4, RG = 256 / C4;
-  const int BM = a.bm, GROUPS = (BM + RG - 1) / RG;
-  const int unit = id / GROUPS, rg = id % GROUPS;
+  const int BM = a.bm;
+  int unit, rg;
+  div_mod(id, a.by_groups, unit, rg);
   const int rl = rg * RG + (int)threadIdx.x / C4, c4 = (int)threadIdx.x % C4;
   int qt, bh;
-  decode_workgroup(a.n_whole + unit, a.n_tiles, a.n_bh, a.tile_major, qt, bh);
+  decode_workgroup(a.n_whole + unit, a.by_tiles, a.n_bh, a.by_xcd, a.tile_major, qt, bh);
   qt = a.n_tiles - 1 - qt;
-  const int h = bh % a.n_q_heads, b = bh / a.n_q_heads;
+  int b, h;
+  div_mod(bh, a.by_heads, b, h);
   const int r = qt * BM + rl, S = a.n_split;
   if ((int)threadIdx.x >= RG * C4 || rl >= BM || r >= a.seg_len) return;
   int slot0, slot_step;
@@ -416,11 +423,11 @@ template <typename T, int D> S1F_DEV void bwd_dkdv_body(const AttnArgs &a, int i
 
   const int tid = threadIdx.x, lane = tid & 63, j = lane >> 4, n = lane & 15;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const UnitChunk uc = split_unit(id, a.n_whole, a.n_split, a.n_split_units);
+  const UnitChunk uc = split_unit(id, a.n_whole, a.n_split, a.n_split_units, a.by_split_units);
   int kt, bh;
-  decode_workgroup(uc.unit, a.n_tiles, a.n_bh, a.tile_major, kt, bh);   // early key tiles see every query row: heaviest first
-  const int n_kv_heads = a.n_q_heads / a.group;
-  const int hk = bh % n_kv_heads, b = bh / n_kv_heads;
+  decode_workgroup(uc.unit, a.by_tiles, a.n_bh, a.by_xcd, a.tile_major, kt, bh);   // early key tiles see every query row: heaviest first
+  int b, hk;
+  div_mod(bh, a.by_kv_heads, b, hk);
   const int seg_off = a.seg_off, seg_len = a.seg_len, kv_len = seg_off + seg_len;
   const int j0 = kt * Cfg::BNW;                    // first key of the workgroup
   const int wkey0 = j0 + wave * 16 * CB;                // first key of the wave
@@ -436,8 +443,22 @@ template <typename T, int D> S1F_DEV void bwd_dkdv_body(const AttnArgs &a, int i
   const int n_qt = (seg_len + BQ - 1) / BQ;
   const int per_head = n_qt - qt_first;            // >= 1 because j0 < kv_len
   // All iterations, or one chunk of them.
-  const int it_begin = (int)((int64_t)uc.chunk * per_head * a.group / uc.n_chunks);
-  const int it_end = (int)((int64_t)(uc.chunk + 1) * per_head * a.group / uc.n_chunks);
+  const int all = per_head * a.group;
+  int it_begin = 0, it_end = all;
+  if (uc.n_chunks > 1) {
+    if (all < 1 << 27) {   // (16 chunks at most)
+      it_begin = div(uc.chunk * all, a.by_split);
+      it_end = div((uc.chunk + 1) * all, a.by_split);
+    } else {
+      it_begin = (int)((int64_t)uc.chunk * all / uc.n_chunks);
+      it_end = (int)((int64_t)(uc.chunk + 1) * all / uc.n_chunks);
+    }
+  }
+  int head0 = 0, tile0 = it_begin;   // where iteration it_begin is
+  if (it_begin > 0) {
+    head0 = it_begin / per_head;
+    tile0 = it_begin - head0 * per_head;
+  }
   const float c = uniform(a.scale * kLog2e / (M::UP * M::UP));
   const bool w_active = wkey0 < kv_len;
 
@@ -484,8 +505,8 @@ template <typename T, int D> S1F_DEV void bwd_dkdv_body(const AttnArgs &a, int i
       asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dword %1, %2" : : "s"(dst), "v"(so), "s"(sb) : "m0");
     }
   };
-  Cursor t_iss = {(qt_first + it_begin % per_head) * BQ, hk * a.group + it_begin / per_head, 0};   // next tile to copy
-  Cursor cur = t_iss;                                                                              // tile of the current iteration
+  Cursor t_iss = {(qt_first + tile0) * BQ, hk * a.group + head0, 0};   // next tile to copy
+  Cursor cur = t_iss;                                                  // tile of the current iteration
   if (it_begin < it_end) issue(t_iss);
   advance(t_iss);
   // K rows of the wave's keys stay in registers for the whole kernel.
@@ -730,8 +751,9 @@ template <typename T, int D, int MC> S1F_DEV void bwd_dkdv_merge_body(const Attn
   const int unit = id / DM::GROUPS, g = id % DM::GROUPS;
   const int which = g / (DM::GROUPS / 2), t = (g % (DM::GROUPS / 2)) * 256 + (int)threadIdx.x;
   int kt, bh;
-  decode_workgroup(a.n_whole + unit, a.n_tiles, a.n_bh, a.tile_major, kt, bh);
-  const int n_kv_heads = a.n_q_heads / a.group, hk = bh % n_kv_heads, b = bh / n_kv_heads;
+  decode_workgroup(a.n_whole + unit, a.by_tiles, a.n_bh, a.by_xcd, a.tile_major, kt, bh);
+  int b, hk;
+  div_mod(bh, a.by_kv_heads, b, hk);
   const int key = kt * 128 + t / (D / 4), S = a.n_split - 1;   // partial results
   if (key >= a.seg_off + a.seg_len) return;
   int slot0, slot_step;

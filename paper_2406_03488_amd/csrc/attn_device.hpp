@@ -77,6 +77,25 @@ template <> S1F_DEV void store4<bf16_t>(bf16_t *p, float a, float b, float c, fl
   *reinterpret_cast<bf16x4 *>(p) = r;
 }
 
+// Division by a number that the host knows: n / d = n * mul >> (31 + shift) for 0 <= n < 2^31 (with 2^shift >= d and mul =
+// floor(2^(31 + shift) / d) + 1 the product exceeds n * 2^(31 + shift) / d by less than 2^(31 + shift) / d).  Workgroups decode their
+// number with half a dozen of them before their first load; divisions, of some 30 scalar and vector instructions each, took longer: forward
+// of 4 heads, 256 rows behind 768 keys, bf16, D 64 6.4 -> 6.1 us, 63 backwards of up to 30 us 2 % on average.
+struct Divisor {
+  uint32_t mul, shift;
+  int32_t d;
+  static Divisor of(int64_t d) {
+    uint32_t s = 0;
+    while ((int64_t(1) << s) < d) ++s;
+    return Divisor{(uint32_t)(((uint64_t)1 << (31 + s)) / (uint64_t)d + 1), s, (int32_t)d};
+  }
+};
+S1F_DEV int div(int n, const Divisor &by) { return (int)(((uint64_t)(uint32_t)n * by.mul) >> (31 + by.shift)); }
+S1F_DEV void div_mod(int n, const Divisor &by, int &quotient, int &rest) {
+  quotient = div(n, by);
+  rest = n - quotient * by.d;
+}
+
 // Workgroup id -> (tile, batch*head).  The hardware hands consecutive workgroup ids to the 8 XCDs in turn,
 // and each XCD has its own L2.  All tiles of one (batch, head) stream the same K/V prefix (or the same
 // Q/dO segment), so they are given ids that land on one XCD: the shared operand is then fetched from HBM once
@@ -86,21 +105,15 @@ template <> S1F_DEV void store4<bf16_t>(bf16_t *p, float a, float b, float c, fl
 // heads (`tile_major` = 1: the light tiles of every head come last, which shortens the end of a launch whose
 // tiles differ a lot, i.e. the first segments; and heads that share K/V rows walk them together).  Falls back to
 // the plain order when the number of (batch, head) pairs is not a multiple of 8.
-S1F_DEV void decode_workgroup(int id, int n_tiles, int n_bh, int tile_major, int &tile, int &bh) {
+// tiles: per (batch, head) pair; per_xcd: an eighth of the pairs, where that is a whole number
+S1F_DEV void decode_workgroup(int id, const Divisor &tiles, int n_bh, const Divisor &per_xcd, int tile_major, int &tile, int &bh) {
   if ((n_bh & 7) == 0) {
-    const int xcd = id & 7, slot = id >> 3;
-    const int per_xcd = n_bh >> 3;
-    const int first = xcd * per_xcd;
-    if (tile_major) {
-      bh = first + slot % per_xcd;
-      tile = slot / per_xcd;
-    } else {
-      bh = first + slot / n_tiles;
-      tile = slot % n_tiles;
-    }
+    const int slot = id >> 3;
+    if (tile_major) div_mod(slot, per_xcd, tile, bh);
+    else div_mod(slot, tiles, bh, tile);
+    bh += (id & 7) * per_xcd.d;
   } else {
-    bh = id / n_tiles;
-    tile = id % n_tiles;
+    div_mod(id, tiles, bh, tile);
   }
 }
 
@@ -124,9 +137,10 @@ struct UnitChunk {
 // the longest.  A chunk keeps its unit's XCD (workgroup ids go to the XCDs in turn, and decode_workgroup ties a unit
 // to the XCD of its id) whenever n_whole and the number of split units are multiples of 8, which they are when the
 // heads are pinned to XCDs.
-S1F_DEV UnitChunk split_unit(int id, int n_whole, int n_split, int n_split_units) {
+S1F_DEV UnitChunk split_unit(int id, int n_whole, int n_split, int n_split_units, const Divisor &split_units) {
   if (id < n_whole) return UnitChunk{id, 0, 1, -1};
-  const int j = id - n_whole, pass = j / n_split_units, idx = j - pass * n_split_units;
+  int pass, idx;
+  div_mod(id - n_whole, split_units, pass, idx);
   const int chunk = n_split - 1 - pass;
   return UnitChunk{n_whole + idx, chunk, n_split, chunk * n_split_units + idx};
 }
@@ -135,9 +149,10 @@ S1F_DEV void chunk_slots(int unit_idx, int n_split_units, int &first, int &step)
   first = unit_idx;
   step = n_split_units;
 }
-S1F_DEV void chunk_range(const UnitChunk &u, int full, int total, int &begin, int &end) {
-  begin = u.chunk * full / u.n_chunks;
-  end = u.chunk + 1 < u.n_chunks ? (u.chunk + 1) * full / u.n_chunks : total;
+// (at most 16 chunks of 2^25 pieces)
+S1F_DEV void chunk_range(const UnitChunk &u, const Divisor &split, int full, int total, int &begin, int &end) {
+  begin = u.chunk == 0 ? 0 : div(u.chunk * full, split);
+  end = u.chunk + 1 < u.n_chunks ? div((u.chunk + 1) * full, split) : total;
 }
 
 // Arguments common to the three kernels (all strides in elements of the tensor they index).
@@ -152,7 +167,7 @@ struct AttnArgs {
   int64_t q_sb, q_sh, q_ss;
   int64_t kv_sb, kv_sh, kv_ss;
   int32_t seg_off, seg_len;
-  int32_t n_q_heads, group;              // group = Hq / Hkv
+  int32_t n_q_heads, n_kv_heads, group;  // group = Hq / Hkv
   int32_t n_tiles, n_bh;                 // launch shape: tiles per (batch, head) and number of (batch, head) pairs
   int32_t tile_major;                    // order of the workgroups within an XCD (see decode_workgroup)
   float scale;                           // 1/sqrt(head_dim)
@@ -161,7 +176,11 @@ struct AttnArgs {
   int32_t n_whole, n_split, n_split_units;
   int32_t bm;                            // forward and dQ: rows per unit
   int32_t first_id;                      // forward: > 0 in a second launch, over the rows of the units from n_whole = first_id on
-  int32_t rag_tiles;                     // in it: tiles per (batch, head) over the rows behind the n_tiles whole units
+  Divisor by_heads, by_kv_heads, by_group;   // what a workgroup's number is decoded with: n_q_heads, n_kv_heads, group,
+  Divisor by_tiles, by_xcd;                  // n_tiles, n_bh / 8 (see decode_workgroup),
+  Divisor by_split, by_split_units;          // n_split, n_split_units,
+  Divisor by_rag;                            // second launch of a forward: its tiles per (batch, head) behind the n_tiles whole units,
+  Divisor by_groups;                         // workgroups per unit of a merge, or per (batch, head) of the row statistics
   float *part;                           // partial results of the chunks: [chunk][cut unit][rows per unit][head_dim]
   float *part_ml;                        // forward only: running maximum (log2 units) and row sum, [..][rows per unit][2]
 };

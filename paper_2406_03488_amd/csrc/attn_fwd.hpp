@@ -252,27 +252,29 @@ __global__ void __launch_bounds__(64 * WAVES, OCC) seg_attn_fwd_kernel(const Att
   if constexpr (REST) {   // a chunk is a tile of BM of the unit's a.bm rows
     const int cut = a.n_split * a.n_split_units;
     if ((int)blockIdx.x < cut) {
-      uc = split_unit(blockIdx.x + a.first_id, a.first_id, a.n_split, a.n_split_units);
-      decode_workgroup(uc.unit, a.n_tiles, a.n_bh, a.tile_major, qt, bh);
+      uc = split_unit(blockIdx.x + a.first_id, a.first_id, a.n_split, a.n_split_units, a.by_split_units);
+      decode_workgroup(uc.unit, a.by_tiles, a.n_bh, a.by_xcd, a.tile_major, qt, bh);
       row0 = (a.n_tiles - 1 - qt) * a.bm + uc.chunk * BM;
     } else {
-      decode_workgroup(blockIdx.x - cut, a.rag_tiles, a.n_bh, 1, qt, bh);
+      decode_workgroup(blockIdx.x - cut, a.by_rag, a.n_bh, a.by_xcd, 1, qt, bh);
       row0 = a.n_tiles * a.bm + qt * BM;
     }
     if (row0 >= seg_len) return;
     uc = UnitChunk{0, 0, 1, -1};
   } else {
-    uc = split_unit(blockIdx.x, a.n_whole, a.n_split, a.n_split_units);
-    decode_workgroup(uc.unit, a.n_tiles, a.n_bh, a.tile_major, qt, bh);
+    uc = split_unit(blockIdx.x, a.n_whole, a.n_split, a.n_split_units, a.by_split_units);
+    decode_workgroup(uc.unit, a.by_tiles, a.n_bh, a.by_xcd, a.tile_major, qt, bh);
     row0 = (a.n_tiles - 1 - qt) * BM;   // later (heavier) row tiles are scheduled first
   }
-  const int h = bh % a.n_q_heads, b = bh / a.n_q_heads, hk = h / a.group;
+  int b, h;
+  div_mod(bh, a.by_heads, b, h);
+  const int hk = div(h, a.by_group);
   const int wrow0 = row0 + wave * 16 * NC;
   const int last_row = (row0 + BM < seg_len ? row0 + BM : seg_len) - 1;
   // This workgroup's 32-key tiles: all that hold keys 0 .. seg_off+last_row, or one chunk of them.  From here on
   // keys are counted from the chunk's first key: seg_off and kv_len are relative to it.
   int kt0, kt1;
-  chunk_range(uc, (a.seg_off + row0) / BN, (a.seg_off + last_row) / BN + 1, kt0, kt1);
+  chunk_range(uc, a.by_split, (a.seg_off + row0) / BN, (a.seg_off + last_row) / BN + 1, kt0, kt1);
   const int seg_off = a.seg_off - BN * kt0, kv_len = seg_off + seg_len;
   const int n_kt = kt1 - kt0;
   if (n_kt <= 0) {   // more chunks than this unit has whole tiles: a result that the merge gives no weight
@@ -444,13 +446,15 @@ template <int D> struct MergeRows {
 template <typename T, int D, int MC>
 __global__ void __launch_bounds__(256) seg_attn_fwd_merge_kernel(const AttnArgs a) {
   typedef MergeRows<D> MR;
-  const int BM = a.bm, groups = MR::groups(BM);
-  const int unit = (int)blockIdx.x / groups, rg = (int)blockIdx.x % groups;
+  const int BM = a.bm;
+  int unit, rg;
+  div_mod(blockIdx.x, a.by_groups, unit, rg);
   const int rl = rg * MR::RG + (int)threadIdx.x / MR::C4, c4 = (int)threadIdx.x % MR::C4;
   int qt, bh;
-  decode_workgroup(a.n_whole + unit, a.n_tiles, a.n_bh, a.tile_major, qt, bh);
+  decode_workgroup(a.n_whole + unit, a.by_tiles, a.n_bh, a.by_xcd, a.tile_major, qt, bh);
   qt = a.n_tiles - 1 - qt;
-  const int h = bh % a.n_q_heads, b = bh / a.n_q_heads;
+  int b, h;
+  div_mod(bh, a.by_heads, b, h);
   const int r = qt * BM + rl, S = a.n_split;
   if ((int)threadIdx.x >= MR::RG * MR::C4 || rl >= BM || r >= a.seg_len) return;
   int slot0, slot_step;

@@ -131,13 +131,15 @@ __global__ void __launch_bounds__(64 * W, (W + 3) / 4) seg_attn_fwd_kernel_by_ke
   const int tid = threadIdx.x, lane = tid & 63, j = lane >> 4, n = lane & 15;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   int qt, bh;
-  decode_workgroup(blockIdx.x, a.n_tiles, a.n_bh, a.tile_major, qt, bh);
-  const int h = bh % a.n_q_heads, b = bh / a.n_q_heads, hk = h / a.group;
+  decode_workgroup(blockIdx.x, a.by_tiles, a.n_bh, a.by_xcd, a.tile_major, qt, bh);
+  int b, h;
+  div_mod(bh, a.by_heads, b, h);
+  const int hk = div(h, a.by_group);
   const int seg_len = a.seg_len, row0 = (a.n_tiles - 1 - qt) * ROWS;
   const int last_row = (row0 + ROWS < seg_len ? row0 + ROWS : seg_len) - 1;
   // The wave's 32-key tiles.  From here on keys are counted from its first one.
   int kt0, kt1;
-  chunk_range(UnitChunk{0, wave, W, 0}, (a.seg_off + row0) / BN, (a.seg_off + last_row) / BN + 1, kt0, kt1);
+  chunk_range(UnitChunk{0, wave, W, 0}, a.by_split, (a.seg_off + row0) / BN, (a.seg_off + last_row) / BN + 1, kt0, kt1);
   const int seg_off = a.seg_off - BN * kt0, kv_len = seg_off + seg_len, n_kt = kt1 - kt0;
   const T *qb = reinterpret_cast<const T *>(a.q) + b * a.q_sb + h * a.q_sh;
   const int64_t kv_first = b * a.kv_sb + hk * a.kv_sh + (int64_t)(BN * kt0) * a.kv_ss;

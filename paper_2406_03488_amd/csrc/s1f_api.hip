@@ -70,7 +70,8 @@ AttnArgs make_args(const s1f_desc *d, int64_t seg_off, int64_t seg_len) {
   a.q_sb = d->q_stride_b; a.q_sh = d->q_stride_h; a.q_ss = d->q_stride_s;
   a.kv_sb = d->kv_stride_b; a.kv_sh = d->kv_stride_h; a.kv_ss = d->kv_stride_s;
   a.seg_off = (int32_t)seg_off; a.seg_len = (int32_t)seg_len;
-  a.n_q_heads = d->n_q_heads; a.group = d->n_q_heads / d->n_kv_heads;
+  a.n_q_heads = d->n_q_heads; a.n_kv_heads = d->n_kv_heads; a.group = d->n_q_heads / d->n_kv_heads;
+  a.by_heads = Divisor::of(a.n_q_heads); a.by_kv_heads = Divisor::of(a.n_kv_heads); a.by_group = Divisor::of(a.group);
   a.scale = (float)(1.0 / std::sqrt((double)d->head_dim));
   return a;
 }
@@ -287,6 +288,10 @@ void fill_launch(AttnArgs *a, int64_t n_bh, int tile_major, const SplitPlan &p) 
   a->n_split = p.n_split;
   a->n_split_units = (int32_t)p.n_split_units;
   a->bm = 64 * p.nc;
+  a->by_tiles = Divisor::of(p.n_tiles);
+  a->by_xcd = Divisor::of(n_bh < 8 ? 1 : n_bh / 8);
+  a->by_split = Divisor::of(p.n_split);
+  a->by_split_units = Divisor::of(p.n_split_units < 1 ? 1 : p.n_split_units);
 }
 template <auto KERNEL> int launch(int lds_bytes, const SplitPlan &p, int64_t n_bh, AttnArgs a, hipStream_t st, int threads) {
   if (p.n_tiles * n_bh > 0x7fffffff || !one_launch(p.grid(), threads)) return S1F_EUNSUPPORTED;
@@ -300,6 +305,7 @@ template <auto KERNEL> int launch(int lds_bytes, const SplitPlan &p, int64_t n_b
 
 // The merge kernel behind a split launch: `groups` workgroups (of a few rows each) per split unit.
 template <typename K> int launch_merge(K kernel, AttnArgs a, const SplitPlan &plan, int groups, hipStream_t st) {
+  a.by_groups = Divisor::of(groups);
   void *params[] = {&a};
   const hipError_t e = hipLaunchKernel(reinterpret_cast<const void *>(kernel), dim3((unsigned)(plan.n_split_units * groups)),
                                        dim3(256), params, 0, st);
@@ -514,6 +520,7 @@ template <typename T, int D, int NC> int launch_keys(const s1f_desc *d, AttnArgs
   constexpr int W = KeysShape<T, D, NC>::W;
   const int64_t n_bh = (int64_t)d->n_q_heads * d->batch;
   fill_launch(&a, n_bh, row_tile_order(d, a), p);
+  a.by_split = Divisor::of(W);   // (a unit's waves)
   return launch<seg_attn_fwd_kernel_by_keys<T, D, NC, W>>(FwdKeysCfg<T, D, NC, W>::LDS_BYTES, p, n_bh, a, st, 64 * W);
 }
 
@@ -531,13 +538,14 @@ template <typename T, int D> int fwd_run(const s1f_desc *d, AttnArgs a, const Sp
   a.first_id = 0;
   Tail t;
   if (fwd_tail<F>(a, p, n_bh, &t)) {
-    a.rag_tiles = (int32_t)t.rag;
+    a.by_rag = Divisor::of(t.rag < 1 ? 1 : t.rag);
     fill_launch(&a, n_bh, row_tile_order(d, a), t.head);
     const int rc = launch_rows<F>(t.head, n_bh, a, st);
     if (rc != S1F_OK) return rc;
     a.first_id = (int32_t)t.head.n_whole;
     a.n_split = t.rest.n_split;
     a.n_split_units = (int32_t)t.rest.n_split_units;
+    a.by_split_units = Divisor::of(t.rest.n_split_units < 1 ? 1 : t.rest.n_split_units);
     return launch<F::rest_kernel()>(F::LDS, t.rest, n_bh, a, st, F::threads(1));
   }
   const int rc = launch_rows<F>(p, n_bh, a, st);
@@ -756,7 +764,8 @@ template <typename T, int D> int bwd_plans_impl(const s1f_desc *d, int64_t seg_o
 template <typename T, int D> int launch_stats(const s1f_desc *d, AttnArgs a, hipStream_t st) {
   // (within one launch wherever both halves are: more than 2^24 workgroups of 64 rows and still fewer than that of wider tiles need
   // 65 rows each, 2^30 in all, and bwd_prepare allows 2^28)
-  const int64_t grid = ((int64_t)a.seg_len + 63) / 64 * d->n_q_heads * d->batch;
+  const int64_t groups = ((int64_t)a.seg_len + 63) / 64, grid = groups * d->n_q_heads * d->batch;
+  a.by_groups = Divisor::of(groups);
   void *params[] = {&a};
   const hipError_t e = hipLaunchKernel(reinterpret_cast<const void *>(seg_attn_bwd_stats_kernel<T, D>), dim3((unsigned)grid), dim3(256),
                                        params, 0, st);
@@ -766,6 +775,7 @@ template <typename T, int D> int launch_stats(const s1f_desc *d, AttnArgs a, hip
 template <typename T, int D, int MC>
 int launch_bwd_merge_of(AttnArgs aq, AttnArgs ak, int64_t q_groups, int64_t k_groups, hipStream_t st) {
   int n = (int)q_groups;
+  if (q_groups > 0) aq.by_groups = Divisor::of(MergeRows<D>::groups(aq.bm));
   void *params[] = {&aq, &ak, &n};
   const hipError_t e = hipLaunchKernel(reinterpret_cast<const void *>(seg_attn_bwd_merge_kernel<T, D, MC>),
                                        dim3((unsigned)(q_groups + k_groups)), dim3(256), params, 0, st);
