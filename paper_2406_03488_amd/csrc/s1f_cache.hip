@@ -17,6 +17,7 @@ struct CopyArgs {
   void *dst0, *dst1;
   int64_t src_sb, src_sh, src_ss, dst_sb, dst_sh, dst_ss;   // elements of the respective tensor
   int32_t batch, rows, heads, chunks;                        // chunks of 8 elements per row
+  Divisor by_rows, by_chunks;
 };
 
 // One thread moves 8 consecutive head_dim elements of one row of both tensors of one batch entry; the grid's y runs over
@@ -32,6 +33,8 @@ struct CopyArgs {
 // stored, since a store in between holds back the loads behind it.  Append of 32 heads x 20000 rows, head_dim 64, 157 -> 124 us (32
 // bytes side by side, both tensors first: 121), of 8 heads x 1000, 128, 4.5 -> 4.1 (4.6).  bf16, whose loads take whole lines as they are,
 // loses with both tensors first (56 heads x 10000, 80: 62 -> 65).
+// A thread finds its row by multiplications with the reciprocals of rows and chunks (see Divisor): 2 x 2 heads x 340 rows 2.85 -> 2.74 us, emit
+// of 8 heads x 4096 8.8 -> 8.5.
 // SRC/DST: element types (float or bf16_t); float -> bf16 rounds to nearest even.
 template <typename SRC, typename DST> __global__ void __launch_bounds__(256) rows_kernel(const CopyArgs a) {
   const int64_t id = (int64_t)blockIdx.x * 256 + threadIdx.x, per_head = (int64_t)a.rows * a.chunks;
@@ -39,10 +42,11 @@ template <typename SRC, typename DST> __global__ void __launch_bounds__(256) row
   int64_t h, r;
   int c;
   if (per_head * a.heads <= 0x7fffffff) {
-    const unsigned row = (unsigned)id / (unsigned)a.chunks;
-    c = (int)((unsigned)id % (unsigned)a.chunks);
-    h = row / (unsigned)a.rows;
-    r = row % (unsigned)a.rows;
+    int row, head, in_head;
+    div_mod((int)id, a.by_chunks, row, c);
+    div_mod(row, a.by_rows, head, in_head);
+    h = head;
+    r = in_head;
   } else {
     const int64_t row = id / a.chunks;
     c = (int)(id % a.chunks);
@@ -83,6 +87,8 @@ template <typename SRC, typename DST> int launch_rows(const CopyArgs &a, hipStre
   const int64_t blocks = ((int64_t)a.heads * a.rows * a.chunks + 255) / 256;
   if (blocks > 0x7fffffff) return S1F_EUNSUPPORTED;
   CopyArgs args = a;
+  args.by_rows = Divisor::of(a.rows);
+  args.by_chunks = Divisor::of(a.chunks);
   void *params[] = {&args};
   const dim3 grid((unsigned)blocks, a.batch < 65535 ? a.batch : 65535);
   const hipError_t e = hipLaunchKernel(reinterpret_cast<const void *>(&rows_kernel<SRC, DST>), grid, dim3(256), params, 0, st);
