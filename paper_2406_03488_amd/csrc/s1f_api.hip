@@ -173,11 +173,8 @@ template <> struct Cost<bf16_t, 128> {
   static constexpr StepUs fwd = {0.29, 0.17, 0.36, 0.32, 0, 0}, dq = {0.2, 0.26, 0.32, 0.52, 0, 0}, dkdv = {1.05, 0, 1.65, 0, 0, 0};
 };
 // fp32: the forward at head_dim 80 and 128, dQ at 80 and dK/dV as measured.  Not so the forward at head_dim 64 (up to 19 % above) and
-// dQ at 64 and 128 (alone: up to 1.9 and 2.1 times above; merge 0.7): those values are chosen for the plans that they lead to, cut
-// 64-row dQ units for some launches of less than a round, which the tests of tile widths ask for by shape.  With the measured ones such
-// calls would run in 128-row tiles, faster where that was timed (8/2 heads, head_dim 128: backward of a first segment of 1240 rows
-// 125 -> 98 us, of 941 rows behind 2300 keys 254 -> 213); over 400 shapes the plan taken is predicted to cost 0.1, 1.8 and 2.9 % on
-// average over the best one.
+// dQ at 64 and 128 (alone: up to 1.9 and 2.1 times above; merge 0.7): those values are chosen for the plans that they lead to, some of which
+// the tests of tile widths ask for by shape.  What cut 64-row dQ units cost above head_dim 64 is kept out by DqFamily::cut_narrow.
 template <> struct Cost<float, 64> {
   static constexpr StepUs fwd = {0.72, 0.46, 0.885, 0.92, 0, 0}, dq = {-1.17, 2.23, 0.37, 1.615, 0, 0, 0.7}, dkdv = {2.75, 0, 4.7, 0, 0, 0};
 };
