@@ -20,6 +20,7 @@ typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 
 constexpr float kLog2e = 1.4426950408889634f;
 constexpr float kLn2 = 0.6931471805599453f;
+constexpr float kMaxFloat = 3.402823466e38f;
 
 template <typename T> struct Elem;
 template <> struct Elem<float> { static constexpr int CE = 4; };    // elements per 16-byte chunk

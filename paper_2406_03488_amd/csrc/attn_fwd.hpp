@@ -82,6 +82,29 @@ template <int NC> S1F_DEV void fwd_probs(f32x4 (&p)[2][NC], const f32x4 (&s)[2][
   }
 }
 
+// A tile that sets the maxima of its rows: the running maximum, finite also where every score is minus infinity (which then has weight
+// zero), and probabilities whose products are rounded as those in the maxima are, so that no exponent is above zero.  (A fused product differs
+// from a rounded one by up to half a spacing of m: from scores of 2^31 on, as a lowest value in K makes them, that is 2^7 and more, and
+// p infinite.)
+template <int NC> S1F_DEV void fwd_finite_max(const f32x4 (&s)[2][NC], float (&mx)[NC], float c) {
+  fwd_row_max(s, mx, c);
+#pragma unroll
+  for (int cb = 0; cb < NC; ++cb) mx[cb] = fmaxf(mx[cb], -kMaxFloat);
+}
+template <int NC> S1F_DEV void fwd_probs_of_max(f32x4 (&p)[2][NC], const f32x4 (&s)[2][NC], const float (&m)[NC], float c, float (&rs)[NC]) {
+#pragma clang fp contract(off)
+#pragma unroll
+  for (int cb = 0; cb < NC; ++cb) {
+    rs[cb] = 0.f;
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {
+      const float t = s[i >> 2][cb][i & 3] * c, x = exp2_fast(t - m[cb]);
+      p[i >> 2][cb][i & 3] = x;
+      rs[cb] += x;
+    }
+  }
+}
+
 // Scores of a tile: s[rb][cb] = K[rows 16*rb..] Q[cb]^T   (outside the loop, which uses fwd_step)
 template <typename M, int NC>
 S1F_DEV void fwd_scores(f32x4 (&s)[2][NC], const typename M::RowOp (&q)[NC], const M &rd, lds_addr ktile) {

@@ -197,15 +197,20 @@ __global__ void __launch_bounds__(64 * W, (W + 3) / 4) seg_attn_fwd_kernel_by_ke
       fwd_mask(s, 0, ahead);
       fwd_mask(s, 1, ahead);
     }
-    // The first tile of a wave has a key that each row sees; from then on maxima are raised as in seg_attn_fwd_kernel.
-    if (k == 0) fwd_row_max(s, m, c);
+    // The first tile of a wave has a key that each row sees, but with any score (keys that are to have no weight may fill it); from then
+    // on maxima are raised as in seg_attn_fwd_kernel.
     f32x4 p[2][NC];
-    fwd_probs(p, s, m, c, rs);
+    if (k == 0) {
+      fwd_finite_max(s, m, c);
+      fwd_probs_of_max(p, s, m, c, rs);
+    } else {
+      fwd_probs(p, s, m, c, rs);
+    }
     bool raise = false;
 #pragma unroll
     for (int cb = 0; cb < NC; ++cb) raise = raise || !(rs[cb] <= kRescaleLimit);
     if (__builtin_expect(__builtin_amdgcn_ballot_w64(raise) != 0, 0)) {
-      fwd_row_max(s, mx, c);
+      fwd_finite_max(s, mx, c);
 #pragma unroll
       for (int cb = 0; cb < NC; ++cb) {
         const float m_up = mx[cb] > m[cb] + (kRescaleTau - 3.f) ? mx[cb] : m[cb];
@@ -215,7 +220,7 @@ __global__ void __launch_bounds__(64 * W, (W + 3) / 4) seg_attn_fwd_kernel_by_ke
 #pragma unroll
         for (int db = 0; db < DB; ++db) o[cb][db] = o[cb][db] * alpha;
       }
-      fwd_probs(p, s, m, c, rs);
+      fwd_probs_of_max(p, s, m, c, rs);
     }
     typename M::Slab pf[NC];
 #pragma unroll

@@ -62,7 +62,8 @@ S1F_DEV void fwd_plain(const float *q, const float *k, const float *v, int64_t k
   for (int key = 0; key < keys; ++key) {
     kr.load(k + key * kv_ss, j);
     vr.load(v + key * kv_ss, j);
-    const float s = plain_dot<D>(qr, kr) * c;
+    float s = plain_dot<D>(qr, kr) * c;
+    settle(s);   // the product that the maximum is taken of, rounded: see fwd_probs_of_max
     if (key <= last) {
       const float m_up = fmaxf(m, s), base = m_up == -INFINITY ? 0.f : m_up;
       const float alpha = exp2_fast(m - base), p = exp2_fast(s - base);
