@@ -445,14 +445,9 @@ template <typename T, int D> S1F_DEV void bwd_dkdv_body(const AttnArgs &a, int i
   // All iterations, or one chunk of them.
   const int all = per_head * a.group;
   int it_begin = 0, it_end = all;
-  if (uc.n_chunks > 1) {
-    if (all < 1 << 27) {   // (16 chunks at most)
-      it_begin = div(uc.chunk * all, a.by_split);
-      it_end = div((uc.chunk + 1) * all, a.by_split);
-    } else {
-      it_begin = (int)((int64_t)uc.chunk * all / uc.n_chunks);
-      it_end = (int)((int64_t)(uc.chunk + 1) * all / uc.n_chunks);
-    }
+  if (uc.n_chunks > 1) {   // (at most 16 chunks of 2^28 / 32 + 65535 iterations: batch * heads * rows are at most 2^28)
+    it_begin = div(uc.chunk * all, a.by_split);
+    it_end = div((uc.chunk + 1) * all, a.by_split);
   }
   int head0 = 0, tile0 = it_begin;   // where iteration it_begin is
   if (it_begin > 0) {

@@ -168,7 +168,7 @@ struct AttnArgs {
   int64_t q_sb, q_sh, q_ss;
   int64_t kv_sb, kv_sh, kv_ss;
   int32_t seg_off, seg_len;
-  int32_t n_q_heads, n_kv_heads, group;  // group = Hq / Hkv
+  int32_t n_q_heads, group;              // group = Hq / Hkv
   int32_t n_tiles, n_bh;                 // launch shape: tiles per (batch, head) and number of (batch, head) pairs
   int32_t tile_major;                    // order of the workgroups within an XCD (see decode_workgroup)
   float scale;                           // 1/sqrt(head_dim)
@@ -177,7 +177,7 @@ struct AttnArgs {
   int32_t n_whole, n_split, n_split_units;
   int32_t bm;                            // forward and dQ: rows per unit
   int32_t first_id;                      // forward: > 0 in a second launch, over the rows of the units from n_whole = first_id on
-  Divisor by_heads, by_kv_heads, by_group;   // what a workgroup's number is decoded with: n_q_heads, n_kv_heads, group,
+  Divisor by_heads, by_kv_heads, by_group;   // what a workgroup's number is decoded with: query and K/V heads, group,
   Divisor by_tiles, by_xcd;                  // n_tiles, n_bh / 8 (see decode_workgroup),
   Divisor by_split, by_split_units;          // n_split, n_split_units,
   Divisor by_rag;                            // second launch of a forward: its tiles per (batch, head) behind the n_tiles whole units,

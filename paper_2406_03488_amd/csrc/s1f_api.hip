@@ -70,8 +70,8 @@ AttnArgs make_args(const s1f_desc *d, int64_t seg_off, int64_t seg_len) {
   a.q_sb = d->q_stride_b; a.q_sh = d->q_stride_h; a.q_ss = d->q_stride_s;
   a.kv_sb = d->kv_stride_b; a.kv_sh = d->kv_stride_h; a.kv_ss = d->kv_stride_s;
   a.seg_off = (int32_t)seg_off; a.seg_len = (int32_t)seg_len;
-  a.n_q_heads = d->n_q_heads; a.n_kv_heads = d->n_kv_heads; a.group = d->n_q_heads / d->n_kv_heads;
-  a.by_heads = Divisor::of(a.n_q_heads); a.by_kv_heads = Divisor::of(a.n_kv_heads); a.by_group = Divisor::of(a.group);
+  a.n_q_heads = d->n_q_heads; a.group = d->n_q_heads / d->n_kv_heads;
+  a.by_heads = Divisor::of(a.n_q_heads); a.by_kv_heads = Divisor::of(d->n_kv_heads); a.by_group = Divisor::of(a.group);
   a.scale = (float)(1.0 / std::sqrt((double)d->head_dim));
   return a;
 }
@@ -517,6 +517,7 @@ template <typename T, int D, int NC> int launch_keys(const s1f_desc *d, AttnArgs
   constexpr int W = KeysShape<T, D, NC>::W;
   const int64_t n_bh = (int64_t)d->n_q_heads * d->batch;
   fill_launch(&a, n_bh, row_tile_order(d, a), p);
+  a.bm = 16 * NC;
   a.by_split = Divisor::of(W);   // (a unit's waves)
   return launch<seg_attn_fwd_kernel_by_keys<T, D, NC, W>>(FwdKeysCfg<T, D, NC, W>::LDS_BYTES, p, n_bh, a, st, 64 * W);
 }
@@ -632,12 +633,12 @@ struct Group {
   int64_t count;
   double us;
 };
-double groups_us(const Group *g, int n, int64_t slots) {
-  struct { double at; int64_t count; } ends[64];   // when slots become free, in order
+double groups_us(const Group (&g)[4], int64_t slots) {
+  struct { double at; int64_t count; } ends[5];   // when slots become free, in order (a group adds at most one time)
   int n_ends = 1;
   ends[0] = {0, slots};
   double last = 0;
-  for (int i = 0; i < n; ++i)
+  for (int i = 0; i < 4; ++i)
     for (int64_t left = g[i].count; left > 0;) {
       const double end = ends[0].at + g[i].us;
       const int64_t now = left < ends[0].count ? left : ends[0].count;
@@ -649,7 +650,6 @@ double groups_us(const Group *g, int n, int64_t slots) {
       }
       int x = n_ends;
       while (x > 0 && ends[x - 1].at > end) --x;
-      if (n_ends == 64) return 1e300;
       for (int y = n_ends; y > x; --y) ends[y] = ends[y - 1];
       ends[x] = {end, now};
       ++n_ends;
@@ -688,7 +688,7 @@ template <typename T, int D> void plan_together(const s1f_desc *d, int64_t seg_o
                                {k.n_whole, lk + kRoundUs}, {k.chunks(), lk / k.n_split + kRoundUs}};
       const int a = q_one >= k_one ? 0 : 2;
       const Group in_order[4] = {groups[a], groups[a + 1], groups[2 - a], groups[3 - a]};
-      const double all = groups_us(in_order, 4, s.total);
+      const double all = groups_us(in_order, s.total);
       us = all > 0.75 * us ? all : 0.75 * us;   // (the longest unit shares its compute unit for about half of its life)
     }
     if (q.n_split_units + k.n_split_units > 0) us += kMergeUs + (double)(q.chunks() * q_bytes + part) / kMergeBytesPerUs;
