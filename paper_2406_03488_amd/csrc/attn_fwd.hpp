@@ -92,13 +92,14 @@ template <int NC> S1F_DEV void fwd_finite_max(const f32x4 (&s)[2][NC], float (&m
   for (int cb = 0; cb < NC; ++cb) mx[cb] = fmaxf(mx[cb], -kMaxFloat);
 }
 template <int NC> S1F_DEV void fwd_probs_of_max(f32x4 (&p)[2][NC], const f32x4 (&s)[2][NC], const float (&m)[NC], float c, float (&rs)[NC]) {
-#pragma clang fp contract(off)
 #pragma unroll
   for (int cb = 0; cb < NC; ++cb) {
     rs[cb] = 0.f;
 #pragma unroll
     for (int i = 0; i < 8; ++i) {
-      const float t = s[i >> 2][cb][i & 3] * c, x = exp2_fast(t - m[cb]);
+      float t = s[i >> 2][cb][i & 3] * c;
+      settle(t);
+      const float x = exp2_fast(t - m[cb]);
       p[i >> 2][cb][i & 3] = x;
       rs[cb] += x;
     }
@@ -353,8 +354,8 @@ __global__ void __launch_bounds__(64 * WAVES, OCC) seg_attn_fwd_kernel(const Att
     fwd_mask(s, 0, seg_off + wrow0);
     fwd_mask(s, 1, seg_off + wrow0);
   }
-  fwd_row_max(s, m, c);      // key 0 is visible to every row: finite
-  fwd_probs(s, s, m, c, l);  // from here on `s` holds the probabilities of the current tile, l their sums
+  fwd_finite_max(s, m, c);
+  fwd_probs_of_max(s, s, m, c, l);  // from here on `s` holds the probabilities of the current tile, l their sums
 
   int k = 0;   // current tile
   if (wrow0 >= seg_len) {   // no rows of its own: the wave only copies its share of the tiles
@@ -383,7 +384,7 @@ __global__ void __launch_bounds__(64 * WAVES, OCC) seg_attn_fwd_kernel(const Att
         fwd_mask(s, 0, ahead);
         fwd_mask(s, 1, ahead);
       }
-      fwd_row_max(s, mx, c);
+      fwd_finite_max(s, mx, c);
 #pragma unroll
       for (int cb = 0; cb < NC; ++cb) {
         const float m_up = mx[cb] > m[cb] + (kRescaleTau - 3.f) ? mx[cb] : m[cb];
@@ -393,7 +394,7 @@ __global__ void __launch_bounds__(64 * WAVES, OCC) seg_attn_fwd_kernel(const Att
 #pragma unroll
         for (int db = 0; db < DB; ++db) o[cb][db] = o[cb][db] * alpha;
       }
-      fwd_probs(s, s, m, c, rs);   // the current tile's probabilities again, against the raised maxima
+      fwd_probs_of_max(s, s, m, c, rs);   // the current tile's probabilities again, against the raised maxima
     }
 #pragma unroll
     for (int cb = 0; cb < NC; ++cb) l[cb] += rs[cb];

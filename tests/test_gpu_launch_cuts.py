@@ -287,3 +287,33 @@ def test_every_tile_width_in_halves(dtype, d, shape, plans):
         res.append((dq, dk, dv))
     for name, x, y in zip(("dq", "dk", "dv"), *res):
         assert torch.isfinite(x).all() and torch.equal(x, y), name
+
+
+@pytest.mark.parametrize("odd", [0, 1])
+@pytest.mark.parametrize("dtype,d,shape,plans", WIDTHS)
+def test_every_tile_width_on_tiles_of_keys_without_weight(dtype, d, shape, plans, odd):
+    """Every other tile of 32 keys has scores far below the others, as a column of K makes them (q has 0.25 to 1.75 in it): the first
+    tiles of walks and of chunks, and those that raise the maximum from one such tile to the next.  -1e12: finite, and spaced wider than
+    exponents are."""
+    nb, hq, hkv, off, m = shape
+    q, do, k, v = _device_data(9100 + off + m + d, dtype, d, *shape, False)
+    q[..., d - 1] = q[..., d - 1].abs().clamp(0.25, 1.75)
+    tiles = torch.arange(off + m, device="cuda") // 32
+    low = torch.tensor([-1e12, -3.3895e38, float("-inf")], device="cuda")[tiles // 2 % 3]
+    k[..., d - 1] = torch.where(tiles % 2 == odd, low, 0.0)
+    first = max(0, 32 - off) if odd == 0 else 0   # rows before see no other key
+    for workspace in (False, True):
+        out, lse = torch.full_like(q, float("nan")), torch.full(q.shape[:3], float("nan"), device="cuda")
+        if workspace:
+            nbytes = s1f.fwd_workspace_bytes(q, k, off)
+            s1f.seg_attn_fwd_ws(q, k, v, off, out, lse, torch.empty(nbytes, dtype=torch.uint8, device="cuda") if nbytes else None)
+        else:
+            s1f.seg_attn_fwd(q, k, v, off, out, lse)
+        host = lambda x: x.double().cpu().numpy()
+        for b, h in ((0, 0), (nb - 1, hq - 1)):
+            g = h // (hq // hkv)
+            with np.errstate(invalid="ignore"):
+                want, want_lse = A.segment_forward(host(q[b, h:h + 1]), host(k[b, g:g + 1]), host(v[b, g:g + 1]), off)
+            assert np.isfinite(want[:, first:]).all()
+            _close({"out": host(out[b, h:h + 1, first:]), "lse": host(lse[b, h:h + 1, first:])},
+                   {"out": want[:, first:], "lse": want_lse[:, first:]}, dtype, f"entry {b} head {h} workspace {workspace}: ")
