@@ -14,9 +14,6 @@ PROBE_LIB = os.path.join(HERE, "libs1f_probe.so")   # measurement aid used by be
 
 SOURCES = ["s1f_api.hip", "s1f_cache.hip", "s1f_partition.cpp", "s1f_schedule.cpp", "s1f_pipeline.cpp"]
 FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-shared", "-Wall", "-Werror=array-bounds",
-         # loops on lines of the instruction cache: where the forward's main loop came to lie otherwise, instructions in front of it decided
-         # (64/8 heads, 4000 rows behind 127000 keys, the same loop at two places 8460 and 8590 us, aligned 8430)
-         "-falign-loops=64",
          # packed fp32 VALU forms are kept out of generated code on this target
          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops"]
 
