@@ -658,12 +658,20 @@ double groups_us(const Group (&g)[4], int64_t slots) {
 }
 // The cut of the dK/dV half, and the number of chunks of the dQ half where all of its units are cut, for the one launch of a segment
 // behind a prefix: its slots and its merge are shared, and as long as there is a compute unit for every workgroup, steps are short.  Each
-// half cut as if it ran alone / so, backward of a segment, us: 2 x 8/2 heads, D 64, 340 rows behind 1017 29.0 / 27.4 (228 workgroups instead
-// of 316); 4 heads fp32, D 64, 256 behind 768 26.2 / 24.6 (256 instead of 416); 4 heads, D 128, 427 behind 2318 35.5 / 31.0; 8/2 heads, D
-// 128, 645 behind 8640 126 / 100.  The prediction is good for about 10 %, hence the margins; of first segments, whose units differ in
-// length, it is not (1.25 times slower at worst).  Of 320 random calls 26 get another plan: 0.86 to 1.04 of the time, 0.955 on average.
+// half cut as if it ran alone / so, backward of a segment, us: 4 heads fp32, D 64, 256 rows behind 768 25.9 / 23.6; 2 x 8/2 heads, D 64, 350
+// behind 389 21.4 / 20.1; 3 heads, D 80, 387 behind 779 23.9 / 19.8; 64/8 heads, D 128, 467 behind 4486 285 / 225.  The prediction is good
+// for about 10 %, hence the margin; of first segments, whose units differ in length, it is not (1.25 times slower at worst).
+// The halves called one after the other have the same cuts, since they give the same bits.  Hence none that lengthens either by itself:
+//   kHalfUs     the longest walk of a half, by its step times alone, grows by at most this.  (Without a limit, over 151 random calls: dQ alone up
+//               to 1.43 times as long, dK/dV 1.40; 4 heads, D 128, 427 behind 2318, 9 chunks to 3: dQ 17.5 -> 21.7)
+//   no more chunks than alone     and of units that stay whole alone, not all, but for few: their sums would wait for a second kernel (8
+//               heads, D 80, 403 behind 626, 72 units in 3 chunks: dK/dV 17.8 -> 21.9, the one launch 23.9 -> 26.3)
+// Over 115 random calls that get another plan, time against each half cut alone: the one call 0.75 .. 0.99, 0.91 on average, dQ by itself 0.89
+// .. 1.07, dK/dV by itself 0.79 .. 1.06, both of them 0.98 on average and 1.02 at most.
 // A function of the plan that the dQ half has with the built-in scratch, so that dK and dV do not depend on the workspace.
 constexpr int64_t kJointRounds = 8;   // (longer launches: as alone)
+constexpr double kHalfUs = 2.25;
+constexpr int64_t kFewUnits = 12;    // (an n-th of the compute units)
 template <typename T, int D> void plan_together(const s1f_desc *d, int64_t seg_off, int64_t seg_len, BwdPlans *p) {
   typedef DkdvFamily<T, D> K;
   const Slots s = K::slots();
@@ -674,13 +682,13 @@ template <typename T, int D> void plan_together(const s1f_desc *d, int64_t seg_o
   const double k_mean = K::mean_steps(d, seg_off, seg_len), k_most = K::most_steps(d, seg_len);
   const int64_t q_bytes = DqFamily<T, D>::row_bytes * 64 * q.nc;
   const bool cut_q = q.n_whole == 0 && q.n_split_units > 0, whole_k = k.n_split_units == 0;
-  double best = 1e300;
-  auto consider = [&]() {
-    const int64_t part = (k.chunks() - k.n_split_units) * K::part_bytes;
-    if (part > kStaticPartBytes) return;
-    const int64_t n = q.grid() + k.grid(), per_cu = n >= s.total ? s.total / s.cus : (n + s.cus - 1) / s.cus;
-    const double q_step = Cost<T, D>::dq.at(q.nc, per_cu), k_step = Cost<T, D>::dkdv.at(0, per_cu);
-    const double q_one = q_step * q_most / (q.n_whole > 0 ? 1 : q.n_split), k_one = k_step * k_most / (k.n_whole > 0 ? 1 : k.n_split);
+  auto per_cu = [&](int64_t n) { return n >= s.total ? s.total / s.cus : (n + s.cus - 1) / s.cus; };
+  auto longest = [](double steps, const SplitPlan &x) { return steps / (x.n_whole > 0 ? 1 : x.n_split); };
+  auto predict = [&]() {
+    const int64_t n = q.grid() + k.grid(), part = (k.chunks() - k.n_split_units) * K::part_bytes;
+    if (part > kStaticPartBytes) return 1e300;
+    const double q_step = Cost<T, D>::dq.at(q.nc, per_cu(n)), k_step = Cost<T, D>::dkdv.at(0, per_cu(n));
+    const double q_one = q_step * longest(q_most, q), k_one = k_step * longest(k_most, k);
     double us = (q_one > k_one ? q_one : k_one) + kRoundUs;   // side by side
     if (n > s.total) {
       const double lq = q_step * q_mean, lk = k_step * k_mean;
@@ -691,30 +699,37 @@ template <typename T, int D> void plan_together(const s1f_desc *d, int64_t seg_o
       const double all = groups_us(in_order, s.total);
       us = all > 0.75 * us ? all : 0.75 * us;   // (the longest unit shares its compute unit for about half of its life)
     }
-    if (q.n_split_units + k.n_split_units > 0) us += kMergeUs + (double)(q.chunks() * q_bytes + part) / kMergeBytesPerUs;
-    // The first is the plan as alone; others have to be better by more than the prediction is good for.
-    if (best == 1e300) best = 0.88 * us;
-    if (us >= (whole_k && k.n_split > 1 ? 0.9 : 1.0) * best) return;
-    best = us;
-    p->k = k;
-    if (cut_q) p->q.n_split = p->q_both.n_split = q.n_split;
+    return q.n_split_units + k.n_split_units > 0 ? us + kMergeUs + (double)(q.chunks() * q_bytes + part) / kMergeBytesPerUs : us;
   };
-  consider();
+  // What either half may walk by itself, and what others have to beat: the plan as alone, by more than the prediction is good for.
+  const double q_limit = longest(q_most, q) + kHalfUs / Cost<T, D>::dq.at(q.nc, per_cu(q.grid()));
+  const double k_limit = longest(k_most, k) + kHalfUs / Cost<T, D>::dkdv.at(0, per_cu(k.grid()));
+  double best = 0.88 * predict();
+  // (more units than slots: no cut takes less than all of their steps evenly shared out)
+  const double q_all = (double)uq * q_mean * Cost<T, D>::dq.at(q.nc, s.total / s.cus), k_all = (double)uk * k_mean * Cost<T, D>::dkdv.at(0, s.total / s.cus);
+  if (uq + uk > s.total && q_all + k_all >= best * s.total) return;
   const double over = (double)uq * q_mean * Cost<T, D>::dq.at(q.nc, 2) / (k_mean * Cost<T, D>::dkdv.at(0, 2)) + (double)uk;
   // units to cut: all, those of the last, partial round if all ran in rounds of the dK/dV half's, and if there were no other half
   const int64_t rests[3] = {uk, ((int64_t)over % s.total + 7) / 8 * 8, uk % s.total};
-  const int planned = q.n_split;
+  const int planned = q.n_split, p_k = k.n_split;
   for (int nq : {planned, 8, 6, 4, 3}) {
-    if (nq != planned && (!cut_q || nq > planned)) continue;
     q.n_split = nq;
-    for (int n : {1, 2, 3, 4, 6, 8}) {
+    if (nq != planned && (!cut_q || nq > planned || longest(q_most, q) > q_limit)) continue;
+    for (int n : {1, 2, 3, 4, 5, 6, 8}) {
       if (n > 1 && k_mean < n) break;
+      if (!whole_k && n > p_k) break;
       for (int64_t r : rests) {
         if (r == 0 || r > uk || (r < uk && uq + uk < s.total)) continue;
+        if (whole_k && n > 1 && r == uk && (n == 2 || kFewUnits * uk > s.cus)) continue;
         k.n_split = n;
         k.n_split_units = n == 1 ? 0 : r;
         k.n_whole = uk - k.n_split_units;
-        consider();
+        const double us = longest(k_most, k) > k_limit ? 1e300 : predict();
+        if (us < (whole_k && n > 1 ? 0.9 : 1.0) * best) {
+          best = us;
+          p->k = k;
+          if (cut_q) p->q.n_split = p->q_both.n_split = nq;
+        }
         if (n == 1) break;
       }
     }

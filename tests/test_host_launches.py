@@ -90,3 +90,33 @@ def test_paths_are_the_ones_that_calls_take(runtime, tmp_path):
             take("bwd_merge")
         seen |= {("one launch", one_bwd), ("second launch", second > 0), ("partly filled units", tiles > 0)}
     assert not launches and len(seen) == 6
+
+
+PLANS = """
+import ctypes, sys
+ctypes.CDLL(sys.argv[1], mode=ctypes.RTLD_GLOBAL)
+import paper_2406_03488_amd as s1f
+from paper_2406_03488_amd.binding import Desc
+lib = s1f.load_library()
+for dtype, nb, hq, hk, d, off, m in eval(sys.argv[2]):
+    desc = ctypes.byref(Desc(nb, hq, hk, d, dtype, 0, hq * m * d, m * d, d, hk * (off + m) * d, (off + m) * d, d, off + m))
+    for launch in (s1f.PLAN_DQ, s1f.PLAN_DKDV):
+        plan = (ctypes.c_int64 * 5)()
+        assert lib.s1f_launch_plan(desc, launch, off, m, plan) == 0
+        print(*plan)
+"""
+# ((element type, batch, heads, K/V heads, head_dim, offset, rows), fewest chunks of dQ units, of dK/dV units, most of those): calls whose halves
+# by themselves took 1.1 to 1.4 times as long in fewer chunks, or with dK/dV units in two chunks instead of whole
+HALVES = [((1, 1, 4, 4, 128, 2318, 427), 5, 1, 1), ((1, 1, 8, 8, 80, 17519, 1044), 9, 1, 1), ((1, 1, 1, 1, 128, 13211, 621), 14, 1, 1),
+          ((1, 3, 8, 2, 80, 669, 349), 1, 4, 5), ((1, 2, 4, 4, 128, 723, 289), 3, 1, 1), ((1, 2, 3, 3, 64, 1122, 277), 3, 1, 1),
+          ((0, 3, 3, 3, 128, 359, 217), 1, 4, 4)]
+
+
+def test_cuts_of_one_launch_serve_the_halves_too(runtime, tmp_path):
+    env = dict(os.environ, RECORD=str(tmp_path / "record"), PYTHONPATH=ROOT)
+    run = subprocess.run([sys.executable, "-c", PLANS, runtime, repr([c for c, *_ in HALVES])], env=env, capture_output=True, text=True, cwd=ROOT)
+    assert run.returncode == 0, run.stderr
+    plans = [[int(x) for x in line.split()] for line in run.stdout.splitlines()]
+    for i, (call, dq, least, most) in enumerate(HALVES):
+        assert plans[2 * i][3] >= dq, call
+        assert least <= plans[2 * i + 1][3] <= most, call
