@@ -70,7 +70,8 @@ template <typename T, int D> constexpr int kDqRing = sizeof(T) == 2 ? 4 : D == 6
 
 // id: number of the workgroup among those of this half; smem: TileRing::LDS_BYTES
 // STATS: computes the row statistics and leaves them for the dK/dV half, instead of reading them
-template <typename T, int D, int NC, int WAVES, bool STATS> S1F_DEV void bwd_dq_body(const AttnArgs &a, int id, char *smem) {
+// PAIR: a workgroup has one of the two tiles of a chunk of a unit of a.bm = 2 * BM rows: the same sums as in one tile of a.bm
+template <typename T, int D, int NC, int WAVES, bool STATS, bool PAIR = false> S1F_DEV void bwd_dq_body(const AttnArgs &a, int id, char *smem) {
   typedef Mat<T, D> M;
   typedef typename M::Frag Frag;
   typedef TileRing<T, D, WAVES> Ring;
@@ -80,7 +81,12 @@ template <typename T, int D, int NC, int WAVES, bool STATS> S1F_DEV void bwd_dq_
 
   const int tid = threadIdx.x, lane = tid & 63, j = lane >> 4, n = lane & 15;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const UnitChunk uc = split_unit(id, a.n_whole, a.n_split, a.n_split_units, a.by_split_units);
+  UnitChunk uc = split_unit(id, a.n_whole, PAIR ? 2 * a.n_split : a.n_split, a.n_split_units, a.by_split_units);
+  int second = 0;
+  if (PAIR) {   // (no unit is whole)
+    second = uc.chunk & 1;
+    uc = UnitChunk{uc.unit, uc.chunk >> 1, a.n_split, (uc.chunk >> 1) * a.n_split_units + uc.unit};
+  }
   int qt, bh;
   decode_workgroup(uc.unit, a.by_tiles, a.n_bh, a.by_xcd, a.tile_major, qt, bh);
   qt = a.n_tiles - 1 - qt;   // later (heavier) row tiles are scheduled first
@@ -88,14 +94,16 @@ template <typename T, int D, int NC, int WAVES, bool STATS> S1F_DEV void bwd_dq_
   div_mod(bh, a.by_heads, b, h);
   const int hk = div(h, a.by_group);
   const int seg_len = a.seg_len;
-  const int row0 = qt * BM, wrow0 = row0 + wave * 16 * NC;
+  const int unit_row0 = qt * (PAIR ? 2 * BM : BM), row0 = unit_row0 + second * BM, wrow0 = row0 + wave * 16 * NC;
+  if (PAIR && row0 >= seg_len) return;
   const int last_row = (row0 + BM < seg_len ? row0 + BM : seg_len) - 1;
   // This workgroup's key tiles: all that hold keys 0 .. seg_off+last_row, or one chunk of them.  From here on keys
   // are counted from the chunk's first key: seg_off and kv_len are relative to it.
   int kt0, kt1;
-  chunk_range(uc, a.by_split, (a.seg_off + row0) / BN, (a.seg_off + last_row) / BN + 1, kt0, kt1);
+  chunk_range(uc, a.by_split, (a.seg_off + unit_row0) / BN, (a.seg_off + last_row) / BN + 1, kt0, kt1);
   const int seg_off = a.seg_off - BN * kt0, kv_len = seg_off + seg_len;
   const int n_kt = kt1 - kt0;
+  const int64_t part_at = ((int64_t)uc.slot * (PAIR ? 2 : 1) + second) * (BM * D);   // of a chunk's tile
 
   const int64_t qoff = b * a.q_sb + h * a.q_sh;
   const int64_t kv_first = b * a.kv_sb + hk * a.kv_sh + (int64_t)(BN * kt0) * a.kv_ss;
@@ -143,7 +151,7 @@ template <typename T, int D, int NC, int WAVES, bool STATS> S1F_DEV void bwd_dq_
     for (int i = 0; i < M::NK; ++i) { settle(q[cb].f[i]); settle(dor[cb].f[i]); }
 
   if (n_kt <= 0) {   // more chunks than this unit has whole tiles: nothing to add
-    float *pd = a.part + (int64_t)uc.slot * (BM * D);
+    float *pd = a.part + part_at;
     for (int i = tid; i < BM * D; i += 64 * WAVES) pd[i] = 0.f;
     return;
   }
@@ -319,10 +327,10 @@ template <typename T, int D, int NC, int WAVES, bool STATS> S1F_DEV void bwd_dq_
     }
   }
   if (uc.slot >= 0) {   // a chunk: its unscaled share of the unit's dQ rows goes to the workspace
-    float *pd = a.part + (int64_t)uc.slot * (BM * D);
+    float *pd = a.part + part_at;
 #pragma unroll
     for (int cb = 0; cb < NC; ++cb) {
-      const int rl = wave * 16 * NC + 16 * cb + n;   // row within the unit
+      const int rl = wave * 16 * NC + 16 * cb + n;   // row within the tile
 #pragma unroll
       for (int x = 0; x < DB; ++x) *reinterpret_cast<f32x4 *>(pd + rl * D + M::quad_d0(x, j)) = M::quad(dq[cb], x);
     }
@@ -767,10 +775,10 @@ template <typename T, int D, int MC> S1F_DEV void bwd_dkdv_merge_body(const Attn
 }
 
 // ---- the kernels: one half by itself, and both ----
-template <typename T, int D, int NC, int OCC, int WAVES>
+template <typename T, int D, int NC, int OCC, int WAVES, bool PAIR = false>
 __global__ void __launch_bounds__(64 * WAVES, OCC) seg_attn_bwd_dq_kernel(const AttnArgs a) {
   extern __shared__ __attribute__((aligned(1024))) char smem[];
-  bwd_dq_body<T, D, NC, WAVES, true>(a, blockIdx.x, smem);
+  bwd_dq_body<T, D, NC, WAVES, true, PAIR>(a, blockIdx.x, smem);
 }
 template <typename T, int D, int WGS>   // WGS: waves meant to share a SIMD
 __global__ void __launch_bounds__((64 * BwdDkdvCfg<T, D>::WAVES), WGS) seg_attn_bwd_dkdv_kernel(const AttnArgs a) {

@@ -349,10 +349,24 @@ template <typename T, int D> struct DqFamily {
     constexpr int W = Shape<T, D>::waves(NC);
     return seg_attn_bwd_dq_kernel<T, D, 4 * NC / W, Shape<T, D>::dq_occ(NC), W>;
   }
+  static constexpr auto pair_kernel() { return seg_attn_bwd_dq_kernel<T, D, 1, Shape<T, D>::dq_occ(1), 4, sizeof(T) == 4 && D != 64>; }
 };
 template <typename F, int NC> Slots family_slots() {
   static std::atomic<int64_t> cache[kMaxDevices];
   return resident_slots<F::template kernel<NC>()>(F::LDS, cache, F::threads(NC));
+}
+// The dQ half by itself in fp32 above head_dim 64, planned in units of 128 rows (eight waves): does it run as two tiles of 64 rows for each,
+// in four waves?  The same sums; half as long a launch of few units, where every tile then has a compute unit of its own, and still shorter
+// where chunks are so short that starting a workgroup counts.  In units of 128 / in pairs, us: 3 heads, head_dim 128, first segment of 366
+// rows 26.9 / 22.5; 2/1 heads, 80, 230 behind 3539 33.2 / 27.4; 4 heads, 128, 233 behind 771 34.1 / 28.9; over 87 random calls that the rule takes
+// 0.78 .. 1.00 of the time, 0.86 on average; beyond it pairs take up to 1.4 times as long (4 heads, 80, first segment of 4088 154.9 / 220.1).
+// (By itself this half would be faster still in 64-row units with chunks of their own, for the calls of this rule 1.12 times on average; the one
+// call of both halves, 0.66 .. 0.9 of its former time in units of 128, has to have the same chunks.)
+template <typename T, int D> bool dq_in_pairs(const AttnArgs &a, const SplitPlan &p) {
+  if (sizeof(T) == 2 || D == 64 || p.nc != 2 || p.n_whole > 0) return false;
+  const int64_t cus = family_slots<DqFamily<T, D>, 2>().cus;
+  const double walk = ((double)a.seg_off + 0.5 * a.seg_len) / 32 / p.n_split;
+  return 2 * p.grid() <= cus || (p.grid() < cus && walk <= 2);
 }
 template <typename F, int NC> void plan_rows_nc(const s1f_desc *d, int64_t seg_off, int64_t seg_len, int64_t cap, SplitPlan *best, double *t) {
   const Slots s = family_slots<F, NC>();
@@ -821,7 +835,14 @@ template <typename T, int D> int bwd_dq_impl(const s1f_desc *d, const AttnArgs &
       return bwd_dq_impl<T, D>(half, x, p.uncut((int64_t)d->n_q_heads * half->batch), st);
     });
   const AttnArgs a = dq_args<T, D>(d, a0, p);
-  const int rc = launch_rows<DqFamily<T, D>>(p, a.n_bh, a, st);
+  int rc;
+  if (dq_in_pairs<T, D>(a, p)) {
+    SplitPlan pairs = p;
+    pairs.n_split *= 2;
+    rc = launch<DqFamily<T, D>::pair_kernel()>(DqFamily<T, D>::LDS, pairs, a.n_bh, a, st, DqFamily<T, D>::threads(1));
+  } else {
+    rc = launch_rows<DqFamily<T, D>>(p, a.n_bh, a, st);
+  }
   return rc == S1F_OK ? launch_bwd_merge<T, D>(a, a, p.n_split_units, 0, st) : rc;
 }
 

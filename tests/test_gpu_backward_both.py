@@ -3,6 +3,7 @@ import pytest
 import torch
 
 import paper_2406_03488_amd as s1f
+from test_host_launches import PAIRS
 
 pytestmark = pytest.mark.gpu
 
@@ -83,3 +84,26 @@ def test_one_launch_equals_two(dtype, d, nb, hq, hk, off, m, layout, rows, dq_fi
                 assert (x.double() - want).norm() <= bound * want.norm()   # (one row that sees one key: zero)
             else:
                 assert torch.equal(x, got["halves"][name]), (how, name)
+
+
+@pytest.mark.parametrize("layout", ["bhsd", "bshd"])
+@pytest.mark.parametrize("d", [80, 128])
+@pytest.mark.parametrize("nb,hq,hk,off,m", PAIRS)
+def test_units_in_pairs_of_tiles_equal_the_one_launch(nb, hq, hk, off, m, d, layout):
+    """The dQ half by itself in two 64-row tiles for each unit of 128 rows: the bits of the one launch, whose units are 128 rows."""
+    q, do, k, v = _data(90 + off + m, "f32", d, nb, hq, hk, off, m, layout)
+    out, lse = torch.empty_like(q), torch.empty((nb, hq, m), device="cuda")
+    s1f.seg_attn_fwd(q, k, v, off, out, lse)
+    assert s1f.launch_paths(q, k, off)[:2] == (1, 128), "the one call no longer takes the path it is here for"
+    like_k, need = torch.empty_like(k, dtype=torch.float32), s1f.bwd_workspace_bytes(q, k, off)
+    dqs = []
+    for halves in (True, False):
+        room = torch.full((need + 4096,), 0xff, dtype=torch.uint8, device="cuda")   # (a chunk that is not written: NaN)
+        dq, dk, dv = torch.full_like(q, float("nan")), like_k.clone().zero_(), like_k.clone().zero_()
+        if halves:
+            s1f.seg_attn_bwd_dq(do, q, k, v, out, lse, off, dq, room[:need])
+        else:
+            s1f.seg_attn_bwd(do, q, k, v, out, lse, off, dq, dk, dv, room[:need])
+        assert (room[need:] == 0xff).all()
+        dqs.append(dq)
+    assert torch.isfinite(dqs[0]).all() and torch.equal(*dqs)

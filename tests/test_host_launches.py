@@ -92,6 +92,18 @@ def test_paths_are_the_ones_that_calls_take(runtime, tmp_path):
     assert not launches and len(seen) == 6
 
 
+# fp32 calls whose dQ half by itself runs each unit of 128 rows as two tiles of 64: (batch, heads, K/V heads, offset, rows); a last unit whose second
+# tile has no rows, one row, all but one; more chunks than some units have tiles; 16 chunks of few units; more tiles than compute units
+PAIRS = [(1, 1, 1, 0, 246), (1, 3, 3, 33, 700), (2, 2, 1, 7, 449), (1, 2, 1, 3539, 255), (1, 1, 1, 0, 640), (2, 4, 4, 771, 233), (1, 8, 8, 45, 338)]
+
+
+def test_dq_half_of_few_units_runs_in_pairs_of_tiles(runtime, tmp_path):
+    lines, _ = record(runtime, tmp_path, [(hq, hk, off, m) for nb, hq, hk, off, m in PAIRS if nb == 1])
+    names = [name for what, name, *_ in lines if what == "launch"]
+    in_pairs = [name for name in names if "bwd_dq_kernelIf" in name and "Lb1E" in name]
+    assert len(in_pairs) == 2 * sum(nb == 1 for nb, *_ in PAIRS)   # (head_dim 80 and 128)
+
+
 PLANS = """
 import ctypes, sys
 ctypes.CDLL(sys.argv[1], mode=ctypes.RTLD_GLOBAL)
