@@ -676,12 +676,12 @@ double groups_us(const Group (&g)[4], int64_t slots) {
 // behind 389 21.4 / 20.1; 3 heads, D 80, 387 behind 779 23.9 / 19.8; 64/8 heads, D 128, 467 behind 4486 285 / 225.  The prediction is good
 // for about 10 %, hence the margin; of first segments, whose units differ in length, it is not (1.25 times slower at worst).
 // The halves called one after the other have the same cuts, since they give the same bits.  Hence none that lengthens either by itself:
-//   kHalfUs     the longest walk of a half, by its step times alone, grows by at most this.  (Without a limit, over 151 random calls: dQ alone up
+//   kHalfUs     the longest walk of a half, and of dK/dV all of its rounds, by its step times alone, grow by at most this.  (Without a limit, over 151 random calls: dQ alone up
 //               to 1.43 times as long, dK/dV 1.40; 4 heads, D 128, 427 behind 2318, 9 chunks to 3: dQ 17.5 -> 21.7)
 //   no more chunks than alone     and of units that stay whole alone, not all, but for few: their sums would wait for a second kernel (8
 //               heads, D 80, 403 behind 626, 72 units in 3 chunks: dK/dV 17.8 -> 21.9, the one launch 23.9 -> 26.3)
-// Over 115 random calls that get another plan, time against each half cut alone: the one call 0.75 .. 0.99, 0.91 on average, dQ by itself 0.89
-// .. 1.07, dK/dV by itself 0.79 .. 1.06, both of them 0.98 on average and 1.02 at most.
+// Over 220 random calls that get another plan, time against each half cut alone: the one call 0.74 .. 1.03, 0.91 on average, dQ by itself 0.89
+// .. 1.07, dK/dV by itself 0.79 .. 1.06, both of them 0.97 on average and 1.03 at most.
 // A function of the plan that the dQ half has with the built-in scratch, so that dK and dV do not depend on the workspace.
 constexpr int64_t kJointRounds = 8;   // (longer launches: as alone)
 constexpr double kHalfUs = 2.25;
@@ -698,6 +698,8 @@ template <typename T, int D> void plan_together(const s1f_desc *d, int64_t seg_o
   const bool cut_q = q.n_whole == 0 && q.n_split_units > 0, whole_k = k.n_split_units == 0;
   auto per_cu = [&](int64_t n) { return n >= s.total ? s.total / s.cus : (n + s.cus - 1) / s.cus; };
   auto longest = [](double steps, const SplitPlan &x) { return steps / (x.n_whole > 0 ? 1 : x.n_split); };
+  auto rounds = [&](int64_t n) { return n <= s.total ? n > 0 : (n + s.total - 1) / s.total; };
+  auto in_rounds = [&](double steps, const SplitPlan &x) { return steps * ((double)rounds(x.n_whole) + (double)rounds(x.chunks()) / x.n_split); };
   auto predict = [&]() {
     const int64_t n = q.grid() + k.grid(), part = (k.chunks() - k.n_split_units) * K::part_bytes;
     if (part > kStaticPartBytes) return 1e300;
@@ -717,7 +719,7 @@ template <typename T, int D> void plan_together(const s1f_desc *d, int64_t seg_o
   };
   // What either half may walk by itself, and what others have to beat: the plan as alone, by more than the prediction is good for.
   const double q_limit = longest(q_most, q) + kHalfUs / Cost<T, D>::dq.at(q.nc, per_cu(q.grid()));
-  const double k_limit = longest(k_most, k) + kHalfUs / Cost<T, D>::dkdv.at(0, per_cu(k.grid()));
+  const double k_more = kHalfUs / Cost<T, D>::dkdv.at(0, per_cu(k.grid())), k_limit = longest(k_most, k) + k_more, k_rounds = in_rounds(k_mean, k) + k_more;
   double best = 0.88 * predict();
   // (more units than slots: no cut takes less than all of their steps evenly shared out)
   const double q_all = (double)uq * q_mean * Cost<T, D>::dq.at(q.nc, s.total / s.cus), k_all = (double)uk * k_mean * Cost<T, D>::dkdv.at(0, s.total / s.cus);
@@ -738,7 +740,7 @@ template <typename T, int D> void plan_together(const s1f_desc *d, int64_t seg_o
         k.n_split = n;
         k.n_split_units = n == 1 ? 0 : r;
         k.n_whole = uk - k.n_split_units;
-        const double us = longest(k_most, k) > k_limit ? 1e300 : predict();
+        const double us = longest(k_most, k) > k_limit || in_rounds(k_mean, k) > k_rounds ? 1e300 : predict();
         if (us < (whole_k && n > 1 ? 0.9 : 1.0) * best) {
           best = us;
           p->k = k;
