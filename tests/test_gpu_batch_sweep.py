@@ -127,7 +127,7 @@ def test_prefix_accumulation_over_every_launch(n_seg, hq, hkv, hidden):
 
 def _sweep_cases(count, seed):
     """(seg_off, seg_len, head_dim, Hq, Hkv, dtype, layout): lengths of one to three times 128 rows plus or minus a token
-    and a few tiny ones (all of these calls run in tiles of 64 rows), offsets from 0 to a few key tiles (aligned and not)."""
+    and a few tiny ones (their backwards run in tiles of 64 rows, but for some in fp32), offsets from 0 to a few key tiles (aligned and not)."""
     rng = np.random.Generator(np.random.Philox(seed))
     lens = [1, 2, 31, 33, 127, 128, 129, 255, 256, 257, 383, 384, 385]
     offs = [0, 0, 1, 31, 32, 63, 64, 65, 127, 128, 255, 256, 257, 300, 511, 512, 640, 777]
@@ -203,7 +203,7 @@ def test_rising_scores_raise_the_running_maximum(dtype, d):
     by a wide margin; N(0, 1) operands never make it do so.  Here the scores of many rows climb by tens of nats along
     the keys (and fall as far for others, whose late probabilities underflow to zero), through several segments and
     through a launch whose row tiles are cut along the keys, where the chunks of one row differ as much in their
-    maxima.  (Launches this small run in tiles of 64 rows; test_gpu_launch_cuts does the same to the wider ones.)"""
+    maxima.  (test_gpu_launch_cuts does the same to every width of row tiles, test_gpu_forward_by_keys to waves that share keys.)"""
     from gpu_harness import run_schedule, run_segment
     hq, hkv, n = 4, 2, BOUNDS[-1]
     q, k, v, do = _rising(910 + d, hq, hkv, n, d, dtype)

@@ -17,7 +17,8 @@ from test_gpu_batch_sweep import _check, _sequence
 pytestmark = pytest.mark.gpu
 
 # (query heads, K/V heads, offset, rows): one row; one row more and less than 64, 128 and 192; a first segment (its early
-# units have fewer key tiles than chunks); 64 heads.  All of them run in tiles of 64 rows.
+# units have fewer key tiles than chunks); 64 heads.  Their backwards run in tiles of 64 rows (fp32 above head_dim 64: some in 128), and
+# the fp32 forward with a workspace; other forwards of fewer than 32 heads share keys among waves.
 SHAPES = [(2, 1, 700, 1), (4, 2, 0, 63), (4, 2, 33, 65), (8, 2, 400, 127), (3, 1, 1000, 129), (2, 2, 5, 191),
           (8, 8, 95, 193), (4, 4, 0, 640), (64, 8, 300, 200)]
 
@@ -317,3 +318,44 @@ def test_every_tile_width_on_tiles_of_keys_without_weight(dtype, d, shape, plans
             assert np.isfinite(want[:, first:]).all()
             _close({"out": host(out[b, h:h + 1, first:]), "lse": host(lse[b, h:h + 1, first:])},
                    {"out": want[:, first:], "lse": want_lse[:, first:]}, dtype, f"entry {b} head {h} workspace {workspace}: ")
+
+
+# Forwards in tiles of 64 rows, whole without a workspace and cut with one, whole either way, and cut where few rows share keys without a
+# workspace: one row, one more and less than 64 and 128, three tiles; first segments, whose early units have fewer tiles than chunks;
+# 16 chunks.
+EDGES_64 = [
+    ((1, 32, 8, 1000, 1), "64", "64 cut"), ((1, 32, 32, 1499, 63), "64", "64 cut"), ((1, 33, 11, 1000, 65), "64", "64 cut"),
+    ((2, 16, 4, 2100, 127), "64", "64 cut"), ((1, 32, 8, 1000, 129), "64", "64 cut"), ((1, 32, 32, 2600, 191), "64", "64 cut"),
+    ((2, 16, 4, 0, 63), "64", "64"), ((1, 32, 8, 5, 65), "64", "64"), ((1, 33, 11, 0, 193), "64", "64"), ((1, 40, 8, 31, 129), "64", "64"),
+    ((1, 3, 3, 0, 3000), "64", "64 cut"), ((1, 1, 1, 0, 1600), "16", "64 cut"), ((1, 2, 1, 3000, 1), "16", "64 cut"),
+]
+
+
+@pytest.mark.parametrize("rising", [False, True])
+@pytest.mark.parametrize("d", [64, 80, 128])
+@pytest.mark.parametrize("shape,plain,cut", EDGES_64)
+def test_edges_of_64_row_forwards(shape, plain, cut, d, rising):
+    nb, hq, hkv, off, m = shape
+    q, _, k, v = _device_data(9200 + off + m + d, "bf16", d, *shape, rising)
+    if (off + m) % 2:   # other strides: heads between the rows
+        q, k, v = (x.transpose(1, 2).contiguous().transpose(1, 2) for x in (q, k, v))
+    for launch, want in ((s1f.PLAN_FWD, plain), (s1f.PLAN_FWD_WS, cut)):
+        rows, _, units, chunks, _ = s1f.launch_plan(q, k, off, launch)
+        assert f"{rows}{' cut' if units else ''}" == want, "the shape no longer takes the path it is here for"
+    assert off > 0 or not cut.endswith("cut") or chunks > 2   # (the first unit has two key tiles)
+    host = lambda x: x.double().cpu().numpy()
+    for workspace in (False, True):
+        out, lse = torch.full_like(q, float("nan")), torch.full(q.shape[:3], float("nan"), device="cuda")
+        if workspace:
+            nbytes = s1f.fwd_workspace_bytes(q, k, off)
+            room = torch.full((nbytes + 4096,), 0xff, dtype=torch.uint8, device="cuda")   # (a partial result that is not written: NaN)
+            s1f.seg_attn_fwd_ws(q, k, v, off, out, lse, room[:nbytes] if nbytes else None)
+            assert (room[nbytes:] == 0xff).all()
+        else:
+            s1f.seg_attn_fwd(q, k, v, off, out, lse)
+        assert torch.isfinite(out.float()).all() and torch.isfinite(lse).all()
+        for b, h in sorted({(0, 0), (nb - 1, hq // 2), (nb - 1, hq - 1)}):
+            g = h // (hq // hkv)
+            want, want_lse = A.segment_forward(host(q[b, h:h + 1]), host(k[b, g:g + 1]), host(v[b, g:g + 1]), off)
+            _close({"out": host(out[b, h:h + 1]), "lse": host(lse[b, h:h + 1])}, {"out": want, "lse": want_lse}, "bf16",
+                   f"entry {b} head {h} workspace {workspace}: ")
