@@ -339,8 +339,10 @@ template <typename T, int D> struct DqFamily {
   static constexpr int64_t row_bytes = D * 4;
   // Are units of 64 rows ever cut?  fp32 above head_dim 64: not unless those of 128 rows (eight waves, and a kernel for both halves in one
   // launch) would compute too many rows for nothing.  Cut in 64 rows / as then planned, backward of a segment, us: 8/2 heads, head_dim
-  // 128, first segment of 1240 rows 130 / 107, 941 rows behind 2300 252 / 227; 4 heads, 80, first segment of 934 63 / 48.5.  Over 41 random
-  // calls that this changes 0.71 to 0.96 of the time, 0.82 on average.  (It would gain beyond 3/16 as well; tests ask for such plans.)
+  // 128, first segment of 1240 rows 125 / 99, 941 rows behind 2300 252 / 220; 4 heads, 80, first segment of 930 63 / 48.  Over 218 random
+  // calls that this changes the one call takes 0.65 to 1.04 of the time, 0.80 on average; both halves one after the other 0.87 to 1.15, 1.02 on
+  // average, for the dQ half by itself had been faster in small calls (see dq_in_pairs).  (The one call would gain beyond 3/16 as well; tests
+  // ask for such plans.)
   static bool cut_narrow(int64_t seg_len) {
     return sizeof(T) == 2 || D == 64 || 16 * ((seg_len + 127) / 128 * 128 - seg_len) > 3 * seg_len;
   }
@@ -634,10 +636,22 @@ struct BwdPlans {
 //                      second half start one by one and no longer walk the same rows side by side
 // Over 170 random calls that run in one launch (20 us to 20 ms), time against two: bf16 0.82 on average, worst 1.044 (64/8 heads,
 // head_dim 64, 913 rows behind 6179) and 1.028 (3 x 56 heads, head_dim 128, first segment of 267 rows); fp32 0.85, worst 1.008.
-constexpr double kBothUs = 3000.0;
+constexpr double kBothUs = 3000.0, kLongWalk = 24;
 template <typename T, int D> bool both_halves(const s1f_desc *d, int64_t seg_off, int64_t seg_len, const BwdPlans &p) {
   if (!Shape<T, D>::both(p.q_both.nc) || !one_launch(p.q_both.grid() + p.k.grid(), DkdvFamily<T, D>::THREADS)) return false;
   if (p.q.n_split_units == 0) return true;
+  // fp32 at head_dim 128, one workgroup to a compute unit: a few workgroups too many for both halves in one round, and the launch lasts as
+  // long as the halves one after the other, or longer where the dQ half by itself runs in pairs of tiles.  2/1 heads, 470 rows behind 18102
+  // keys, 128 and 146 workgroups: in one launch 251 us, apart 225; over 37 such calls 0.97 to 1.16 times as long.  Not so where the dK/dV units on
+  // the diagonal, which are short, make up for them (914 rows behind 15703, 130 workgroups: 147, apart 212), at head_dim 80 (0.87), with
+  // more workgroups of the dQ half (592 rows behind 16796, 160 and 136: 217, apart 283), nor where walks are short.
+  if (sizeof(T) == 4 && D == 128) {
+    const Slots s = DkdvFamily<T, D>::slots();
+    const int64_t over = p.q_both.grid() + p.k.grid() - s.total;
+    if (s.total == s.cus && over * DkdvFamily<T, D>::Cfg::BNW > seg_len && 4 * over <= s.total && 2 * p.q_both.grid() <= s.cus && p.q_both.n_whole == 0 &&
+        p.k.n_split_units == 0 && DkdvFamily<T, D>::most_steps(d, seg_len) >= kLongWalk)
+      return false;
+  }
   const double cells = ((double)seg_off + 0.5 * (double)seg_len) * (double)seg_len * d->n_q_heads * d->batch;   // (query, key) pairs
   const double step_us = Cost<T, D>::dq.at(p.q.nc, 2) / (64 * p.q.nc) + Cost<T, D>::dkdv.at(0, 2) / 128;        // per 32 of them
   return cells / 32 * step_us / 512 < kBothUs;   // (two workgroups on each of 256 compute units, as the step times presume)

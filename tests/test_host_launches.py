@@ -116,6 +116,9 @@ for dtype, nb, hq, hk, d, off, m in eval(sys.argv[2]):
         plan = (ctypes.c_int64 * 5)()
         assert lib.s1f_launch_plan(desc, launch, off, m, plan) == 0
         print(*plan)
+    paths = (ctypes.c_int64 * 5)()
+    assert lib.s1f_launch_paths(desc, off, m, paths) == 0
+    print(*paths)
 """
 # ((element type, batch, heads, K/V heads, head_dim, offset, rows), fewest chunks of dQ units, of dK/dV units, most of those): calls whose halves
 # by themselves took 1.1 to 1.4 times as long in fewer chunks, or with dK/dV units in two chunks instead of whole
@@ -124,11 +127,24 @@ HALVES = [((1, 1, 4, 4, 128, 2318, 427), 5, 1, 1), ((1, 1, 8, 8, 80, 17519, 1044
           ((0, 3, 3, 3, 128, 359, 217), 1, 4, 4)]
 
 
-def test_cuts_of_one_launch_serve_the_halves_too(runtime, tmp_path):
+def plans_of(runtime, tmp_path, calls):
+    """Plan of the dQ half, of the dK/dV half, and paths of each call."""
     env = dict(os.environ, RECORD=str(tmp_path / "record"), PYTHONPATH=ROOT)
-    run = subprocess.run([sys.executable, "-c", PLANS, runtime, repr([c for c, *_ in HALVES])], env=env, capture_output=True, text=True, cwd=ROOT)
+    run = subprocess.run([sys.executable, "-c", PLANS, runtime, repr(calls)], env=env, capture_output=True, text=True, cwd=ROOT)
     assert run.returncode == 0, run.stderr
-    plans = [[int(x) for x in line.split()] for line in run.stdout.splitlines()]
-    for i, (call, dq, least, most) in enumerate(HALVES):
-        assert plans[2 * i][3] >= dq, call
-        assert least <= plans[2 * i + 1][3] <= most, call
+    lines = [[int(x) for x in line.split()] for line in run.stdout.splitlines()]
+    return [lines[i:i + 3] for i in range(0, len(lines), 3)]
+
+
+def test_cuts_of_one_launch_serve_the_halves_too(runtime, tmp_path):
+    for (call, least_dq, least, most), (dq, dkdv, _) in zip(HALVES, plans_of(runtime, tmp_path, [c for c, *_ in HALVES])):
+        assert dq[3] >= least_dq, call
+        assert least <= dkdv[3] <= most, call
+
+
+def test_a_few_workgroups_too_many_for_one_round_run_apart(runtime, tmp_path):
+    """fp32, head_dim 128, one workgroup to a compute unit: 128 workgroups of the dQ half and 146 or 130 of the other."""
+    over, short = plans_of(runtime, tmp_path, [(0, 1, 2, 1, 128, 18102, 470), (0, 1, 1, 1, 128, 15703, 914)])
+    assert all(dq[2] * dq[3] == 128 for dq, _, _ in (over, short))
+    assert over[1][1] == 146 and short[1][1] == 130   # (two of 130 follow seven short ones on the diagonal)
+    assert over[2][0] == 0 and short[2][0] == 1
