@@ -473,16 +473,19 @@ template <typename F> bool fwd_tail(const AttnArgs &a, const SplitPlan &p, int64
 
 // The forward whose waves share the keys of a unit (seg_attn_fwd_kernel_by_keys).  Its time in microseconds, fitted to calls of 4 to 500
 // us: base + step per 32 keys (which a workgroup's waves walk side by side), for units of 16 and of 32 rows with a compute unit each.
+// least1, least2: steps from which on it is faster.  Row tiles walk fewer in less time than waves need to meet: bf16, D 64, 16 rows and keys 2.97
+// us in row tiles, 3.44 by keys; fp32, 20 rows behind 60 6.17, 8.98; bf16, D 128, 399 rows behind 8, units of 32 9.0, 10.4
 struct KeysUs {
   double base1, step1, base2, step2;
+  int least1, least2;
 };
 template <typename T, int D> struct KeysCost;
-template <> struct KeysCost<bf16_t, 64> { static constexpr KeysUs us = {4.0, 0.073, 5.0, 0.105}; };
-template <> struct KeysCost<bf16_t, 80> { static constexpr KeysUs us = {4.2, 0.103, 6.3, 0.125}; };
-template <> struct KeysCost<bf16_t, 128> { static constexpr KeysUs us = {4.8, 0.146, 8.0, 0.17}; };
-template <> struct KeysCost<float, 64> { static constexpr KeysUs us = {6.0, 0.33, 10.0, 0.45}; };
-template <> struct KeysCost<float, 80> { static constexpr KeysUs us = {6.5, 0.45, 10.0, 0.75}; };
-template <> struct KeysCost<float, 128> { static constexpr KeysUs us = {8.0, 0.85, 17.0, 1.0}; };
+template <> struct KeysCost<bf16_t, 64> { static constexpr KeysUs us = {4.0, 0.073, 5.0, 0.105, 5, 16}; };
+template <> struct KeysCost<bf16_t, 80> { static constexpr KeysUs us = {4.2, 0.103, 6.3, 0.125, 6, 16}; };
+template <> struct KeysCost<bf16_t, 128> { static constexpr KeysUs us = {4.8, 0.146, 8.0, 0.17, 8, 16}; };
+template <> struct KeysCost<float, 64> { static constexpr KeysUs us = {6.0, 0.33, 10.0, 0.45, 7, 16}; };
+template <> struct KeysCost<float, 80> { static constexpr KeysUs us = {6.5, 0.45, 10.0, 0.75, 7, 16}; };
+template <> struct KeysCost<float, 128> { static constexpr KeysUs us = {8.0, 0.85, 17.0, 1.0, 12, 24}; };
 template <typename T, int D, int NC> struct KeysShape {
   // fp32 at head_dim 80: eight waves of two column blocks spill; 128: LDS
   static constexpr int W = sizeof(T) == 2 || D == 64 || (D == 80 && NC == 1) ? 8 : 4;
@@ -494,23 +497,25 @@ template <typename T, int D, int NC> struct KeysShape {
 //                     768 keys, D 64 cut into chunks 13.4 us, by keys 17.7; without a workspace 34.9, by keys 17.7
 //   with a workspace, up to 48 steps, or up to 80 if units take more than half of the chip   chunks use the compute units that few units
 //                     leave idle: 2/1 heads, 839 rows behind 2668, D 80 14.6 us in chunks, 15.1 by keys; 4 heads, 368 behind 2578, 13.4 and
-//                     13.6 (few units of 50 to 80 steps would still gain up to 25 %; tests ask for chunks there)
+//                     13.6 (few units of 50 to 80 steps would still gain up to 25 %; tests ask for chunks there).  Above D 64 a handful of
+//                     units up to 24 steps (one head, 46 rows behind 1227, D 128 9.0 in chunks, 10.2 by keys), D 128 a sixth of the chip up to 32
+//                     (40 rows behind 1228 of 2 entries 1.10, 16 heads, 11 behind 1063 1.04 times as long)
 //   fewer than 32 (batch, head) pairs   with a workspace there is nothing in it beyond (32 heads, 129 rows behind 4011 keys, D 64: 18.7 us in
 //                     chunks, 18.5 by keys); without one there would be (40.4 us), but tests ask for the tile widths of such calls by shape
-// Over 60 random calls of up to 256 units, time of the row tiles against this rule's choice, with / without a workspace: bf16 0.99 .. 1.48 /
-// 1.08 .. 3.1 (2/1 heads, 3046 rows behind 31131, D 80: 371 -> 119 us), fp32 without one 1.02 .. 2.8.
+// Over 600 random calls that run so, of one to 4200 rows, time against row tiles: bf16 with a workspace 0.56 .. 1.11, 0.81 on average, without
+// 0.23 .. 1.05, 0.56, fp32 without 0.35 .. 1.08, 0.61 (2/1 heads, 3046 rows behind 31131, D 80: 371 -> 119 us).
 template <typename T, int D> int keys_nc(const s1f_desc *d, int64_t seg_off, int64_t seg_len, int64_t cap, double plan_us) {
   const int64_t cus = family_slots<FwdFamily<T, D>, 1>().cus, n_bh = (int64_t)d->n_q_heads * d->batch;
   if (cus <= 0 || 8 * n_bh >= cus || (sizeof(T) == 4 && cap > 0)) return 0;
   constexpr KeysUs us = KeysCost<T, D>::us;
   const double steps = (double)((seg_off + seg_len + 31) / 32);
   const int64_t units1 = (seg_len + 15) / 16 * n_bh, units2 = (seg_len + 31) / 32 * n_bh;
-  if (cap > 0 && steps > (2 * units1 > cus ? 80 : 48)) return 0;
+  if (cap > 0 && steps > (2 * units1 > cus ? 80 : D > 64 && 32 * units1 < cus ? 24 : D == 128 && 6 * units1 < cus ? 32 : 48)) return 0;
   int nc = 0;
   // (two units of 16 rows on a compute unit: each step takes 1.6 times as long)
   const double us1 = us.base1 + us.step1 * steps * (units1 > cus ? 1.6 : 1.0), us2 = us.base2 + us.step2 * steps;
-  if (units1 <= KeysShape<T, D, 1>::PER_CU * cus && us1 < plan_us) { nc = 1; plan_us = us1; }
-  if (units1 > cus && units2 <= cus && us2 < plan_us) nc = 2;
+  if (units1 <= KeysShape<T, D, 1>::PER_CU * cus && steps >= us.least1 && us1 < plan_us) { nc = 1; plan_us = us1; }
+  if (units1 > cus && units2 <= cus && steps >= us.least2 && us2 < plan_us) nc = 2;
   return nc;
 }
 // The plan of a forward, and how many column blocks its waves hold where they share keys (0: they do not; then as planned).

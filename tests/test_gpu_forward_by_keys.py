@@ -11,9 +11,9 @@ from test_gpu_launch_cuts import _close, _device_data
 pytestmark = pytest.mark.gpu
 
 # (batch, query heads, K/V heads, offset, rows), rows per unit: one row; one row more and less than a block and than a unit;
-# fewer tiles than waves; one unit of 16 rows per compute unit, and more (bf16 at head_dim 64 has two of them before it takes
+# units with fewer tiles than waves; one unit of 16 rows per compute unit, and more (bf16 at head_dim 64 has two of them before it takes
 # units of 32, unless walks are long); a last unit of one row; offsets that put a diagonal on two tiles
-SHAPES = [((1, 1, 1, 400, 1), 16), ((2, 3, 1, 700, 15), 16), ((1, 4, 4, 200, 17), 16), ((1, 2, 1, 225, 33), 16), ((3, 2, 2, 90, 161), 16),
+SHAPES = [((1, 1, 1, 400, 1), 16), ((2, 3, 1, 700, 15), 16), ((1, 4, 4, 360, 17), 16), ((1, 2, 1, 353, 33), 16), ((3, 2, 2, 218, 161), 16),
           ((1, 8, 2, 1500, 512), 16), ((1, 8, 2, 1499, 625), 32), ((2, 15, 5, 777, 225), 32), ((1, 8, 2, 3500, 577), 32)]
 
 
@@ -99,3 +99,23 @@ def test_tiles_of_keys_without_weight(shape, rows, d, dtype, odd, low):
         want, want_lse = A.segment_forward(host(q), host(k), host(v), off)
     assert np.isfinite(want).all()
     _close({"out": host(out), "lse": host(lse)}, {"out": want, "lse": want_lse}, dtype, "")
+
+
+# Few keys: row tiles take less time than waves need to meet.  One row, rows and keys around a block and a tile, and units of 32 rows
+FEW_KEYS = [(1, 1, 1, 0, 1), (2, 4, 2, 0, 16), (1, 3, 3, 15, 17), (1, 8, 2, 31, 33), (3, 2, 1, 60, 20), (1, 6, 1, 0, 64), (2, 8, 8, 8, 399)]
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+@pytest.mark.parametrize("d", [64, 80, 128])
+@pytest.mark.parametrize("shape", FEW_KEYS)
+def test_few_keys_run_in_row_tiles(shape, d, dtype):
+    nb, hq, hkv, off, m = shape
+    q, _, k, v = _device_data(400 + off + m + d, dtype, d, *shape, False)
+    if not (m == 399 and dtype == "bf16" and d == 64):   # (two units of 16 rows on a compute unit)
+        assert s1f.launch_plan(q, k, off, s1f.PLAN_FWD)[0] == 64
+    out, lse = torch.full_like(q, float("nan")), torch.full(q.shape[:3], float("nan"), device="cuda")
+    s1f.seg_attn_fwd(q, k, v, off, out, lse)
+    host = lambda x: x.double().cpu().numpy()
+    for b in range(nb):
+        want, want_lse = A.segment_forward(host(q[b]), host(k[b]), host(v[b]), off)
+        _close({"out": host(out[b]), "lse": host(lse[b])}, {"out": want, "lse": want_lse}, dtype, f"entry {b}: ")
