@@ -259,6 +259,13 @@ S1F_DEV void fwd_finish_fp32(const AttnArgs &a, const T *qb, const T *kbase, con
   }
 }
 
+// Where the main loop lies within 32 bytes of code decides about up to 5 % of a launch (instructions are fetched in such pieces), and what
+// stands in front of it would move it: words of padding behind a multiple of 32 bytes, each instance's best of eight places (fp32: all the same).
+// With the loop of 32 heads, head_dim 80, 128-row tiles at 0, 8, 16, 24 bytes: 2406 first rows 47.4 46.9 46.4 46.9 us, 1757 behind 6435 keys
+// 155.4 156.0 151.9 153.3; 64/8 heads, 128, 192 rows, 2626 behind 128446, at 4, 12, 20, 28: 8555 8574 8685 8456; 64-row tiles, by words 0 .. 7: 8
+// heads, 128, 2785 behind 4881 106.8 108.7 110.3 110.5 107.8 110.7 111.4 108.1.
+template <typename T, int D, int NC> constexpr int kLoopPad = sizeof(T) == 2 && NC == 1 ? (D == 128 ? 0 : D == 80 ? 4 : 2) : 3;
+
 // REST: the second launch, over the rows of units that the first left over (an instance of its own: in the 64-row kernel itself
 // the decision cost 2 to 6 % of launches of 30 to 300 us)
 template <typename T, int D, int NC, int OCC, int WAVES, bool REST = false>
@@ -407,11 +414,7 @@ __global__ void __launch_bounds__(64 * WAVES, OCC) seg_attn_fwd_kernel(const Att
   int n_full = (seg_off + wrow0 + 1) / BN;
   n_full = n_full < n_kt - 1 ? n_full : n_kt - 1;
   const int n_fast = n_full < n_kt - 4 ? n_full : n_kt - 4;
-  // Where the main loop lies within 32 bytes of code decides about up to 3 % of a launch (instructions are fetched in such pieces), and
-  // what stands in front of it would move it.  Three words past a multiple suit both of the widest uses, whose loops then begin at 16 (head_dim
-  // 80, 128 rows) and 28 (128, 192 rows).  32 heads, head_dim 80, 2406 first rows / 1757 behind 6435 keys, with the loop at 0, 8, 16, 24: 47.4
-  // 46.9 46.4 46.9 / 155.4 156.0 151.9 153.3 us; 64/8 heads, 128, 2626 behind 128446, at 4, 12, 20, 28: 8555 8574 8685 8456.
-  asm volatile(".p2align 5\n\t.fill 3, 4, 0xbf800000");   // (s_nop 0)
+  asm volatile(".p2align 5\n\t.fill %0, 4, 0xbf800000" ::"n"(kLoopPad<T, D, NC>));   // (s_nop 0)
   while (k + 1 < n_fast) steady(no, yes);
   while (k + 1 < n_full) steady(no, no);
   while (k + 1 < n_own) steady(yes, no);
