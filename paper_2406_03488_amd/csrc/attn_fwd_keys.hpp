@@ -176,6 +176,9 @@ __global__ void __launch_bounds__(64 * W, (W + 3) / 4) seg_attn_fwd_kernel_by_ke
     for (int i = 0; i < NK; ++i) settle(q[cb].f[i]);
   const int hidden = hidden_blocks<BN>(seg_off + row0, n_kt);   // (of the last tile of the unit, which the last wave walks)
 
+  // (place of the loop: see kLoopPad.  Of eight, 3 and 4 words are the fastest: bf16, D 64, 8 heads, 428 rows behind 443 keys, 0 .. 7 words 6.38 6.41 6.36
+  // 6.29 6.27 6.28 6.33 6.34 us; other instances within 1 %)
+  asm volatile(".p2align 5\n\t.fill 4, 4, 0xbf800000");
   for (int k = 0; k < n_kt; ++k) {
     const bool more = k + 1 < n_kt;
     const int64_t next = (int64_t)(BN * (k + 1)) * a.kv_ss;
