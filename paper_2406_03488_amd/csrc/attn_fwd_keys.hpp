@@ -7,9 +7,9 @@
 // barrier in the loop; while a wave waits for its tile, the others on its SIMD compute.
 // Bound by the latency of a step, and in long walks by what a compute unit reads from the L2: every unit of 16*NC rows reads all keys
 // itself, at 116 GB/s per compute unit of 2/1 heads, D 64, 511 rows behind 15830 keys (64 bytes a clock are 154), 37 to 60 in calls of 6 to
-// 17 us, with the matrix pipe 7 to 20 % busy (profiles/forward_by_keys_kernel_trace_and_counters.txt).  Calls in us, row tiles / by keys: bf16, 4 heads, 256 rows behind 768 keys, D 64 9.6 / 6.4, D 128 11.2 / 9.2;
-// 2 x 8/2 heads, 340 behind 1017, D 64 14.4 / 10.3, D 80 16.1 / 11.4; without a workspace 2/1 heads, 511 behind 15830, D 64 148 / 35, fp32
-// 492 / 167.
+// 17 us, with the matrix pipe 7 to 20 % busy (profiles/forward_by_keys_kernel_trace_and_counters.txt).  Calls in us, row tiles / by
+// keys: bf16, 4 heads, 256 rows behind 768 keys, D 64 9.6 / 6.4, D 128 11.2 / 9.2; 2 x 8/2 heads, 340 behind 1017, D 64 14.4 / 10.3, D 80
+// 16.1 / 11.4; without a workspace 2/1 heads, 511 behind 15830, D 64 148 / 35, fp32 492 / 167.
 #pragma once
 #include "attn_fwd.hpp"
 
@@ -273,7 +273,7 @@ __global__ void __launch_bounds__(64 * W, (W + 3) / 4) seg_attn_fwd_kernel_by_ke
     f32x4 acc = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
     for (int w = 0; w < W; ++w) {
-      const float weight = w_ml[w][0] == top ? 1.f : exp2_fast(w_ml[w][0] - top);   // (1 also where no key has a score above -inf)
+      const float weight = w_ml[w][0] == top ? 1.f : exp2_fast(w_ml[w][0] - top);   // (1 also if all are -inf, which plain arithmetic leaves)
       sum += weight * w_ml[w][1];
       acc += weight * *reinterpret_cast<const f32x4 *>(part + (w * ROWS + rl) * Cfg::O_ROW + 4 * c4);
     }

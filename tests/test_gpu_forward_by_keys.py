@@ -79,16 +79,17 @@ def test_keys_that_are_not_finite_leave_earlier_rows_alone(dtype, off, m, rows):
 # Keys that are to have no weight, as a column of K makes them (q has 0.25 to 1.75 in it): the lowest bf16, scores from which a
 # rounding is larger than exponents are, and minus infinity
 @pytest.mark.parametrize("low", [-3.3895e38, -1e12, float("-inf")])
-@pytest.mark.parametrize("odd", [0, 1])
+@pytest.mark.parametrize("run,odd", [(1, 0), (1, 1), (4, 0), (4, 1)])
 @pytest.mark.parametrize("dtype", ["bf16", "f32"])
 @pytest.mark.parametrize("d", [64, 80, 128])
 @pytest.mark.parametrize("shape,rows", [((1, 4, 2, 900, 100), 16), ((1, 8, 2, 1499, 625), 32)])
-def test_tiles_of_keys_without_weight(shape, rows, d, dtype, odd, low):
-    """Every other tile of 32 keys has scores far below all others: among the even or the odd ones is the first tile of every wave."""
+def test_tiles_of_keys_without_weight(shape, rows, d, dtype, run, odd, low):
+    """Every other run of tiles of 32 keys has scores far below all others: among the even or the odd ones is the first tile of every
+    wave, and in longer runs all that a wave walks."""
     nb, hq, hkv, off, m = shape
     q, _, k, v = _device_data(off + d, dtype, d, *shape, False)
     q[..., d - 1] = q[..., d - 1].abs().clamp(0.25, 1.75)
-    k[..., d - 1] = torch.where(torch.arange(off + m, device="cuda") // 32 % 2 == odd, low, 0.0)
+    k[..., d - 1] = torch.where(torch.arange(off + m, device="cuda") // (32 * run) % 2 == odd, low, 0.0)
     if dtype == "bf16" and d == 64:
         rows = 16
     assert s1f.launch_plan(q, k, off, s1f.PLAN_FWD)[0] == rows

@@ -290,19 +290,21 @@ def test_every_tile_width_in_halves(dtype, d, shape, plans):
         assert torch.isfinite(x).all() and torch.equal(x, y), name
 
 
-@pytest.mark.parametrize("odd", [0, 1])
+@pytest.mark.parametrize("run,odd", [(1, 0), (1, 1), (3, 0)])
 @pytest.mark.parametrize("dtype,d,shape,plans", WIDTHS)
-def test_every_tile_width_on_tiles_of_keys_without_weight(dtype, d, shape, plans, odd):
-    """Every other tile of 32 keys has scores far below the others, as a column of K makes them (q has 0.25 to 1.75 in it): the first
-    tiles of walks and of chunks, and those that raise the maximum from one such tile to the next.  -1e12: finite, and spaced wider than
-    exponents are."""
+def test_every_tile_width_on_tiles_of_keys_without_weight(dtype, d, shape, plans, run, odd):
+    """Every other tile of 32 keys, or run of three, has scores far below the others, as a column of K makes them (q has 0.25 to 1.75 in it):
+    the first tiles of walks and of chunks, and those that raise the maximum from one such tile to the next.  -1e12: finite, and spaced wider
+    than exponents are."""
     nb, hq, hkv, off, m = shape
     q, do, k, v = _device_data(9100 + off + m + d, dtype, d, *shape, False)
     q[..., d - 1] = q[..., d - 1].abs().clamp(0.25, 1.75)
     tiles = torch.arange(off + m, device="cuda") // 32
     low = torch.tensor([-1e12, -3.3895e38, float("-inf")], device="cuda")[tiles // 2 % 3]
-    k[..., d - 1] = torch.where(tiles % 2 == odd, low, 0.0)
-    first = max(0, 32 - off) if odd == 0 else 0   # rows before see no other key
+    k[..., d - 1] = torch.where(tiles // run % 2 == odd, low, 0.0)
+    first = min(max(0, 32 * run - off), m - 1) if odd == 0 else 0   # rows before see no other key
+    if off + m <= 32 * run:
+        k[..., -1, d - 1] = 0.0   # (the last row does)
     for workspace in (False, True):
         out, lse = torch.full_like(q, float("nan")), torch.full(q.shape[:3], float("nan"), device="cuda")
         if workspace:
